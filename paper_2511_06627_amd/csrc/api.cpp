@@ -70,7 +70,8 @@ OpWs carve_op(const mpi3d_plan *pl, void *ws)
     w.rtb = (uint16_t *)(b + pl->ws_rtb);
     w.rtsc = (float *)(b + pl->ws_rtsc);
     w.sig = (float *)(b + pl->ws_sig);
-    w.fac = (float *)(b + pl->ws_fac);
+    w.fac = (uint32_t *)(b + pl->ws_fac);
+    w.lexp = (int *)(b + pl->ws_lexp);
     return w;
 }
 
@@ -135,24 +136,27 @@ static FacArgs fac_args(const LineJob &lj)
     a.job.in_stride = lj.in_stride;
     a.job.part = lj.w->part;
     a.job.part_stride = pj->L * pj->nup;
-    a.job.kf = f.kf;
-    a.job.ka = f.ka;
+    a.kf = f.kf;
+    a.ka = f.ka;
     a.job.rows = lg.rows;
     a.job.map_per = lg.per;
     a.job.map_nz = lg.gnz;
     a.job.map_off = lg.off;
     a.job.map_step = lg.step;
     a.ef = f.ef; a.ea = f.ea; a.wf = f.wf; a.wa = f.wa;
-    a.uq = f.uq; a.ubin = f.ubin; a.qbin = f.qbin; a.qsteps = f.qsteps;
+    a.unit0 = f.unit0; a.qbin = f.qbin;
     a.y = lj.w->fac;
+    a.lexp = lj.w->lexp;
     a.ylines = (lg.rows + 31) / 32 * 32;
-    a.nu = pj->nu; a.nup = pj->nup; a.nbp2 = pj->nbp2;
-    a.P = f.P; a.Pp = f.Pp; a.cj = f.cj;
-    a.yc = 2 * f.zst; a.zst = f.zst; a.R = f.R; a.U = f.U; a.rct = f.rct;
-    a.nsplit = f.nsplit; a.nsplit_adj = f.nsplit_adj; a.usplit = f.usplit; a.nzstage = f.nzstage;
+    a.nu = pj->nu; a.nup = pj->nup;
+    a.P = f.P; a.cj = f.cj; a.ucols = 32 * f.U;
+    a.yc = 2 * f.zst; a.zst = f.zst; a.R = f.R; a.U = f.U; a.qmax = f.qmax;
+    a.nsplit = f.nsplit; a.nsplit_adj = f.nsplit_adj; a.nzstage = f.nzstage;
     a.psplit = f.psplit; a.zsplit = f.zsplit;
-    a.fwd_part_stride = pj->L * pj->nbp2;
+    a.fwd_part_stride = pj->L * 32 * f.U;
     a.tiles = (lg.rows + 31) / 32;
+    a.s_scale = f.s_scale; a.g_scale = f.g_scale; a.y_scale = f.y_scale; a.z_scale = f.z_scale;
+    a.y_exp = f.y_exp; a.z_exp = f.z_exp; a.w_exp = f.w_exp; a.r_exp = f.r_exp;
     return a;
 }
 
@@ -203,8 +207,8 @@ static void line_jobs(const LineJob &lj, int prec, bool fwd, bool serve, std::ve
             sj.part_stride = part_stride;
             sj.row_scale = lj.w->rowscale;
             const size_t ko = (size_t)(lg.table + e) * pj->k_elems;
-            sj.kf = pj->kf + ko;
-            sj.ka = pj->ka + ko;
+            sj.kf = pj->kf ? pj->kf + ko : nullptr;
+            sj.ka = pj->ka ? pj->ka + ko : nullptr;
             sj.kf16 = pj->kf16 ? pj->kf16 + ko : nullptr;
             sj.ka16 = pj->ka16 ? pj->ka16 + ko : nullptr;
             sj.rows = lg.rows;
@@ -323,10 +327,11 @@ int sig_adjoint_jobs(int prec, const LineJob *jobs, int n, bool serve, hipStream
 static int reduce_forward(const mpi3d_plan *pl, int prec, const OpWs &w, bool serve, float *out, const float *b_sub,
                           double *norm_parts, int *nnorm, hipStream_t st)
 {
-    const bool mixed = prec == MPI3D_MIXED;
-    TRY(launch_reduce_fwd(pl->L, pl->nb2, pl->nbp2, fwd_parts(pl, prec, serve), pl->L * pl->nbp2, w.part,
+    const bool mixed = prec == MPI3D_MIXED, fac = fac_on(pl, prec);
+    const int pitch = fac ? 32 * pl->fac.U : pl->nbp2;   // floats per line of the partial sums
+    TRY(launch_reduce_fwd(pl->L, pl->nb2, pitch, fwd_parts(pl, prec, serve), pl->L * pitch, w.part,
                           mixed ? w.rowscale : nullptr, mixed ? pl->col_scale : nullptr, pl->op_scale, b_sub, out,
-                          norm_parts, nnorm, st, row_passes(pl, true, prec)));
+                          norm_parts, nnorm, st, row_passes(pl, true, prec), fac ? pl->fac.bcol : nullptr));
     return MPI3D_OK;
 }
 

@@ -70,43 +70,52 @@ __host__ __device__ inline long job_line(const SigJob &j, int r)
 }
 
 // The band DFT factored over drive cycles (FP32 scans with one PSF table and
-// one line group): time t = n1 + P n2 with n1 < P, n2 < C, T = C P, C a
-// multiple of 32.  The R distinct residues q of the kept bins mod C take
-// 2 zst columns (re/im per residue, zst = R rounded up to 4) of the phase
-// sums Y (forward) and Z (adjoint), per 32-line tile [P][2 zst][32 lines]
-// floats in the workspace (plus one spare line of P 2 zst floats).  The
-// forward's outer sum runs over units of at most 16 bins of one residue; the
-// adjoint's over each residue's bins, at most kQMax.
-constexpr int kFacWavesFwd = 8;     // waves (32-line tiles) per block of the forward line-tile kernel
-                                    // (two per SIMD: one hides the other's wait at the chunk barrier)
-constexpr int kFacWavesAdj = 8;     // and of the adjoint line-tile kernel
-constexpr int kQMax = 24;           // bins per residue (adjoint outer sum, register operands)
-constexpr int kFacInWaves = 8;      // waves of the adjoint outer sum; wave w takes residues w + 8 i
-constexpr int kMaxFacSplit = 4;     // forward outer-sum blocks per line tile (40 units each)
+// one line group): time t = n1 + P n2 with n1 < P, n2 < C, T = C P, C = 32 or
+// 64.  The time signal is real, so its C-point DFT over n2 needs one slot of
+// two columns (cos, sin) per residue pair {r, C - r} of the kept bins mod C;
+// residues 0 and C / 2, whose sine columns vanish, share a slot (columns: the
+// plain and the alternating sum).  C = 32 always fits 16 slots; C = 64 is
+// taken where the harmonics bunch into at most 24.  The phase sums Y (forward)
+// and Z (adjoint) are words [P][2 zst][32 lines] per 32-line tile in the
+// workspace (plus one spare line of P 2 zst words), zst slots in all (zero
+// columns past R); a word is a value as a pair of fp16 numbers, hi + lo.  The
+// forward's outer sum runs over units of at most 16 bins of one slot; the
+// adjoint's over each slot's bins, at most qmax.
+constexpr int kFacWaves = 8;        // waves (32-line tiles) per block of the line-tile kernels
+                                    // (two per SIMD: one hides the other's wait at the stage barrier)
+constexpr int kFacInWaves = 8;      // waves of the adjoint outer sum; wave w takes slots w + 8 i
 
 struct FacArgs {
-    SigJob job;              // input lines, partial sums (part, part_stride), row map; kf / ka: the PSF
-                             // tables with their time rows in chunk order (n1, 32-cycle block)
-    const float *ef, *ea;    // residue DFT: forward B operand, adjoint A operand (swizzled)
-    const float *wf, *wa;    // outer sums: forward per unit, adjoint per residue and 16-phase stage
-    const int *uq;           // [U] residue of unit u
-    const int *ubin;         // [U][16] bins of unit u (-1: none)
-    const int *qbin;         // [R][kQMax] bins of residue q (-1: none)
-    const int *qsteps;       // [R] bins of residue q rounded up to 4
-    float *y;                // phase sums Y or Z per 32-line tile, [P][yc][32 lines] (for Z the
-                             // columns are [re/im][zst]); ylines = 32 tiles; then a spare row of
-                             // P yc floats taking the stores that carry nothing
+    SigJob job;              // input lines, partial sums (part, part_stride), row map
+    const __half *kf, *ka;   // PSF tables, time rows in chunk order (n1, 32-cycle block), as fp16
+                             // fragment pairs hi, lo scaled by a power of two
+    const __half *ef, *ea;   // residue DFT (both as A operands), pairs hi, lo of 2^14 E
+    const __half *wf, *wa;   // outer sums, fragment pairs: forward per unit and 8-phase stage (B
+                             // operand), adjoint per slot and 16-phase stage (A operand)
+    const int *unit0;        // [R + 1] first unit of slot q
+    const int *qbin;         // [R][qmax] bins of slot q (-1: none)
+    uint32_t *y;             // phase sums Y or Z per 32-line tile, [P][yc][32 lines] (column 2 slot +
+                             // cos/sin), words of split pairs; ylines = 32 tiles; then a spare row of
+                             // P yc words taking the stores that carry nothing
+    int *lexp;               // [ylines] power-of-two exponent of each line's Y or Z
     int ylines;
-    int nu, nup, nbp2;
-    int P, Pp, cj;           // phases, phases rounded up to 8, 32-cycle blocks per phase (C / 32)
-    int yc, zst, R, U, rct;  // yc = 2 zst; rct: 32-column tiles of the residue DFT (1 or 2)
+    int nu, nup;
+    int P, cj;               // phases, 32-cycle blocks per phase (C / 32)
+    int yc, zst, R, U;       // yc = 2 zst
+    int ucols;               // 32 U: columns of the forward's partial sums (unit, bin, re/im)
+    int qmax;
     int nsplit, nsplit_adj;  // phase ranges of the forward and adjoint line-tile kernels
-    int usplit;              // unit split of the forward outer sum
     int psplit, zsplit;      // stage ranges of the forward outer sum (partial sums each) and of the
                              // adjoint outer sum (disjoint phases of Z)
     long fwd_part_stride;    // floats between the forward outer sum's partial-sum blocks
     int nzstage;             // 16-phase stages of the adjoint outer sum
     int tiles;               // 32-line tiles of the job
+    // Power-of-two scales: of the time signal before its split (forward,
+    // adjoint), of Y and Z before theirs.  A line of Y holds Y 2^lexp (lexp: the
+    // line's exponent + y_exp), of Z likewise (+ z_exp); the forward's partial
+    // sums are results 2^-(lexp + w_exp), the adjoint's 2^-(lexp + r_exp).
+    float s_scale, g_scale, y_scale, z_scale;
+    int y_exp, z_exp, w_exp, r_exp;
 };
 
 struct SigArgs {
@@ -196,9 +205,13 @@ struct mpi3d_plan {
     // time when it pays; tables in the plan's allocation
     struct Fac {
         bool on = false;
-        int C, P, Pp, cj, R, zst, U, rct, nsplit, nsplit_adj, usplit, psplit, zsplit, nzstage;
-        float *kf, *ka, *ef, *ea, *wf, *wa;
-        int *uq, *ubin, *qbin, *qsteps;
+        int C, P, cj, R, zst, U, qmax, nsplit, nsplit_adj, psplit, zsplit, nzstage;
+        int res;                  // distinct residues of the kept bins mod C
+        float s_scale, g_scale, y_scale, z_scale;
+        int y_exp, z_exp, w_exp, r_exp;
+        __half *kf, *ka, *ef, *ea, *wf, *wa;
+        int *unit0, *qbin;
+        int *bcol;                // [nb] column of bin j's real part in the forward's partial sums
     } fac;
     uint64_t line_key;             // equal keys <=> identical line tables
     // projection configuration
@@ -244,7 +257,7 @@ struct mpi3d_plan {
     float *gta = nullptr; // and their transposes G [2 nb][n_up] (the adjoint's operand)
     size_t gt_elems = 0;  // floats per line matrix
     // operator workspace layout (bytes from ws base)
-    size_t ws_rt, ws_part, ws_norm, ws_rowscale, ws_xb, ws_in16, ws_rtb, ws_rtsc, ws_sig, ws_fac, op_ws_bytes;
+    size_t ws_rt, ws_part, ws_norm, ws_rowscale, ws_xb, ws_in16, ws_rtb, ws_rtsc, ws_sig, ws_fac, ws_lexp, op_ws_bytes;
     int in16_cols;        // halves per fp16 operand line: max(nup, nbp2)
     // solver workspace layout
     size_t sw_op, sw_r, sw_q, sw_s, sw_p, sw_scal, sw_parts, sw_d, sw_g, sw_v, solve_ws_bytes;
@@ -277,9 +290,9 @@ int sig_fwd_supported(int nup, int gct, int precision, int pairs);
 int sig_adj_supported(int nup, int gct, int precision, int pairs);
 int sig_fused_supported(int nupf, int gct);
 // Factored band DFT (sigfac.hip): forward writes Y then the job's partial
-// sums (psplit blocks of nbp2 columns); adjoint writes Z then nsplit_adj
+// sums (psplit blocks of 32 U columns); adjoint writes Z then nsplit_adj
 // splits of nup-column partial sums.
-int fac_supported(int nup, int rct, int zst, int cj);
+int fac_supported(int nup, int zst, int cj);
 hipError_t launch_fac_fwd(const FacArgs &a, hipStream_t st);
 hipError_t launch_fac_adj(const FacArgs &a, hipStream_t st);
 // one kernel of those stages: forward PSF contraction + residue DFT, forward
@@ -331,9 +344,11 @@ struct RowPasses {
 // L nup and nup; the fused pass: nup and (R + 1) nup, a virtual line per l).
 hipError_t launch_sym_lines(const float *rho, int in_stride, int nu, int nup, RowPasses rp, float *sig,
                             long pass_stride, long line_stride, hipStream_t st);
+// (bcol: bin j's partial sums are columns bcol[j], bcol[j] + 1; null: 2 j, 2 j + 1)
 hipError_t launch_reduce_fwd(long rows, int nb2, int nbp2, int nparts, long part_stride, const float *part,
                              const float *row_scale, const float *col_scale, double scale, const float *b_sub,
-                             float *out, double *norm_parts, int *nnorm, hipStream_t st, RowPasses rp);
+                             float *out, double *norm_parts, int *nnorm, hipStream_t st, RowPasses rp,
+                             const int *bcol = nullptr);
 hipError_t launch_reduce_lines_strided(long rows, int nu, int nup, int out_stride, int nparts, long part_stride,
                                        const float *part, const float *row_scale, double scale, float *out,
                                        hipStream_t st, RowPasses rp);
@@ -406,8 +421,9 @@ struct OpWs {
     float *sig;       // [n_passes][L][nup] tensor PSF: the passes' symmetric line sums (forward)
     uint16_t *rtb;    // [L][nup] fp16 lines of the mixed adjoint (its backprojection gathers)
     float *rtsc;      // [L] their per-line inverse scales
-    float *fac;       // phase sums of the factored band DFT (FP32): ceil(L / 32) tiles of
-                      // [P][2 zst][32 lines], then a spare line of P 2 zst floats
+    uint32_t *fac;    // phase sums of the factored band DFT (FP32): ceil(L / 32) tiles of
+                      // [P][2 zst][32 lines], then a spare line of P 2 zst words
+    int *lexp;        // [ceil(L / 32) 32] their line exponents
 };
 OpWs carve_op(const mpi3d_plan *pl, void *ws);
 int check_prec(const mpi3d_plan *pl, int32_t precision);

@@ -86,6 +86,34 @@ double psf_xx(double du, double dz, double w)
 // double -> fp16, rounded once (clang's _Float16 conversion is correctly rounded)
 inline _Float16 to_f16(double v) { return (_Float16)v; }
 
+// v (|v| < 2^15) as the nearest pair of fp16 numbers: hi = rn16(v), lo =
+// rn16(v - hi).  By integer arithmetic on the double's bits, several times
+// faster than the library conversion over a table's millions of entries.
+inline uint16_t half_bits(double v, double *rounded)
+{
+    const double a = std::fabs(v);
+    const uint16_t sign = std::signbit(v) ? 0x8000 : 0;
+    if (a < 6.103515625e-05) {                     // below 2^-14: multiples of 2^-24
+        const double q = (a * 16777216.0 + 4503599627370496.0) - 4503599627370496.0;
+        *rounded = std::copysign(q / 16777216.0, v);
+        return sign | (uint16_t)q;
+    }
+    uint64_t b;
+    std::memcpy(&b, &a, 8);
+    b += 0x1ffffffffffull + ((b >> 42) & 1);       // to 10 fraction bits, ties to even
+    b &= ~0x3ffffffffffull;
+    double r;
+    std::memcpy(&r, &b, 8);
+    *rounded = std::copysign(r, v);
+    return sign | (uint16_t)((((b >> 52) - 1008) << 10) + ((b >> 42) & 0x3ff));
+}
+inline void half_pair(double v, uint16_t &hi, uint16_t &lo)
+{
+    double h, l;
+    hi = half_bits(v, &h);
+    lo = half_bits(v - h, &l);
+}
+
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
@@ -182,6 +210,47 @@ void choose_split(const mpi3d_plan *pl, bool fp32, mpi3d_plan::SigCfg &c, int nu
     c.serve_nsplit = std::min(pl->nchunks, 16);
     c.serve_cps = (pl->nchunks + c.serve_nsplit - 1) / c.serve_nsplit;
     c.serve_nsplit = (pl->nchunks + c.serve_cps - 1) / c.serve_cps;
+}
+
+// The operator workspace's layout (bytes from its base), with or without the
+// factored FP32 stage.
+void op_layout(mpi3d_plan *pl, bool fac)
+{
+    const mpi3d_plan::Fac &f = pl->fac;
+    const bool mixed = pl->precisions & (1 << MPI3D_MIXED);
+    size_t o = 0;
+    auto put = [&](size_t bytes) { o = align256(o); size_t r = o; o += bytes; return r; };
+    pl->ws_rt = put(sizeof(float) * pl->L * pl->nup);
+    size_t parts = 0;   // split partial sums: forward [splits][L][nbp2], adjoint [splits][groups][L][nup]
+    for (int i = fac ? 1 : 0; i < 2; ++i) {
+        if (fac && !mixed) break;
+        const mpi3d_plan::SigCfg &c = pl->sc[i];
+        parts = std::max(parts, (size_t)std::max(c.nsplit, c.serve_nsplit) *
+                                    std::max<size_t>(pl->nbp2, (size_t)c.ngroups * pl->nup));
+    }
+    size_t part_floats = (size_t)pl->n_passes * pl->L * parts;
+    if (pl->fused)   // one pass; adjoint lines of nupf
+        part_floats = std::max(part_floats, (size_t)pl->L * std::max(pl->scf.nsplit, pl->scf.serve_nsplit) *
+                                                std::max<size_t>(pl->nbp2, (size_t)pl->nupf));
+    if (fac)   // adjoint: nsplit blocks of nup-column lines; forward: psplit of 32 U columns
+        part_floats =
+            std::max(part_floats, (size_t)pl->L * std::max(f.nsplit_adj * pl->nup, f.psplit * 32 * f.U));
+    pl->ws_part = put(sizeof(float) * part_floats);
+    pl->ws_norm = put(sizeof(double) * pl->max_parts);
+    // per tensor-PSF pass: the forward's symmetric line sums, their
+    // scales and fp16 operands (one block each without coupling)
+    const size_t np = pl->n_passes;
+    pl->ws_rowscale = put(sizeof(float) * np * pl->L);
+    pl->ws_xb = put(mixed ? sizeof(uint16_t) * pl->nvox : 0);
+    pl->in16_cols = std::max(pl->nup, pl->nbp2);
+    pl->ws_in16 = put(mixed ? sizeof(uint16_t) * np * pl->L * pl->in16_cols : 0);
+    pl->ws_rtb = put(mixed ? sizeof(uint16_t) * pl->L * pl->nup : 0);
+    pl->ws_rtsc = put(mixed ? sizeof(float) * pl->L : 0);
+    pl->ws_sig = put(np > 1 ? sizeof(float) * np * pl->L * pl->nup : 0);
+    const long tile_lines = (pl->L + 31) / 32 * 32;
+    pl->ws_fac = put(fac ? sizeof(uint32_t) * (tile_lines + 1) * f.P * 2 * f.zst : 0);
+    pl->ws_lexp = put(fac ? sizeof(int) * tile_lines : 0);
+    pl->op_ws_bytes = align256(o);
 }
 
 template <class T>
@@ -439,14 +508,346 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             }
         }
     }
+    if (g->rx_filter)
+        for (int j = 0; j < 2 * NB; ++j)
+            if (!std::isfinite(g->rx_filter[j])) { delete pl; return MPI3D_EINVAL; }
+
+    // ---- band DFT factored over drive cycles (FP32) --------------------------
+    // t = n1 + P n2 (T = C P, C = 32 or 64): the kept bin omega_j
+    // contributes e^{2 pi i omega_j n1 / T} e^{2 pi i (omega_j mod C) n2 / C},
+    // so the forward first sums each phase n1's C cycles against the residues
+    // r = omega_j mod C, then each bin's P phases.  s is real, so residues r
+    // and C - r share the columns cos, sin of one slot, and 0 and C / 2 (no
+    // sine) share another.  Taken when its time per line, by the rates below,
+    // is under the dense form's; C minimises it.
+    std::vector<uint16_t> fkf, fka, fef, fea, fwf, fwa;   // fp16 bits
+    std::vector<int> funit0, fubin, fqbin, fbcol;
+    // A plan that also holds the mixed operator takes it only where the bins'
+    // residues bunch (at most 24 distinct): its refinement sweeps start from
+    // the FP32 operator, and their inner iterations blow a difference in its
+    // last bits up, through the 16-bit roundings, to some 1e-5 of the result;
+    // scans that bunch less keep the dense form's bits there.
+    if ((precisions & (1 << MPI3D_FP32)) && !pl->fused && pl->n_passes == 1 && pl->n_line_groups == 1 &&
+        n_ktab == 1 && T % 32 == 0) {
+        // slot of residue r: 0 for r = 0 and C / 2, else min(r, C - r)
+        auto slot_of = [](long r, int C) { return (int)(2 * r == C ? 0 : std::min(r, C - r)); };
+        auto slots_of = [](int R, int C) { return C == 32 ? 16 : std::max(16, (R + 3) / 4 * 4); };
+        // seconds per line: dense fp32 products at 1.1e14 flop/s; factored
+        // split products (three each) at 8e14, the phase sums written and read
+        // at 4 TB/s, the outer sum's fp32 products (32 columns a unit) at 1e14
+        double best = 2.0 * T * (NUP + NBP2) / 1.1e14;
+        int bestC = 0;
+        for (int C = 32; C <= T && C <= 64; C += 32) {
+            if (T % C) continue;
+            std::vector<int> cnt(C / 2, 0);
+            std::vector<char> seen(C, 0);
+            for (int j = 0; j < NB; ++j) {
+                ++cnt[slot_of(bins[j] % C, C)];
+                seen[bins[j] % C] = 1;
+            }
+            if ((precisions & (1 << MPI3D_MIXED)) && std::count(seen.begin(), seen.end(), 1) > 24) continue;
+            int R = 0, U = 0, mx = 0;
+            for (int c : cnt)
+                if (c) {
+                    ++R;
+                    U += (c + 15) / 16;
+                    mx = std::max(mx, c);
+                }
+            const int zst = slots_of(R, C), rct = (2 * zst + 31) / 32, P = T / C;
+            if (!(R <= 16 && mx <= 32) && !(R <= 24 && mx <= 24)) continue;
+            if (!fac_supported(NUP, zst, C / 32) ||
+                (double)((pl->L + 31) / 32 * 32 + 1) * P * 2 * zst >= 2147483647.0 || 4.0 * T * NUP >= 2147483647.0)
+                continue;
+            const double cost = 6.0 * T * (NUP + 32 * rct) / 8e14 + 16.0 * P * zst / 4e12 + 128.0 * P * U / 1e14;
+            if (cost < best) {
+                best = cost;
+                bestC = C;
+            }
+        }
+        std::vector<int> res;                // least residue of each slot
+        std::vector<std::vector<int>> qb;    // bins of each slot
+        if (bestC) {
+            mpi3d_plan::Fac &f = pl->fac;
+            f.C = bestC;
+            f.P = T / bestC;
+            f.cj = bestC / 32;
+            f.nzstage = (f.P + 15) / 16;
+            // Slot order: the adjoint outer sum's wave w takes slots
+            // w, w + 8, w + 16 (so waves w < R % 8 take one more when 8 does
+            // not divide R) and spends a step per bin, so slots are dealt
+            // largest first to the least loaded wave with room, and numbered
+            // by (wave, turn).  Units: a slot's bins (ascending) 16 at a time.
+            std::vector<int> cnt(bestC / 2, 0), byc;
+            std::vector<char> seen(bestC, 0);
+            for (int j = 0; j < NB; ++j) {
+                ++cnt[slot_of(bins[j] % bestC, bestC)];
+                seen[bins[j] % bestC] = 1;
+            }
+            f.res = (int)std::count(seen.begin(), seen.end(), 1);
+            for (int r = 0; r < bestC / 2; ++r)
+                if (cnt[r]) byc.push_back(r);
+            std::stable_sort(byc.begin(), byc.end(), [&](int x, int y) { return cnt[x] > cnt[y]; });
+            const int nw = kFacInWaves, nr = (int)byc.size();
+            std::vector<std::vector<int>> wres(nw);
+            std::vector<int> load(nw, 0), room(nw);
+            for (int w = 0; w < nw; ++w) room[w] = nr / nw + (w < nr % nw ? 1 : 0);
+            for (int r : byc) {
+                int bw2 = -1;
+                for (int w = 0; w < nw; ++w)
+                    if ((int)wres[w].size() < room[w] && (bw2 < 0 || load[w] < load[bw2])) bw2 = w;
+                wres[bw2].push_back(r);
+                load[bw2] += (cnt[r] + 3) / 4 * 4;
+            }
+            std::vector<int> slot(bestC / 2, -1);   // slot number of a least residue
+            res.assign(byc.size(), -1);
+            for (int w = 0; w < nw; ++w)
+                for (size_t i = 0; i < wres[w].size(); ++i) {
+                    const int q = w + nw * (int)i;
+                    res[q] = wres[w][i];
+                    slot[wres[w][i]] = q;
+                }
+            f.R = (int)res.size();
+            f.zst = slots_of(f.R, bestC);
+            f.qmax = f.R <= 16 ? 32 : 24;
+            const int QM = f.qmax;
+            qb.resize(f.R);
+            for (int j = 0; j < NB; ++j) qb[slot[slot_of(bins[j] % bestC, bestC)]].push_back(j);
+            fqbin.assign((size_t)f.R * QM, -1);
+            fbcol.assign(NB, 0);
+            for (int q = 0; q < f.R; ++q) {
+                for (size_t i = 0; i < qb[q].size(); ++i) fqbin[(size_t)q * QM + i] = qb[q][i];
+                funit0.push_back((int)fubin.size() / 16);
+                for (size_t i = 0; i < qb[q].size(); ++i) fbcol[qb[q][i]] = 2 * ((int)fubin.size() + (int)i);
+                for (size_t i0 = 0; i0 < qb[q].size(); i0 += 16)
+                    for (size_t i = 0; i < 16; ++i) fubin.push_back(i0 + i < qb[q].size() ? qb[q][i0 + i] : -1);
+            }
+            f.U = (int)fubin.size() / 16;
+            funit0.push_back(f.U);
+            // The outer sums: forward waves of two tiles and a slot, adjoint
+            // blocks of a tile; small scans also split the phase stages (8 and
+            // 16 phases) until about 2048 waves (256 blocks) run.
+            const long tiles = (pl->L + 31) / 32;
+            f.psplit = (int)std::max<long>(1, std::min<long>({8, 2048 / ((tiles + 1) / 2 * f.R), (f.P + 7) / 8}));
+            f.zsplit = (int)std::max<long>(1, std::min<long>({8, 256 / tiles, (f.P + 15) / 16}));
+            // Phase ranges of the line-tile kernels (8 tiles a block, one block a
+            // CU): the least estimated time.  A block takes about 4 us to load
+            // its lines and first stages, then its phases at two waves a SIMD
+            // (MFMAs of 32 cycles at about 60% busy, 2.4 GHz); each range of
+            // the adjoint costs the reduction one more partial sum (its chain
+            // of loads, about 0.1 us, and the bytes at 4 TB/s).
+            const long tgroups = (tiles + kFacWaves - 1) / kFacWaves;
+            const double t_phase = f.cj * (3.0 * NUP / 16 + 6.0 * ((2 * f.zst + 31) / 32)) * 64 / 0.6 / 2.4e9;
+            auto splits = [&](double per_range) {
+                double tbest = 1e30;
+                int nbest = 1;
+                for (int ns = 1; ns <= std::min(f.P, 256); ++ns) {
+                    const double t = (double)((tgroups * ns + 255) / 256) * (4e-6 + (f.P + ns - 1) / ns * t_phase) +
+                                     ns * per_range;
+                    if (t < tbest * (1.0 - 1e-9)) {
+                        tbest = t;
+                        nbest = ns;
+                    }
+                }
+                return nbest;
+            };
+            f.nsplit = splits(0.0);
+            f.nsplit_adj = splits(1e-7 + 8.0 * pl->L * NUP / 4e12);
+            // a scan whose bins bunch little and that fits the no-allocation
+            // entry point's scratch in the dense form stays dense where the
+            // phase sums would not fit it
+            op_layout(pl, false);
+            const size_t dense_ws = pl->op_ws_bytes;
+            op_layout(pl, true);
+            f.on = f.res <= 24 || !(dense_ws <= MPI3D_NOALLOC_SCRATCH_BYTES && pl->op_ws_bytes > MPI3D_NOALLOC_SCRATCH_BYTES);
+        }
+        if (pl->fac.on) {
+            mpi3d_plan::Fac &f = pl->fac;
+            // tables
+            const int QM = f.qmax, C = bestC, P = f.P, CJ = f.cj, ZST = f.zst, YC = 2 * ZST;
+            const int RCT = (YC + 31) / 32, NZS = (YC + 15) / 16;
+            auto tp16 = [](int e2, int h) { return 8 * (e2 / 4) + 4 * h + (e2 % 4); };
+            auto tof = [&](int c, int i) { return (c / CJ) + P * (32 * (c % CJ) + i); };   // chunk row -> time
+            const double *K0 = &K[0];
+            // PSF table scaled so its largest entry is in [2^14, 2^15); s_scale
+            // keeps a time signal of lines below 2^15 at or below 2^15 by the
+            // largest row sum
+            double kmax = 0, ksum = 0;
+            for (int n = 0; n < T; ++n) {
+                double sum = 0;
+                for (int p = 0; p < NUP; ++p) {
+                    const double v = std::fabs(K0[(size_t)n * NUP + p]);
+                    kmax = std::max(kmax, v);
+                    sum += v;
+                }
+                ksum = std::max(ksum, sum);
+            }
+            int kexp = 0, sexp = 0;
+            if (kmax > 0) {
+                std::frexp(kmax, &kexp);
+                kexp = 15 - kexp;
+                std::frexp(std::ldexp(ksum, kexp), &sexp);   // row sums < 2^sexp
+            }
+            f.s_scale = (float)std::ldexp(1.0, -sexp);
+            // |Y| <= C 2^14 2^15 before y_scale
+            f.y_scale = (float)std::ldexp(1.0, -(bestC == 32 ? 19 : 20));
+            f.y_exp = kexp - sexp + 14 - (bestC == 32 ? 19 : 20);
+            // |2^14 E| <= 2^14 and |Z| <= 2^15 over at most 2 R columns
+            int cexp = 0;
+            while ((1 << cexp) < 2 * f.R) ++cexp;
+            f.g_scale = (float)std::ldexp(1.0, -(14 + cexp));
+            f.r_exp = kexp - cexp;   // 14 - (14 + cexp) + kexp
+            // fragments of 64 lanes x 8 halves, hi then lo:
+            //  kf [c][p / 16][hi, lo]: K[time row l % 32][p = 16 ks + 8 (l / 32) + e]
+            //  ka [c][time step][p / 32][hi, lo]: K[time row 16 q + tp16(e, l / 32)][p = 32 pt + l % 32]
+            fkf.assign(2 * KE, 0);
+            fka.assign(2 * KE, 0);
+            std::vector<uint16_t> kh(32 * NUP), kl(32 * NUP);   // one chunk's pairs
+            const double ksc = std::ldexp(1.0, kexp);
+            for (int c = 0; c < P * CJ; ++c) {
+                for (int i = 0; i < 32; ++i)
+                    for (int p = 0; p < NUP; ++p)
+                        half_pair(K0[(size_t)tof(c, i) * NUP + p] * ksc, kh[i * NUP + p], kl[i * NUP + p]);
+                for (int ks = 0; ks < NUP / 16; ++ks)
+                    for (int l = 0; l < 64; ++l)
+                        for (int e2 = 0; e2 < 8; ++e2) {
+                            const size_t o = (((size_t)c * (NUP / 16) + ks) * 2 * 64 + l) * 8 + e2;
+                            const int i = (l % 32) * NUP + 16 * ks + 8 * (l / 32) + e2;
+                            fkf[o] = kh[i];
+                            fkf[o + 512] = kl[i];
+                        }
+                for (int q = 0; q < 2; ++q)
+                    for (int pt = 0; pt < NUP / 32; ++pt)
+                        for (int l = 0; l < 64; ++l)
+                            for (int e2 = 0; e2 < 8; ++e2) {
+                                const size_t o = ((((size_t)c * 2 + q) * (NUP / 32) + pt) * 2 * 64 + l) * 8 + e2;
+                                const int i = (16 * q + tp16(e2, l / 32)) * NUP + 32 * pt + l % 32;
+                                fka[o] = kh[i];
+                                fka[o + 512] = kl[i];
+                            }
+            }
+            // E[n2][2q] = cos, E[n2][2q + 1] = sin of 2 pi (r n2 mod C) / C, r the
+            // slot's least residue; the slot of 0 and C / 2: 1 and (-1)^n2
+            auto E = [&](int n2, int q, int part) -> double {
+                if (q >= f.R) return 0.0;
+                if (res[q] == 0) return part == 0 ? 1.0 : (n2 % 2 ? -1.0 : 1.0);
+                const long ph = (long)res[q] * n2 % C;
+                const double a = 2.0 * kPi * (double)ph / C;
+                return part ? std::sin(a) : std::cos(a);
+            };
+            // ef [j][g][time step][hi, lo]: row = column 32 g + l % 32 (2 slot + part),
+            // k = time 32 j + 16 q + tp16(e, l / 32)
+            fef.assign((size_t)CJ * RCT * 4 * 512, 0);
+            for (int j = 0; j < CJ; ++j)
+                for (int g2 = 0; g2 < RCT; ++g2)
+                    for (int q = 0; q < 2; ++q)
+                        for (int l = 0; l < 64; ++l)
+                            for (int e2 = 0; e2 < 8; ++e2) {
+                                const int col = 32 * g2 + l % 32;
+                                const size_t o = ((((size_t)j * RCT + g2) * 2 + q) * 2 * 64 + l) * 8 + e2;
+                                half_pair(std::ldexp(E(32 * j + 16 * q + tp16(e2, l / 32), col / 2, col % 2), 14), fef[o],
+                                       fef[o + 512]);
+                            }
+            // ea [j][column step][hi, lo]: row = time 32 j + l % 32, k = column
+            // 16 ks + 8 (l / 32) + e (2 slot + part)
+            fea.assign((size_t)CJ * NZS * 2 * 512, 0);
+            for (int j = 0; j < CJ; ++j)
+                for (int ks = 0; ks < NZS; ++ks)
+                    for (int l = 0; l < 64; ++l)
+                        for (int e2 = 0; e2 < 8; ++e2) {
+                            const int col = 16 * ks + 8 * (l / 32) + e2;
+                            if (col >= YC) continue;
+                            const size_t o = (((size_t)j * NZS + ks) * 2 * 64 + l) * 8 + e2;
+                            half_pair(std::ldexp(E(32 * j + l % 32, col / 2, col % 2), 14), fea[o], fea[o + 512]);
+                        }
+            // G_j[n1] = D_j e^{2 pi i (omega_j n1 mod T) / T} / sqrt(T)
+            const double inv = 1.0 / std::sqrt((double)T);
+            std::vector<double> Gt((size_t)NB * P * 2);
+            for (int j = 0; j < NB; ++j) {
+                double dre = 1.0, dim = 0.0;
+                if (g->rx_filter) { dre = g->rx_filter[2 * j]; dim = g->rx_filter[2 * j + 1]; }
+                for (int n1 = 0; n1 < P; ++n1) {
+                    const long ph = (long)(((unsigned long long)bins[j] * (unsigned long long)n1) %
+                                           (unsigned long long)T);
+                    const double a = 2.0 * kPi * (double)ph / T;
+                    const double co = std::cos(a), si = std::sin(a);
+                    Gt[2 * ((size_t)j * P + n1)] = (dre * co - dim * si) * inv;
+                    Gt[2 * ((size_t)j * P + n1) + 1] = (dre * si + dim * co) * inv;
+                }
+            }
+            // weight of slot column cy (cos, sin) in part cb (re, im) of bin j:
+            // residue r: b = G (c0 + i c1); C - r: G (c0 - i c1); 0: G c0; C / 2: G c1
+            auto weight = [&](int j, int n1, int cy, int cb) -> double {
+                const double gr = Gt[2 * ((size_t)j * P + n1)], gi = Gt[2 * ((size_t)j * P + n1) + 1];
+                const long r = bins[j] % C;
+                if (r == 0 || 2 * r == C) return (cy == 1) == (r != 0) ? (cb == 0 ? gr : gi) : 0.0;
+                if (cy == 0) return cb == 0 ? gr : gi;
+                const double sg = 2 * r < C ? 1.0 : -1.0;
+                return cb == 0 ? -sg * gi : sg * gr;
+            };
+            // outer tables scaled by 2^wexp so that no weight exceeds 2^15; the
+            // adjoint's sums over a slot's bins are below 2^zsum of that
+            double wmax = 0, gsum = 0;
+            for (int q = 0; q < f.R; ++q) {
+                double sum = 0;
+                for (int j : qb[q]) {
+                    double d = 1.0;
+                    if (g->rx_filter) d = std::hypot((double)g->rx_filter[2 * j], (double)g->rx_filter[2 * j + 1]);
+                    wmax = std::max(wmax, d * inv);
+                    sum += 1.4142136 * d * inv;      // |re| + |im| of a weight
+                }
+                gsum = std::max(gsum, sum);
+            }
+            int wexp = 0, zsum = 0;
+            if (wmax > 0) {
+                std::frexp(wmax * 1.0000001, &wexp);
+                wexp = 15 - wexp;
+                std::frexp(std::ldexp(gsum, wexp), &zsum);
+            }
+            f.w_exp = wexp;
+            f.z_scale = (float)std::ldexp(1.0, -zsum);
+            f.z_exp = wexp - zsum;
+            // forward outer B operand [unit][8-phase stage][hi, lo]: k = (column of
+            // Y = l / 32, phase 8 stg + e), column l % 32 = (bin of the unit, re/im)
+            const int nst8 = (P + 7) / 8;
+            fwf.assign((size_t)f.U * nst8 * 1024, 0);
+            for (int u = 0; u < f.U; ++u)
+                for (int n1 = 0; n1 < P; ++n1)
+                    for (int l = 0; l < 64; ++l) {
+                        const int col = l % 32, jb = fubin[(size_t)u * 16 + col / 2];
+                        if (jb < 0) continue;
+                        const size_t o = (((size_t)u * nst8 + n1 / 8) * 2 * 64 + l) * 8 + n1 % 8;
+                        half_pair(std::ldexp(weight(jb, n1, l / 32, col % 2), wexp), fwf[o], fwf[o + 512]);
+                    }
+            // adjoint outer A operand [slot][16-phase stage][bin step][hi, lo]: row
+            // l % 32 = (phase 16 stg + row / 2, column of Z = row % 2), k = (bin
+            // 8 ks + 4 (l / 32) + e / 2, re/im = e % 2)
+            fwa.assign((size_t)f.R * f.nzstage * (QM / 8) * 1024, 0);
+            for (int q = 0; q < f.R; ++q)
+                for (int stg = 0; stg < f.nzstage; ++stg)
+                    for (int ks = 0; ks < QM / 8; ++ks)
+                        for (int l = 0; l < 64; ++l)
+                            for (int e2 = 0; e2 < 8; ++e2) {
+                                const int jb = fqbin[(size_t)q * QM + 8 * ks + 4 * (l / 32) + e2 / 2];
+                                const int n1 = 16 * stg + (l % 32) / 2;
+                                if (jb < 0 || n1 >= P) continue;
+                                const size_t o =
+                                    ((((size_t)q * f.nzstage + stg) * (QM / 8) + ks) * 2 * 64 + l) * 8 + e2;
+                                half_pair(std::ldexp(weight(jb, n1, l % 2, e2 % 2), wexp), fwa[o], fwa[o + 512]);
+                            }
+        }
+    }
+
     // band DFT F[n][c] (real columns: 2j = Re, 2j+1 = Im)
-    std::vector<double> F((size_t)TP * NBP2, 0.0);
-    {
+    // -- not for a plan whose only signal stage is the factored one
+    const bool precomp = precisions & (1 << MPI3D_PRECOMPOSED), mixed = precisions & (1 << MPI3D_MIXED);
+    const bool dense = !pl->fac.on;      // the dense FP32 kernels' tables
+    std::vector<double> F;
+    if (dense || mixed || precomp) {
+        F.assign((size_t)TP * NBP2, 0.0);
         const double inv = 1.0 / std::sqrt((double)T);
         for (int j = 0; j < NB; ++j) {
             double dre = 1.0, dim = 0.0;
             if (g->rx_filter) { dre = g->rx_filter[2 * j]; dim = g->rx_filter[2 * j + 1]; }
-            if (!std::isfinite(dre) || !std::isfinite(dim)) { delete pl; return MPI3D_EINVAL; }
             for (int n = 0; n < T; ++n) {
                 long ph = (long)(((unsigned long long)bins[j] * (unsigned long long)n) % (unsigned long long)T);
                 double a = 2.0 * kPi * (double)ph / T;
@@ -459,7 +860,6 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
 
     // precomposed line matrices Gt[p][c] = sum_n K[n][p] F[n][c] (the whole
     // A_DC of one line, c_A aside), one per PSF table, float64 accumulation
-    const bool precomp = precisions & (1 << MPI3D_PRECOMPOSED);
     std::vector<float> gt;
     pl->gt_elems = (size_t)NUP * 2 * NB;
     if (precomp) {
@@ -481,198 +881,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         }
     }
 
-    // ---- band DFT factored over drive cycles (FP32) --------------------------
-    // t = n1 + P n2 (T = C P, C = 32 or 64): the kept bin omega_j
-    // contributes e^{2 pi i omega_j n1 / T} e^{2 pi i (omega_j mod C) n2 / C},
-    // so the forward first sums each phase n1's C cycles against the R distinct
-    // residues (omega_j mod C), then each bin's P phases.  Taken when its MFMA
-    // work per line, T (n_up + 32 rct) + 64 P U, is under 3/4 of the dense
-    // T (n_up + nbp2); C minimises it.
-    std::vector<float> fkf, fka, fef, fea, fwf, fwa;
-    std::vector<int> fuq, fubin, fqbin, fqsteps;
-    if ((precisions & (1 << MPI3D_FP32)) && !pl->fused && pl->n_passes == 1 && pl->n_line_groups == 1 &&
-        n_ktab == 1 && T % 32 == 0) {
-        double best = 0.75 * (double)T * (NUP + NBP2);
-        int bestC = 0;
-        for (int C = 32; C <= T && C <= 64; C += 32) {
-            if (T % C) continue;
-            std::vector<int> cnt(C, 0);
-            for (int j = 0; j < NB; ++j) ++cnt[bins[j] % C];
-            int R = 0, U = 0, mx = 0;
-            for (int r = 0; r < C; ++r)
-                if (cnt[r]) {
-                    ++R;
-                    U += (cnt[r] + 15) / 16;
-                    mx = std::max(mx, cnt[r]);
-                }
-            const int zst = (R + 3) / 4 * 4, rct = (2 * zst + 31) / 32;
-            const int P = T / C;
-            if (R > 24 || mx > kQMax || U > 40 * kMaxFacSplit || !fac_supported(NUP, rct, zst, C / 32) ||
-                (double)((pl->L + 31) / 32 * 32 + 1) * P * 2 * zst >= 2147483647.0)
-                continue;
-            const double cost = (double)T * (NUP + 32 * rct) + 64.0 * (P + 7) / 8 * 8 * U;
-            if (cost < best) {
-                best = cost;
-                bestC = C;
-            }
-        }
-        if (bestC) {
-            mpi3d_plan::Fac &f = pl->fac;
-            f.on = true;
-            f.C = bestC;
-            f.P = T / bestC;
-            f.Pp = (f.P + 7) / 8 * 8;
-            f.cj = bestC / 32;
-            f.nzstage = (f.P + 15) / 16;
-            // Residue order: the adjoint outer sum's wave w takes residues
-            // w, w + 8, w + 16 (so waves w < R % 8 take one more when 8 does
-            // not divide R) and spends a step per bin, so residues are dealt
-            // largest first to the least loaded wave with room, and numbered
-            // by (wave, turn).  Units: a residue's bins (ascending) 16 at a time.
-            std::vector<int> cnt(bestC, 0), byc;
-            for (int j = 0; j < NB; ++j) ++cnt[bins[j] % bestC];
-            for (int r = 0; r < bestC; ++r)
-                if (cnt[r]) byc.push_back(r);
-            std::stable_sort(byc.begin(), byc.end(), [&](int x, int y) { return cnt[x] > cnt[y]; });
-            const int nw = kFacInWaves, nr = (int)byc.size();
-            std::vector<std::vector<int>> wres(nw);
-            std::vector<int> load(nw, 0), room(nw);
-            for (int w = 0; w < nw; ++w) room[w] = nr / nw + (w < nr % nw ? 1 : 0);
-            for (int r : byc) {
-                int best = -1;
-                for (int w = 0; w < nw; ++w)
-                    if ((int)wres[w].size() < room[w] && (best < 0 || load[w] < load[best])) best = w;
-                wres[best].push_back(r);
-                load[best] += (cnt[r] + 3) / 4 * 4;
-            }
-            std::vector<int> slot(bestC, -1), res(byc.size(), -1);
-            for (int w = 0; w < nw; ++w)
-                for (size_t i = 0; i < wres[w].size(); ++i) {
-                    const int q = w + nw * (int)i;
-                    res[q] = wres[w][i];
-                    slot[wres[w][i]] = q;
-                }
-            f.R = (int)res.size();
-            f.zst = (f.R + 3) / 4 * 4;
-            f.rct = (2 * f.zst + 31) / 32;
-            std::vector<std::vector<int>> qb(f.R);
-            for (int j = 0; j < NB; ++j) qb[slot[bins[j] % bestC]].push_back(j);
-            fqbin.assign((size_t)f.R * kQMax, -1);
-            fqsteps.assign(f.R, 0);
-            for (int q = 0; q < f.R; ++q) {
-                for (size_t i = 0; i < qb[q].size(); ++i) fqbin[(size_t)q * kQMax + i] = qb[q][i];
-                fqsteps[q] = ((int)qb[q].size() + 3) / 4 * 4;
-                for (size_t i0 = 0; i0 < qb[q].size(); i0 += 16) {
-                    fuq.push_back(q);
-                    for (size_t i = 0; i < 16; ++i) fubin.push_back(i0 + i < qb[q].size() ? qb[q][i0 + i] : -1);
-                }
-            }
-            f.U = (int)fuq.size();
-            f.usplit = (f.U + 39) / 40;
-            // the outer sums' blocks: one per line tile (and unit split); small
-            // scans also split the phase stages so about 256 blocks run
-            const long tiles = (pl->L + 31) / 32;
-            f.psplit = (int)std::max<long>(1, std::min<long>({4, 256 / (tiles * f.usplit), (f.P + 7) / 8}));
-            f.zsplit = (int)std::max<long>(1, std::min<long>({4, 256 / tiles, (f.P + 15) / 16}));
-            // phase ranges of the line-tile kernels (8 tiles a block, one block a
-            // CU): the fewest splits within 2% of the best time, counted as
-            // rounds of 256 blocks times the phases of the longest range
-            auto splits = [&](int waves) {
-                const long tgroups = ((pl->L + 31) / 32 + waves - 1) / waves;
-                auto per_phase = [&](int ns) {
-                    return (double)((tgroups * ns + 255) / 256) * (double)((f.P + ns - 1) / ns) / f.P;
-                };
-                double pbest = 1e30;
-                for (int ns = 1; ns <= std::min(f.P, 64); ++ns) pbest = std::min(pbest, per_phase(ns));
-                int ns = 1;
-                while (ns < std::min(f.P, 64) && per_phase(ns) > 1.02 * pbest) ++ns;
-                return ns;
-            };
-            f.nsplit = splits(kFacWavesFwd);
-            f.nsplit_adj = splits(kFacWavesAdj);
-            // tables
-            const int C = bestC, P = f.P, CJ = f.cj, ZST = f.zst, RCT = f.rct, YC = 2 * ZST;
-            auto tperm = [](int s2, int h) { return 8 * (s2 / 4) + 4 * h + (s2 % 4); };
-            auto tof = [&](int c, int i) { return (c / CJ) + P * (32 * (c % CJ) + i); };   // chunk row -> time
-            const double *K0 = &K[0];
-            fkf.assign(KE, 0.f);
-            fka.assign(KE, 0.f);
-            for (int c = 0; c < P * CJ; ++c) {
-                for (int st = 0; st < NUP / 2; ++st)
-                    for (int l = 0; l < 64; ++l)
-                        fkf[(((size_t)c * (NUP / 8) + st / 4) * 64 + l) * 4 + st % 4] =
-                            (float)K0[(size_t)tof(c, l % 32) * NUP + 2 * st + l / 32];
-                for (int pt = 0; pt < NUP / 32; ++pt)
-                    for (int s2 = 0; s2 < 16; ++s2)
-                        for (int l = 0; l < 64; ++l)
-                            fka[((((size_t)c * (NUP / 32) + pt) * 4 + s2 / 4) * 64 + l) * 4 + s2 % 4] =
-                                (float)K0[(size_t)tof(c, tperm(s2, l / 32)) * NUP + 32 * pt + l % 32];
-            }
-            // E[n2][2q] = cos, E[n2][2q + 1] = sin of 2 pi (r_q n2 mod C) / C
-            auto E = [&](int n2, int col) -> double {
-                if (col >= 2 * f.R) return 0.0;
-                const long ph = (long)res[col / 2] * n2 % C;
-                const double a = 2.0 * kPi * (double)ph / C;
-                return col % 2 ? std::sin(a) : std::cos(a);
-            };
-            fef.assign((size_t)C * 32 * RCT, 0.f);
-            for (int j = 0; j < CJ; ++j)
-                for (int g2 = 0; g2 < RCT; ++g2)
-                    for (int s2 = 0; s2 < 16; ++s2)
-                        for (int l = 0; l < 64; ++l)
-                            fef[((((size_t)j * RCT + g2) * 4 + s2 / 4) * 64 + l) * 4 + s2 % 4] =
-                                (float)E(32 * j + tperm(s2, l / 32), 32 * g2 + l % 32);
-            fea.assign((size_t)C * YC, 0.f);
-            for (int j = 0; j < CJ; ++j)
-                for (int st = 0; st < ZST; ++st)
-                    for (int l = 0; l < 64; ++l)
-                        fea[(((size_t)j * (ZST / 4) + st / 4) * 64 + l) * 4 + st % 4] =
-                            (float)E(32 * j + l % 32, 2 * st + l / 32);
-            // G_j[n1] = D_j e^{2 pi i (omega_j n1 mod T) / T} / sqrt(T)
-            const double inv = 1.0 / std::sqrt((double)T);
-            auto G = [&](int j, int n1, double &gr, double &gi) {
-                double dre = 1.0, dim = 0.0;
-                if (g->rx_filter) { dre = g->rx_filter[2 * j]; dim = g->rx_filter[2 * j + 1]; }
-                const long ph = (long)(((unsigned long long)bins[j] * (unsigned long long)n1) % (unsigned long long)T);
-                const double a = 2.0 * kPi * (double)ph / T;
-                gr = (dre * std::cos(a) - dim * std::sin(a)) * inv;
-                gi = (dre * std::sin(a) + dim * std::cos(a)) * inv;
-            };
-            // forward outer B operand: k = (n1 = st, re/im of Y = l / 32), column
-            // l % 32 = (bin slot, re/im of b)
-            fwf.assign((size_t)f.U * f.Pp * 64, 0.f);
-            for (int u = 0; u < f.U; ++u)
-                for (int st = 0; st < P; ++st)
-                    for (int l = 0; l < 64; ++l) {
-                        const int col = l % 32, jb = fubin[(size_t)u * 16 + col / 2];
-                        if (jb < 0) continue;
-                        double gr, gi;
-                        G(jb, st, gr, gi);
-                        const int cy = l / 32, cb = col % 2;
-                        const double v = cb == 0 ? (cy == 0 ? gr : -gi) : (cy == 0 ? gi : gr);
-                        fwf[(((size_t)u * (f.Pp / 4) + st / 4) * 64 + l) * 4 + st % 4] = (float)v;
-                    }
-            // adjoint outer B operand: k = (bin slot st, re/im of the data =
-            // l / 32), column l % 32 = (phase stg 16 + col / 2, re/im of Z)
-            fwa.assign((size_t)f.R * f.nzstage * kQMax * 64, 0.f);
-            for (int q = 0; q < f.R; ++q)
-                for (int stg = 0; stg < f.nzstage; ++stg)
-                    for (int st = 0; st < kQMax; ++st)
-                        for (int l = 0; l < 64; ++l) {
-                            const int jb = fqbin[(size_t)q * kQMax + st], col = l % 32, n1 = 16 * stg + col / 2;
-                            if (jb < 0 || n1 >= P) continue;
-                            double gr, gi;
-                            G(jb, n1, gr, gi);
-                            const int cd = l / 32, cz = col % 2;
-                            const double v = cz == 0 ? (cd == 0 ? gr : gi) : (cd == 0 ? -gi : gr);
-                            fwa[((((size_t)q * f.nzstage + stg) * (kQMax / 4) + st / 4) * 64 + l) * 4 + st % 4] =
-                                (float)v;
-                        }
-        }
-    }
-
     // ---- table layout in one device allocation -----------------------------
-    bool mixed = precisions & (1 << MPI3D_MIXED);
     size_t off = 0;
     char *nullbase = nullptr;
     size_t o_cs, o_ax, o_ay, o_kf, o_ff, o_fa, o_ka, o_kf16 = 0, o_ff16 = 0, o_fa16 = 0, o_ka16 = 0, o_cols = 0, o_bands = 0;
@@ -680,26 +889,25 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     o_cs = place(sizeof(float2) * M);
     o_ax = place(sizeof(float) * M * NU);
     o_ay = place(sizeof(float) * M * NU);
-    o_kf = place(sizeof(float) * KE * n_ktab);
-    o_ff = place(sizeof(float) * (size_t)TP * NBP2);
-    o_fa = place(sizeof(float) * (size_t)TP * NBP2);
-    o_ka = place(sizeof(float) * KE * n_ktab);
+    o_kf = place(dense ? sizeof(float) * KE * n_ktab : 0);
+    o_ff = place(dense ? sizeof(float) * (size_t)TP * NBP2 : 0);
+    o_fa = place(dense ? sizeof(float) * (size_t)TP * NBP2 : 0);
+    o_ka = place(dense ? sizeof(float) * KE * n_ktab : 0);
     const size_t KEF = KE * pl->n_passes * pl->n_line_groups;   // fused tables, all groups
     const size_t o_kff = pl->fused ? place(sizeof(float) * KEF) : 0;
     const size_t o_kaf = pl->fused ? place(sizeof(float) * KEF) : 0;
     const size_t o_gt = precomp ? place(sizeof(float) * gt.size()) : 0;
     const size_t o_gta = precomp ? place(sizeof(float) * gt.size()) : 0;
     const bool fac = pl->fac.on;
-    const size_t o_fkf = fac ? place(sizeof(float) * fkf.size()) : 0;
-    const size_t o_fka = fac ? place(sizeof(float) * fka.size()) : 0;
-    const size_t o_fef = fac ? place(sizeof(float) * fef.size()) : 0;
-    const size_t o_fea = fac ? place(sizeof(float) * fea.size()) : 0;
-    const size_t o_fwf = fac ? place(sizeof(float) * fwf.size()) : 0;
-    const size_t o_fwa = fac ? place(sizeof(float) * fwa.size()) : 0;
-    const size_t o_fuq = fac ? place(sizeof(int) * fuq.size()) : 0;
-    const size_t o_fubin = fac ? place(sizeof(int) * fubin.size()) : 0;
+    const size_t o_fkf = fac ? place(sizeof(_Float16) * fkf.size()) : 0;
+    const size_t o_fka = fac ? place(sizeof(_Float16) * fka.size()) : 0;
+    const size_t o_fef = fac ? place(sizeof(_Float16) * fef.size()) : 0;
+    const size_t o_fea = fac ? place(sizeof(_Float16) * fea.size()) : 0;
+    const size_t o_fwf = fac ? place(sizeof(_Float16) * fwf.size()) : 0;
+    const size_t o_fwa = fac ? place(sizeof(_Float16) * fwa.size()) : 0;
+    const size_t o_funit0 = fac ? place(sizeof(int) * funit0.size()) : 0;
     const size_t o_fqbin = fac ? place(sizeof(int) * fqbin.size()) : 0;
-    const size_t o_fqsteps = fac ? place(sizeof(int) * fqsteps.size()) : 0;
+    const size_t o_fbcol = fac ? place(sizeof(int) * fbcol.size()) : 0;
     if (mixed) {
         o_kf16 = place(sizeof(__half) * KE * n_ktab);
         o_ff16 = place(sizeof(__half) * (size_t)TP * NBP2);
@@ -719,9 +927,9 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     //  ka: adj GEMM2 B operand  K[t = 32c + tperm(s, l/32)][32pt + l%32]  [c][pt][s/4][l][s%4]
     // tperm(s, h) = 8(s/4) + 4h + s%4 is the time index that the 32x32 MFMA
     // result layout leaves in register s of lane half h.
-    std::vector<float> kf(KE * n_ktab), ff((size_t)TP * NBP2), fa((size_t)TP * NBP2), ka(KE * n_ktab);
+    std::vector<float> kf(dense ? KE * n_ktab : 0), ff(dense ? (size_t)TP * NBP2 : 0), fa(ff.size()), ka(kf.size());
     auto tperm = [](int s, int h) { return 8 * (s / 4) + 4 * h + (s % 4); };
-    for (int cl = 0; cl < n_ktab; ++cl)
+    for (int cl = 0; dense && cl < n_ktab; ++cl)
         for (int c = 0; c < NC; ++c) {
             const double *Kc = &K[KE * cl];
             float *kfc = &kf[KE * cl], *kac = &ka[KE * cl];
@@ -735,7 +943,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                         kac[((((size_t)c * (NUP / 32) + pt) * 4 + s / 4) * 64 + l) * 4 + s % 4] =
                             (float)Kc[(size_t)(32 * c + tperm(s, l / 32)) * NUP + 32 * pt + l % 32];
         }
-    for (int c = 0; c < NC; ++c) {
+    for (int c = 0; dense && c < NC; ++c) {
         for (int ct = 0; ct < NCT; ++ct)
             for (int s = 0; s < 16; ++s)
                 for (int l = 0; l < 64; ++l)
@@ -845,17 +1053,19 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     pl->cs = (float2 *)(tb + o_cs);
     pl->ax = (float *)(tb + o_ax);
     pl->ay = (float *)(tb + o_ay);
-    pl->kf = (float *)(tb + o_kf);
-    pl->ff = (float *)(tb + o_ff);
-    pl->fa = (float *)(tb + o_fa);
-    pl->ka = (float *)(tb + o_ka);
+    if (dense) {
+        pl->kf = (float *)(tb + o_kf);
+        pl->ff = (float *)(tb + o_ff);
+        pl->fa = (float *)(tb + o_fa);
+        pl->ka = (float *)(tb + o_ka);
+    }
     bool ok = hipMemcpy(pl->cs, cs.data(), sizeof(float2) * M, hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(pl->ax, ax.data(), sizeof(float) * ax.size(), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(pl->ay, ay.data(), sizeof(float) * ay.size(), hipMemcpyHostToDevice) == hipSuccess;
-    ok = ok && hipMemcpy(pl->kf, kf.data(), sizeof(float) * kf.size(), hipMemcpyHostToDevice) == hipSuccess;
-    ok = ok && hipMemcpy(pl->ff, ff.data(), sizeof(float) * ff.size(), hipMemcpyHostToDevice) == hipSuccess;
-    ok = ok && hipMemcpy(pl->fa, fa.data(), sizeof(float) * fa.size(), hipMemcpyHostToDevice) == hipSuccess;
-    ok = ok && hipMemcpy(pl->ka, ka.data(), sizeof(float) * ka.size(), hipMemcpyHostToDevice) == hipSuccess;
+    ok = ok && (!dense || hipMemcpy(pl->kf, kf.data(), sizeof(float) * kf.size(), hipMemcpyHostToDevice) == hipSuccess);
+    ok = ok && (!dense || hipMemcpy(pl->ff, ff.data(), sizeof(float) * ff.size(), hipMemcpyHostToDevice) == hipSuccess);
+    ok = ok && (!dense || hipMemcpy(pl->fa, fa.data(), sizeof(float) * fa.size(), hipMemcpyHostToDevice) == hipSuccess);
+    ok = ok && (!dense || hipMemcpy(pl->ka, ka.data(), sizeof(float) * ka.size(), hipMemcpyHostToDevice) == hipSuccess);
     if (pl->fused) {
         // group g's tables table_g .. table_g + R side by side per time chunk:
         // a chunk of kf / ka holds NUP x 32 floats for detector samples (kf:
@@ -890,10 +1100,9 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         up(f.ea, o_fea, fea);
         up(f.wf, o_fwf, fwf);
         up(f.wa, o_fwa, fwa);
-        up(f.uq, o_fuq, fuq);
-        up(f.ubin, o_fubin, fubin);
+        up(f.unit0, o_funit0, funit0);
         up(f.qbin, o_fqbin, fqbin);
-        up(f.qsteps, o_fqsteps, fqsteps);
+        up(f.bcol, o_fbcol, fbcol);
     }
     if (precomp) {
         pl->gt = (float *)(tb + o_gt);
@@ -929,36 +1138,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     }
 
     // ---- workspace layouts -------------------------------------------------
-    {
-        size_t o = 0;
-        auto put = [&](size_t bytes) { o = align256(o); size_t r = o; o += bytes; return r; };
-        pl->ws_rt = put(sizeof(float) * pl->L * pl->nup);
-        size_t parts = 0;   // split partial sums: forward [splits][L][nbp2], adjoint [splits][groups][L][nup]
-        for (const mpi3d_plan::SigCfg &c : pl->sc)
-            parts = std::max(parts, (size_t)std::max(c.nsplit, c.serve_nsplit) *
-                                        std::max<size_t>(pl->nbp2, (size_t)c.ngroups * pl->nup));
-        size_t part_floats = (size_t)pl->n_passes * pl->L * parts;
-        if (pl->fused)   // one pass; adjoint lines of nupf
-            part_floats = std::max(part_floats, (size_t)pl->L * std::max(pl->scf.nsplit, pl->scf.serve_nsplit) *
-                                                    std::max<size_t>(pl->nbp2, (size_t)pl->nupf));
-        if (pl->fac.on)   // adjoint: nsplit blocks of nup-column lines; forward: psplit of nbp2 columns
-            part_floats = std::max(part_floats, (size_t)std::max(pl->fac.nsplit_adj, pl->fac.psplit) * pl->L *
-                                                    std::max(pl->nup, pl->nbp2));
-        pl->ws_part = put(sizeof(float) * part_floats);
-        pl->ws_norm = put(sizeof(double) * pl->max_parts);
-        // per tensor-PSF pass: the forward's symmetric line sums, their
-        // scales and fp16 operands (one block each without coupling)
-        const size_t np = pl->n_passes;
-        pl->ws_rowscale = put(sizeof(float) * np * pl->L);
-        pl->ws_xb = put(mixed ? sizeof(uint16_t) * pl->nvox : 0);
-        pl->in16_cols = std::max(pl->nup, pl->nbp2);
-        pl->ws_in16 = put(mixed ? sizeof(uint16_t) * np * pl->L * pl->in16_cols : 0);
-        pl->ws_rtb = put(mixed ? sizeof(uint16_t) * pl->L * pl->nup : 0);
-        pl->ws_rtsc = put(mixed ? sizeof(float) * pl->L : 0);
-        pl->ws_sig = put(np > 1 ? sizeof(float) * np * pl->L * pl->nup : 0);
-        pl->ws_fac = put(pl->fac.on ? sizeof(float) * ((pl->L + 31) / 32 * 32 + 1) * pl->fac.P * 2 * pl->fac.zst : 0);
-        pl->op_ws_bytes = align256(o);
-    }
+    op_layout(pl, pl->fac.on);
     {
         size_t o = 0;
         auto put = [&](size_t bytes) { o = align256(o); size_t r = o; o += bytes; return r; };
@@ -1040,6 +1220,6 @@ extern "C" int mpi3d_plan_query(const mpi3d_plan *pl, mpi3d_plan_info *info)
     info->norm_iters = pl->norm_iters;
     info->op_scale = pl->op_scale;
     info->dft_cycles = pl->fac.on ? pl->fac.C : 0;
-    info->dft_residues = pl->fac.on ? pl->fac.R : 0;
+    info->dft_residues = pl->fac.on ? pl->fac.res : 0;
     return MPI3D_OK;
 }

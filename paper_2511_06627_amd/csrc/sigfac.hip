@@ -1,46 +1,57 @@
-// The band DFT factored over drive cycles (FP32, gfx950 v_mfma_f32_32x32x2_f32).
+// The band DFT factored over drive cycles (FP32 results, gfx950
+// v_mfma_f32_32x32x16_f16 on fp16 pairs).
 //
 // The kept bins omega_j (eq. bcompress) are integers, so with time t = n1 + P n2
 // (n1 < P, n2 < C, T = C P) the DFT phase splits exactly:
 //   omega_j t = omega_j n1 + (omega_j mod C) T n2 / C   (mod T),
 // and the band DFT of a line's time signal s (Appendix A, eq. DCmodel)
 //   b[j] = sum_t s[t] D_j e^{+2 pi i omega_j t / T} / sqrt(T)
-// becomes two short sums: a C-point DFT over the drive cycles at the R
-// distinct residues r_q of the kept bins mod C,
-//   Y_q[n1] = sum_n2 s[n1 + P n2] e^{+2 pi i r_q n2 / C},
+// becomes two short sums: a C-point DFT over the drive cycles at the residues
+// r of the kept bins mod C,
+//   Y_r[n1] = sum_n2 s[n1 + P n2] e^{+2 pi i r n2 / C},
 // then, per bin, a P-point sum over the phase within a cycle,
-//   b[j] = sum_n1 G_j[n1] Y_q(j)[n1],   G_j[n1] = D_j e^{+2 pi i omega_j n1 / T} / sqrt(T).
-// When the harmonics are bunched (R small against the 2 nb kept columns) this
-// replaces the T x 2nb contraction by T x 2R and P x 4nb ones.  The adjoint is
-// the exact transpose of both steps.
+//   b[j] = sum_n1 G_j[n1] Y_r(j)[n1],   G_j[n1] = D_j e^{+2 pi i omega_j n1 / T} / sqrt(T).
+// s is real, so Y_{C-r} is the conjugate of Y_r: the two share one slot of two
+// columns (cos, sin), and C = 32 needs 16 slots whatever the bins are.  The
+// adjoint is the exact transpose of both steps.
 //
 // Forward: fac_fwd_kernel runs the PSF contraction of a line tile chunk by
 // chunk (a chunk: 32 cycles n2 of one phase n1, PSF tables with their time
 // rows in that order) and feeds each 32 x 32 (time x line) result straight
 // into the residue DFT (table E), storing the phase sums Y once the C cycles
-// of a phase are in; fac_fwd_out_kernel then forms b per line tile from
-// LDS-staged Y, one 32-column MFMA tile per unit of at most 16 bins of one
-// residue.  Adjoint: fac_adj_in_kernel forms the phase sums Z from the data,
-// fac_adj_kernel runs the residue DFT's transpose and the PSF contraction's
-// transpose, accumulating the lines over its phases (split partial sums
-// added in a fixed order afterwards).  Y and Z are laid out per 32-line tile
-// as [phase][column][line] (Y's columns 2q + re/im, Z's re/im zst + q), the
-// order of an MFMA result's lines.
+// of a phase are in; fac_fwd_out_kernel then forms b, one 32-column MFMA tile
+// per unit of at most 16 bins of one slot.  Adjoint: fac_adj_in_kernel forms
+// the phase sums Z from the data, fac_adj_kernel runs the residue DFT's
+// transpose and the PSF contraction's transpose, accumulating the lines over
+// its phases (split partial sums added in a fixed order afterwards).  Y and Z
+// are laid out per 32-line tile as [phase][column][line] (column 2 slot +
+// cos/sin): lanes are lines in the kernels that write them, so every store and
+// load is whole 128-byte rows.
 //
-// MFMA operand conventions as in sig.hip: lane l supplies A[l % 32][l / 32]
-// and B[l / 32][l % 32]; result register s of lane l holds row
-// 8(s/4) + 4(l/32) + s%4, column l%32.  Every table is pre-swizzled so a lane
-// fetches the operands of four consecutive MFMA steps with one 16-byte load.
+// Every product is of numbers held as two fp16 values (see split8): tables
+// formed in float64, lines scaled by a power of two each.  At 256 x 256 x 128
+// (7680 lines, T = 16384, C = 64, 20 slots) against the same contractions on
+// fp32 MFMA: fac_fwd 715 -> 202 us, fac_adj 654 -> 210, fac_fwd_out 131 -> 74,
+// fac_adj_in 142 -> 104 (1.1 PFLOP/s of fp16 products in the line-tile
+// kernels, as a large fp16 matrix product reaches on this card; the outer sums
+// write and read 315 MB of Y or Z at 3 to 4 TB/s); error of A against float64
+// 4.4e-7 -> 2.7e-7.
+//
+// MFMA operand conventions: lane l supplies A[l % 32][8 (l / 32) + e] and
+// B[8 (l / 32) + e][l % 32], e < 8; result register s of lane l holds row
+// 8(s/4) + 4(l/32) + s%4, column l%32.  Every table is pre-swizzled so a
+// lane's operand is one 16-byte word and a wave's 1 KB fragment is contiguous.
 
 #include "device.h"
 
 namespace mpi3d {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 namespace {
 
-#define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32((a), (b), (c), 0, 0, 0)
+#define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_f16((a), (b), (c), 0, 0, 0)
 
 // Wave position of the two line-tile kernels: a block of WAVES waves covers
 // WAVES consecutive 32-line tiles for one of nsplit ranges of phases n1;
@@ -58,148 +69,69 @@ __device__ __forceinline__ FacPos fac_pos(const FacArgs &a, int nsplit)
     const int tgroups = (a.tiles + WAVES - 1) / WAVES;
     FacPos p;
     p.split = lb / tgroups;
-    p.tile = (lb - p.split * tgroups) * WAVES + (int)(threadIdx.x >> 6);
+    p.tile = (lb - p.split * tgroups) * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     p.n1a = (int)((long)p.split * a.P / nsplit);
     p.n1b = (int)((long)(p.split + 1) * a.P / nsplit);
     return p;
 }
 
-// Forward, per wave: 32 lines, phases [n1a, n1b).  Chunk c = n1 CJ + j holds
-// the times n1 + P (32 j + i), i < 32.  The block's waves walk the same
-// phases, so each PSF-table chunk is staged once per block in LDS (two
-// buffers: chunk c + 1 is stored while chunk c is used, chunk c + 2 already
-// requested into registers; one barrier a chunk), and the residue DFT table
-// sits in LDS for the whole launch.  A wave past the last tile still stages.
-// Y is laid out per line tile as [phase][column][32 lines] (lines past the
-// job hold the results of zero lines): a lane's 16 results of a column are
-// four 16-byte runs of lines.  Each phase's stores are unconditional; columns
-// past yc go to the spare row's first 8 floats.
-template <int NUP, int RCT, int CJ>
-__global__ __launch_bounds__(64 * kFacWavesFwd) void fac_fwd_kernel(FacArgs a)
+// A float as the sum of two fp16 values: hi = rn16(v), lo = rn16(v - hi).
+// With |v| <= 2^15 the pair holds v to 2^-23 relative down to |v| = 2^-3 and
+// to an absolute 2^-25 below (2^-40 of the largest value), so a product taken
+// as hi hi + hi lo + lo hi drops only lo lo, 2^-22 of it at most.
+__device__ __forceinline__ void split8(const float (&v)[8], f16x8 &hi, f16x8 &lo)
 {
-    // LDS: two PSF-table chunk buffers (NK x 64 16-byte words each), then the
-    // residue DFT table (CJ x NE x 64 words)
-    extern __shared__ __align__(16) f32x4 lk[];
-    const FacPos fp = fac_pos<kFacWavesFwd>(a, a.nsplit);
-    if (fp.n1a >= fp.n1b) return;                 // the whole block
-    const bool active = fp.tile < a.tiles;        // a wave past the last tile still stages
-    const SigJob &job = a.job;
-    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
-    const int row0 = fp.tile * 32;
-    const int r = row0 + (lane & 31);
-    const long il = active && r < job.rows ? job_line(job, r) : -1;
-    constexpr int NK = NUP / 8;           // PSF-table words per lane per chunk
-    constexpr int NE = 4 * RCT;           // E-table words per lane per chunk
-    constexpr int CW = NK * 64;           // words per chunk
-    constexpr int KPT = CW / (64 * kFacWavesFwd);   // chunk words a thread stages
-    f32x4 *ebuf = lk + 2 * CW;
-
-    // B operand of the PSF contraction: rho[r][2 st + h]
-    float R[NUP / 2];
-    {
-        const float *rin = (const float *)job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride + h;
 #pragma unroll
-        for (int st = 0; st < NUP / 2; ++st) R[st] = (il >= 0 && 2 * st + h < a.nu) ? rin[2 * st] : 0.f;
-    }
-    // this lane's column of residue tile g in the wave's Y tile, or the spare row
-    float *ycol[RCT];
-    int ystep[RCT], jstep[RCT];
+    for (int e = 0; e < 8; ++e) hi[e] = (_Float16)v[e];
 #pragma unroll
-    for (int g = 0; g < RCT; ++g) {
-        const int col = 32 * g + (lane & 31);
-        const bool ok = col < a.yc;
-        ycol[g] = a.y + (ok ? ((size_t)fp.tile * a.P * a.yc + col) * 32 : (size_t)a.ylines * a.P * a.yc) + 4 * h;
-        ystep[g] = ok ? a.yc * 32 : 0;   // per phase
-        jstep[g] = ok ? 8 : 0;           // per run of 4 lines
-    }
-
-    const f32x4 *kf = (const f32x4 *)job.kf;
-    const f32x4 *ef = (const f32x4 *)a.ef;
-    for (int idx = tid; idx < CJ * NE * 64; idx += 64 * kFacWavesFwd) ebuf[idx] = ef[idx];
-    const int c0 = fp.n1a * CJ, c1 = fp.n1b * CJ;
-    f32x4 pk[KPT];
-    auto chunk_load = [&](int cc) {
-#pragma unroll
-        for (int k = 0; k < KPT; ++k) pk[k] = kf[(size_t)cc * CW + tid + 64 * kFacWavesFwd * k];
-    };
-    auto chunk_store = [&](int buf) {
-#pragma unroll
-        for (int k = 0; k < KPT; ++k) lk[buf * CW + tid + 64 * kFacWavesFwd * k] = pk[k];
-    };
-    chunk_load(c0);
-    chunk_store(c0 & 1);
-    if (c0 + 1 < c1) chunk_load(c0 + 1);
-    f32x16 acc[RCT];
-#pragma unroll
-    for (int g = 0; g < RCT; ++g) acc[g] = 0.f;
-    __syncthreads();
-
-    for (int n1 = fp.n1a; n1 < fp.n1b; ++n1) {
-#pragma unroll
-        for (int j = 0; j < CJ; ++j) {
-            const int c = n1 * CJ + j;
-            if (active) {
-                const f32x4 *kb = lk + (c & 1) * CW + lane;
-                f32x16 S = 0.f;
-#pragma unroll
-                for (int i = 0; i < NK; ++i) {
-                    const f32x4 v = kb[i * 64];
-                    S = MFMA32(v[0], R[4 * i + 0], S);
-                    S = MFMA32(v[1], R[4 * i + 1], S);
-                    S = MFMA32(v[2], R[4 * i + 2], S);
-                    S = MFMA32(v[3], R[4 * i + 3], S);
-                }
-                const f32x4 *eb = ebuf + j * NE * 64 + lane;
-#pragma unroll
-                for (int jj = 0; jj < NE; ++jj) {
-                    const f32x4 v = eb[jj * 64];
-                    const int g = jj / 4, s4 = jj % 4;
-                    acc[g] = MFMA32(S[4 * s4 + 0], v[0], acc[g]);
-                    acc[g] = MFMA32(S[4 * s4 + 1], v[1], acc[g]);
-                    acc[g] = MFMA32(S[4 * s4 + 2], v[2], acc[g]);
-                    acc[g] = MFMA32(S[4 * s4 + 3], v[3], acc[g]);
-                }
-            }
-            // chunk c + 1 goes to the buffer chunk c - 1 left (read by every
-            // wave before the last barrier); chunk c + 2 is requested
-            if (c + 1 < c1) {
-                chunk_store((c + 1) & 1);
-                if (c + 2 < c1) chunk_load(c + 2);
-            }
-            __syncthreads();
-        }
-        if (active) {
-#pragma unroll
-            for (int g = 0; g < RCT; ++g) {
-                float *d = ycol[g] + (size_t)n1 * ystep[g];
-#pragma unroll
-                for (int J = 0; J < 4; ++J)
-                    *reinterpret_cast<f32x4 *>(d + J * jstep[g]) =
-                        f32x4{acc[g][4 * J], acc[g][4 * J + 1], acc[g][4 * J + 2], acc[g][4 * J + 3]};
-                acc[g] = 0.f;
-            }
-        }
-    }
+    for (int e = 0; e < 8; ++e) lo[e] = (_Float16)(v[e] - (float)hi[e]);
 }
 
-// Forward outer sum, one block of kOutWaves waves per 32-line tile, unit
-// split and stage range (partial sums ps).  A stage of kOutStage phases of the
-// tile's Y ([phase][column][32 lines]) is one contiguous block of memory, moved
-// straight to LDS in that order by global_load_lds (16 bytes a lane, no
-// registers; pieces of phases past P read phase P - 1, whose table entries are
-// zero), and a lane's A operands for a stage are 8 single reads (one per
-// phase) that the wave spreads over all 64 banks (32 consecutive lines per
-// half-wave, the halves 32 floats apart).  With three buffers (two where three
-// do not fit) stages s + 1 and s + 2 are in flight while stage s's products
-// run.  Block barriers here carry no memory fence: a fence would wait for
-// every stage in flight; each wave instead waits for its own loads of the next
-// stage (vmcnt) and its LDS reads (lgkmcnt) before the barrier.  Wave w takes
-// units us + usplit (w + kOutWaves i).
-constexpr int kOutStage = 8;
-constexpr int kOutWaves = 8;
-constexpr int kUnitsPerWave = 5;
+// The same pair in one 32-bit word (hi in the low half), and eight of them as
+// MFMA operands.
+__device__ __forceinline__ uint32_t pack_split(float v)
+{
+    const _Float16 hi = (_Float16)v, lo = (_Float16)(v - (float)hi);
+    return (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
+}
+__device__ __forceinline__ void unpack8(const uint32_t (&w)[8], f16x8 &hi, f16x8 &lo)
+{
+    uint32_t a[4], b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        a[e] = __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x05040100);
+        b[e] = __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x07060302);
+    }
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    hi = __builtin_bit_cast(f16x8, u32x4{a[0], a[1], a[2], a[3]});
+    lo = __builtin_bit_cast(f16x8, u32x4{b[0], b[1], b[2], b[3]});
+}
 
-constexpr int fac_out_bufs(int zst) { return 3 * kOutStage * 2 * zst * 32 * 4 <= 160 * 1024 ? 3 : 2; }
+// The exponent e that brings a line of largest magnitude m into [2^14, 2^15)
+// (0 for a line of zeros or with a non-finite entry).
+__device__ __forceinline__ int line_exponent(float m)
+{
+    return m > 0.f && m < __builtin_inff() ? 15 - __builtin_amdgcn_frexp_expf(m) : 0;
+}
+
+// N products whose table operands come from LDS: fragment j is read WIN
+// products ahead of its use, and a scheduling barrier after every product
+// keeps that distance.
+template <int N, int WIN, class Frag, class Prod>
+__device__ __forceinline__ void lds_pipelined(Frag frag, Prod prod)
+{
+    constexpr int W = WIN < N ? WIN : N;
+    f16x8 w[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) w[j] = frag(j);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const f16x8 f = w[j % W];
+        if (j + W < N) w[j % W] = frag(j + W);
+        prod(j, f);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
 
 // s_waitcnt vmcnt(n) lgkmcnt(0) (expcnt not waited for), n < 64
 template <int N>
@@ -211,360 +143,586 @@ __device__ __forceinline__ void wait_vm_lgkm()
 
 __device__ __forceinline__ void block_barrier_nofence() { asm volatile("s_barrier" ::: "memory"); }
 
-// 16 bytes a lane from src to LDS at dst + 16 lane (dst wave-uniform).  A
-// function of its own: written inside the kernel template, this gfx950-only
-// form made the host pass drop the kernel's launch stubs without a message.
-__device__ __forceinline__ void dma16(const float *src, float *dst) { __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0); }
-
-template <int ZST>
-__global__ __launch_bounds__(64 * kOutWaves) void fac_fwd_out_kernel(FacArgs a)
+// 16 bytes a lane from byte voff + soff of the buffer rs to LDS at dst + 16 lane
+// (soff and dst wave-uniform).
+__device__ __forceinline__ void buffer_dma16(__amdgpu_buffer_rsrc_t rs, void *dst, int voff, int soff)
 {
-    extern __shared__ __align__(16) float ys[];
-    constexpr int yc = 2 * ZST, NBUF = fac_out_bufs(ZST);
-    constexpr int bufsz = kOutStage * yc * 32;              // floats of a stage
-    constexpr int RPW = bufsz / (4 * 64 * kOutWaves);       // 64-piece runs a wave moves per stage
-    static_assert(bufsz % (4 * 64 * kOutWaves) == 0, "whole runs");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
-    const int tile = blockIdx.x, us = blockIdx.y, nus = gridDim.y, ps = blockIdx.z;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)dst, 16, voff, soff, 0, 0);
+}
+
+// A raw buffer of `bytes` bytes at p (reads past it return 0).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_table(const void *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+
+// The PSF table of the line-tile kernels in LDS.  A chunk (32 times x NUP
+// samples, hi and lo fragments, 128 NUP bytes) is used by all 8 waves of a
+// block; NS chunks (about 32 KB) make a stage, moved by global_load_lds into
+// three buffers so the stage after next is in flight while one is used, with
+// one barrier a stage.  The barrier carries no fence: each wave waits for its
+// own part of the next stage (every load but the youngest stage's) first.
+template <int NUP>
+struct PsfStage {
+    static constexpr int NS = NUP == 64 ? 4 : NUP == 128 ? 2 : 1;
+    static constexpr int kFragChunk = NUP / 8;                 // 1 KB fragments a chunk (hi, lo)
+    static constexpr int kFrags = NS * kFragChunk;
+    static constexpr int kOps = kFrags / kFacWaves;            // fragments a wave moves per stage
+    static constexpr int kBytes = kFrags * 1024;
+    static_assert(kFrags % kFacWaves == 0, "whole fragments a wave");
+    // the stage from chunk c on (counted from the table at rs); chunks from
+    // nchunks on repeat the last one (unused).  Buffer loads, because the
+    // compiler orders its LDS waits behind global_load_lds as behind flat
+    // accesses and then waits for every LDS read in flight at each use.
+    static __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int c, int nchunks, f16x8 *lds, int buf,
+                                                int wave, int lane)
+    {
+#pragma unroll
+        for (int k = 0; k < kOps; ++k) {
+            const int f = k * kFacWaves + wave;
+            const int cc = min(c + f / kFragChunk, nchunks - 1);
+            buffer_dma16(rs, lds + (buf * kFrags + f) * 64, lane * 16, (cc * kFragChunk + f % kFragChunk) * 1024);
+        }
+    }
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t table(const __half *tab, int c0, int chunks)
+    {
+        return buffer_table((const char *)tab + (size_t)c0 * kFragChunk * 1024, chunks * (kFragChunk * 1024));
+    }
+};
+
+// Forward, per wave: 32 lines, phases [n1a, n1b).  Chunk c = n1 CJ + j holds
+// the times n1 + P (32 j + i), i < 32.  Both contractions run on fp16 MFMA in
+// split form (see split8): the lines scaled by a power of two each, the
+// tables by one for all, three products a fragment.  The fp32 matrix unit has
+// 1/16 of the fp16 rate, so three products cost 3/16 of one fp32 product; the
+// errors against float64 are those of the fp32 form or less, because a step
+// adds 16 products to the accumulator instead of 2.  The (time x line) result
+// of the PSF contraction is split again and is the residue DFT's operand as
+// it stands; that one's result rows are the phase's columns, its lanes lines,
+// so a line's scale is undone by one exponent per lane and Y ([phase][column]
+// [32 lines] per tile) is written in whole 128-byte rows.
+template <int NUP, int ZST, int CJ>
+__global__ __launch_bounds__(64 * kFacWaves, 2) void fac_fwd_kernel(FacArgs a)
+{
+    using Stage = PsfStage<NUP>;
+    constexpr int NS = Stage::NS;
+    constexpr int NKS = NUP / 16;                     // PSF contraction steps
+    constexpr int YC = 2 * ZST, RCT = (YC + 31) / 32; // columns of a phase, 32-column tiles
+    constexpr int NE = RCT * 4;                       // residue table fragments a chunk
+    constexpr int GRP = NS > CJ ? NS : CJ;            // chunks of one loop body
+    extern __shared__ __align__(16) f16x8 lk[];
+    f16x8 *ebuf = lk + 3 * Stage::kFrags * 64;
+    const FacPos fp = fac_pos<kFacWaves>(a, a.nsplit);
+    if (fp.n1a >= fp.n1b) return;                 // the whole block
+    const bool active = fp.tile < a.tiles;        // a wave past the last tile still stages
     const SigJob &job = a.job;
-    const int row0 = tile * 32;
-    // run k of wave w moves floats 4 (64 (kOutWaves k + w) + lane) .. + 3 of the stage
-    int pph[RPW], poff[RPW];
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = fp.tile * 32 + (lane & 31);
+    const long il = active && r < job.rows ? job_line(job, r) : -1;
+    const int c0 = fp.n1a * CJ, c1 = fp.n1b * CJ;
+
+    const __amdgpu_buffer_rsrc_t kf = Stage::table(a.kf, c0, c1 - c0);
+    Stage::load(kf, 0, c1 - c0, lk, 0, wave, lane);
+    Stage::load(kf, NS, c1 - c0, lk, 1, wave, lane);
+    const f16x8 *ef = (const f16x8 *)a.ef;
+    for (int idx = tid; idx < CJ * NE * 64; idx += 64 * kFacWaves) ebuf[idx] = ef[idx];
+
+    // the line: samples 16 ks + 8 h + 0..7, scaled and split
+    f16x8 rh[NKS], rl[NKS];
+    {
+        float v[NKS][8];
+        const float *rin = (const float *)job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride;
+        const bool vec = job.in_stride % 4 == 0 && (uintptr_t)job.in % 16 == 0 && job.in_stride >= NUP;
+        if (vec) {
 #pragma unroll
-    for (int k = 0; k < RPW; ++k) {
-        const int f = 4 * (64 * (kOutWaves * k + wave) + lane);
-        pph[k] = f / (yc * 32);
-        poff[k] = f - pph[k] * (yc * 32);
-    }
-    const float *yt = a.y + (size_t)tile * a.P * yc * 32;
-    auto stage_dma = [&](int stg, int buf) {
+            for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-        for (int k = 0; k < RPW; ++k) {
-            const int n1 = min(stg * kOutStage + pph[k], a.P - 1);
-            dma16(yt + (size_t)n1 * yc * 32 + poff[k], ys + buf * bufsz + 256 * (kOutWaves * k + wave));
+                for (int q = 0; q < 2; ++q) {
+                    const int p = 16 * ks + 8 * h + 4 * q;
+                    const f32x4 w = *reinterpret_cast<const f32x4 *>(rin + p);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[ks][4 * q + e] = il >= 0 && p + e < a.nu ? w[e] : 0.f;
+                }
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int p = 16 * ks + 8 * h + e;
+                    v[ks][e] = il >= 0 && p < a.nu ? rin[p] : 0.f;
+                }
         }
-    };
-    f32x16 acc[kUnitsPerWave];
+        float m = 0.f;
 #pragma unroll
-    for (int i = 0; i < kUnitsPerWave; ++i) acc[i] = 0.f;
-    int uu[kUnitsPerWave], aoff[kUnitsPerWave];
+        for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-    for (int i = 0; i < kUnitsPerWave; ++i) {
-        uu[i] = us + nus * (wave + kOutWaves * i);
-        const int q = a.uq[uu[i] < a.U ? uu[i] : 0];   // unconditional: the five loads overlap
-        const int col = 2 * (uu[i] < a.U ? q : 0) + h;
-        aoff[i] = col * 32 + (lane & 31);
-    }
-    // this block's stages [s0, s1): range ps of psplit
-    const int nst = (a.P + kOutStage - 1) / kOutStage;
-    const int s0 = (int)((long)ps * nst / a.psplit), s1 = (int)((long)(ps + 1) * nst / a.psplit);
-    // table operands of stage n1s / kOutStage for this wave's units
-    auto table_load = [&](int n1s, f32x4 (&b0)[kUnitsPerWave], f32x4 (&b1)[kUnitsPerWave]) {
+            for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[ks][e]));
+        m = fmaxf(m, __shfl_xor(m, 32));
+        const int le = line_exponent(m);
 #pragma unroll
-        for (int i = 0; i < kUnitsPerWave; ++i) {
-            const int u = uu[i] < a.U ? uu[i] : 0;
-            const f32x4 *w = (const f32x4 *)a.wf + ((size_t)u * (a.Pp / 4) + n1s / 4) * 64 + lane;
-            b0[i] = w[0];
-            b1[i] = w[64];
+        for (int ks = 0; ks < NKS; ++ks) {
+            float w[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) w[e] = __builtin_ldexpf(v[ks][e], le);
+            split8(w, rh[ks], rl[ks]);
         }
-    };
-    f32x4 b0[kUnitsPerWave], b1[kUnitsPerWave], n0[kUnitsPerWave], n1v[kUnitsPerWave];
-    table_load(s0 * kOutStage, b0, b1);
-    __builtin_amdgcn_sched_barrier(0);   // ahead of the stage loads: in by the first wait
-    // stages s0 .. s0 + NBUF - 2 requested (stage numbers past the range
-    // repeat its last stage, so every wait below counts the same loads)
+        // (every phase range writes the same exponent)
+        if (active && h == 0) a.lexp[r] = le + a.y_exp;
+    }
+    const float sscale = a.s_scale, yscale = a.y_scale;
+    // this lane's line in the wave's Y tile (column 4 h of each group of 8)
+    uint32_t *yrow = a.y + ((size_t)(active ? fp.tile : 0) * a.P * YC + 4 * h) * 32 + (lane & 31);
+
+    f32x16 acc[RCT];
 #pragma unroll
-    for (int k = 0; k < NBUF - 1; ++k) stage_dma(min(s0 + k, s1 - 1), (s0 + k) % NBUF);
-    wait_vm_lgkm<(NBUF - 2) * RPW>();   // stage s0 is in
+    for (int g = 0; g < RCT; ++g) acc[g] = 0.f;
+    wait_vm_lgkm<Stage::kOps>();     // the first stage (and the table stores) are in
     block_barrier_nofence();
-    for (int stg = s0; stg < s1; ++stg) {
-        const int n1s = stg * kOutStage;
-        table_load(min(n1s + kOutStage, (s1 - 1) * kOutStage), n0, n1v);
-        __builtin_amdgcn_sched_barrier(0);
-        // stage stg + NBUF - 1 to the buffer stage stg - 1 left (every wave is
-        // past its products: the barrier at the end of the last stage)
-        stage_dma(min(stg + NBUF - 1, s1 - 1), (stg + NBUF - 1) % NBUF);
-        __builtin_amdgcn_sched_barrier(0);
+
+    int buf = 0, nbuf = 2;
+    for (int cg = c0; cg < c1; cg += GRP) {
 #pragma unroll
-        for (int i = 0; i < kUnitsPerWave; ++i) {
-            if (uu[i] >= a.U) break;
-            const float *src = ys + (stg % NBUF) * bufsz + aoff[i];
-            float av[kOutStage];
+        for (int k = 0; k < GRP; ++k) {
+            const int c = cg + k;
+            if (k % NS == NS - 1) Stage::load(kf, c - c0 + NS + 1, c1 - c0, lk, nbuf, wave, lane);
+            if (active && (GRP == CJ || c < c1)) {
+                const f16x8 *kb = lk + (buf * Stage::kFrags + (k % NS) * Stage::kFragChunk) * 64 + lane;
+                f32x16 S = 0.f;
+                lds_pipelined<2 * NKS, 6>([&](int i) { return kb[i * 64]; },
+                                          [&](int i, const f16x8 &f) {
+                                              S = MFMA16(f, rh[i / 2], S);
+                                              if (i % 2 == 0) S = MFMA16(f, rl[i / 2], S);
+                                          });
+                f16x8 sh[2], sl[2];
 #pragma unroll
-            for (int k = 0; k < kOutStage; ++k) av[k] = src[k * yc * 32];
-            acc[i] = MFMA32(av[0], b0[i][0], acc[i]);
-            acc[i] = MFMA32(av[1], b0[i][1], acc[i]);
-            acc[i] = MFMA32(av[2], b0[i][2], acc[i]);
-            acc[i] = MFMA32(av[3], b0[i][3], acc[i]);
-            acc[i] = MFMA32(av[4], b1[i][0], acc[i]);
-            acc[i] = MFMA32(av[5], b1[i][1], acc[i]);
-            acc[i] = MFMA32(av[6], b1[i][2], acc[i]);
-            acc[i] = MFMA32(av[7], b1[i][3], acc[i]);
+                for (int q = 0; q < 2; ++q) {
+                    float w[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) w[e] = S[8 * q + e] * sscale;
+                    split8(w, sh[q], sl[q]);
+                }
+                const f16x8 *eb = ebuf + (k % CJ) * NE * 64 + lane;
+#pragma unroll
+                for (int g = 0; g < RCT; ++g)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const f16x8 eh = eb[(g * 4 + q * 2) * 64], el = eb[(g * 4 + q * 2 + 1) * 64];
+                        acc[g] = MFMA16(eh, sh[q], acc[g]);
+                        acc[g] = MFMA16(eh, sl[q], acc[g]);
+                        acc[g] = MFMA16(el, sh[q], acc[g]);
+                    }
+            }
+            if (k % NS == NS - 1) {
+                wait_vm_lgkm<Stage::kOps>();      // the next stage is in, this wave's reads are done
+                block_barrier_nofence();
+                buf = buf == 2 ? 0 : buf + 1;
+                nbuf = nbuf == 2 ? 0 : nbuf + 1;
+            }
+            if (k % CJ == CJ - 1) {
+                if (active && (GRP == CJ || c < c1)) {
+                    uint32_t *d = yrow + (size_t)(c / CJ) * YC * 32;
+#pragma unroll
+                    for (int g = 0; g < RCT; ++g)
+#pragma unroll
+                        for (int s = 0; s < 16; ++s)
+                            if (32 * g + 8 * (s / 4) < YC)
+                                d[(32 * g + 8 * (s / 4) + s % 4) * 32] = pack_split(acc[g][s] * yscale);
+                }
+#pragma unroll
+                for (int g = 0; g < RCT; ++g) acc[g] = 0.f;
+            }
         }
-#pragma unroll
-        for (int i = 0; i < kUnitsPerWave; ++i) {
-            b0[i] = n0[i];
-            b1[i] = n1v[i];
-        }
-        // stage stg + 1 is in (only the NBUF - 2 later stages' loads may be
-        // outstanding), and this wave's LDS reads are done
-        wait_vm_lgkm<(NBUF - 2) * RPW>();
-        block_barrier_nofence();
     }
-    // the repeated last-stage loads still in flight land before the block
-    // ends and its LDS is handed to another block
-    wait_vm_lgkm<0>();
-    // column l%32 of unit u: bin slot col/2, re/im col%2
+    wait_vm_lgkm<0>();   // the repeated loads still in flight land before the LDS is handed on
+}
+
+// Forward outer sum.  One wave: one slot, kOutTiles line tiles, a range of
+// 8-phase stages (partial sums ps); no LDS and no barriers, since every value
+// of Y is read by one wave only.  A step's K = 16 is 8 phases x 2 columns: a
+// lane's operand is 8 packed words of its line, one per phase (two adjacent
+// 128-byte rows a load), and the slot's bins are one or two units of 16 (32
+// result columns, re/im).  The next stage's words and table fragments are
+// requested before a stage's products.  What bounds it: Y from HBM, and the
+// tables from L2 (about as many bytes again for one tile a wave, so a wave
+// takes two and the four waves of a block share the slot, hence its table
+// lines in L1).
+constexpr int kOutTiles = 2;
+constexpr int kOutWaves = 4;
+
+template <int NU>
+struct OutStage {
+    uint32_t y[kOutTiles][8];
+    f16x8 w[NU][2];
+};
+
+template <int NU>
+__device__ __forceinline__ void fwd_out(const FacArgs &a, int q, int t0, int ps)
+{
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const SigJob &job = a.job;
+    const int u0 = a.unit0[q];
+    const int nst = (a.P + 7) / 8;
+    const int s0 = (int)((long)ps * nst / a.psplit), s1 = (int)((long)(ps + 1) * nst / a.psplit);
+    const uint32_t *y0 = a.y + ((size_t)t0 * a.P * a.yc + 2 * q) * 32 + lane;   // column 2 q + h, line l % 32
+    const size_t tstep = t0 + 1 < a.tiles ? (size_t)a.P * a.yc * 32 : 0;        // (a missing second tile: the first)
+    const f16x8 *w0 = (const f16x8 *)a.wf + (size_t)u0 * nst * 128 + lane;
+    f32x16 acc[kOutTiles][NU];
 #pragma unroll
-    for (int i = 0; i < kUnitsPerWave; ++i) {
-        const int u = uu[i];
-        if (u >= a.U) break;
-        const int col = lane & 31;
-        const int jb = a.ubin[u * 16 + col / 2];
-        if (jb < 0) continue;
-        const int oc = 2 * jb + (col & 1);
+    for (int t = 0; t < kOutTiles; ++t)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) acc[t][u] = 0.f;
+    // phases past P repeat the last one (their table entries are zero)
+    auto load = [&](int stg, OutStage<NU> &g) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t *yp = y0 + (size_t)min(8 * stg + j, a.P - 1) * a.yc * 32;
+#pragma unroll
+            for (int t = 0; t < kOutTiles; ++t) g.y[t][j] = yp[t * tstep];
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) g.w[u][p] = w0[((size_t)u * nst + stg) * 128 + p * 64];
+    };
+    auto products = [&](const OutStage<NU> &g) {
+#pragma unroll
+        for (int t = 0; t < kOutTiles; ++t) {
+            f16x8 yh, yl;
+            unpack8(g.y[t], yh, yl);
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                acc[t][u] = MFMA16(yh, g.w[u][0], acc[t][u]);
+                acc[t][u] = MFMA16(yl, g.w[u][0], acc[t][u]);
+                acc[t][u] = MFMA16(yh, g.w[u][1], acc[t][u]);
+            }
+        }
+    };
+    int e[kOutTiles][16];
+#pragma unroll
+    for (int t = 0; t < kOutTiles; ++t)
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+            e[t][j] = a.lexp[min(t0 + t, a.tiles - 1) * 32 + 4 * h + 8 * (j / 4) + j % 4] + a.w_exp;
+    OutStage<NU> g0, g1;
+    load(s0, g0);
+    int stg = s0;
+    for (; stg + 1 < s1; stg += 2) {
+        load(stg + 1, g1);
+        __builtin_amdgcn_sched_barrier(0);
+        products(g0);
+        load(min(stg + 2, s1 - 1), g0);
+        __builtin_amdgcn_sched_barrier(0);
+        products(g1);
+    }
+    if (stg < s1) products(g0);
+    // rows: lines 8 (j / 4) + 4 h + j % 4; columns: the unit's 32
+#pragma unroll
+    for (int t = 0; t < kOutTiles; ++t) {
+        const int row0 = (t0 + t) * 32 + 4 * h;
+        if (t0 + t >= a.tiles) break;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int row = row0 + 8 * (j / 4) + 4 * h + (j % 4);
-            if (row < job.rows) job.part[ps * a.fwd_part_stride + (size_t)job_line(job, row) * a.nbp2 + oc] = acc[i][j];
+            const int row = row0 + 8 * (j / 4) + j % 4;
+            if (row >= job.rows) continue;
+            float *o = job.part + ps * a.fwd_part_stride + (size_t)job_line(job, row) * a.ucols + u0 * 32 + (lane & 31);
+#pragma unroll
+            for (int u = 0; u < NU; ++u) o[32 * u] = __builtin_ldexpf(acc[t][u][j], -e[t][j]);
         }
     }
 }
 
-// Adjoint outer sum: Z from the data, one block of kInWaves waves per 32-line
-// tile and stage range; stages of 16 phases (a 32-column MFMA tile: phase
-// col/2, re/im col%2).  Z is laid out per line tile as [phase][re/im][q][32
-// lines], the MFMA result's own order: a lane's 16 results for residue q are
-// four runs of four consecutive lines, written as 16-byte stores straight from
-// the accumulator (no LDS, no barriers).  Wave w takes residue slots
-// w + kInWaves i (the plan numbers the residues so the waves' bin counts
-// balance); slots in [R, zst) are written as zeros, and slots past zst and
-// phases past P go to the spare row, so every stage issues the same stores and
-// its products wait for its own table loads, never for earlier stores.  The
-// data operands (the bins of the wave's residues, up to kQMax steps each) stay
-// in registers, and each stage's table operands are requested during the
-// stage before.
-constexpr int kZStage = 16;
-constexpr int kWaitVmcnt0 = 0x0f70;   // s_waitcnt vmcnt(0), expcnt and lgkmcnt not waited for
-constexpr int kInWaves = kFacInWaves;
-constexpr int kResPerWave = 3;
-
-__global__ __launch_bounds__(64 * kInWaves) void fac_adj_in_kernel(FacArgs a)
+__global__ __launch_bounds__(64 * kOutWaves) void fac_fwd_out_kernel(FacArgs a)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
+    const int t0 = kOutTiles * (blockIdx.x * kOutWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    const int q = blockIdx.y;
+    if (t0 >= a.tiles) return;
+    if (a.unit0[q + 1] - a.unit0[q] == 1)
+        fwd_out<1>(a, q, t0, blockIdx.z);
+    else
+        fwd_out<2>(a, q, t0, blockIdx.z);
+}
+
+// Adjoint outer sum: Z from the data, one block of kInWaves waves per 32-line
+// tile and range of 16-phase stages.  Wave w takes slots w + kInWaves i (the
+// plan numbers the slots so the waves' bin counts balance) and holds their
+// bins of the tile's lines as split B operands (KST steps of 8 bins, re/im);
+// per stage and slot the table's 32 rows (16 phases x 2 columns) times these
+// give the slot's Z, whose lanes are lines: packed words stored in whole
+// 128-byte rows.  No LDS in the loop and no barriers; the next stage's table
+// fragments are requested before a stage's products, and slots in [R, zst)
+// are written as zeros (the spare row takes the stores of slots past zst, so
+// every stage issues the same stores).  What bounds it: Z to HBM, and the
+// tables from L2.  RPW slots a wave of KST steps: 16 slots of up to 32 bins
+// or 24 of up to 24 -- what the registers of two waves a SIMD hold.
+constexpr int kInWaves = kFacInWaves;
+
+template <int RPW, int KST>
+__global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
+{
+    __shared__ float lmax[kInWaves][32];
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = blockIdx.x, zsp = blockIdx.y;
     const SigJob &job = a.job;
     const int row0 = tile * 32;
     const int r = row0 + (lane & 31);
     const long il = r < job.rows ? job_line(job, r) : -1;
-    const int zst = a.zst;
-    int qq[kResPerWave], qs[kResPerWave];
-#pragma unroll
-    for (int i = 0; i < kResPerWave; ++i) {
-        qq[i] = wave + kInWaves * i;
-        qs[i] = qq[i] < a.R ? a.qsteps[qq[i]] : 0;
-    }
-    // A operands: y[r][2 qbin[q][st] + h].  Per residue the bin numbers are
-    // requested together, then the data (clamped addresses, masked values), so
-    // the loads overlap instead of each data load waiting for its bin number.
-    float Yv[kResPerWave][kQMax];
-    {
-        const float *yin = (const float *)job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride + h;
-#pragma unroll
-        for (int i = 0; i < kResPerWave; ++i) {
-            const int *qb = a.qbin + (qq[i] < a.R ? qq[i] : 0) * kQMax;
-            int jb[kQMax];
-#pragma unroll
-            for (int st = 0; st < kQMax; ++st) jb[st] = qb[st];
-#pragma unroll
-            for (int st = 0; st < kQMax; ++st) {
-                const bool ok = qq[i] < a.R && il >= 0 && jb[st] >= 0;
-                const float v = yin[2 * (jb[st] >= 0 ? jb[st] : 0)];
-                Yv[i][st] = ok ? v : 0.f;
-            }
-        }
-    }
+    constexpr int QM = 8 * KST;
     // this block's stages [s0, s1): range zsp of zsplit
-    const int nst = (a.P + kZStage - 1) / kZStage;
+    const int nst = a.nzstage;
     const int s0 = (int)((long)zsp * nst / a.zsplit), s1 = (int)((long)(zsp + 1) * nst / a.zsplit);
-    // table operands of stage stg for this wave's residues
-    auto table_load = [&](int stg, f32x4 (&b)[kResPerWave][kQMax / 4]) {
+    const int sfull = min(s1, a.P / 16);          // stages of 16 phases
+    const float zscale = a.z_scale;
+    auto table_load = [&](int stg, f16x8 (&t)[RPW][KST][2]) {
 #pragma unroll
-        for (int i = 0; i < kResPerWave; ++i) {
-            const int q = qq[i] < a.R ? qq[i] : 0;
-            const f32x4 *w = (const f32x4 *)a.wa + ((size_t)(q * a.nzstage + stg) * (kQMax / 4)) * 64 + lane;
+        for (int i = 0; i < RPW; ++i) {
+            const int q = wave + kInWaves * i;
+            const f16x8 *w = (const f16x8 *)a.wa + ((size_t)((q < a.R ? q : 0) * nst + stg) * KST) * 128 + lane;
 #pragma unroll
-            for (int s4 = 0; s4 < kQMax / 4; ++s4) b[i][s4] = w[s4 * 64];
+            for (int ks = 0; ks < KST; ++ks)
+#pragma unroll
+                for (int p = 0; p < 2; ++p) t[i][ks][p] = w[(2 * ks + p) * 64];
         }
     };
-    // this tile's Z, and the spare row (phase 0) for the stores that carry nothing
-    float *const zt = a.y + (size_t)tile * 32 * a.P * 2 * zst + 4 * h;
-    float *const spare = a.y + (size_t)a.ylines * a.P * 2 * zst + 4 * h;
-    const int col = lane & 31, n1l = col >> 1, cr = col & 1;
-    f32x4 b[kResPerWave][kQMax / 4], bn[kResPerWave][kQMax / 4];
-    table_load(s0, b);
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);   // (so no stage waits for an earlier stage's stores)
-    for (int stg = s0; stg < s1; ++stg) {
-        table_load(min(stg + 1, s1 - 1), bn);   // the next stage's, during this one
-        const int n1 = stg * kZStage + n1l;
+    f16x8 ta[RPW][KST][2], tb[RPW][KST][2];
+    table_load(s0, ta);
+    // B operands: bins 8 ks + 4 h + 0..3 of the wave's slots, re/im.  The bin
+    // numbers are requested together, then the data (clamped addresses,
+    // masked values), so the loads overlap.
+    f16x8 bh[RPW][KST], bl[RPW][KST];
+    {
+        float v[RPW][KST][8];
+        const float *yin = (const float *)job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride;
 #pragma unroll
-        for (int i = 0; i < kResPerWave; ++i) {
+        for (int i = 0; i < RPW; ++i) {
+            const int q = wave + kInWaves * i;
+            const int *qb = a.qbin + (q < a.R ? q : 0) * QM + 4 * h;
+            int jb[KST][4];
+#pragma unroll
+            for (int ks = 0; ks < KST; ++ks)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) jb[ks][e] = qb[8 * ks + e];
+#pragma unroll
+            for (int ks = 0; ks < KST; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int j = jb[ks][e / 2];
+                    const bool ok = q < a.R && il >= 0 && j >= 0;
+                    const float w = yin[2 * max(j, 0) + e % 2];
+                    v[i][ks][e] = ok ? w : 0.f;
+                }
+        }
+        float m = 0.f;
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+#pragma unroll
+            for (int ks = 0; ks < KST; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[i][ks][e]));
+        m = fmaxf(m, __shfl_xor(m, 32));
+        if (lane < 32) lmax[wave][lane] = m;
+        __syncthreads();
+        m = 0.f;
+#pragma unroll
+        for (int w = 0; w < kInWaves; ++w) m = fmaxf(m, lmax[w][lane & 31]);
+        const int le = line_exponent(m);
+        if (wave == 0 && lane < 32) a.lexp[r] = le + a.z_exp;   // (every stage range writes the same)
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+#pragma unroll
+            for (int ks = 0; ks < KST; ++ks) {
+                float w[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = __builtin_ldexpf(v[i][ks][e], le);
+                split8(w, bh[i][ks], bl[i][ks]);
+            }
+    }
+    uint32_t *const zt = a.y + (size_t)tile * 32 * a.P * a.yc;
+    uint32_t *const spare = a.y + (size_t)a.ylines * a.P * a.yc;
+    // result row 8 (s / 4) + 4 h + s % 4: phase row / 2, column row % 2
+    auto stage = [&](int stg, const f16x8 (&t)[RPW][KST][2], bool full) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            const int q = wave + kInWaves * i;
             f32x16 acc = 0.f;
-            if (qq[i] < a.R) {
 #pragma unroll
-                for (int s4 = 0; s4 < kQMax / 4; ++s4) {
-                    if (4 * s4 >= qs[i]) break;
-                    acc = MFMA32(Yv[i][4 * s4 + 0], b[i][s4][0], acc);
-                    acc = MFMA32(Yv[i][4 * s4 + 1], b[i][s4][1], acc);
-                    acc = MFMA32(Yv[i][4 * s4 + 2], b[i][s4][2], acc);
-                    acc = MFMA32(Yv[i][4 * s4 + 3], b[i][s4][3], acc);
+            for (int ks = 0; ks < KST; ++ks) {
+                acc = MFMA16(t[i][ks][0], bh[i][ks], acc);
+                acc = MFMA16(t[i][ks][0], bl[i][ks], acc);
+                acc = MFMA16(t[i][ks][1], bh[i][ks], acc);
+            }
+            if (full) {
+                uint32_t *d = (q < a.zst ? zt + ((size_t)16 * stg * a.yc + 2 * q) * 32 : spare);
+                const int ph = q < a.zst ? a.yc * 32 : 0;   // words per phase
+                d += (size_t)2 * h * ph + (lane & 31);
+#pragma unroll
+                for (int s = 0; s < 16; ++s)
+                    d[(4 * (s / 4) + (s % 4) / 2) * ph + (s % 2) * 32] = q < a.R ? pack_split(acc[s] * zscale) : 0u;
+            } else if (q < a.zst) {
+#pragma unroll
+                for (int s = 0; s < 16; ++s) {
+                    const int n1 = 16 * stg + 4 * (s / 4) + 2 * h + (s % 4) / 2;
+                    if (n1 < a.P)
+                        zt[((size_t)n1 * a.yc + 2 * q + s % 2) * 32 + (lane & 31)] =
+                            q < a.R ? pack_split(acc[s] * zscale) : 0u;
                 }
             }
-            // lines 8 J + 4 h .. + 3 of column (n1, re/im cr), residue slot qq[i];
-            // the stores that carry nothing all go to the spare row's first 8 floats
-            const bool real = n1 < a.P && qq[i] < zst;
-            float *d = real ? zt + ((size_t)(n1 * 2 + cr) * zst + qq[i]) * 32 : spare;
-            const int js = real ? 8 : 0;
-#pragma unroll
-            for (int J = 0; J < 4; ++J)
-                *reinterpret_cast<f32x4 *>(d + js * J) = f32x4{acc[4 * J], acc[4 * J + 1], acc[4 * J + 2], acc[4 * J + 3]};
         }
-#pragma unroll
-        for (int i = 0; i < kResPerWave; ++i)
-#pragma unroll
-            for (int s4 = 0; s4 < kQMax / 4; ++s4) b[i][s4] = bn[i][s4];
+    };
+    int stg = s0;
+    for (; stg + 1 < sfull; stg += 2) {
+        table_load(stg + 1, tb);
+        __builtin_amdgcn_sched_barrier(0);
+        stage(stg, ta, true);
+        table_load(min(stg + 2, s1 - 1), ta);
+        __builtin_amdgcn_sched_barrier(0);
+        stage(stg + 1, tb, true);
+    }
+    if (stg < sfull) {
+        table_load(min(stg + 1, s1 - 1), tb);
+        stage(stg, ta, true);
+        if (stg + 1 < s1) stage(stg + 1, tb, false);
+    } else if (stg < s1) {
+        stage(stg, ta, false);
     }
 }
 
 // Adjoint, per wave: 32 lines, phases [n1a, n1b): for each chunk the residue
-// DFT's transpose (A = E[time n2][col], B = Z[line][col]) then the PSF
+// DFT's transpose (A = E[time n2][column], B = Z[column][line]) then the PSF
 // contraction's transpose into the lines; split partial sums per phase range.
-// The PSF-table chunks are staged once per block in LDS as in the forward,
-// the residue DFT table sits in LDS, and the next phase's Z operands are
-// requested before its CJ chunks.
+// Split fp16 products and PSF-table stages as in the forward; Z comes in split
+// pairs scaled by a power of two per line (lexp, undone in the partial sums),
+// the next phase's words being requested before a phase's chunks.
 template <int NUP, int ZST, int CJ>
-__global__ __launch_bounds__(64 * kFacWavesAdj) void fac_adj_kernel(FacArgs a)
+__global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
 {
-    extern __shared__ __align__(16) f32x4 lk[];
-    const FacPos fp = fac_pos<kFacWavesAdj>(a, a.nsplit_adj);
+    using Stage = PsfStage<NUP>;
+    constexpr int NS = Stage::NS;
+    constexpr int PT = NUP / 32;          // detector tiles
+    constexpr int ZC = 2 * ZST, NZS = (ZC + 15) / 16;   // columns of a phase, steps of the residue DFT
+    constexpr int NE = 2 * NZS;           // residue table fragments a chunk
+    constexpr int GRP = NS > CJ ? NS : CJ;
+    extern __shared__ __align__(16) f16x8 lk[];
+    f16x8 *ebuf = lk + 3 * Stage::kFrags * 64;
+    const FacPos fp = fac_pos<kFacWaves>(a, a.nsplit_adj);
     if (fp.n1a >= fp.n1b) return;                 // the whole block
     const bool active = fp.tile < a.tiles;        // a wave past the last tile still stages
     const SigJob &job = a.job;
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
-    const int row0 = fp.tile * 32;
-    const int r = row0 + (lane & 31);
-    constexpr int PT = NUP / 32;          // detector tiles
-    constexpr int NE = ZST / 4;           // E-table words per lane per chunk
-    constexpr int NK = 4 * PT;            // PSF-table words per lane per chunk
-    constexpr int CW = NK * 64;           // words per chunk
-    constexpr int KPT = CW / (64 * kFacWavesAdj);
-    constexpr int ZC = 2 * ZST;
-    f32x4 *ebuf = lk + 2 * CW;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c0 = fp.n1a * CJ, c1 = fp.n1b * CJ;
 
     f32x16 racc[PT];
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) racc[pt] = 0.f;
-    const f32x4 *ka = (const f32x4 *)job.ka;
-    const f32x4 *ea = (const f32x4 *)a.ea;
-    for (int idx = tid; idx < CJ * NE * 64; idx += 64 * kFacWavesAdj) ebuf[idx] = ea[idx];
-    // B operand of the residue DFT's transpose: Z of this line tile, laid out
-    // [phase][re/im][q][32 lines]: line r, half h, columns st < ZST (lines past
-    // the job hold zeros).  A lane's ZST values of a phase are single floats
-    // 128 bytes apart; the wave's loads of one st are two 128-byte runs.
-    const float *zrow = a.y + (size_t)(active ? fp.tile : 0) * 32 * a.P * ZC + h * ZST * 32 + (lane & 31);
-    auto zload = [&](int n1, float (&zb)[ZST]) {
+    const __amdgpu_buffer_rsrc_t ka = Stage::table(a.ka, c0, c1 - c0);
+    const f16x8 *ea = (const f16x8 *)a.ea;
+    for (int idx = tid; idx < CJ * NE * 64; idx += 64 * kFacWaves) ebuf[idx] = ea[idx];
+    // Z of this line tile, [phase][2 slot + part][32 lines]: this lane's line,
+    // columns 16 ks + 8 h + 0..7 (past the last: a repeated column times zero
+    // table entries)
+    const uint32_t *zrow = a.y + (size_t)(active ? fp.tile : 0) * 32 * a.P * ZC + (lane & 31);
+    auto zload = [&](int n1, uint32_t (&z)[NZS][8]) {
+        const uint32_t *zp = zrow + (size_t)n1 * ZC * 32;
 #pragma unroll
-        for (int st = 0; st < ZST; ++st) zb[st] = zrow[(size_t)n1 * ZC * 32 + st * 32];
-    };
-    const int c0 = fp.n1a * CJ, c1 = fp.n1b * CJ;
-    f32x4 pk[KPT];
-    auto chunk_load = [&](int cc) {
+        for (int ks = 0; ks < NZS; ++ks)
 #pragma unroll
-        for (int k = 0; k < KPT; ++k) pk[k] = ka[(size_t)cc * CW + tid + 64 * kFacWavesAdj * k];
+            for (int e = 0; e < 8; ++e) {
+                const int col = 16 * ks + 8 * h + e;
+                z[ks][e] = zp[(16 * ks + 15 < ZC ? col : min(col, ZC - 1)) * 32];
+            }
     };
-    auto chunk_store = [&](int buf) {
-#pragma unroll
-        for (int k = 0; k < KPT; ++k) lk[buf * CW + tid + 64 * kFacWavesAdj * k] = pk[k];
-    };
-    float zb[ZST], zn[ZST];
-    zload(fp.n1a, zb);
-    chunk_load(c0);
-    chunk_store(c0 & 1);
-    if (c0 + 1 < c1) chunk_load(c0 + 1);
-    __syncthreads();
+    uint32_t zn[NZS][8];
+    zload(fp.n1a, zn);
+    __builtin_amdgcn_sched_barrier(0);
+    Stage::load(ka, 0, c1 - c0, lk, 0, wave, lane);
+    Stage::load(ka, NS, c1 - c0, lk, 1, wave, lane);
+    const float gscale = a.g_scale;
+    wait_vm_lgkm<Stage::kOps>();
+    block_barrier_nofence();
 
-    for (int n1 = fp.n1a; n1 < fp.n1b; ++n1) {
-        zload(min(n1 + 1, fp.n1b - 1), zn);   // the next phase's operands
+    int buf = 0, nbuf = 2;
+    f16x8 zh[NZS], zl[NZS];
+    for (int cg = c0; cg < c1; cg += GRP) {
 #pragma unroll
-        for (int j = 0; j < CJ; ++j) {
-            const int c = n1 * CJ + j;
-            if (active) {
-                const f32x4 *eb = ebuf + j * NE * 64 + lane;
+        for (int k = 0; k < GRP; ++k) {
+            const int c = cg + k;
+            if (k % CJ == 0) {
+#pragma unroll
+                for (int ks = 0; ks < NZS; ++ks) unpack8(zn[ks], zh[ks], zl[ks]);
+                zload(min(c / CJ + 1, fp.n1b - 1), zn);   // the next phase's operands
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (k % NS == NS - 1) Stage::load(ka, c - c0 + NS + 1, c1 - c0, lk, nbuf, wave, lane);
+            if (active && (GRP == CJ || c < c1)) {
+                const f16x8 *eb = ebuf + (k % CJ) * NE * 64 + lane;
                 f32x16 G = 0.f;
 #pragma unroll
-                for (int i = 0; i < NE; ++i) {
-                    const f32x4 v = eb[i * 64];
-                    G = MFMA32(v[0], zb[4 * i + 0], G);
-                    G = MFMA32(v[1], zb[4 * i + 1], G);
-                    G = MFMA32(v[2], zb[4 * i + 2], G);
-                    G = MFMA32(v[3], zb[4 * i + 3], G);
+                for (int ks = 0; ks < NZS; ++ks) {
+                    const f16x8 eh = eb[2 * ks * 64], el = eb[(2 * ks + 1) * 64];
+                    G = MFMA16(eh, zh[ks], G);
+                    G = MFMA16(eh, zl[ks], G);
+                    G = MFMA16(el, zh[ks], G);
                 }
-                const f32x4 *kb = lk + (c & 1) * CW + lane;
+                f16x8 gh[2], gl[2];
 #pragma unroll
-                for (int jj = 0; jj < NK; ++jj) {
-                    const int s4 = jj / PT, pt = jj % PT;
-                    const f32x4 v = kb[(pt * 4 + s4) * 64];
-                    racc[pt] = MFMA32(G[4 * s4 + 0], v[0], racc[pt]);
-                    racc[pt] = MFMA32(G[4 * s4 + 1], v[1], racc[pt]);
-                    racc[pt] = MFMA32(G[4 * s4 + 2], v[2], racc[pt]);
-                    racc[pt] = MFMA32(G[4 * s4 + 3], v[3], racc[pt]);
+                for (int q = 0; q < 2; ++q) {
+                    float w[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) w[e] = G[8 * q + e] * gscale;
+                    split8(w, gh[q], gl[q]);
                 }
+                // fragments in the order [step][tile][hi, lo]: consecutive
+                // products go to different accumulators
+                const f16x8 *kb = lk + (buf * Stage::kFrags + (k % NS) * Stage::kFragChunk) * 64 + lane;
+                lds_pipelined<4 * PT, 4>([&](int i) { return kb[i * 64]; },
+                                         [&](int i, const f16x8 &f) {
+                                             const int q = i / (2 * PT), pt = i / 2 % PT;
+                                             racc[pt] = MFMA16(gh[q], f, racc[pt]);
+                                             if (i % 2 == 0) racc[pt] = MFMA16(gl[q], f, racc[pt]);
+                                         });
             }
-            // chunk c + 1 goes to the buffer chunk c - 1 left (read by every
-            // wave before the last barrier); chunk c + 2 is requested
-            if (c + 1 < c1) {
-                chunk_store((c + 1) & 1);
-                if (c + 2 < c1) chunk_load(c + 2);
+            if (k % NS == NS - 1) {
+                wait_vm_lgkm<Stage::kOps>();      // the next stage is in, this wave's reads are done
+                block_barrier_nofence();
+                buf = buf == 2 ? 0 : buf + 1;
+                nbuf = nbuf == 2 ? 0 : nbuf + 1;
             }
-            __syncthreads();
         }
-#pragma unroll
-        for (int st = 0; st < ZST; ++st) zb[st] = zn[st];
     }
+    wait_vm_lgkm<0>();   // the repeated loads still in flight land before the LDS is handed on
     if (!active) return;
     float *out = job.part + (size_t)fp.split * job.part_stride;
+    const int row0 = fp.tile * 32 + 4 * h;
+    int e[16];
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) {
-        const int col = pt * 32 + (lane & 31);
+    for (int j = 0; j < 16; ++j) e[j] = a.lexp[row0 + 8 * (j / 4) + j % 4];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int row = row0 + 8 * (j / 4) + 4 * h + (j % 4);
-            if (row < job.rows) out[(size_t)job_line(job, row) * NUP + col] = racc[pt][j];
-        }
+    for (int j = 0; j < 16; ++j) {
+        const int row = row0 + 8 * (j / 4) + j % 4;
+        if (row >= job.rows) continue;
+        float *o = out + (size_t)job_line(job, row) * NUP + (lane & 31);
+#pragma unroll
+        for (int pt = 0; pt < PT; ++pt) o[pt * 32] = __builtin_ldexpf(racc[pt][j], -(e[j] + a.r_exp));
     }
 }
 
 typedef void (*FacKernel)(FacArgs);
-struct FacOut {
-    FacKernel fn;
-    int nbuf;
-};
-#define FAC_OUT(Z) {fac_fwd_out_kernel<Z>, fac_out_bufs(Z)}
-const FacOut kFacFwdOut[8] = {FAC_OUT(4),  FAC_OUT(8),  FAC_OUT(12), FAC_OUT(16),
-                              FAC_OUT(20), FAC_OUT(24), FAC_OUT(28), FAC_OUT(32)};
-#undef FAC_OUT
 constexpr int kFacNups[] = {64, 128, 192, 256};
-#define FAC_FWD_ROW(NUP)                                                                                     \
-    {{fac_fwd_kernel<NUP, 1, 1>, fac_fwd_kernel<NUP, 1, 2>}, {fac_fwd_kernel<NUP, 2, 1>, fac_fwd_kernel<NUP, 2, 2>}}
-const FacKernel kFacFwd[4][2][2] = {FAC_FWD_ROW(64), FAC_FWD_ROW(128), FAC_FWD_ROW(192), FAC_FWD_ROW(256)};
-#undef FAC_FWD_ROW
-#define FAC_ADJ_Z(NUP, Z) {fac_adj_kernel<NUP, Z, 1>, fac_adj_kernel<NUP, Z, 2>}
-#define FAC_ADJ_ROW(NUP)                                                                                     \
-    {FAC_ADJ_Z(NUP, 4), FAC_ADJ_Z(NUP, 8), FAC_ADJ_Z(NUP, 12), FAC_ADJ_Z(NUP, 16), FAC_ADJ_Z(NUP, 20),         \
-     FAC_ADJ_Z(NUP, 24), FAC_ADJ_Z(NUP, 28), FAC_ADJ_Z(NUP, 32)}
-const FacKernel kFacAdj[4][8][2] = {FAC_ADJ_ROW(64), FAC_ADJ_ROW(128), FAC_ADJ_ROW(192), FAC_ADJ_ROW(256)};
-#undef FAC_ADJ_ROW
-#undef FAC_ADJ_Z
+// C = 32 (CJ = 1): 16 slots hold every residue; C = 64 (CJ = 2): 16 to 32
+#define FAC_ROW(K, NUP) {K<NUP, 16, 1>, K<NUP, 16, 2>, K<NUP, 20, 2>, K<NUP, 24, 2>}
+#define FAC_TAB(K) {FAC_ROW(K, 64), FAC_ROW(K, 128), FAC_ROW(K, 192), FAC_ROW(K, 256)}
+const FacKernel kFacFwd[4][4] = FAC_TAB(fac_fwd_kernel);
+const FacKernel kFacAdj[4][4] = FAC_TAB(fac_adj_kernel);
+#undef FAC_TAB
+#undef FAC_ROW
+
+int fac_zst_slot(int zst, int cj)
+{
+    if (cj == 1) return zst == 16 ? 0 : -1;
+    return zst >= 16 && zst <= 24 && zst % 4 == 0 ? 1 + (zst - 16) / 4 : -1;
+}
 
 int fac_nup_slot(int nup)
 {
@@ -575,21 +733,30 @@ int fac_nup_slot(int nup)
 
 }  // namespace
 
-int fac_supported(int nup, int rct, int zst, int cj)
+int fac_supported(int nup, int zst, int cj)
 {
-    return fac_nup_slot(nup) >= 0 && rct >= 1 && rct <= 2 && zst >= 4 && zst <= 32 && zst % 4 == 0 && cj >= 1 &&
-           cj <= 2;
+    return fac_nup_slot(nup) >= 0 && cj >= 1 && cj <= 2 && fac_zst_slot(zst, cj) >= 0;
 }
 
 static bool fac_args_ok(const FacArgs &a)
 {
     return a.tiles > 0 && a.P > 0 && a.cj > 0 && a.nsplit >= 1 && a.nsplit <= a.P && a.nsplit_adj >= 1 &&
-           a.nsplit_adj <= a.P && a.yc % 4 == 0 &&
-           a.yc == 2 * a.zst && a.yc <= 32 * a.rct && a.R <= kInWaves * kResPerWave && a.R <= a.zst && a.yc <= 64 &&
-           a.Pp % kOutStage == 0 && a.Pp >= a.P && a.nzstage * kZStage >= a.P &&
-           fac_supported(a.nup, a.rct, a.zst, a.cj) && a.job.rows <= a.tiles * 32 &&
+           a.nsplit_adj <= a.P && a.yc == 2 * a.zst && (a.qmax == 32 ? a.R <= 2 * kInWaves : a.qmax == 24 && a.R <= 3 * kInWaves) && a.R <= a.zst &&
+           a.U >= a.R && a.U <= 2 * a.R && a.ucols == 32 * a.U && a.nzstage == (a.P + 15) / 16 &&
+           fac_supported(a.nup, a.zst, a.cj) && a.job.rows <= a.tiles * 32 &&
            a.ylines >= a.tiles * 32 && (long)(a.ylines + 1) * a.P * a.yc < 0x7fffffffL && a.psplit >= 1 &&
-           a.psplit <= (a.P + kOutStage - 1) / kOutStage && a.zsplit >= 1 && a.zsplit <= a.nzstage;
+           a.psplit <= (a.P + 7) / 8 && a.zsplit >= 1 && a.zsplit <= a.nzstage;
+}
+
+// LDS bytes of a line-tile kernel: three PSF-table stages and its residue
+// table (nfrag fragments of 1 KB).
+static size_t fac_lds(int nup, int nfrag)
+{
+    const int stage = nup == 64   ? PsfStage<64>::kBytes
+                      : nup == 128 ? PsfStage<128>::kBytes
+                      : nup == 192 ? PsfStage<192>::kBytes
+                                   : PsfStage<256>::kBytes;
+    return 3 * (size_t)stage + 1024 * (size_t)nfrag;
 }
 
 hipError_t launch_fac_part(const FacArgs &a, int part, hipStream_t st)
@@ -599,39 +766,36 @@ hipError_t launch_fac_part(const FacArgs &a, int part, hipStream_t st)
     hipError_t e = hipSuccess;
     switch (part) {
     case kFacFwdInner: {
-        const size_t lds = 16 * 64 * (size_t)(2 * a.nup / 8 + a.cj * 4 * a.rct);
-        const FacKernel k = kFacFwd[fac_nup_slot(a.nup)][a.rct - 1][a.cj - 1];
+        const size_t lds = fac_lds(a.nup, a.cj * 4 * ((a.yc + 31) / 32));
+        const FacKernel k = kFacFwd[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
         if (lds > 64 * 1024) {
             e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(k, dim3((a.tiles + kFacWavesFwd - 1) / kFacWavesFwd * a.nsplit), dim3(64 * kFacWavesFwd),
+        hipLaunchKernelGGL(k, dim3((a.tiles + kFacWaves - 1) / kFacWaves * a.nsplit), dim3(64 * kFacWaves),
                            lds, st, a);
         break;
     }
     case kFacFwdOuter: {
-        if (a.usplit < 1 || a.usplit > kMaxFacSplit || a.U > kOutWaves * kUnitsPerWave * a.usplit)
-            return hipErrorInvalidValue;
-        const FacOut &k = kFacFwdOut[a.zst / 4 - 1];
-        const size_t lds = sizeof(float) * (size_t)k.nbuf * kOutStage * 2 * a.zst * 32;
-        if (lds > 64 * 1024) {
-            e = hipFuncSetAttribute((const void *)k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(k.fn, dim3(a.tiles, a.usplit, a.psplit), dim3(64 * kOutWaves), lds, st, a);
+        const int per = kOutTiles * kOutWaves;
+        hipLaunchKernelGGL(fac_fwd_out_kernel, dim3((a.tiles + per - 1) / per, a.R, a.psplit), dim3(64 * kOutWaves), 0,
+                           st, a);
         break;
     }
     case kFacAdjOuter:
-        hipLaunchKernelGGL(fac_adj_in_kernel, dim3(a.tiles, a.zsplit), dim3(64 * kInWaves), 0, st, a);
+        if (a.qmax == 32)
+            hipLaunchKernelGGL((fac_adj_in_kernel<2, 4>), dim3(a.tiles, a.zsplit), dim3(64 * kInWaves), 0, st, a);
+        else
+            hipLaunchKernelGGL((fac_adj_in_kernel<3, 3>), dim3(a.tiles, a.zsplit), dim3(64 * kInWaves), 0, st, a);
         break;
     default: {
-        const size_t lds = 16 * 64 * (size_t)(2 * a.nup / 8 + a.cj * a.zst / 4);
-        const FacKernel k = kFacAdj[fac_nup_slot(a.nup)][a.zst / 4 - 1][a.cj - 1];
+        const size_t lds = fac_lds(a.nup, a.cj * 2 * ((a.yc + 15) / 16));
+        const FacKernel k = kFacAdj[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
         if (lds > 64 * 1024) {
             e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(k, dim3((a.tiles + kFacWavesAdj - 1) / kFacWavesAdj * a.nsplit_adj), dim3(64 * kFacWavesAdj),
+        hipLaunchKernelGGL(k, dim3((a.tiles + kFacWaves - 1) / kFacWaves * a.nsplit_adj), dim3(64 * kFacWaves),
                            lds, st, a);
         break;
     }

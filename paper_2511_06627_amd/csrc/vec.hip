@@ -30,11 +30,19 @@ __device__ __forceinline__ double block_sum(double v, double *red)
     return t;  // valid in thread 0
 }
 
-// sum_s pp[s * stride] in float64, in split order; four loads in flight
+// sum_s pp[s * stride] in float64, in split order; eight loads in flight
+// (a chain of rounds of loads, not bandwidth, is what many splits cost)
 __device__ __forceinline__ double sum_splits(const float *__restrict__ pp, int n, long stride)
 {
     double v = 0.0;
     int s = 0;
+    for (; s + 8 <= n; s += 8) {
+        float a[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a[j] = pp[(long)(s + j) * stride];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v += (double)a[j];
+    }
     for (; s + 4 <= n; s += 4) {
         const float a0 = pp[(long)s * stride], a1 = pp[(long)(s + 1) * stride];
         const float a2 = pp[(long)(s + 2) * stride], a3 = pp[(long)(s + 3) * stride];
@@ -88,13 +96,15 @@ __device__ __forceinline__ double sum_unscaled(const float *__restrict__ pp, int
     return v;
 }
 
-// out[row][c] = sign * sum_s part[s][row][c] * col_scale[c] / row_scale[row] (+ b_sub)
+// out[row][c] = sign * sum_s part[s][row][c] * col_scale[c] / row_scale[row] (+ b_sub);
+// bcol (factored stage): column c = 2 j + part of bin j is column bcol[j] + part of part
 __global__ __launch_bounds__(kThreads) void reduce_fwd_kernel(long rows, int nb2, int nbp2, int nparts,
                                                                long part_stride, const float *__restrict__ part,
                                                                const float *__restrict__ row_scale,
                                                                const float *__restrict__ col_scale, double scale,
                                                                const float *__restrict__ b_sub, float *out,
-                                                               double *norm_parts, RowPasses rp)
+                                                               double *norm_parts, RowPasses rp,
+                                                               const int *__restrict__ bcol)
 {
     __shared__ double red[kThreads / 64];
     const long n = rows * nb2;
@@ -102,7 +112,8 @@ __global__ __launch_bounds__(kThreads) void reduce_fwd_kernel(long rows, int nb2
     for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads) {
         const long row = idx / nb2;
         const int c = (int)(idx - row * nb2);
-        const double v0 = sum_unscaled(part + row * nbp2 + c, nparts, part_stride, row, row_scale, rp);
+        const int pc = bcol ? bcol[c >> 1] + (c & 1) : c;
+        const double v0 = sum_unscaled(part + row * nbp2 + pc, nparts, part_stride, row, row_scale, rp);
         double v = v0 * scale;
         if (col_scale) v *= (double)col_scale[c];
         if (b_sub) v = (double)b_sub[idx] - v;
@@ -482,12 +493,13 @@ int scal_slot_gamma0() { return S_GAMMA0; }
 
 hipError_t launch_reduce_fwd(long rows, int nb2, int nbp2, int nparts, long part_stride, const float *part,
                              const float *row_scale, const float *col_scale, double scale, const float *b_sub,
-                             float *out, double *norm_parts, int *nnorm, hipStream_t st, RowPasses rp)
+                             float *out, double *norm_parts, int *nnorm, hipStream_t st, RowPasses rp,
+                             const int *bcol)
 {
     const int g = grid_for(rows * nb2, kReduceBlocks);
     if (nnorm) *nnorm = g;
     hipLaunchKernelGGL(reduce_fwd_kernel, dim3(g), dim3(kThreads), 0, st, rows, nb2, nbp2, nparts, part_stride,
-                       part, row_scale, col_scale, scale, b_sub, out, norm_parts, rp);
+                       part, row_scale, col_scale, scale, b_sub, out, norm_parts, rp, bcol);
     return hipGetLastError();
 }
 

@@ -1,0 +1,81 @@
+"""The factored FP32 signal stage's fp16-pair products (hi + lo) at their edges.
+
+Stage entries against the FP64 oracle's dense definition: every residue of C =
+32 present (the slot shared by residues 0 and C / 2, conjugate pairs), C = 64
+with 20 and 24 slots, all padded widths, odd line strides, a ragged last line
+tile, phase counts that no stage divides.  Tolerance: a pair holds a number to
+2^-23, so a product of two pairs without lo lo is within 2^-22 + 2 2^-23 of
+exact; three such contractions in a row and their fp32 sums stay below
+8 x 2^-22 = 1.9e-6 of a line's norm.
+"""
+import numpy as np
+import pytest
+
+from oracle import signal
+from helpers import oracle_geometry, random_data
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1.9e-6
+
+# name: (nx, ny, nz, M, T, drive cycles, w, k_lo, k_hi, half band, C the plan takes)
+CASES = {
+    "all_residues_u150": (150, 20, 5, 7, 6144, 6144 / 256 + 1 / 3, 3.0, 1, 20, 3, 32),
+    "slots20_u256": (256, 16, 3, 11, 8192, 64 + 1 / 3, 3.0, 1, 47, 3, 64),
+    "slots24_u100": (100, 16, 4, 9, 8192, 64 + 1 / 3, 3.0, 1, 56, 3, 64),
+    "p63_u33": (33, 24, 8, 9, 2016, 2016 / 256 + 1 / 3, 2.0, 1, 15, 2, 32),
+    "one_line": (64, 16, 1, 1, 4096, 4096 / 256 + 1 / 3, 2.0, 1, 31, 3, 32),
+}
+
+
+def _plan(name):
+    from paper_2511_06627_amd.plan import Plan
+    nx, ny, nz, M, T, P, w, klo, khi, D, C = CASES[name]
+    g = oracle_geometry(nx, ny, nz, M, T, P, w, klo, khi, D)
+    plan = Plan(nx, ny, nz, M, T, P, w, klo, khi, D, 1.0)
+    assert plan.dft_cycles == C, "plan took C = %d" % plan.dft_cycles
+    return g, plan
+
+
+def _line_errors(a, b):
+    a, b = np.asarray(a), np.asarray(b)
+    a, b = a.reshape(-1, a.shape[-1]), b.reshape(-1, b.shape[-1])
+    return np.linalg.norm(a - b, axis=1) / np.linalg.norm(b, axis=1)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_stages_per_line(name):
+    """Each line on its own, lines scaled apart by powers of two."""
+    import torch
+    g, plan = _plan(name)
+    rng = np.random.default_rng(5)
+    L = g.n_lines
+    sc = 2.0 ** rng.integers(-80, 81, L)
+    rho = (rng.uniform(0, 1, (L, g.n_u)) ** 3).astype(np.float32)
+    want = signal.forward(g, rho) * sc[:, None]
+    x = torch.from_numpy((rho * sc[:, None]).astype(np.float32).reshape(plan.lines_shape)).cuda()
+    ef = _line_errors(plan.signal_fwd(x).cpu().numpy(), want.reshape(plan.data_shape))
+    y = np.asarray(random_data(g, 6)).reshape(L, -1).astype(np.complex64)
+    want = signal.adjoint(g, y) * sc[:, None]
+    b = torch.from_numpy((y * sc[:, None]).astype(np.complex64).reshape(plan.data_shape)).cuda()
+    ea = _line_errors(plan.signal_adj(b).cpu().numpy(), want.reshape(plan.lines_shape))
+    print("%s: forward %.2e adjoint %.2e" % (name, ef.max(), ea.max()), flush=True)
+    assert ef.max() <= TOL and ea.max() <= TOL
+
+
+def test_non_finite_line_stays_alone():
+    """A line with an infinity or a NaN gives non-finite results and leaves every other line's bits."""
+    import torch
+    g, plan = _plan("p63_u33")
+    rng = np.random.default_rng(7)
+    rho = torch.from_numpy(rng.uniform(0, 1, plan.lines_shape).astype(np.float32)).cuda()
+    ref = plan.signal_fwd(rho).cpu()
+    y = torch.from_numpy(np.asarray(random_data(g, 8)).astype(np.complex64).reshape(plan.data_shape)).cuda()
+    refa = plan.signal_adj(y).cpu()
+    keep = torch.ones(ref.shape[:2], dtype=torch.bool)
+    keep[2, 3] = keep[5, 0] = False
+    rho[2, 3, 10], rho[5, 0, 4] = float("inf"), float("nan")
+    y[2, 3, 10], y[5, 0, 4] = float("inf"), float("nan")
+    got, gota = plan.signal_fwd(rho).cpu(), plan.signal_adj(y).cpu()
+    assert torch.equal(torch.view_as_real(got[keep]), torch.view_as_real(ref[keep])) and torch.equal(gota[keep], refa[keep])
+    assert not torch.isfinite(torch.view_as_real(got[~keep])).any() and not torch.isfinite(gota[~keep]).any()
