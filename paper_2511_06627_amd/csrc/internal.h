@@ -152,8 +152,12 @@ struct ProjArgs {
     const float2 *cs;           // [M] (cos, sin)
     const float *ax;            // [M][nu] forward x-coordinate bases
     const float *ay;            // [M][nu] forward y-coordinate bases
+    const float *ay1;           // the same + 1 (row 0 the zero border), formed in float64
+    const int *order;           // [M] angles, the n_steep with |cos| >= |sin| first
+    int n_steep;
+    int parts[2];               // blocks a slice group's steep and other angles are dealt to
     int nx, ny, nz, M, nu, nup, nr;
-    int band_rows, n_bands;
+    int band_rows, n_bands, band_cols;
     int kz, n_zgroups, tiles_x, tiles_y, adj_chunk;
     float half_nr, half_nu, cx, cy;
 };
@@ -216,6 +220,13 @@ struct mpi3d_plan {
     uint64_t line_key;             // equal keys <=> identical line tables
     // projection configuration
     mpi3d::FwdConfig fwd32, fwd16;  // forward projection, fp32 and bf16 gathers
+    // fp32 forward projection in four-slice texels: base rows (steep angles) and
+    // columns (the others) of a band, blocks (0: not taken) and blocks a slice
+    // group and angle class
+    struct { int rows, cols, blocks, parts[2]; } band;
+    int n_steep;
+    int *order;
+    float *ay1;
     int kz, adj_chunk;
     int max_parts;                 // float64 norm partials a launch may write (>= kMaxNormParts)
     // device tables (one allocation)

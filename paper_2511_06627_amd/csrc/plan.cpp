@@ -432,6 +432,22 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             if (!fwd_config(1, 4, pl->fwd32)) { delete pl; return MPI3D_ENOTSUP; }
         }
         if (!fwd_config(2, 4, pl->fwd16)) { delete pl; return MPI3D_ENOTSUP; }
+        // FP32 in four-slice texels (proj_fwd_band_kernel): possible where bands
+        // of at least 8 rows and columns fit; dealt to blocks, and compared with
+        // the kernels above, once the angles are known.
+        {
+            const int texels = 160 * 1024 / 16;
+            const int rmax = texels / mpi3d::proj_pitch(pl->nx) - 1;
+            int cmax = texels / (pl->ny + 2) - 1;             // pitch (cols + 1) | 1
+            if (((cmax + 1) | 1) * (pl->ny + 2) > texels) --cmax;
+            pl->band.blocks = 0;
+            if (rmax >= 8 && cmax >= 8) {
+                auto even = [](int n, int mx) { const int k = (n + mx - 1) / mx; return (n + k - 1) / k; };
+                pl->band.rows = even(pl->ny + 1, rmax);
+                pl->band.cols = even(pl->nx + 1, cmax);
+                pl->band.blocks = 1;
+            }
+        }
         // Backprojection: 16 x 16 voxel tiles times kz slices per block.  The
         // ray weights are formed once per voxel and angle and reused over kz
         // slices, so take the largest kz that still gives about three blocks
@@ -461,7 +477,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     const double cx = 0.5 * (pl->nx - 1), cy = 0.5 * (pl->ny - 1), cu = 0.5 * (NU - 1);
 
     std::vector<float2> cs(M);
-    std::vector<float> ax((size_t)M * NU), ay((size_t)M * NU);
+    std::vector<float> ax((size_t)M * NU), ay((size_t)M * NU), ay1((size_t)M * NU);
     for (int m = 0; m < M; ++m) {
         double c = std::cos(theta[m]), s = std::sin(theta[m]);
         cs[m] = make_float2((float)c, (float)s);
@@ -472,7 +488,51 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             // grid column -1, hence the +1).
             ax[(size_t)m * NU + p] = (float)(up * c + cx + 1.0);
             ay[(size_t)m * NU + p] = (float)(-up * s + cy);
+            ay1[(size_t)m * NU + p] = (float)(-up * s + cy + 1.0);
         }
+    }
+    std::vector<int> order;    // angles by class: |c| >= |s| first
+    for (int steep = 1; steep >= 0; --steep) {
+        for (int m = 0; m < M; ++m)
+            if ((std::fabs(cs[m].x) >= std::fabs(cs[m].y)) == (steep == 1)) order.push_back(m);
+        if (steep) pl->n_steep = (int)order.size();
+    }
+    if (pl->band.blocks) {
+        // Blocks a group and class: at most 2 rays a thread, and the least
+        // estimated time.  The estimates are fits to both kernels' times at 14
+        // shapes from 64^3 x 24 angles to 256^2 x 128 x 60: a round of blocks of
+        // the four-slice kernel takes 11 us, 25 us a MB of staged slices and
+        // 0.31 ns a ray sample of the longest block; the others 9 us and 0.26 ns
+        // in slice pairs (a third more where rows are not whole vectors), or 3 us
+        // and 0.155 ns (0.23 ns in row bands) slice by slice.  Measured at the
+        // edges, old -> new: 64^3 x 24 11.9 -> 15.2 us, 192^2 x 64 x 36 54 -> 64
+        // (not taken), 192^2 x 96 x 36 82 -> 71, 100^3 x 60 45 -> 37, 256^2 x 64 x 24
+        // 102 -> 77 (taken).  It has to win by a twelfth.
+        const int ng4 = (pl->nz + 3) / 4, nm[2] = {pl->n_steep, M - pl->n_steep};
+        const int amax = 2 * kFwdThreads / NU, len = std::max(pl->nx, pl->ny);
+        const double stage = 16.0 * pl->nx * pl->ny * 25e-12;
+        double best = 1e30;
+        for (int amx = 1; amx <= amax; ++amx) {
+            int parts[2], big = 0;
+            for (int k = 0; k < 2; ++k) {
+                parts[k] = (nm[k] + amx - 1) / amx;
+                if (parts[k]) big = std::max(big, (nm[k] + parts[k] - 1) / parts[k]);
+            }
+            const long blocks = (long)ng4 * (parts[0] + parts[1]);
+            const double t = (double)((blocks + 255) / 256) * (11e-6 + stage + (double)big * NU * len * 0.31e-9);
+            if (t < best * (1.0 - 1e-9)) {
+                best = t;
+                pl->band.blocks = (int)blocks;
+                pl->band.parts[0] = parts[0];
+                pl->band.parts[1] = parts[1];
+            }
+        }
+        const mpi3d::FwdConfig &fc = pl->fwd32;
+        const long units = (long)((pl->nz + fc.slices - 1) / fc.slices) * M;
+        const double x = (double)((fc.blocks + 255) / 256) * ((units + fc.blocks - 1) / fc.blocks) * NU * len;
+        const double other = fc.slices == 2 ? 9e-6 + (pl->nx % 4 ? 0.35e-9 : 0.26e-9) * x
+                                            : 3e-6 + (fc.n_bands > 1 ? 0.23e-9 : 0.155e-9) * x;
+        if (best > 0.92 * other) pl->band.blocks = 0;
     }
 
     // PSF kernel K[n][p] of every table (n < T, p < NU; zero padding
@@ -884,11 +944,13 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     // ---- table layout in one device allocation -----------------------------
     size_t off = 0;
     char *nullbase = nullptr;
-    size_t o_cs, o_ax, o_ay, o_kf, o_ff, o_fa, o_ka, o_kf16 = 0, o_ff16 = 0, o_fa16 = 0, o_ka16 = 0, o_cols = 0, o_bands = 0;
+    size_t o_cs, o_ax, o_ay, o_ay1, o_order, o_kf, o_ff, o_fa, o_ka, o_kf16 = 0, o_ff16 = 0, o_fa16 = 0, o_ka16 = 0, o_cols = 0, o_bands = 0;
     auto place = [&](size_t bytes) { off = align256(off); size_t o = off; off += bytes; return o; };
     o_cs = place(sizeof(float2) * M);
     o_ax = place(sizeof(float) * M * NU);
     o_ay = place(sizeof(float) * M * NU);
+    o_ay1 = place(sizeof(float) * M * NU);
+    o_order = place(sizeof(int) * M);
     o_kf = place(dense ? sizeof(float) * KE * n_ktab : 0);
     o_ff = place(dense ? sizeof(float) * (size_t)TP * NBP2 : 0);
     o_fa = place(dense ? sizeof(float) * (size_t)TP * NBP2 : 0);
@@ -1053,6 +1115,8 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     pl->cs = (float2 *)(tb + o_cs);
     pl->ax = (float *)(tb + o_ax);
     pl->ay = (float *)(tb + o_ay);
+    pl->ay1 = (float *)(tb + o_ay1);
+    pl->order = (int *)(tb + o_order);
     if (dense) {
         pl->kf = (float *)(tb + o_kf);
         pl->ff = (float *)(tb + o_ff);
@@ -1062,6 +1126,8 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     bool ok = hipMemcpy(pl->cs, cs.data(), sizeof(float2) * M, hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(pl->ax, ax.data(), sizeof(float) * ax.size(), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(pl->ay, ay.data(), sizeof(float) * ay.size(), hipMemcpyHostToDevice) == hipSuccess;
+    ok = ok && hipMemcpy(pl->ay1, ay1.data(), sizeof(float) * ay1.size(), hipMemcpyHostToDevice) == hipSuccess;
+    ok = ok && hipMemcpy(pl->order, order.data(), sizeof(int) * M, hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && (!dense || hipMemcpy(pl->kf, kf.data(), sizeof(float) * kf.size(), hipMemcpyHostToDevice) == hipSuccess);
     ok = ok && (!dense || hipMemcpy(pl->ff, ff.data(), sizeof(float) * ff.size(), hipMemcpyHostToDevice) == hipSuccess);
     ok = ok && (!dense || hipMemcpy(pl->fa, fa.data(), sizeof(float) * fa.size(), hipMemcpyHostToDevice) == hipSuccess);

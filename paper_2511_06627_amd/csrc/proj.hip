@@ -22,6 +22,7 @@
 // <= 32 rays) are staged in LDS.  The epilogue optionally forms
 // out = acc + x_add - lambda * x_sub and a float64 partial sum of out^2 (CGLS).
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device.h"
@@ -415,6 +416,280 @@ __global__ __launch_bounds__(kFwdThreads) void proj_fwd_kernel(ProjArgs a, const
     }
 }
 
+// ---------------------------------------------------------------------------
+// Forward projection, four slices a texel.  The kernel above spends most of
+// its time forming each sample's address and weights (about 16 vector
+// operations a sample and slice); a texel of four consecutive slices shares
+// them four ways and one 16-byte LDS read serves a corner of all four, which
+// leaves about 8.  160 KB then hold a band of the slice group only, so
+//  - angles are taken in two classes, dealt apart: steep ones (|c| >= |s|)
+//    with bands of rows, the others with bands of columns.  Every ray then
+//    crosses every band at 45 degrees or more, in about the same number of
+//    samples, and no wave idles while others work;
+//  - a ray's samples in a band, and those inside the grid, are found exactly:
+//    sample coordinates are monotone in the sample number, so the first sample
+//    past a threshold is its estimate or a neighbour, decided by the sample's
+//    own coordinate.  The samples of a range then need no test: their base
+//    texel and its right and lower neighbours lie in the staged band.
+// Coordinates are shifted by one (index 0 is the zero border), so truncation
+// is floor.  What bounds it: vector work (about 80% busy; 17 of 34 operations a
+// sample are address and weights) and the LDS reads, half of whose cycles are
+// bank conflicts (16 lanes read over up to 23 texels, so two share a bank
+// whatever the pitch).  Measured 432 -> 240 us at 256 x 256 x 128, 60 angles;
+// 285 -> 127 us at 224 x 224 x 112, 48; 82 -> 71 us at 192 x 192 x 96, 36.
+// ---------------------------------------------------------------------------
+constexpr int kBandRays = 2;                     // rays a thread owns
+constexpr int kBandSlices = 4;
+constexpr int kBandTexels = 160 * 1024 / 16;     // LDS texels
+
+// Sample q's coordinate on an axis: b + y_q k, as the sampling loop forms it.
+__device__ __forceinline__ float coord(int q, float half_nr, float k, float b) { return fmaf((float)q - half_nr, k, b); }
+
+// The first sample q of [0, nr] from which the coordinate is at least t (k > 0)
+// or below t (k < 0).  |k| >= 1e-3: the estimate is within 0.1 of the real
+// crossing, so the sample is the estimate or a neighbour; below that (rays
+// along a grid axis) by bisection.
+__device__ __forceinline__ int first_past(float t, int nr, float half_nr, float k, float rk, float b)
+{
+    const bool up = k > 0.f;
+    auto past = [&](int q) {
+        const float f = coord(q, half_nr, k, b);
+        return up ? f >= t : f < t;
+    };
+    if (fabsf(k) >= 1e-3f) {
+        const float e = fminf(fmaxf(ceilf((t - b) * rk + half_nr), 0.f), (float)nr);
+        int q = (int)e;
+        if (q > 0 && past(q - 1))
+            --q;
+        else if (q < nr && !past(q))
+            ++q;
+        return q;
+    }
+    int lo = 0, hi = nr;                         // past(hi - 1) or hi = nr; not past(lo - 1)
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (past(mid))
+            hi = mid;
+        else
+            lo = mid + 1;
+    }
+    return lo;
+}
+
+// The samples [q0, q1) whose coordinate is in [lo, hi).
+__device__ __forceinline__ void samples_in(float lo, float hi, int nr, float half_nr, float k, float rk, float b,
+                                           int &q0, int &q1)
+{
+    if (k == 0.f) {
+        q0 = 0;
+        q1 = b >= lo && b < hi ? nr : 0;
+    } else {
+        q0 = first_past(k > 0.f ? lo : hi, nr, half_nr, k, rk, b);
+        q1 = first_past(k > 0.f ? hi : lo, nr, half_nr, k, rk, b);
+    }
+}
+
+// Two consecutive samples: their corners' texels, read one pair ahead of
+// their use, and weights.
+struct SamplePair {
+    float4 t[2][4];
+    float wx[2], wy[2];
+};
+
+// Samples at coordinate numbers y and y + 1, no further than ylast.
+__device__ __forceinline__ void pair_load(SamplePair &g, const unsigned char *lds, unsigned base, unsigned Wb, float bx,
+                                          float by, float s, float c, float y, float ylast)
+{
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const float yj = fminf(y + (float)j, ylast);
+        const float fx = fmaf(yj, s, bx), fy = fmaf(yj, c, by);
+        g.wx[j] = __builtin_amdgcn_fractf(fx);
+        g.wy[j] = __builtin_amdgcn_fractf(fy);
+        const unsigned o = __umul24((unsigned)fy, Wb) + base + (unsigned)fx * 16u;
+        g.t[j][0] = *reinterpret_cast<const float4 *>(lds + o);
+        g.t[j][1] = *reinterpret_cast<const float4 *>(lds + o + 16);
+        g.t[j][2] = *reinterpret_cast<const float4 *>(lds + o + Wb);
+        g.t[j][3] = *reinterpret_cast<const float4 *>(lds + o + Wb + 16);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Their interpolants, summed before they join the ray's sum: the long sum is
+// then rounded once a pair, not once a corner.
+template <int N>
+__device__ __forceinline__ void pair_sum(const SamplePair &g, float (&acc)[kBandSlices])
+{
+    float v[kBandSlices];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const float w11 = g.wx[j] * g.wy[j], w10 = g.wx[j] - w11, w01 = g.wy[j] - w11, w00 = (1.f - g.wx[j]) - w01;
+        const float w[4] = {w00, w10, w01, w11};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float4 t = g.t[j][k];
+            const bool first = j == 0 && k == 0;
+            v[0] = first ? t.x * w[k] : fmaf(t.x, w[k], v[0]);
+            v[1] = first ? t.y * w[k] : fmaf(t.y, w[k], v[1]);
+            v[2] = first ? t.z * w[k] : fmaf(t.z, w[k], v[2]);
+            v[3] = first ? t.w * w[k] : fmaf(t.w, w[k], v[3]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kBandSlices; ++k) acc[k] += v[k];
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Stages LDS rows 0 .. rows - 1 of cols texels (grid rows j0 + r - 1, grid
+// columns i0 + c - 1; zeros outside the grid and past the last slice).
+__device__ __forceinline__ void stage_band4(float4 *lds, const float *vol, int k0, const ProjArgs &a, int j0, int i0,
+                                            int rows, int cols, int W, int tid)
+{
+    constexpr int U = 10;      // a full band (10240 texels) in one round of loads
+    const int total = rows * cols;
+    const size_t slice = (size_t)a.nx * a.ny;
+    const int ns = min(kBandSlices, a.nz - k0);
+    const float *v0 = vol + (size_t)k0 * slice;
+    const int dr = kFwdThreads / cols, dc = kFwdThreads - dr * cols;
+    int r = tid / cols, c = tid - r * cols;
+    for (int e0 = tid; e0 < total; e0 += U * kFwdThreads) {
+        float v[U][kBandSlices];
+        int dst[U];
+        unsigned inside = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool live = e0 + u * kFwdThreads < total;
+            const int gj = j0 + r - 1, gi = i0 + c - 1;
+            const bool in = live && (unsigned)gj < (unsigned)a.ny && (unsigned)gi < (unsigned)a.nx;
+            const unsigned off = in ? (unsigned)(gj * a.nx + gi) : 0u;
+            inside |= in ? 1u << u : 0u;
+#pragma unroll
+            for (int k = 0; k < kBandSlices; ++k) v[u][k] = (v0 + (k < ns ? k * slice : 0))[off];
+            dst[u] = live ? r * W + c : -1;
+            r += dr;
+            c += dc;
+            if (c >= cols) {
+                c -= cols;
+                ++r;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (dst[u] >= 0) {
+                const bool in = inside & (1u << u);
+                lds[dst[u]] = make_float4(in ? v[u][0] : 0.f, in && ns > 1 ? v[u][1] : 0.f,
+                                          in && ns > 2 ? v[u][2] : 0.f, in && ns > 3 ? v[u][3] : 0.f);
+            }
+    }
+}
+
+__global__ __launch_bounds__(kFwdThreads) void proj_fwd_band_kernel(ProjArgs a, const float *vol, int out_stride)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int nb = gridDim.x;
+    const int lb = xcd_logical(blockIdx.x, nb);
+    const int tid = threadIdx.x;
+    // a.parts[0] blocks share the steep angles of a slice group, a.parts[1] the
+    // others (a.order: a.n_steep steep ones first)
+    const int per = a.parts[0] + a.parts[1];
+    {
+        const int g = lb / per;
+        const int pp = lb - g * per;
+        const bool steep = pp < a.parts[0];
+        const int part = steep ? pp : pp - a.parts[0], np = steep ? a.parts[0] : a.parts[1];
+        const int n0 = steep ? 0 : a.n_steep, nm = steep ? a.n_steep : a.M - a.n_steep;
+        const int i0 = n0 + part * nm / np, i1 = n0 + (part + 1) * nm / np;
+        const int k0 = kBandSlices * g, ns = min(kBandSlices, a.nz - k0);
+        const int nrays = (i1 - i0) * a.nu;
+        // band geometry: base indices [0, n_base) of the banded axis, nband a band
+        const int n_base = (steep ? a.ny : a.nx) + 1, nband = steep ? a.band_rows : a.band_cols;
+        const int W = steep ? proj_pitch(a.nx) : (a.band_cols + 1) | 1;
+        const unsigned Wb = 16u * (unsigned)W;
+
+        float bx[kBandRays], by[kBandRays], c[kBandRays], s[kBandRays], acc[kBandRays][kBandSlices];
+        int glo[kBandRays], ghi[kBandRays];
+        float *dst[kBandRays];
+#pragma unroll
+        for (int i = 0; i < kBandRays; ++i) {
+            const int ray = tid + kFwdThreads * i;
+            const bool ok = ray < nrays;
+            glo[i] = ghi[i] = 0;
+            if (ray - (tid & 63) >= nrays) continue;     // a wave without rays
+            const int m = a.order[i0 + (ok ? ray / a.nu : 0)], p = ok ? ray % a.nu : 0;
+            const float2 csv = a.cs[m];
+            c[i] = csv.x;
+            s[i] = csv.y;
+            bx[i] = a.ax[(size_t)m * a.nu + p];
+            by[i] = a.ay1[(size_t)m * a.nu + p];
+            dst[i] = a.rt + ((size_t)m * a.nz + k0) * out_stride + p;
+#pragma unroll
+            for (int k = 0; k < kBandSlices; ++k) acc[i][k] = 0.f;
+            // samples inside the bordered grid
+            int x0, x1, y0, y1;
+            samples_in(0.f, (float)(a.nx + 1), a.nr, a.half_nr, s[i], 1.f / s[i], bx[i], x0, x1);
+            samples_in(0.f, (float)(a.ny + 1), a.nr, a.half_nr, c[i], 1.f / c[i], by[i], y0, y1);
+            glo[i] = max(x0, y0);
+            ghi[i] = ok ? min(x1, y1) : 0;
+        }
+        for (int b0 = 0; b0 < n_base; b0 += nband) {
+            const int b1 = min(b0 + nband, n_base);
+            __syncthreads();                     // the previous band is consumed
+            if (steep)
+                stage_band4(reinterpret_cast<float4 *>(lds_raw), vol, k0, a, b0, 0, b1 - b0 + 1, a.nx + 2, W, tid);
+            else
+                stage_band4(reinterpret_cast<float4 *>(lds_raw), vol, k0, a, 0, b0, a.ny + 2, b1 - b0 + 1, W, tid);
+            __syncthreads();
+            const unsigned base = 0u - (steep ? (unsigned)b0 * Wb : (unsigned)b0 * 16u);
+#pragma unroll
+            for (int i = 0; i < kBandRays; ++i) {
+                if (kFwdThreads * i + (tid & ~63) >= nrays) continue;
+                const float k = steep ? c[i] : s[i], b = steep ? by[i] : bx[i];
+                int q0, q1;
+                samples_in((float)b0, (float)b1, a.nr, a.half_nr, k, 1.f / k, b, q0, q1);
+                q0 = max(q0, glo[i]);
+                q1 = min(q1, ghi[i]);
+                if (q0 >= q1) continue;
+                auto get = [&](SamplePair &g, int q) {
+                    pair_load(g, lds_raw, base, Wb, bx[i], by[i], s[i], c[i], (float)q - a.half_nr,
+                              (float)(q1 - 1) - a.half_nr);
+                };
+                SamplePair ga, gb;
+                int q = q0;
+                get(ga, q);
+                for (; q + 4 <= q1; q += 4) {
+                    get(gb, q + 2);
+                    pair_sum<2>(ga, acc[i]);
+                    get(ga, q + 4);              // (past the end: the last sample again)
+                    pair_sum<2>(gb, acc[i]);
+                }
+                const int left = q1 - q;
+                if (left >= 2) {
+                    get(gb, q + 2);
+                    pair_sum<2>(ga, acc[i]);
+                    if (left == 3) pair_sum<1>(gb, acc[i]);
+                } else if (left == 1) {
+                    pair_sum<1>(ga, acc[i]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kBandRays; ++i) {
+            if (tid + kFwdThreads * i >= nrays) continue;
+#pragma unroll
+            for (int k = 0; k < kBandSlices; ++k)
+                if (k < ns) dst[i][(size_t)k * out_stride] = acc[i][k];
+        }
+        // zero the padding columns of the lines this block owns
+        if (out_stride > a.nu) {
+            const int pad = out_stride - a.nu;
+            for (int idx = tid; idx < (i1 - i0) * ns * pad; idx += kFwdThreads) {
+                const int l = idx / pad, m = a.order[i0 + l / ns];
+                a.rt[((size_t)m * a.nz + k0 + l % ns) * out_stride + a.nu + idx % pad] = 0.f;
+            }
+        }
+    }
+}
+
 constexpr int kTile = 16;
 constexpr int kPW = 32;     // staged rays per angle per tile
 constexpr int kAdjStage = 8;   // staged entries per thread per round of loads
@@ -684,6 +959,9 @@ static ProjArgs base_args(const mpi3d_plan *pl)
     a.cs = pl->cs;
     a.ax = pl->ax;
     a.ay = pl->ay;
+    a.ay1 = pl->ay1;
+    a.order = pl->order;
+    a.n_steep = pl->n_steep;
     a.nx = pl->nx; a.ny = pl->ny; a.nz = pl->nz; a.M = pl->M; a.nu = pl->nu; a.nup = pl->nup; a.nr = pl->nr;
     a.kz = pl->kz;
     a.adj_chunk = pl->adj_chunk;
@@ -717,6 +995,26 @@ static hipError_t launch_fwd(const mpi3d_plan *pl, const typename Texel<T>::V *v
 
 static hipError_t launch_fwd32(const mpi3d_plan *pl, const float *x, float *rt, int out_stride, hipStream_t st)
 {
+    if (pl->band.blocks > 0) {
+        ProjArgs a = base_args(pl);
+        a.rt = rt;
+        a.band_rows = pl->band.rows;
+        a.band_cols = pl->band.cols;
+        const int texels = std::max((a.band_rows + 1) * proj_pitch(a.nx), (a.ny + 2) * ((a.band_cols + 1) | 1));
+        const int nm[2] = {a.n_steep, a.M - a.n_steep};
+        for (int k = 0; k < 2; ++k) {
+            a.parts[k] = pl->band.parts[k];
+            if (nm[k] > 0 && (a.parts[k] < 1 || (long)((nm[k] + a.parts[k] - 1) / a.parts[k]) * a.nu > kFwdThreads * kBandRays))
+                return hipErrorInvalidValue;
+        }
+        if (texels > kBandTexels) return hipErrorInvalidValue;
+        const int lds = 16 * texels;
+        hipError_t e = hipFuncSetAttribute((const void *)proj_fwd_band_kernel,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(proj_fwd_band_kernel, dim3(pl->band.blocks), dim3(kFwdThreads), lds, st, a, x, out_stride);
+        return hipGetLastError();
+    }
     if (pl->fwd32.slices == 2) return launch_fwd<float2>(pl, x, pl->fwd32, rt, out_stride, st);
     return launch_fwd<float>(pl, x, pl->fwd32, rt, out_stride, st);
 }
