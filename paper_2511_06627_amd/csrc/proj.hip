@@ -351,12 +351,14 @@ __global__ __launch_bounds__(kFwdThreads) void proj_fwd_kernel(ProjArgs a, const
                 const float byb = by - (float)jb0;
                 float ylo = -a.half_nr, yhi = a.half_nr;
                 float ilo = -a.half_nr, ihi = a.half_nr;
-                if (s > 0.f) {
+                if (s != 0.f) {
                     const float rs = 1.f / s;
-                    ylo = fmaxf(ylo, (-kRange - bx) * rs);
-                    yhi = fminf(yhi, ((float)(a.nx + 1) + kRange - bx) * rs);
-                    ilo = fmaxf(ilo, (kEdge - bx) * rs);
-                    ihi = fminf(ihi, ((float)(a.nx + 1) - kEdge - bx) * rs);
+                    const float e0 = (-kRange - bx) * rs, e1 = ((float)(a.nx + 1) + kRange - bx) * rs;
+                    const float i0 = (kEdge - bx) * rs, i1 = ((float)(a.nx + 1) - kEdge - bx) * rs;
+                    ylo = fmaxf(ylo, fminf(e0, e1));
+                    yhi = fminf(yhi, fmaxf(e0, e1));
+                    ilo = fmaxf(ilo, fminf(i0, i1));
+                    ihi = fminf(ihi, fmaxf(i0, i1));
                 } else if (bx < kEdge || bx > (float)(a.nx + 1) - kEdge) {
                     ihi = ilo - 2.f;
                 }

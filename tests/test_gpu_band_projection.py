@@ -43,3 +43,18 @@ def test_band_projection(name):
     # lines are padded with zeros in the operator's workspace: A sees the same projections
     b = plan.forward(torch.from_numpy(np.ascontiguousarray(x)).float().cuda())
     assert torch.equal(b, plan.signal_fwd(torch.from_numpy(got).cuda()))
+
+
+def test_angles_beyond_half_turn():
+    """Rays with sin < 0 through the one- and two-slice kernels (a scan too small for the band kernel)."""
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    nx, ny, nz, M = 40, 28, 5, 7
+    theta = np.array([3.3, 4.0, 4.7124, 5.0, 6.0, -0.4, -2.0])
+    g = oracle_geometry(nx, ny, nz, M, 2048, 2048 / 256 + 1 / 3, 2.0, 1, 4, 1)
+    g.theta = theta
+    plan = Plan(nx, ny, nz, M, 2048, 2048 / 256 + 1 / 3, 2.0, 1, 4, 1, 1.0, theta=theta)
+    x = random_volume(g, 5)
+    want = projector.project(g, np.asarray(x, dtype=np.float64))
+    got = plan.project(torch.from_numpy(np.ascontiguousarray(x)).float().cuda()).cpu().numpy()
+    assert rel_l2(got, want) <= TOL32
