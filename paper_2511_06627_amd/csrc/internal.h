@@ -227,7 +227,8 @@ struct mpi3d_plan {
     int n_steep;
     int *order;
     float *ay1;
-    int kz, adj_chunk;
+    int kz, adj_chunk;             // backprojection: slices a block, angles a staged chunk; fp16 lines
+    int kz16, adj_chunk16;
     int max_parts;                 // float64 norm partials a launch may write (>= kMaxNormParts)
     // device tables (one allocation)
     void *tables;

@@ -448,23 +448,40 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                 pl->band.blocks = 1;
             }
         }
-        // Backprojection: 16 x 16 voxel tiles times kz slices per block.  The
-        // ray weights are formed once per voxel and angle and reused over kz
-        // slices, so take the largest kz that still gives about three blocks
-        // per CU; angles are staged in LDS in chunks of at most 40 KB.
+        // Backprojection: 16 x 16 voxel tiles times kz slices per block, the kz
+        // with the least estimated time: 5 us, then the blocks of a CU one after
+        // the other, each angle 52 ns for the weights and 10 ns a slice (fits to
+        // both kernels at 7 shapes from 32^3 x 8 to 256^2 x 128 x 60, within
+        // 15%); a CU with one block waits as long as it works, with two a
+        // quarter of that.  Measured at 192^2 x 96 x 36, kz 8 / 16 / 24 / 32: 41 / 37 /
+        // 39 / 37 us; 256^2 x 128 x 60: 127 / 102 / 98 / 88, 64: 102; 128^2 x 64 x 24:
+        // 13 / 17 / 21 / 23.  fp16 lines take units of 8 slices, so kz >= 8.
+        // Angles are staged in LDS in chunks of at most 40 KB, or 20 KB where
+        // more than four blocks share a CU (kz 8 at 256^2 x 128: 137 -> 127 us).
         const long tiles = (long)((pl->nx + 15) / 16) * ((pl->ny + 15) / 16);
-        pl->kz = 8;
-        for (int kz : {32, 16}) {
-            if (tiles * ((pl->nz + kz - 1) / kz) >= 768) {
-                pl->kz = kz;
-                break;
+        pl->max_parts = kMaxNormParts;
+        auto back_config = [&](int kmin, int unit_slices, int &kz_out, int &chunk_out) {
+            double best = 1e30;
+            long blocks = 0;
+            for (int kz : {4, 8, 16, 24, 32, 64}) {
+                if (kz < kmin) continue;
+                const long nb = tiles * ((pl->nz + kz - 1) / kz), b = (nb + 255) / 256;
+                const double wait = b == 1 ? 2.0 : b == 2 ? 1.25 : b == 3 ? 1.1 : 1.0;
+                const double t = 5e-6 + (double)b * pl->M * (52e-9 + 10e-9 * kz) * wait;
+                if (t < best * (1.0 - 1e-9)) {
+                    best = t;
+                    kz_out = kz;
+                    blocks = nb;
+                }
             }
-        }
-        const int chunk_max = std::max(1, (40 * 1024) / (pl->kz * 32 * (int)sizeof(float)));
-        const int nchunk = (pl->M + chunk_max - 1) / chunk_max;
-        pl->adj_chunk = (pl->M + nchunk - 1) / nchunk;
-        const long adj_blocks = tiles * ((pl->nz + pl->kz - 1) / pl->kz);
-        pl->max_parts = (int)std::max<long>(kMaxNormParts, adj_blocks);
+            const int kb = blocks > 4 * 256 ? 20 : 40;
+            const int chunk_max = std::max(1, kb * 1024 / ((kz_out / unit_slices | 1) * 16 * 32));
+            const int nchunk = (pl->M + chunk_max - 1) / chunk_max;
+            chunk_out = (pl->M + nchunk - 1) / nchunk;
+            pl->max_parts = (int)std::max<long>(pl->max_parts, blocks);
+        };
+        back_config(4, 4, pl->kz, pl->adj_chunk);
+        back_config(8, 8, pl->kz16, pl->adj_chunk16);
     }
 
     // ---- float64 host tables ------------------------------------------------
