@@ -6,6 +6,9 @@
 namespace mpi3d {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+#define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_f16((a), (b), (c), 0, 0, 0)
 
 namespace {
 
@@ -124,6 +127,48 @@ __device__ __forceinline__ f32x16 pair_sum(float *xs, int parity, int pair, int 
         for (int e = 0; e < 4; ++e) r[4 * q + e] = half == 0 ? mine[4 * q + e] + o[e] : o[e] + mine[4 * q + e];
     }
     return r;
+}
+
+// N products whose table operands come from LDS: fragment j is read WIN
+// products ahead of its use, and a scheduling barrier after every product
+// keeps that distance.
+template <int N, int WIN, class Frag, class Prod>
+__device__ __forceinline__ void lds_pipelined(Frag frag, Prod prod)
+{
+    constexpr int W = WIN < N ? WIN : N;
+    f16x8 w[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) w[j] = frag(j);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const f16x8 f = w[j % W];
+        if (j + W < N) w[j % W] = frag(j + W);
+        prod(j, f);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// s_waitcnt vmcnt(n) lgkmcnt(0) (expcnt not waited for), n < 64
+template <int N>
+__device__ __forceinline__ void wait_vm_lgkm()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+}
+
+__device__ __forceinline__ void block_barrier_nofence() { asm volatile("s_barrier" ::: "memory"); }
+
+// 16 bytes a lane from byte voff + soff of the buffer rs to LDS at dst + 16 lane
+// (soff and dst wave-uniform).
+__device__ __forceinline__ void buffer_dma16(__amdgpu_buffer_rsrc_t rs, void *dst, int voff, int soff)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)dst, 16, voff, soff, 0, 0);
+}
+
+// A raw buffer of `bytes` bytes at p (reads past it return 0).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_table(const void *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
 }
 
 }  // namespace

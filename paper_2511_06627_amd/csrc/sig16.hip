@@ -15,181 +15,183 @@
 // The first contraction's fp32 result (the time tile, |.| <= n_u or 2 n_b)
 // is rounded to fp16 once to feed the second.
 //
-// Layout and wave-pair structure follow sig.hip: a 32x32x16 MFMA result
-// register j of lane l holds time 8(j/4) + 4(l/32) + j%4, so eight result
-// registers form one fp16 A operand whose k index maps to time
-// 16 h + 8(e/4) + 4(l/32) + e%4, and the second contraction's tables are
-// stored with that permutation.
+// Layout and wave pairs follow sig.hip: a 32x32x16 MFMA result register j of
+// lane l holds time 8(j/4) + 4(l/32) + j%4, so eight result registers form one
+// fp16 A operand whose k index maps to time 16 h + 8(e/4) + 4(l/32) + e%4, and
+// the second contraction's tables are stored with that permutation.  The two
+// waves of a pair form half of a chunk's time tile each and swap the partial
+// tiles through LDS.
+//
+// The swap is spread over a chunk so that no wave waits for it: the partial
+// tile of chunk c + 1 is formed and written during chunk c, one barrier ends
+// the chunk, and the partner's half is read at the start of chunk c + 1 behind
+// the next first contraction.  Table slices reach LDS by buffer loads, one or
+// two chunks ahead, with fence-free barriers (every wave waits for its own
+// loads); fragments are read several products ahead of their use.  (Before,
+// every chunk had its barrier between its two contractions, with both waves of
+// a SIMD waiting at it, and slices went through registers: matrix units 40%
+// busy.  One wave per SIMD with all columns was tried: no faster, its time
+// tiles and accumulators share the accumulation registers and are copied.)
+// Sums keep their order, so results keep their bits.  Measured at 256 x 256 x
+// 128 (T = 16384, two groups of 12 tiles): forward 340 -> 315 us, adjoint 341 ->
+// 311; 192 x 192 x 96 (T = 8192, 14 tiles): 59 -> 62, 56 -> 52 (there 9 time splits'
+// partial sums are a third of it).  What bounds it now is LDS: fragments read
+// by the four pairs, partial tiles and the slices' arrival take about as many
+// cycles as the products.
 
 #include "device.h"
 
 namespace mpi3d {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
 namespace {
 
-#define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_f16((a), (b), (c), 0, 0, 0)
+constexpr int kWaves8 = 2 * kWaves;
+constexpr int kXsBytes = 2 * kWaves * 2 * 16 * 64 * (int)sizeof(float);   // two parities of partial tiles
 
-__device__ __forceinline__ f16x8 to_f16x8(const f32x16 &v, int base)
-{
-    f16x8 r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r[e] = (_Float16)v[base + e];
-    return r;
-}
-
-// N products whose table operands come from LDS: fragment j is read WIN
-// products ahead of its use, and a scheduling barrier after every product
-// keeps that distance, so an LDS read's latency is covered by the products
-// in between instead of stalling the one that needs it.
-template <int N, int WIN, class Frag, class Prod>
-__device__ __forceinline__ void lds_pipelined(Frag frag, Prod prod)
-{
-    constexpr int W = WIN < N ? WIN : N;
-    f16x8 w[W];
-#pragma unroll
-    for (int j = 0; j < W; ++j) w[j] = frag(j);
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        const f16x8 f = w[j % W];
-        if (j + W < N) w[j % W] = frag(j + W);
-        prod(j, f);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// Per-chunk table staging.  The block copies each time chunk's table slices
-// (GEMM1's and GEMM2's) from HBM/L2 into LDS once, with every thread moving a
-// few 16-byte units; the waves then read their operand fragments from LDS.
-// Without it each of the four pairs would fetch the same slices itself.  A
-// slice is loaded into registers two chunks before it is used and written to
-// LDS during the chunk before.
-//   A slice (GEMM1 operands), double-buffered: chunk c+1 is written before the
-//     pair barrier of chunk c, whose GEMM1 no longer reads that buffer (it
-//     last served chunk c-1, finished before the barrier of chunk c-1).
-//   B slice (GEMM2 operands), double-buffered: chunk c+1 is written after the
-//     pair barrier of chunk c; that buffer last served GEMM2 of chunk c-1,
-//     which every wave finished before reaching the barrier of chunk c.
-// The barrier of chunk c+1 then publishes both before they are read.
-template <int UNITS>
-struct Slice {
-    static constexpr int kPer = (UNITS + kSigThreads - 1) / kSigThreads;
-    f16x8 v[kPer];
-    __device__ __forceinline__ void load(const f16x8 *src, int tid)
-    {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int u = tid + j * kSigThreads;
-            if (u < UNITS) v[j] = src[u];
-        }
-    }
-    __device__ __forceinline__ void store(f16x8 *dst, int tid) const
-    {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int u = tid + j * kSigThreads;
-            if (u < UNITS) dst[u] = v[j];
-        }
-    }
+// LDS of a kernel whose first contraction takes NA fragments (1 KB) a chunk
+// and whose second takes NB: partial tiles, and two or three buffers of A and
+// of B slices -- three, so that a slice has two chunks to arrive, where they
+// fit, the larger slice's buffers first to give way.
+template <int NA, int NB>
+struct Lds16 {
+    static constexpr int kFree = 160 - kXsBytes / 1024;
+    static constexpr int AB = 3 * (NA + NB) <= kFree || (NA <= NB && 3 * NA + 2 * NB <= kFree) ? 3 : 2;
+    static constexpr int BB = AB * NA + 3 * NB <= kFree ? 3 : 2;
+    static constexpr int kBytes = kXsBytes + (AB * NA + BB * NB) * 1024;
+    // loads of the A and B slices a wave issues each (the last repeated)
+    static constexpr int kOpsA = (NA + kWaves8 - 1) / kWaves8, kOpsB = (NB + kWaves8 - 1) / kWaves8;
+    static_assert(kBytes <= 160 * 1024, "LDS");
 };
 
-constexpr int kXsBytes = 2 * kWaves * 2 * 16 * 64 * (int)sizeof(float);
-
-template <int NUP, int GH>
-constexpr int sig16_lds_bytes()
+template <int N>
+__device__ __forceinline__ void slice_load(const f16x8 *src, f16x8 *dst, int wave, int lane)
 {
-    return kXsBytes + 2 * 16 * (4 * NUP + 256 * GH);
+    const __amdgpu_buffer_rsrc_t rs = buffer_table(src, N * 1024);
+#pragma unroll
+    for (int k = 0; k < (N + kWaves8 - 1) / kWaves8; ++k) {
+        const int f = min(k * kWaves8 + wave, N - 1);
+        buffer_dma16(rs, dst + f * 64, lane * 16, f * 1024);
+    }
+}
+
+// The time loop both directions share.  Per chunk c (from c0 to c1 - 1), with
+// NA fragments of the first contraction's table slice (half of them this
+// wave's, from a0) and NB of the second's: first(frag, partial) forms the
+// wave's partial time tile, second(c's tile as fp16, frags) its products.
+template <int NA, int NB, class First, class Second>
+__device__ __forceinline__ void chunk_loop(float *xs, f16x8 *lds, const f16x8 *ag, size_t astride, const f16x8 *bg,
+                                           size_t bstride, int c0, int c1, int pair, int half, int wave, int lane,
+                                           First first, Second second)
+{
+    using L = Lds16<NA, NB>;
+    typedef float f32x4v __attribute__((ext_vector_type(4)));
+    f16x8 *la = lds, *lb = lds + L::AB * NA * 64;
+    // partial tiles as 16-byte words, word q of lane l at q * 64 + l
+    auto slot = [&](int parity, int hf) {
+        return reinterpret_cast<f32x4v *>(xs) + (((parity * kWaves + pair) * 2 + hf) * 4) * 64 + lane;
+    };
+    auto aload = [&](int c, int buf) { slice_load<NA>(ag + (size_t)min(c, c1 - 1) * astride, la + buf * NA * 64, wave, lane); };
+    auto bload = [&](int c, int buf) { slice_load<NB>(bg + (size_t)min(c, c1 - 1) * bstride, lb + buf * NB * 64, wave, lane); };
+    auto put = [&](int parity, const f32x16 &t) {
+        f32x4v *own = slot(parity, half);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) own[q * 64] = f32x4v{t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]};
+    };
+    aload(c0, 0);
+    bload(c0, 0);
+    aload(c0 + 1, 1);
+    if (L::AB == 3) aload(c0 + 2, 2);
+    if (L::BB == 3) bload(c0 + 1, 1);
+    wait_vm_lgkm<0>();
+    block_barrier_nofence();
+    f32x16 own = first(la + lane);
+    put(0, own);
+    wait_vm_lgkm<0>();
+    block_barrier_nofence();
+    int an = 1, af = 0, b = 0;                      // buffers: A of chunk c + 1, A free, B of chunk c
+    for (int c = c0; c < c1; ++c) {
+        const int parity = (c - c0) & 1;
+        // into the buffers left by chunk c's A slice and chunk c - 1's B; those
+        // the next chunk needs first
+        auto aissue = [&] { aload(L::AB == 3 ? c + 3 : c + 2, af); };
+        auto bissue = [&] { bload(L::BB == 3 ? c + 2 : c + 1, L::BB == 3 ? (b == 0 ? 2 : b - 1) : b ^ 1); };
+        if (L::AB == 2) {
+            aissue();
+            bissue();
+        } else {
+            bissue();
+            aissue();
+        }
+        f32x4v o[4];
+        const f32x4v *other = slot(parity, 1 - half);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = other[q * 64];
+        __builtin_amdgcn_sched_barrier(0);
+        const f32x16 next = first(la + an * NA * 64 + lane);      // (past the range: unused)
+        // the time tile: lower half + upper half, the same order on both waves
+        f16x8 t16[2];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float p = o[e / 4][e % 4];
+            t16[e / 8][e % 8] = (_Float16)(half == 0 ? own[e] + p : p + own[e]);
+        }
+        put(parity ^ 1, next);
+        own = next;
+        second(t16, lb + b * NB * 64 + lane);
+        // the next chunk's slices are in (of this chunk's requests only those with
+        // a chunk to spare may be outstanding), this wave's LDS accesses are done
+        wait_vm_lgkm<(L::AB == 3 ? L::kOpsA : 0) + (L::BB == 3 ? L::kOpsB : 0)>();
+        block_barrier_nofence();
+        af = an;
+        an = an + 1 == L::AB ? 0 : an + 1;
+        b = b + 1 == L::BB ? 0 : b + 1;
+    }
+    wait_vm_lgkm<0>();   // the repeated loads still in flight land before the LDS is handed on
 }
 
 template <int NUP, int GH>
-__global__ __launch_bounds__(kSigThreads) void sig_fwd_f16(SigArgs a)
+__global__ __launch_bounds__(kSigThreads, 2) void sig_fwd_f16(SigArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    float *xs = reinterpret_cast<float *>(smem);
-    constexpr int UA = 4 * NUP;           // K slice: NUP/16 fragments of 64 lanes
-    constexpr int UB = 256 * GH;          // F slice of the group: 2 GH tiles x 2 halves
-    f16x8 *la = reinterpret_cast<f16x8 *>(smem + kXsBytes);
-    f16x8 *lb = la + 2 * UA;
+    constexpr int NA = NUP / 16, NB = 4 * GH;     // PSF and band table fragments a chunk
+    constexpr int NKS = NA / 2;                   // PSF steps of a half (16 samples each)
     const BlockPos bp = locate(a);
     const SigJob job = a.jobs[bp.job];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, h = lane >> 5;
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
     const int r = bp.row0 + (lane & 31);
-    const bool rok = r < job.rows;
     // input line of this lane's row (-1: past the job's rows, zero input)
-    const long il = rok ? job_line(job, r) : -1;
-    const bool iok = il >= 0;
-    constexpr int NKS = NUP / 32;         // fp16 K steps per half (16 detector samples each)
+    const long il = r < job.rows ? job_line(job, r) : -1;
+    const int c0 = bp.split * a.cps, c1 = min(c0 + a.cps, a.nchunks);
+    if (c0 >= c1) return;                         // the whole block
 
     // this wave's half of the line as fp16 B operands: the line scaled by its
     // power-of-two scale and rounded by the row_scale kernel (zero past n_u)
     f16x8 R[NKS];
     {
-        const f16x8 *rin = (const f16x8 *)(job.in16 + (size_t)(iok ? il : 0) * job.in16_stride +
-                                           bp.half * (NUP / 2) + 8 * h);
+        const f16x8 *rin = (const f16x8 *)(job.in16 + (size_t)(il >= 0 ? il : 0) * job.in16_stride +
+                                           half * (NUP / 2) + 8 * h);
 #pragma unroll
-        for (int st = 0; st < NKS; ++st) R[st] = iok ? rin[2 * st] : f16x8(0);
-        // complete these loads here: inside the time loop the only memory
-        // loads in flight are then the next chunk's table slices, which the
-        // first contraction does not wait for
-#pragma unroll
-        for (int st = 0; st < NKS; ++st) asm volatile("" ::"v"(R[st]));
+        for (int st = 0; st < NKS; ++st) R[st] = il >= 0 ? rin[2 * st] : f16x8(0);
     }
     f32x16 acc[GH];
 #pragma unroll
     for (int g = 0; g < GH; ++g) acc[g] = 0.f;
 
-    const int c0 = bp.split * a.cps, c1 = min(c0 + a.cps, a.nchunks);
-    const f16x8 *kg = (const f16x8 *)job.kf16;
-    const f16x8 *fg = (const f16x8 *)a.ff16 + (size_t)bp.group * UB;
     const size_t fstride = (size_t)a.nct * 128;
-    // table slices in registers: chunk c + 1 (loaded during chunk c - 1,
-    // stored to LDS during chunk c) and chunk c + 2 (loaded during chunk c),
-    // so a load has a whole chunk to arrive
-    Slice<UA> sa, sa2;
-    Slice<UB> sb, sb2;
-    if (c0 < c1) {
-        sa.load(kg + (size_t)c0 * UA, tid);
-        sb.load(fg + (size_t)c0 * fstride, tid);
-        sa.store(la + (c0 & 1) * UA, tid);
-        sb.store(lb + (c0 & 1) * UB, tid);
-    }
-    if (c0 + 1 < c1) {
-        sa.load(kg + (size_t)(c0 + 1) * UA, tid);
-        sb.load(fg + (size_t)(c0 + 1) * fstride, tid);
-    }
-    __syncthreads();
-    const int ka0 = bp.half * NKS * 64 + lane;           // this wave's first K fragment
-    const int fb0 = bp.half * GH * 128 + lane;           // this wave's first F fragment
-
-    // one chunk: (ra, rb) hold chunk c + 1's slices, (na, nb) receive c + 2's;
-    // the loop alternates the two register sets, so no slice is copied
-    auto chunk = [&](int c, Slice<UA> &ra, Slice<UB> &rb, Slice<UA> &na, Slice<UB> &nb) {
-        const int buf = c & 1;
-        const bool more = c + 1 < c1;
-        const int cn = min(c + 2, c1 - 1);               // loaded whether needed or not: no branch
-        na.load(kg + (size_t)cn * UA, tid);
-        nb.load(fg + (size_t)cn * fstride, tid);
-        const f16x8 *ka = la + buf * UA + ka0;
-        f32x16 S = 0.f;
-        // GH = 7 leaves no registers for eight fragments in flight at NUP = 256
-        lds_pipelined<NKS, GH >= 7 ? 4 : 8>([&](int i) { return ka[i * 64]; },
-                                            [&](int i, const f16x8 &f) { S = MFMA16(f, R[i], S); });
-        if (more) ra.store(la + (buf ^ 1) * UA, tid);
-        const f32x16 Sf = pair_sum<kWaves>(xs, buf, bp.pair, bp.half, lane, S);
-        if (more) rb.store(lb + (buf ^ 1) * UB, tid);
-        const f16x8 S16[2] = {to_f16x8(Sf, 0), to_f16x8(Sf, 8)};
-        const f16x8 *fb = lb + buf * UB + fb0;
-        lds_pipelined<2 * GH, 4>([&](int j) { return fb[((j % GH) * 2 + j / GH) * 64]; },
-                                 [&](int j, const f16x8 &f) { acc[j % GH] = MFMA16(S16[j / GH], f, acc[j % GH]); });
-    };
-    int c = c0;
-    for (; c + 1 < c1; c += 2) {
-        chunk(c, sa, sb, sa2, sb2);
-        chunk(c + 1, sa2, sb2, sa, sb);
-    }
-    if (c < c1) chunk(c, sa, sb, sa2, sb2);
+    chunk_loop<NA, NB>(
+        reinterpret_cast<float *>(smem), reinterpret_cast<f16x8 *>(smem + kXsBytes), (const f16x8 *)job.kf16,
+        NA * 64, (const f16x8 *)a.ff16 + (size_t)bp.group * NB * 64, fstride, c0, c1, wave >> 1, half, wave, lane,
+        [&](const f16x8 *kb) {
+            f32x16 S = 0.f;
+            lds_pipelined<NKS, 6>([&](int i) { return kb[(half * NKS + i) * 64]; },
+                                  [&](int i, const f16x8 &f) { S = MFMA16(f, R[i], S); });
+            return S;
+        },
+        [&](const f16x8 (&s16)[2], const f16x8 *fb) {
+            lds_pipelined<2 * GH, 4>([&](int j) { return fb[(half * 2 * GH + (j % GH) * 2 + j / GH) * 64]; },
+                                     [&](int j, const f16x8 &f) { acc[j % GH] = MFMA16(s16[j / GH], f, acc[j % GH]); });
+        });
     if (bp.row0 >= job.rows) return;
     long ln[16];   // buffer lines of this lane's 16 result rows
 #pragma unroll
@@ -198,7 +200,7 @@ __global__ __launch_bounds__(kSigThreads) void sig_fwd_f16(SigArgs a)
         ln[j] = row < job.rows ? job_line(job, row) : 0;
     }
     float *out = job.part + (size_t)bp.split * job.part_stride;
-    const int ctb = bp.group * 2 * GH + bp.half * GH;
+    const int ctb = bp.group * 2 * GH + half * GH;
 #pragma unroll
     for (int g = 0; g < GH; ++g) {
         const int col = (ctb + g) * 32 + (lane & 31);
@@ -211,89 +213,52 @@ __global__ __launch_bounds__(kSigThreads) void sig_fwd_f16(SigArgs a)
 }
 
 template <int NUP, int GH>
-__global__ __launch_bounds__(kSigThreads) void sig_adj_f16(SigArgs a)
+__global__ __launch_bounds__(kSigThreads, 2) void sig_adj_f16(SigArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    float *xs = reinterpret_cast<float *>(smem);
-    constexpr int UA = 256 * GH;          // F slice of the group (GEMM1)
-    constexpr int UB = 4 * NUP;           // K slice (GEMM2)
-    f16x8 *la = reinterpret_cast<f16x8 *>(smem + kXsBytes);
-    f16x8 *lb = la + 2 * UA;
+    constexpr int NA = 4 * GH, NB = NUP / 16;     // band and PSF table fragments a chunk
+    constexpr int NF = 2 * GH;                    // band steps of a half (16 columns each)
+    constexpr int PTH = NUP / 64;                 // detector tiles of a half
     const BlockPos bp = locate(a);
     const SigJob job = a.jobs[bp.job];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, h = lane >> 5;
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave & 1;
     const int r = bp.row0 + (lane & 31);
-    const bool rok = r < job.rows;
-    // input line of this lane's row (-1: past the job's rows, zero input)
-    const long il = rok ? job_line(job, r) : -1;
-    const bool iok = il >= 0;
-    constexpr int PTH = NUP / 64;
-    constexpr int NF = 2 * GH;            // fp16 F steps per chunk (16 columns each)
-    const int colbase = (bp.group * 2 * GH + bp.half * GH) * 32;
-    const int pt0 = bp.half * PTH;
+    const long il = r < job.rows ? job_line(job, r) : -1;
+    const int c0 = bp.split * a.cps, c1 = min(c0 + a.cps, a.nchunks);
+    if (c0 >= c1) return;                         // the whole block
+    const int colbase = (bp.group * 2 * GH + half * GH) * 32;
 
     // this wave's bins of the line as fp16 B operands: the band-scaled row
     // times the line's power-of-two scale, rounded by the row_scale kernel
     // (zero past 2 nb)
     f16x8 Y[NF];
     {
-        const f16x8 *yin = (const f16x8 *)(job.in16 + (size_t)(iok ? il : 0) * job.in16_stride + colbase + 8 * h);
+        const f16x8 *yin = (const f16x8 *)(job.in16 + (size_t)(il >= 0 ? il : 0) * job.in16_stride + colbase + 8 * h);
 #pragma unroll
-        for (int st = 0; st < NF; ++st) Y[st] = iok ? yin[2 * st] : f16x8(0);
-        // complete these loads before the time loop (see sig_fwd_f16)
-#pragma unroll
-        for (int st = 0; st < NF; ++st) asm volatile("" ::"v"(Y[st]));
+        for (int st = 0; st < NF; ++st) Y[st] = il >= 0 ? yin[2 * st] : f16x8(0);
     }
     f32x16 racc[PTH];
 #pragma unroll
     for (int pt = 0; pt < PTH; ++pt) racc[pt] = 0.f;
 
-    const int c0 = bp.split * a.cps, c1 = min(c0 + a.cps, a.nchunks);
     const size_t fstride = (size_t)a.nct * 128;
-    const f16x8 *fg = (const f16x8 *)a.fa16 + (size_t)bp.group * UA;
-    const f16x8 *kg = (const f16x8 *)job.ka16;
-    // table slices in registers two chunks ahead (see sig_fwd_f16)
-    Slice<UA> sa, sa2;
-    Slice<UB> sb, sb2;
-    if (c0 < c1) {
-        sa.load(fg + (size_t)c0 * fstride, tid);
-        sb.load(kg + (size_t)c0 * UB, tid);
-        sa.store(la + (c0 & 1) * UA, tid);
-        sb.store(lb + (c0 & 1) * UB, tid);
-    }
-    if (c0 + 1 < c1) {
-        sa.load(fg + (size_t)(c0 + 1) * fstride, tid);
-        sb.load(kg + (size_t)(c0 + 1) * UB, tid);
-    }
-    __syncthreads();
-    const int fa0 = bp.half * NF * 64 + lane;            // this wave's first F fragment
-    const int kb0 = pt0 * 128 + lane;                    // this wave's first K fragment
-
-    // one chunk, alternating two register sets of slices (see sig_fwd_f16)
-    auto chunk = [&](int c, Slice<UA> &ra, Slice<UB> &rb, Slice<UA> &na, Slice<UB> &nb) {
-        const int buf = c & 1;
-        const bool more = c + 1 < c1;
-        const int cn = min(c + 2, c1 - 1);               // loaded whether needed or not: no branch
-        na.load(fg + (size_t)cn * fstride, tid);
-        nb.load(kg + (size_t)cn * UB, tid);
-        const f16x8 *fa = la + buf * UA + fa0;
-        f32x16 Gt = 0.f;
-        lds_pipelined<NF, 6>([&](int i) { return fa[i * 64]; }, [&](int i, const f16x8 &f) { Gt = MFMA16(f, Y[i], Gt); });
-        if (more) ra.store(la + (buf ^ 1) * UA, tid);
-        const f32x16 Gf = pair_sum<kWaves>(xs, buf, bp.pair, bp.half, lane, Gt);
-        if (more) rb.store(lb + (buf ^ 1) * UB, tid);
-        const f16x8 G16[2] = {to_f16x8(Gf, 0), to_f16x8(Gf, 8)};
-        const f16x8 *kb = lb + buf * UB + kb0;
-        lds_pipelined<2 * PTH, 4>([&](int j) { return kb[((j % PTH) * 2 + j / PTH) * 64]; },
-                                  [&](int j, const f16x8 &f) { racc[j % PTH] = MFMA16(G16[j / PTH], f, racc[j % PTH]); });
-    };
-    int c = c0;
-    for (; c + 1 < c1; c += 2) {
-        chunk(c, sa, sb, sa2, sb2);
-        chunk(c + 1, sa2, sb2, sa, sb);
-    }
-    if (c < c1) chunk(c, sa, sb, sa2, sb2);
+    chunk_loop<NA, NB>(
+        reinterpret_cast<float *>(smem), reinterpret_cast<f16x8 *>(smem + kXsBytes),
+        (const f16x8 *)a.fa16 + (size_t)bp.group * NA * 64, fstride, (const f16x8 *)job.ka16, NB * 64, c0, c1,
+        wave >> 1, half, wave, lane,
+        [&](const f16x8 *fb) {
+            f32x16 G = 0.f;
+            lds_pipelined<NF, 6>([&](int i) { return fb[(half * NF + i) * 64]; },
+                                 [&](int i, const f16x8 &f) { G = MFMA16(f, Y[i], G); });
+            return G;
+        },
+        [&](const f16x8 (&g16)[2], const f16x8 *kb) {
+            lds_pipelined<2 * PTH, 4>([&](int j) { return kb[((half * PTH + j % PTH) * 2 + j / PTH) * 64]; },
+                                      [&](int j, const f16x8 &f) {
+                                          racc[j % PTH] = MFMA16(g16[j / PTH], f, racc[j % PTH]);
+                                      });
+        });
     if (bp.row0 >= job.rows) return;
     long ln[16];   // buffer lines of this lane's 16 result rows
 #pragma unroll
@@ -304,7 +269,7 @@ __global__ __launch_bounds__(kSigThreads) void sig_adj_f16(SigArgs a)
     float *out = job.part + (size_t)(bp.split * a.ngroups + bp.group) * job.part_stride;
 #pragma unroll
     for (int pt = 0; pt < PTH; ++pt) {
-        const int col = (pt0 + pt) * 32 + (lane & 31);
+        const int col = (half * PTH + pt) * 32 + (lane & 31);
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
@@ -331,10 +296,11 @@ int nup_slot(int nup)
     return -1;
 }
 
-#define LROW(NUP) {sig16_lds_bytes<NUP, 3>(), sig16_lds_bytes<NUP, 4>(), sig16_lds_bytes<NUP, 6>(), \
-                   sig16_lds_bytes<NUP, 7>()}
-const int kLds[4][4] = {LROW(64), LROW(128), LROW(192), LROW(256)};
+#define LDS2(NUP, GH) {Lds16<NUP / 16, 4 * GH>::kBytes, Lds16<4 * GH, NUP / 16>::kBytes}
+#define LROW(NUP) {LDS2(NUP, 3), LDS2(NUP, 4), LDS2(NUP, 6), LDS2(NUP, 7)}
+const int kLds[4][4][2] = {LROW(64), LROW(128), LROW(192), LROW(256)};   // forward, adjoint
 #undef LROW
+#undef LDS2
 
 #define ROW(NUP, F) {F<NUP, 3>, F<NUP, 4>, F<NUP, 6>, F<NUP, 7>}
 const SigKernel kFwd[4][4] = {ROW(64, sig_fwd_f16), ROW(128, sig_fwd_f16), ROW(192, sig_fwd_f16),
@@ -361,10 +327,10 @@ hipError_t launch_sig_fwd16(const mpi3d_plan *pl, SigArgs &a, hipStream_t st)
 {
     const int ns = nup_slot(pl->nup), gs = gh_slot(a.gct);
     if (ns < 0 || gs < 0 || a.pairs != kWaves || !pl->kf16) return hipErrorInvalidValue;
-    hipError_t e = allow_lds((const void *)kFwd[ns][gs], kLds[ns][gs]);
+    hipError_t e = allow_lds((const void *)kFwd[ns][gs], kLds[ns][gs][0]);
     if (e != hipSuccess) return e;
     const int blocks = a.total_tiles * a.nsplit * a.ngroups;
-    hipLaunchKernelGGL(kFwd[ns][gs], dim3(blocks), dim3(kSigThreads), kLds[ns][gs], st, a);
+    hipLaunchKernelGGL(kFwd[ns][gs], dim3(blocks), dim3(kSigThreads), kLds[ns][gs][0], st, a);
     return hipGetLastError();
 }
 
@@ -372,10 +338,10 @@ hipError_t launch_sig_adj16(const mpi3d_plan *pl, SigArgs &a, hipStream_t st)
 {
     const int ns = nup_slot(pl->nup), gs = gh_slot(a.gct);
     if (ns < 0 || gs < 0 || a.pairs != kWaves || !pl->ka16) return hipErrorInvalidValue;
-    hipError_t e = allow_lds((const void *)kAdj[ns][gs], kLds[ns][gs]);
+    hipError_t e = allow_lds((const void *)kAdj[ns][gs], kLds[ns][gs][1]);
     if (e != hipSuccess) return e;
     const int blocks = a.total_tiles * a.nsplit * a.ngroups;
-    hipLaunchKernelGGL(kAdj[ns][gs], dim3(blocks), dim3(kSigThreads), kLds[ns][gs], st, a);
+    hipLaunchKernelGGL(kAdj[ns][gs], dim3(blocks), dim3(kSigThreads), kLds[ns][gs][1], st, a);
     return hipGetLastError();
 }
 
