@@ -126,18 +126,24 @@ static int adj_parts(const mpi3d_plan *pl, int prec, bool serve)
     return (fused_pass(pl, prec) ? 1 : pl->n_passes) * nsplit_of(pl, prec, serve) * sig_cfg(pl, prec).ngroups;
 }
 
-static FacArgs fac_args(const LineJob &lj)
+// Line group gi of a line job; fwd under the tensor PSF: the lines are the
+// virtual lines of symmetric sums in the workspace.
+static FacArgs fac_args(const LineJob &lj, int gi, bool fwd)
 {
     const mpi3d_plan *pj = lj.pl;
     const mpi3d_plan::Fac &f = pj->fac;
-    const mpi3d_plan::LineGroup &lg = pj->groups[0];
+    const mpi3d_plan::LineGroup &lg = pj->groups[gi];
+    const int np = pj->n_passes;
     FacArgs a{};
-    a.job.in = lj.in;
-    a.job.in_stride = lj.in_stride;
+    a.job.in = fwd && np > 1 ? lj.w->sig : lj.in;
+    a.job.in_stride = fwd && np > 1 ? np * pj->nup : lj.in_stride;
     a.job.part = lj.w->part;
-    a.job.part_stride = pj->L * pj->nup;
-    a.kf = f.kf;
-    a.ka = f.ka;
+    a.np = np;
+    a.adj_pitch = np * pj->nup;
+    a.job.part_stride = pj->L * a.adj_pitch;
+    a.kf = f.kf + gi * f.k_stride;
+    a.ka = f.ka + gi * f.k_stride;
+    a.ka_stride = 2 * (long)pj->k_elems;
     a.job.rows = lg.rows;
     a.job.map_per = lg.per;
     a.job.map_nz = lg.gnz;
@@ -187,8 +193,8 @@ static void line_jobs(const LineJob &lj, int prec, bool fwd, bool serve, std::ve
             sj.part = lj.w->part;
             sj.part_stride = part_stride;
             const size_t ko = (size_t)gi * pj->n_passes * pj->k_elems;
-            sj.kf = pj->kff + ko;
-            sj.ka = pj->kaf + ko;
+            sj.kf = pj->kff ? pj->kff + ko : nullptr;
+            sj.ka = pj->kaf ? pj->kaf + ko : nullptr;
             sj.rows = lg.rows;
             sj.map_per = lg.per;
             sj.map_nz = lg.gnz;
@@ -269,9 +275,16 @@ static int sig_jobs(bool fwd, int prec, const LineJob *jobs, int n, bool serve, 
     const mpi3d_plan *pl = jobs[0].pl;
     if (fac_on(pl, prec)) {
         // one factored stage per line job (its own phase sums in its workspace)
+        // and line group after line group
         for (int j = 0; j < n; ++j) {
-            if (jobs[j].pl->line_key != pl->line_key || !jobs[j].pl->fac.on) return MPI3D_EINVAL;
-            TRY(fwd ? launch_fac_fwd(fac_args(jobs[j]), st) : launch_fac_adj(fac_args(jobs[j]), st));
+            const mpi3d_plan *pj = jobs[j].pl;
+            if (pj->line_key != pl->line_key || !pj->fac.on) return MPI3D_EINVAL;
+            if (fwd && pj->n_passes > 1)
+                TRY(launch_sym_lines(jobs[j].in, jobs[j].in_stride, pj->nu, pj->nup, row_passes(pj, true, MPI3D_MIXED),
+                                     jobs[j].w->sig, pj->nup, pj->nupf, st));
+            for (int gi = 0; gi < pj->n_line_groups; ++gi)
+                TRY(fwd ? launch_fac_fwd(fac_args(jobs[j], gi, true), st)
+                        : launch_fac_adj(fac_args(jobs[j], gi, false), st));
         }
         return MPI3D_OK;
     }
@@ -957,8 +970,9 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
         }
     }
     // the factored band DFT's stages and kernels (FP32 plans that take it)
-    const FacArgs fwd_fac = fac_on(pl, precision) ? fac_args(LineJob{pl, w.rt, pl->nup, &w}) : FacArgs{};
-    const FacArgs adj_fac = fac_on(pl, precision) ? fac_args(LineJob{pl, b, pl->nb2, &w}) : FacArgs{};
+    // (of the first line group)
+    const FacArgs fwd_fac = fac_on(pl, precision) ? fac_args(LineJob{pl, w.rt, pl->nup, &w}, 0, true) : FacArgs{};
+    const FacArgs adj_fac = fac_on(pl, precision) ? fac_args(LineJob{pl, b, pl->nb2, &w}, 0, false) : FacArgs{};
     const bool mixed = precision == MPI3D_MIXED;
     hipError_t err = mixed && kernel == 0 ? launch_to_bf16(pl->nvox, x, w.xb, st) : hipSuccess;
     // the mixed signal kernels read fp16 operand lines: prepared once, untimed

@@ -69,9 +69,10 @@ __host__ __device__ inline long job_line(const SigJob &j, int r)
     return (long)g * j.map_nz + j.map_off + (long)j.map_step * (r - g * j.map_per);
 }
 
-// The band DFT factored over drive cycles (FP32 scans with one PSF table and
-// one line group): time t = n1 + P n2 with n1 < P, n2 < C, T = C P, C = 32 or
-// 64.  The time signal is real, so its C-point DFT over n2 needs one slot of
+// The band DFT factored over drive cycles (FP32), one launch per line group
+// (each with its own PSF tables; under the tensor PSF np = R + 1 of them, the
+// forward's lines being np symmetric line sums laid end to end): time
+// t = n1 + P n2 with n1 < P, n2 < C, T = C P, C = 32 or 64.  The time signal is real, so its C-point DFT over n2 needs one slot of
 // two columns (cos, sin) per residue pair {r, C - r} of the kept bins mod C;
 // residues 0 and C / 2, whose sine columns vanish, share a slot (columns: the
 // plain and the alternating sum).  C = 32 always fits 16 slots; C = 64 is
@@ -100,6 +101,9 @@ struct FacArgs {
     int *lexp;               // [ylines] power-of-two exponent of each line's Y or Z
     int ylines;
     int nu, nup;
+    int np;                  // tables a line (1: no tensor PSF)
+    long ka_stride;          // halves between the tables of ka
+    int adj_pitch;           // floats a line of the adjoint's partial sums (np nup)
     int P, cj;               // phases, 32-cycle blocks per phase (C / 32)
     int yc, zst, R, U;       // yc = 2 zst
     int ucols;               // 32 U: columns of the forward's partial sums (unit, bin, re/im)
@@ -213,6 +217,8 @@ struct mpi3d_plan {
         int res;                  // distinct residues of the kept bins mod C
         float s_scale, g_scale, y_scale, z_scale;
         int y_exp, z_exp, w_exp, r_exp;
+        long max_rows;            // lines of the largest line group
+        long k_stride;            // halves between the line groups' tables in kf and in ka
         __half *kf, *ka, *ef, *ea, *wf, *wa;
         int *unit0, *qbin;
         int *bcol;                // [nb] column of bin j's real part in the forward's partial sums
@@ -304,7 +310,7 @@ int sig_fused_supported(int nupf, int gct);
 // Factored band DFT (sigfac.hip): forward writes Y then the job's partial
 // sums (psplit blocks of 32 U columns); adjoint writes Z then nsplit_adj
 // splits of nup-column partial sums.
-int fac_supported(int nup, int zst, int cj);
+int fac_supported(int nup, int zst, int cj, int np);
 hipError_t launch_fac_fwd(const FacArgs &a, hipStream_t st);
 hipError_t launch_fac_adj(const FacArgs &a, hipStream_t st);
 // one kernel of those stages: forward PSF contraction + residue DFT, forward
@@ -433,9 +439,9 @@ struct OpWs {
     float *sig;       // [n_passes][L][nup] tensor PSF: the passes' symmetric line sums (forward)
     uint16_t *rtb;    // [L][nup] fp16 lines of the mixed adjoint (its backprojection gathers)
     float *rtsc;      // [L] their per-line inverse scales
-    uint32_t *fac;    // phase sums of the factored band DFT (FP32): ceil(L / 32) tiles of
+    uint32_t *fac;    // phase sums of the factored band DFT (FP32; one line group's at a time): tiles of
                       // [P][2 zst][32 lines], then a spare line of P 2 zst words
-    int *lexp;        // [ceil(L / 32) 32] their line exponents
+    int *lexp;        // their line exponents
 };
 OpWs carve_op(const mpi3d_plan *pl, void *ws);
 int check_prec(const mpi3d_plan *pl, int32_t precision);

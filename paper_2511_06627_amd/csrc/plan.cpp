@@ -229,12 +229,12 @@ void op_layout(mpi3d_plan *pl, bool fac)
                                     std::max<size_t>(pl->nbp2, (size_t)c.ngroups * pl->nup));
     }
     size_t part_floats = (size_t)pl->n_passes * pl->L * parts;
-    if (pl->fused)   // one pass; adjoint lines of nupf
+    if (pl->fused && !fac)   // one pass; adjoint lines of nupf
         part_floats = std::max(part_floats, (size_t)pl->L * std::max(pl->scf.nsplit, pl->scf.serve_nsplit) *
                                                 std::max<size_t>(pl->nbp2, (size_t)pl->nupf));
     if (fac)   // adjoint: nsplit blocks of nup-column lines; forward: psplit of 32 U columns
         part_floats =
-            std::max(part_floats, (size_t)pl->L * std::max(f.nsplit_adj * pl->nup, f.psplit * 32 * f.U));
+            std::max(part_floats, (size_t)pl->L * std::max(f.nsplit_adj * pl->n_passes * pl->nup, f.psplit * 32 * f.U));
     pl->ws_part = put(sizeof(float) * part_floats);
     pl->ws_norm = put(sizeof(double) * pl->max_parts);
     // per tensor-PSF pass: the forward's symmetric line sums, their
@@ -247,7 +247,7 @@ void op_layout(mpi3d_plan *pl, bool fac)
     pl->ws_rtb = put(mixed ? sizeof(uint16_t) * pl->L * pl->nup : 0);
     pl->ws_rtsc = put(mixed ? sizeof(float) * pl->L : 0);
     pl->ws_sig = put(np > 1 ? sizeof(float) * np * pl->L * pl->nup : 0);
-    const long tile_lines = (pl->L + 31) / 32 * 32;
+    const long tile_lines = (f.max_rows + 31) / 32 * 32;   // one line group at a time
     pl->ws_fac = put(fac ? sizeof(uint32_t) * (tile_lines + 1) * f.P * 2 * f.zst : 0);
     pl->ws_lexp = put(fac ? sizeof(int) * tile_lines : 0);
     pl->op_ws_bytes = align256(o);
@@ -604,15 +604,21 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     // the FP32 operator, and their inner iterations blow a difference in its
     // last bits up, through the 16-bit roundings, to some 1e-5 of the result;
     // scans that bunch less keep the dense form's bits there.
-    if ((precisions & (1 << MPI3D_FP32)) && !pl->fused && pl->n_passes == 1 && pl->n_line_groups == 1 &&
-        n_ktab == 1 && T % 32 == 0) {
+    const int NPASS = pl->n_passes;
+    bool same_coup = true;     // every line group coupled over the same range
+    pl->fac.max_rows = 0;
+    for (int gi = 0; gi < pl->n_line_groups; ++gi) {
+        same_coup = same_coup && pl->groups[gi].coup == pl->pass_r;
+        pl->fac.max_rows = std::max<long>(pl->fac.max_rows, pl->groups[gi].rows);
+    }
+    if ((precisions & (1 << MPI3D_FP32)) && same_coup && T % 32 == 0) {
         // slot of residue r: 0 for r = 0 and C / 2, else min(r, C - r)
         auto slot_of = [](long r, int C) { return (int)(2 * r == C ? 0 : std::min(r, C - r)); };
         auto slots_of = [](int R, int C) { return C == 32 ? 16 : std::max(16, (R + 3) / 4 * 4); };
         // seconds per line: dense fp32 products at 1.1e14 flop/s; factored
         // split products (three each) at 8e14, the phase sums written and read
         // at 4 TB/s, the outer sum's fp32 products (32 columns a unit) at 1e14
-        double best = 2.0 * T * (NUP + NBP2) / 1.1e14;
+        double best = 2.0 * T * (NPASS * NUP + NBP2) / 1.1e14;
         int bestC = 0;
         for (int C = 32; C <= T && C <= 64; C += 32) {
             if (T % C) continue;
@@ -632,10 +638,11 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                 }
             const int zst = slots_of(R, C), rct = (2 * zst + 31) / 32, P = T / C;
             if (!(R <= 16 && mx <= 32) && !(R <= 24 && mx <= 24)) continue;
-            if (!fac_supported(NUP, zst, C / 32) ||
-                (double)((pl->L + 31) / 32 * 32 + 1) * P * 2 * zst >= 2147483647.0 || 4.0 * T * NUP >= 2147483647.0)
+            if (!fac_supported(NUP, zst, C / 32, NPASS) ||
+                (double)((pl->fac.max_rows + 31) / 32 * 32 + 1) * P * 2 * zst >= 2147483647.0 ||
+                4.0 * T * NUP * NPASS >= 2147483647.0)
                 continue;
-            const double cost = 6.0 * T * (NUP + 32 * rct) / 8e14 + 16.0 * P * zst / 4e12 + 128.0 * P * U / 1e14;
+            const double cost = 6.0 * T * (NPASS * NUP + 32 * rct) / 8e14 + 16.0 * P * zst / 4e12 + 128.0 * P * U / 1e14;
             if (cost < best) {
                 best = cost;
                 bestC = C;
@@ -703,7 +710,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             // The outer sums: forward waves of two tiles and a slot, adjoint
             // blocks of a tile; small scans also split the phase stages (8 and
             // 16 phases) until about 2048 waves (256 blocks) run.
-            const long tiles = (pl->L + 31) / 32;
+            const long tiles = (f.max_rows + 31) / 32;
             f.psplit = (int)std::max<long>(1, std::min<long>({8, 2048 / ((tiles + 1) / 2 * f.R), (f.P + 7) / 8}));
             f.zsplit = (int)std::max<long>(1, std::min<long>({8, 256 / tiles, (f.P + 15) / 16}));
             // Phase ranges of the line-tile kernels (8 tiles a block, one block a
@@ -714,11 +721,11 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             // of loads, about 0.1 us, and the bytes at 4 TB/s).
             const long tgroups = (tiles + kFacWaves - 1) / kFacWaves;
             const double t_phase = f.cj * (3.0 * NUP / 16 + 6.0 * ((2 * f.zst + 31) / 32)) * 64 / 0.6 / 2.4e9;
-            auto splits = [&](double per_range) {
+            auto splits = [&](long groups, double per_range) {
                 double tbest = 1e30;
                 int nbest = 1;
                 for (int ns = 1; ns <= std::min(f.P, 256); ++ns) {
-                    const double t = (double)((tgroups * ns + 255) / 256) * (4e-6 + (f.P + ns - 1) / ns * t_phase) +
+                    const double t = (double)((groups * ns + 255) / 256) * (4e-6 + (f.P + ns - 1) / ns * t_phase) +
                                      ns * per_range;
                     if (t < tbest * (1.0 - 1e-9)) {
                         tbest = t;
@@ -727,37 +734,48 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                 }
                 return nbest;
             };
-            f.nsplit = splits(0.0);
-            f.nsplit_adj = splits(1e-7 + 8.0 * pl->L * NUP / 4e12);
+            // (tensor lines: the forward's blocks are of 4 tiles, the adjoint's are np times as many)
+            f.nsplit = splits(NPASS * NUP <= 256 ? tgroups : (tiles + 3) / 4, 0.0);
+            f.nsplit_adj = splits(tgroups * NPASS, 1e-7 + 8.0 * pl->L * NUP * NPASS / 4e12);
             // a scan whose bins bunch little and that fits the no-allocation
             // entry point's scratch in the dense form stays dense where the
             // phase sums would not fit it
             op_layout(pl, false);
             const size_t dense_ws = pl->op_ws_bytes;
             op_layout(pl, true);
-            f.on = f.res <= 24 || !(dense_ws <= MPI3D_NOALLOC_SCRATCH_BYTES && pl->op_ws_bytes > MPI3D_NOALLOC_SCRATCH_BYTES);
+            f.on = (f.res <= 24 && n_ktab == 1) || !(dense_ws <= MPI3D_NOALLOC_SCRATCH_BYTES && pl->op_ws_bytes > MPI3D_NOALLOC_SCRATCH_BYTES);
         }
         if (pl->fac.on) {
             mpi3d_plan::Fac &f = pl->fac;
+            if (NPASS > 1) {       // virtual lines, as the fused dense pass has them
+                if (!pl->fused)    // (whose launch configuration nothing uses then)
+                    pl->scf = mpi3d_plan::SigCfg{kWidePairs, 1, 14, pl->nchunks, 1, 0, 0, pl->nchunks, 1};
+                pl->fused = true;
+                pl->nupf = NPASS * NUP;
+            }
+            f.k_stride = 2 * (long)KE * NPASS;
             // tables
             const int QM = f.qmax, C = bestC, P = f.P, CJ = f.cj, ZST = f.zst, YC = 2 * ZST;
             const int RCT = (YC + 31) / 32, NZS = (YC + 15) / 16;
             auto tp16 = [](int e2, int h) { return 8 * (e2 / 4) + 4 * h + (e2 % 4); };
             auto tof = [&](int c, int i) { return (c / CJ) + P * (32 * (c % CJ) + i); };   // chunk row -> time
-            const double *K0 = &K[0];
-            // PSF table scaled so its largest entry is in [2^14, 2^15); s_scale
+            // PSF tables scaled so their largest entry is in [2^14, 2^15); s_scale
             // keeps a time signal of lines below 2^15 at or below 2^15 by the
-            // largest row sum
+            // largest row sum (over a line's tables)
             double kmax = 0, ksum = 0;
-            for (int n = 0; n < T; ++n) {
-                double sum = 0;
-                for (int p = 0; p < NUP; ++p) {
-                    const double v = std::fabs(K0[(size_t)n * NUP + p]);
-                    kmax = std::max(kmax, v);
-                    sum += v;
+            for (int gi = 0; gi < pl->n_line_groups; ++gi)
+                for (int n = 0; n < T; ++n) {
+                    double sum = 0;
+                    for (int e2 = 0; e2 < NPASS; ++e2) {
+                        const double *row = &K[KE * (pl->groups[gi].table + e2) + (size_t)n * NUP];
+                        for (int p = 0; p < NUP; ++p) {
+                            const double v = std::fabs(row[p]);
+                            kmax = std::max(kmax, v);
+                            sum += v;
+                        }
+                    }
+                    ksum = std::max(ksum, sum);
                 }
-                ksum = std::max(ksum, sum);
-            }
             int kexp = 0, sexp = 0;
             if (kmax > 0) {
                 std::frexp(kmax, &kexp);
@@ -776,32 +794,40 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             // fragments of 64 lanes x 8 halves, hi then lo:
             //  kf [c][p / 16][hi, lo]: K[time row l % 32][p = 16 ks + 8 (l / 32) + e]
             //  ka [c][time step][p / 32][hi, lo]: K[time row 16 q + tp16(e, l / 32)][p = 32 pt + l % 32]
-            fkf.assign(2 * KE, 0);
-            fka.assign(2 * KE, 0);
+            // (kf: a chunk's tables e = 0 .. R one after the other; ka: table after
+            // table; line group after line group)
+            const size_t KG = 2 * KE * NPASS;       // halves a line group
+            fkf.assign(KG * pl->n_line_groups, 0);
+            fka.assign(KG * pl->n_line_groups, 0);
             std::vector<uint16_t> kh(32 * NUP), kl(32 * NUP);   // one chunk's pairs
             const double ksc = std::ldexp(1.0, kexp);
-            for (int c = 0; c < P * CJ; ++c) {
-                for (int i = 0; i < 32; ++i)
-                    for (int p = 0; p < NUP; ++p)
-                        half_pair(K0[(size_t)tof(c, i) * NUP + p] * ksc, kh[i * NUP + p], kl[i * NUP + p]);
-                for (int ks = 0; ks < NUP / 16; ++ks)
-                    for (int l = 0; l < 64; ++l)
-                        for (int e2 = 0; e2 < 8; ++e2) {
-                            const size_t o = (((size_t)c * (NUP / 16) + ks) * 2 * 64 + l) * 8 + e2;
-                            const int i = (l % 32) * NUP + 16 * ks + 8 * (l / 32) + e2;
-                            fkf[o] = kh[i];
-                            fkf[o + 512] = kl[i];
-                        }
-                for (int q = 0; q < 2; ++q)
-                    for (int pt = 0; pt < NUP / 32; ++pt)
-                        for (int l = 0; l < 64; ++l)
-                            for (int e2 = 0; e2 < 8; ++e2) {
-                                const size_t o = ((((size_t)c * 2 + q) * (NUP / 32) + pt) * 2 * 64 + l) * 8 + e2;
-                                const int i = (16 * q + tp16(e2, l / 32)) * NUP + 32 * pt + l % 32;
-                                fka[o] = kh[i];
-                                fka[o + 512] = kl[i];
-                            }
-            }
+            for (int gi = 0; gi < pl->n_line_groups; ++gi)
+                for (int e3 = 0; e3 < NPASS; ++e3)
+                    for (int c = 0; c < P * CJ; ++c) {
+                        const double *K0 = &K[KE * (pl->groups[gi].table + e3)];
+                        uint16_t *ckf = &fkf[KG * gi + ((size_t)c * NPASS + e3) * 64 * NUP];
+                        uint16_t *cka = &fka[KG * gi + 2 * KE * e3 + (size_t)c * 64 * NUP];
+                        for (int i = 0; i < 32; ++i)
+                            for (int p = 0; p < NUP; ++p)
+                                half_pair(K0[(size_t)tof(c, i) * NUP + p] * ksc, kh[i * NUP + p], kl[i * NUP + p]);
+                        for (int ks = 0; ks < NUP / 16; ++ks)
+                            for (int l = 0; l < 64; ++l)
+                                for (int e2 = 0; e2 < 8; ++e2) {
+                                    const size_t o = ((size_t)ks * 2 * 64 + l) * 8 + e2;
+                                    const int i = (l % 32) * NUP + 16 * ks + 8 * (l / 32) + e2;
+                                    ckf[o] = kh[i];
+                                    ckf[o + 512] = kl[i];
+                                }
+                        for (int q = 0; q < 2; ++q)
+                            for (int pt = 0; pt < NUP / 32; ++pt)
+                                for (int l = 0; l < 64; ++l)
+                                    for (int e2 = 0; e2 < 8; ++e2) {
+                                        const size_t o = (((size_t)q * (NUP / 32) + pt) * 2 * 64 + l) * 8 + e2;
+                                        const int i = (16 * q + tp16(e2, l / 32)) * NUP + 32 * pt + l % 32;
+                                        cka[o] = kh[i];
+                                        cka[o + 512] = kl[i];
+                                    }
+                    }
             // E[n2][2q] = cos, E[n2][2q + 1] = sin of 2 pi (r n2 mod C) / C, r the
             // slot's least residue; the slot of 0 and C / 2: 1 and (-1)^n2
             auto E = [&](int n2, int q, int part) -> double {
@@ -973,8 +999,8 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     o_fa = place(dense ? sizeof(float) * (size_t)TP * NBP2 : 0);
     o_ka = place(dense ? sizeof(float) * KE * n_ktab : 0);
     const size_t KEF = KE * pl->n_passes * pl->n_line_groups;   // fused tables, all groups
-    const size_t o_kff = pl->fused ? place(sizeof(float) * KEF) : 0;
-    const size_t o_kaf = pl->fused ? place(sizeof(float) * KEF) : 0;
+    const size_t o_kff = pl->fused && dense ? place(sizeof(float) * KEF) : 0;
+    const size_t o_kaf = pl->fused && dense ? place(sizeof(float) * KEF) : 0;
     const size_t o_gt = precomp ? place(sizeof(float) * gt.size()) : 0;
     const size_t o_gta = precomp ? place(sizeof(float) * gt.size()) : 0;
     const bool fac = pl->fac.on;
@@ -1149,7 +1175,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     ok = ok && (!dense || hipMemcpy(pl->ff, ff.data(), sizeof(float) * ff.size(), hipMemcpyHostToDevice) == hipSuccess);
     ok = ok && (!dense || hipMemcpy(pl->fa, fa.data(), sizeof(float) * fa.size(), hipMemcpyHostToDevice) == hipSuccess);
     ok = ok && (!dense || hipMemcpy(pl->ka, ka.data(), sizeof(float) * ka.size(), hipMemcpyHostToDevice) == hipSuccess);
-    if (pl->fused) {
+    if (pl->fused && dense) {
         // group g's tables table_g .. table_g + R side by side per time chunk:
         // a chunk of kf / ka holds NUP x 32 floats for detector samples (kf:
         // 8 per float4 step, ka: 32 per column tile) in the order the kernels

@@ -113,29 +113,28 @@ __device__ __forceinline__ int line_exponent(float m)
 }
 
 // The PSF table of the line-tile kernels in LDS.  A chunk (32 times x NUP
-// samples, hi and lo fragments, 128 NUP bytes) is used by all 8 waves of a
-// block; NS chunks (about 32 KB) make a stage, moved by global_load_lds into
-// three buffers so the stage after next is in flight while one is used, with
-// one barrier a stage.  The barrier carries no fence: each wave waits for its
-// own part of the next stage (every load but the youngest stage's) first.
-template <int NUP>
+// samples, hi and lo fragments, 128 NUP bytes) is used by all waves of a
+// block; NS chunks make a stage, moved by buffer loads into three buffers so
+// the stage after next is in flight while one is used, with one barrier a
+// stage.  The barrier carries no fence: each wave waits for its own part of
+// the next stage (every load but the youngest stage's) first.  (Buffer loads,
+// because the compiler orders its LDS waits behind global_load_lds as behind
+// flat accesses and then waits for every LDS read in flight at each use.)
+template <int NUP, int NS, int WAVES>
 struct PsfStage {
-    static constexpr int NS = NUP == 64 ? 4 : NUP == 128 ? 2 : 1;
     static constexpr int kFragChunk = NUP / 8;                 // 1 KB fragments a chunk (hi, lo)
     static constexpr int kFrags = NS * kFragChunk;
-    static constexpr int kOps = kFrags / kFacWaves;            // fragments a wave moves per stage
+    static constexpr int kOps = kFrags / WAVES;                // fragments a wave moves per stage
     static constexpr int kBytes = kFrags * 1024;
-    static_assert(kFrags % kFacWaves == 0, "whole fragments a wave");
+    static_assert(kFrags % WAVES == 0, "whole fragments a wave");
     // the stage from chunk c on (counted from the table at rs); chunks from
-    // nchunks on repeat the last one (unused).  Buffer loads, because the
-    // compiler orders its LDS waits behind global_load_lds as behind flat
-    // accesses and then waits for every LDS read in flight at each use.
+    // nchunks on repeat the last one (unused)
     static __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int c, int nchunks, f16x8 *lds, int buf,
                                                 int wave, int lane)
     {
 #pragma unroll
         for (int k = 0; k < kOps; ++k) {
-            const int f = k * kFacWaves + wave;
+            const int f = k * WAVES + wave;
             const int cc = min(c + f / kFragChunk, nchunks - 1);
             buffer_dma16(rs, lds + (buf * kFrags + f) * 64, lane * 16, (cc * kFragChunk + f % kFragChunk) * 1024);
         }
@@ -145,6 +144,17 @@ struct PsfStage {
         return buffer_table((const char *)tab + (size_t)c0 * kFragChunk * 1024, chunks * (kFragChunk * 1024));
     }
 };
+
+// Chunks a stage: about 32 KB for plain lines; a tensor line's NP tables are
+// staged one by one (or all of a chunk's where they are small).
+constexpr int stage_chunks(int nup, int np)
+{
+    if (np > 1) return nup == 64 && np % 2 == 0 ? np : 1;
+    return nup == 64 ? 4 : nup == 128 ? 2 : 1;
+}
+// Waves of the forward line-tile kernel: two a SIMD while a line's operands
+// (NP NUP / 2 registers) leave room, else one.
+constexpr int fwd_waves(int nup, int np) { return np * nup <= 256 ? kFacWaves : 4; }
 
 // Forward, per wave: 32 lines, phases [n1a, n1b).  Chunk c = n1 CJ + j holds
 // the times n1 + P (32 j + i), i < 32.  Both contractions run on fp16 MFMA in
@@ -157,18 +167,27 @@ struct PsfStage {
 // it stands; that one's result rows are the phase's columns, its lanes lines,
 // so a line's scale is undone by one exponent per lane and Y ([phase][column]
 // [32 lines] per tile) is written in whole 128-byte rows.
-template <int NUP, int ZST, int CJ>
-__global__ __launch_bounds__(64 * kFacWaves, 2) void fac_fwd_kernel(FacArgs a)
+//
+// NP > 1, the tensor PSF: a line is the R + 1 = NP symmetric line sums laid
+// end to end (NP NUP samples), its chunk the NP tables of a chunk one after
+// the other, and their products go to one time tile.  The lines stay in
+// registers (2 NP NUP / 64 words a lane, hi and lo), so above 256 samples a
+// block is 4 waves of up to 512 registers.  At 192 x 192 x 96, 36 angles,
+// T = 8192, four tables: 169 us against 628 for the dense pass on fp32 MFMA
+// (0.76 PFLOP/s of fp16 products; with one wave a SIMD the splits of a time
+// tile are not hidden), the adjoint 167 against 598.
+template <int NUP, int ZST, int CJ, int NP>
+__global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) void fac_fwd_kernel(FacArgs a)
 {
-    using Stage = PsfStage<NUP>;
-    constexpr int NS = Stage::NS;
-    constexpr int NKS = NUP / 16;                     // PSF contraction steps
+    constexpr int WAVES = fwd_waves(NUP, NP), NS = stage_chunks(NUP, NP);
+    using Stage = PsfStage<NUP, NS, WAVES>;
+    constexpr int NKS = NUP / 16;                     // PSF contraction steps a table
     constexpr int YC = 2 * ZST, RCT = (YC + 31) / 32; // columns of a phase, 32-column tiles
     constexpr int NE = RCT * 4;                       // residue table fragments a chunk
-    constexpr int GRP = NS > CJ ? NS : CJ;            // chunks of one loop body
+    constexpr int GRP = NP == 1 && NS > CJ ? NS : CJ;            // chunks of one loop body
     extern __shared__ __align__(16) f16x8 lk[];
     f16x8 *ebuf = lk + 3 * Stage::kFrags * 64;
-    const FacPos fp = fac_pos<kFacWaves>(a, a.nsplit);
+    const FacPos fp = fac_pos<WAVES>(a, a.nsplit);
     if (fp.n1a >= fp.n1b) return;                 // the whole block
     const bool active = fp.tile < a.tiles;        // a wave past the last tile still stages
     const SigJob &job = a.job;
@@ -178,50 +197,75 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_fwd_kernel(FacArgs a)
     const long il = active && r < job.rows ? job_line(job, r) : -1;
     const int c0 = fp.n1a * CJ, c1 = fp.n1b * CJ;
 
-    const __amdgpu_buffer_rsrc_t kf = Stage::table(a.kf, c0, c1 - c0);
-    Stage::load(kf, 0, c1 - c0, lk, 0, wave, lane);
-    Stage::load(kf, NS, c1 - c0, lk, 1, wave, lane);
+    const __amdgpu_buffer_rsrc_t kf = Stage::table(a.kf, c0 * NP, (c1 - c0) * NP);
+    Stage::load(kf, 0, (c1 - c0) * NP, lk, 0, wave, lane);
+    Stage::load(kf, NS, (c1 - c0) * NP, lk, 1, wave, lane);
     const f16x8 *ef = (const f16x8 *)a.ef;
-    for (int idx = tid; idx < CJ * NE * 64; idx += 64 * kFacWaves) ebuf[idx] = ef[idx];
+    for (int idx = tid; idx < CJ * NE * 64; idx += 64 * WAVES) ebuf[idx] = ef[idx];
 
     // the line: samples 16 ks + 8 h + 0..7, scaled and split
-    f16x8 rh[NKS], rl[NKS];
+    f16x8 rh[NP * NKS], rl[NP * NKS];
     {
-        float v[NKS][8];
         const float *rin = (const float *)job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride;
-        const bool vec = job.in_stride % 4 == 0 && (uintptr_t)job.in % 16 == 0 && job.in_stride >= NUP;
-        if (vec) {
+        const bool vec = job.in_stride % 4 == 0 && (uintptr_t)job.in % 16 == 0 && job.in_stride >= NP * NUP;
+        auto get4 = [&](int ks, float (&v)[8]) {     // 16-byte loads
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
+            for (int q = 0; q < 2; ++q) {
+                const int p = 16 * ks + 8 * h + 4 * q;
+                const f32x4 w = *reinterpret_cast<const f32x4 *>(rin + p);
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int p = 16 * ks + 8 * h + 4 * q;
-                    const f32x4 w = *reinterpret_cast<const f32x4 *>(rin + p);
+                for (int e = 0; e < 4; ++e) v[4 * q + e] = (il >= 0) & (NP > 1 | p + e < a.nu) ? w[e] : 0.f;
+            }
+        };
+        auto get1 = [&](int ks, float (&v)[8]) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[ks][4 * q + e] = il >= 0 && p + e < a.nu ? w[e] : 0.f;
-                }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int p = 16 * ks + 8 * h + e;
-                    v[ks][e] = il >= 0 && p < a.nu ? rin[p] : 0.f;
-                }
-        }
+            for (int e = 0; e < 8; ++e) {
+                const int p = 16 * ks + 8 * h + e;
+                v[e] = il >= 0 && p < a.nu ? rin[p] : 0.f;
+            }
+        };
         float m = 0.f;
+        auto scan = [&](const float (&v)[8]) {
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[ks][e]));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        const int le = line_exponent(m);
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
+            for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[e]));
+        };
+        auto split = [&](int ks, int le, const float (&v)[8]) {
             float w[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) w[e] = __builtin_ldexpf(v[ks][e], le);
+            for (int e = 0; e < 8; ++e) w[e] = __builtin_ldexpf(v[e], le);
             split8(w, rh[ks], rl[ks]);
+        };
+        int le;
+        if constexpr (NP == 1) {
+            float v[NKS][8];
+            if (vec) {               // (one branch: the loads of either form overlap)
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) get4(ks, v[ks]);
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) get1(ks, v[ks]);
+            }
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) scan(v[ks]);
+            m = fmaxf(m, __shfl_xor(m, 32));
+            le = line_exponent(m);
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) split(ks, le, v[ks]);
+        } else {   // in two passes: the registers hold no whole line (the workspace's, 16-byte aligned)
+#pragma unroll 4
+            for (int ks = 0; ks < NP * NKS; ++ks) {
+                float v[8];
+                get4(ks, v);
+                scan(v);
+            }
+            m = fmaxf(m, __shfl_xor(m, 32));
+            le = line_exponent(m);
+#pragma unroll
+            for (int ks = 0; ks < NP * NKS; ++ks) {
+                float v[8];
+                get4(ks, v);
+                split(ks, le, v);
+            }
         }
         // (every phase range writes the same exponent)
         if (active && h == 0) a.lexp[r] = le + a.y_exp;
@@ -241,39 +285,49 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_fwd_kernel(FacArgs a)
 #pragma unroll
         for (int k = 0; k < GRP; ++k) {
             const int c = cg + k;
-            if (k % NS == NS - 1) Stage::load(kf, c - c0 + NS + 1, c1 - c0, lk, nbuf, wave, lane);
-            if (active && (GRP == CJ || c < c1)) {
-                const f16x8 *kb = lk + (buf * Stage::kFrags + (k % NS) * Stage::kFragChunk) * 64 + lane;
-                f32x16 S = 0.f;
-                lds_pipelined<2 * NKS, 6>([&](int i) { return kb[i * 64]; },
-                                          [&](int i, const f16x8 &f) {
-                                              S = MFMA16(f, rh[i / 2], S);
-                                              if (i % 2 == 0) S = MFMA16(f, rl[i / 2], S);
-                                          });
-                f16x8 sh[2], sl[2];
+            // (with one wave a SIMD the waves past the last tile compute, too:
+            // a branch around the time tile costs copies of it)
+            const bool work = (NP > 1 || active) && (GRP == CJ || c < c1);
+            f32x16 S;
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    float w[8];
+            for (int e = 0; e < NP; ++e) {
+                const int t = k * NP + e;
+                if (t % NS == NS - 1) Stage::load(kf, (c - c0) * NP + e + NS + 1, (c1 - c0) * NP, lk, nbuf, wave, lane);
+                if (work) {
+                    const f16x8 *kb = lk + (buf * Stage::kFrags + (t % NS) * Stage::kFragChunk) * 64 + lane;
+                    if (e == 0) S = 0.f;
+                    lds_pipelined<2 * NKS, 6>([&](int i) { return kb[i * 64]; },
+                                              [&](int i, const f16x8 &f) {
+                                                  S = MFMA16(f, rh[e * NKS + i / 2], S);
+                                                  if (i % 2 == 0) S = MFMA16(f, rl[e * NKS + i / 2], S);
+                                              });
+                    if (e == NP - 1) {
+                        f16x8 sh[2], sl[2];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) w[e] = S[8 * q + e] * sscale;
-                    split8(w, sh[q], sl[q]);
-                }
-                const f16x8 *eb = ebuf + (k % CJ) * NE * 64 + lane;
+                        for (int q = 0; q < 2; ++q) {
+                            float w[8];
 #pragma unroll
-                for (int g = 0; g < RCT; ++g)
+                            for (int x = 0; x < 8; ++x) w[x] = S[8 * q + x] * sscale;
+                            split8(w, sh[q], sl[q]);
+                        }
+                        const f16x8 *eb = ebuf + (k % CJ) * NE * 64 + lane;
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const f16x8 eh = eb[(g * 4 + q * 2) * 64], el = eb[(g * 4 + q * 2 + 1) * 64];
-                        acc[g] = MFMA16(eh, sh[q], acc[g]);
-                        acc[g] = MFMA16(eh, sl[q], acc[g]);
-                        acc[g] = MFMA16(el, sh[q], acc[g]);
+                        for (int g = 0; g < RCT; ++g)
+#pragma unroll
+                            for (int q = 0; q < 2; ++q) {
+                                const f16x8 eh = eb[(g * 4 + q * 2) * 64], el = eb[(g * 4 + q * 2 + 1) * 64];
+                                acc[g] = MFMA16(eh, sh[q], acc[g]);
+                                acc[g] = MFMA16(eh, sl[q], acc[g]);
+                                acc[g] = MFMA16(el, sh[q], acc[g]);
+                            }
                     }
-            }
-            if (k % NS == NS - 1) {
-                wait_vm_lgkm<Stage::kOps>();      // the next stage is in, this wave's reads are done
-                block_barrier_nofence();
-                buf = buf == 2 ? 0 : buf + 1;
-                nbuf = nbuf == 2 ? 0 : nbuf + 1;
+                }
+                if (t % NS == NS - 1) {
+                    wait_vm_lgkm<Stage::kOps>();      // the next stage is in, this wave's reads are done
+                    block_barrier_nofence();
+                    buf = buf == 2 ? 0 : buf + 1;
+                    nbuf = nbuf == 2 ? 0 : nbuf + 1;
+                }
             }
             if (k % CJ == CJ - 1) {
                 if (active && (GRP == CJ || c < c1)) {
@@ -549,12 +603,14 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
 // contraction's transpose into the lines; split partial sums per phase range.
 // Split fp16 products and PSF-table stages as in the forward; Z comes in split
 // pairs scaled by a power of two per line (lexp, undone in the partial sums),
-// the next phase's words being requested before a phase's chunks.
+// the next phase's words being requested before a phase's chunks.  The tensor
+// PSF's tables are taken by blocks of their own (blockIdx.y = offset e, whose
+// lines are columns e NUP .. of the partial sums).
 template <int NUP, int ZST, int CJ>
 __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
 {
-    using Stage = PsfStage<NUP>;
-    constexpr int NS = Stage::NS;
+    constexpr int NS = stage_chunks(NUP, 1);
+    using Stage = PsfStage<NUP, NS, kFacWaves>;
     constexpr int PT = NUP / 32;          // detector tiles
     constexpr int ZC = 2 * ZST, NZS = (ZC + 15) / 16;   // columns of a phase, steps of the residue DFT
     constexpr int NE = 2 * NZS;           // residue table fragments a chunk
@@ -572,7 +628,8 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
     f32x16 racc[PT];
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) racc[pt] = 0.f;
-    const __amdgpu_buffer_rsrc_t ka = Stage::table(a.ka, c0, c1 - c0);
+    const int pass = blockIdx.y;
+    const __amdgpu_buffer_rsrc_t ka = Stage::table(a.ka + pass * a.ka_stride, c0, c1 - c0);
     const f16x8 *ea = (const f16x8 *)a.ea;
     for (int idx = tid; idx < CJ * NE * 64; idx += 64 * kFacWaves) ebuf[idx] = ea[idx];
     // Z of this line tile, [phase][2 slot + part][32 lines]: this lane's line,
@@ -658,7 +715,7 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
     for (int j = 0; j < 16; ++j) {
         const int row = row0 + 8 * (j / 4) + j % 4;
         if (row >= job.rows) continue;
-        float *o = out + (size_t)job_line(job, row) * NUP + (lane & 31);
+        float *o = out + (size_t)job_line(job, row) * a.adj_pitch + pass * NUP + (lane & 31);
 #pragma unroll
         for (int pt = 0; pt < PT; ++pt) o[pt * 32] = __builtin_ldexpf(racc[pt][j], -(e[j] + a.r_exp));
     }
@@ -666,13 +723,20 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
 
 typedef void (*FacKernel)(FacArgs);
 constexpr int kFacNups[] = {64, 128, 192, 256};
-// C = 32 (CJ = 1): 16 slots hold every residue; C = 64 (CJ = 2): 16 to 32
-#define FAC_ROW(K, NUP) {K<NUP, 16, 1>, K<NUP, 16, 2>, K<NUP, 20, 2>, K<NUP, 24, 2>}
-#define FAC_TAB(K) {FAC_ROW(K, 64), FAC_ROW(K, 128), FAC_ROW(K, 192), FAC_ROW(K, 256)}
-const FacKernel kFacFwd[4][4] = FAC_TAB(fac_fwd_kernel);
-const FacKernel kFacAdj[4][4] = FAC_TAB(fac_adj_kernel);
-#undef FAC_TAB
-#undef FAC_ROW
+// C = 32 (CJ = 1): 16 slots hold every residue; C = 64 (CJ = 2): 16 to 24
+#define FWD_ROW(NUP) \
+    {fac_fwd_kernel<NUP, 16, 1, 1>, fac_fwd_kernel<NUP, 16, 2, 1>, fac_fwd_kernel<NUP, 20, 2, 1>, fac_fwd_kernel<NUP, 24, 2, 1>}
+#define ADJ_ROW(NUP) \
+    {fac_adj_kernel<NUP, 16, 1>, fac_adj_kernel<NUP, 16, 2>, fac_adj_kernel<NUP, 20, 2>, fac_adj_kernel<NUP, 24, 2>}
+const FacKernel kFacFwd[4][4] = {FWD_ROW(64), FWD_ROW(128), FWD_ROW(192), FWD_ROW(256)};
+const FacKernel kFacAdj[4][4] = {ADJ_ROW(64), ADJ_ROW(128), ADJ_ROW(192), ADJ_ROW(256)};
+#undef FWD_ROW
+#undef ADJ_ROW
+// tensor lines of 2 to 4 sums, at most 768 samples (what the registers hold), C = 32
+#define NP_ROW(NUP) {fac_fwd_kernel<NUP, 16, 1, 2>, fac_fwd_kernel<NUP, 16, 1, 3>, fac_fwd_kernel<NUP, 16, 1, 4>}
+const FacKernel kFacFwdNp[4][3] = {NP_ROW(64), NP_ROW(128), NP_ROW(192),
+                                   {fac_fwd_kernel<256, 16, 1, 2>, fac_fwd_kernel<256, 16, 1, 3>, nullptr}};
+#undef NP_ROW
 
 int fac_zst_slot(int zst, int cj)
 {
@@ -689,8 +753,9 @@ int fac_nup_slot(int nup)
 
 }  // namespace
 
-int fac_supported(int nup, int zst, int cj)
+int fac_supported(int nup, int zst, int cj, int np)
 {
+    if (np > 1 && (np > 4 || cj != 1 || np * nup > 768)) return 0;
     return fac_nup_slot(nup) >= 0 && cj >= 1 && cj <= 2 && fac_zst_slot(zst, cj) >= 0;
 }
 
@@ -699,37 +764,35 @@ static bool fac_args_ok(const FacArgs &a)
     return a.tiles > 0 && a.P > 0 && a.cj > 0 && a.nsplit >= 1 && a.nsplit <= a.P && a.nsplit_adj >= 1 &&
            a.nsplit_adj <= a.P && a.yc == 2 * a.zst && (a.qmax == 32 ? a.R <= 2 * kInWaves : a.qmax == 24 && a.R <= 3 * kInWaves) && a.R <= a.zst &&
            a.U >= a.R && a.U <= 2 * a.R && a.ucols == 32 * a.U && a.nzstage == (a.P + 15) / 16 &&
-           fac_supported(a.nup, a.zst, a.cj) && a.job.rows <= a.tiles * 32 &&
+           fac_supported(a.nup, a.zst, a.cj, a.np) && a.np >= 1 && a.adj_pitch == a.np * a.nup && a.job.rows <= a.tiles * 32 &&
            a.ylines >= a.tiles * 32 && (long)(a.ylines + 1) * a.P * a.yc < 0x7fffffffL && a.psplit >= 1 &&
            a.psplit <= (a.P + 7) / 8 && a.zsplit >= 1 && a.zsplit <= a.nzstage;
 }
 
 // LDS bytes of a line-tile kernel: three PSF-table stages and its residue
 // table (nfrag fragments of 1 KB).
-static size_t fac_lds(int nup, int nfrag)
+static size_t fac_lds(int nup, int np, int nfrag)
 {
-    const int stage = nup == 64   ? PsfStage<64>::kBytes
-                      : nup == 128 ? PsfStage<128>::kBytes
-                      : nup == 192 ? PsfStage<192>::kBytes
-                                   : PsfStage<256>::kBytes;
-    return 3 * (size_t)stage + 1024 * (size_t)nfrag;
+    return 1024 * (size_t)(3 * stage_chunks(nup, np) * (nup / 8) + nfrag);
 }
 
 hipError_t launch_fac_part(const FacArgs &a, int part, hipStream_t st)
 {
     if (a.job.rows <= 0) return hipSuccess;
+    if (a.np > 1 && part == kFacFwdInner && (a.job.in_stride != a.np * a.nup || (uintptr_t)a.job.in % 16)) return hipErrorInvalidValue;
     if (!fac_args_ok(a) || part < 0 || part > 3) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     switch (part) {
     case kFacFwdInner: {
-        const size_t lds = fac_lds(a.nup, a.cj * 4 * ((a.yc + 31) / 32));
-        const FacKernel k = kFacFwd[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
+        const size_t lds = fac_lds(a.nup, a.np, a.cj * 4 * ((a.yc + 31) / 32));
+        const FacKernel k = a.np > 1 ? kFacFwdNp[fac_nup_slot(a.nup)][a.np - 2]
+                                     : kFacFwd[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
+        const int waves = fwd_waves(a.nup, a.np);
         if (lds > 64 * 1024) {
             e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(k, dim3((a.tiles + kFacWaves - 1) / kFacWaves * a.nsplit), dim3(64 * kFacWaves),
-                           lds, st, a);
+        hipLaunchKernelGGL(k, dim3((a.tiles + waves - 1) / waves * a.nsplit), dim3(64 * waves), lds, st, a);
         break;
     }
     case kFacFwdOuter: {
@@ -745,13 +808,13 @@ hipError_t launch_fac_part(const FacArgs &a, int part, hipStream_t st)
             hipLaunchKernelGGL((fac_adj_in_kernel<3, 3>), dim3(a.tiles, a.zsplit), dim3(64 * kInWaves), 0, st, a);
         break;
     default: {
-        const size_t lds = fac_lds(a.nup, a.cj * 2 * ((a.yc + 15) / 16));
+        const size_t lds = fac_lds(a.nup, 1, a.cj * 2 * ((a.yc + 15) / 16));
         const FacKernel k = kFacAdj[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
         if (lds > 64 * 1024) {
             e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(k, dim3((a.tiles + kFacWaves - 1) / kFacWaves * a.nsplit_adj), dim3(64 * kFacWaves),
+        hipLaunchKernelGGL(k, dim3((a.tiles + kFacWaves - 1) / kFacWaves * a.nsplit_adj, a.np), dim3(64 * kFacWaves),
                            lds, st, a);
         break;
     }

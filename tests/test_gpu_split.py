@@ -79,3 +79,44 @@ def test_non_finite_line_stays_alone():
     got, gota = plan.signal_fwd(rho).cpu(), plan.signal_adj(y).cpu()
     assert torch.equal(torch.view_as_real(got[keep]), torch.view_as_real(ref[keep])) and torch.equal(gota[keep], refa[keep])
     assert not torch.isfinite(torch.view_as_real(got[~keep])).any() and not torch.isfinite(gota[~keep]).any()
+
+
+@pytest.mark.parametrize("nu,rows", [(33, 1), (33, 2), (64, 3), (100, 1), (128, 2), (70, 3), (150, 1), (192, 2), (180, 3),
+                                     (256, 1), (200, 2)])
+def test_tensor_lines(nu, rows):
+    """The forward's virtual lines of 2 to 4 symmetric sums, the adjoint's tables of their own."""
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    nz, M, T = 6, 7, 2048
+    args = (nu, 12, nz, M, T, T / 256 + 1 / 3, 2.0, 1, 15, 2)
+    g = oracle_geometry(*args)
+    g.psf_rows = rows
+    plan = Plan(*args, 1.0, psf_rows=rows)
+    assert plan.dft_cycles == 32
+    rng = np.random.default_rng(9)
+    rho = rng.uniform(0, 1, (g.n_lines, nu)).astype(np.float32)
+    got = plan.signal_fwd(torch.from_numpy(rho.reshape(plan.lines_shape)).cuda()).cpu().numpy()
+    ef = _line_errors(got, signal.forward(g, rho).reshape(plan.data_shape)).max()
+    y = np.asarray(random_data(g, 10)).reshape(g.n_lines, -1).astype(np.complex64)
+    got = plan.signal_adj(torch.from_numpy(y.reshape(plan.data_shape)).cuda()).cpu().numpy()
+    ea = _line_errors(got, signal.adjoint(g, y).reshape(plan.lines_shape)).max()
+    print("n_u %d R %d: forward %.2e adjoint %.2e" % (nu, rows, ef, ea), flush=True)
+    assert ef <= TOL and ea <= TOL
+
+
+def test_two_line_groups():
+    """A raster's two classes, each with its own tables: classes of unequal size, ragged tiles."""
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    args = (90, 12, 7, 9, 2048, 2048 / 256 + 1 / 3, 2.0, 1, 15, 2)
+    g = oracle_geometry(*args)
+    g.raster_sweep = 45.0
+    plan = Plan(*args, 1.0, raster_sweep=45.0)
+    assert plan.dft_cycles == 32
+    rng = np.random.default_rng(11)
+    rho = rng.uniform(0, 1, (g.n_lines, g.n_u)).astype(np.float32)
+    got = plan.signal_fwd(torch.from_numpy(rho.reshape(plan.lines_shape)).cuda()).cpu().numpy()
+    assert _line_errors(got, signal.forward(g, rho).reshape(plan.data_shape)).max() <= TOL
+    y = np.asarray(random_data(g, 12)).reshape(g.n_lines, -1).astype(np.complex64)
+    got = plan.signal_adj(torch.from_numpy(y.reshape(plan.data_shape)).cuda()).cpu().numpy()
+    assert _line_errors(got, signal.adjoint(g, y).reshape(plan.lines_shape)).max() <= TOL
