@@ -112,17 +112,21 @@ static int rows_per_block(const mpi3d_plan *pl, int prec) { return kRowsPerWave 
 
 // The FP32 signal stage of plans with the band DFT factored over drive cycles.
 static bool fac_on(const mpi3d_plan *pl, int prec) { return prec == MPI3D_FP32 && pl->fac.on; }
+// ... and of plans with the dense stage on fp16 pairs.
+static bool split_on(const mpi3d_plan *pl, int prec) { return prec == MPI3D_FP32 && pl->split.on; }
 
 // Split partial-sum blocks the reductions add: forward (nbp2 columns a line),
 // adjoint (nup or nupf columns a line).
 static int fwd_parts(const mpi3d_plan *pl, int prec, bool serve)
 {
     if (fac_on(pl, prec)) return pl->fac.psplit;
+    if (split_on(pl, prec)) return pl->split.fwd.nsplit;
     return (fused_pass(pl, prec) ? 1 : pl->n_passes) * nsplit_of(pl, prec, serve);
 }
 static int adj_parts(const mpi3d_plan *pl, int prec, bool serve)
 {
     if (fac_on(pl, prec)) return pl->fac.nsplit_adj;
+    if (split_on(pl, prec)) return pl->split.adj.nsplit * pl->split.adj.ngroups;
     return (fused_pass(pl, prec) ? 1 : pl->n_passes) * nsplit_of(pl, prec, serve) * sig_cfg(pl, prec).ngroups;
 }
 
@@ -163,6 +167,44 @@ static FacArgs fac_args(const LineJob &lj, int gi, bool fwd)
     a.tiles = (lg.rows + 31) / 32;
     a.s_scale = f.s_scale; a.g_scale = f.g_scale; a.y_scale = f.y_scale; a.z_scale = f.z_scale;
     a.y_exp = f.y_exp; a.z_exp = f.z_exp; a.w_exp = f.w_exp; a.r_exp = f.r_exp;
+    return a;
+}
+
+// Every line group of a line job, one launch.
+static SplitArgs split_args(const LineJob &lj, bool fwd)
+{
+    const mpi3d_plan *pj = lj.pl;
+    const mpi3d_plan::Split &s = pj->split;
+    const mpi3d_plan::Split::Dir &d = fwd ? s.fwd : s.adj;
+    SplitArgs a{};
+    int gt = 0, waves = 8;
+    (void)split_config(d.config, pj->nup, &gt, &waves);
+    a.config = d.config;
+    a.njobs = pj->n_line_groups;
+    for (int gi = 0; gi < a.njobs; ++gi) {
+        const mpi3d_plan::LineGroup &lg = pj->groups[gi];
+        SigJob &sj = a.jobs[gi];
+        sj.in = lj.in;
+        sj.in_stride = lj.in_stride;
+        sj.kf16 = s.kf + 2 * (size_t)lg.table * pj->k_elems;
+        sj.ka16 = s.ka + 2 * (size_t)lg.table * pj->k_elems;
+        sj.rows = lg.rows;
+        sj.tile0 = a.tgroups;
+        a.tgroups += (lg.rows + 32 * waves - 1) / (32 * waves);
+        sj.map_per = lg.per;
+        sj.map_nz = lg.gnz;
+        sj.map_off = lg.off;
+        sj.map_step = lg.step;
+    }
+    a.ff = s.ff; a.fa = s.fa;
+    a.part = lj.w->part;
+    a.pitch = fwd ? 32 * s.nct : pj->nup;
+    a.part_stride = pj->L * a.pitch;
+    a.nu = pj->nu; a.nup = pj->nup; a.nb2 = pj->nb2; a.nct = s.nct;
+    a.nchunks = pj->nchunks;
+    a.nsplit = d.nsplit; a.ngroups = d.ngroups;
+    a.s_scale = fwd ? s.s_scale : s.g_scale;
+    a.out_exp = fwd ? s.fwd_exp : s.adj_exp;
     return a;
 }
 
@@ -288,6 +330,13 @@ static int sig_jobs(bool fwd, int prec, const LineJob *jobs, int n, bool serve, 
         }
         return MPI3D_OK;
     }
+    if (split_on(pl, prec)) {
+        for (int j = 0; j < n; ++j) {
+            if (jobs[j].pl->line_key != pl->line_key || !jobs[j].pl->split.on) return MPI3D_EINVAL;
+            TRY(launch_split(split_args(jobs[j], fwd), fwd, st));
+        }
+        return MPI3D_OK;
+    }
     SigArgs a = sig_args(pl, prec, serve);
     const int rpb = rows_per_block(pl, prec);
     int tiles = 0, nj = 0;
@@ -341,7 +390,8 @@ static int reduce_forward(const mpi3d_plan *pl, int prec, const OpWs &w, bool se
                           double *norm_parts, int *nnorm, hipStream_t st)
 {
     const bool mixed = prec == MPI3D_MIXED, fac = fac_on(pl, prec);
-    const int pitch = fac ? 32 * pl->fac.U : pl->nbp2;   // floats per line of the partial sums
+    // floats per line of the partial sums
+    const int pitch = fac ? 32 * pl->fac.U : split_on(pl, prec) ? 32 * pl->split.nct : pl->nbp2;
     TRY(launch_reduce_fwd(pl->L, pl->nb2, pitch, fwd_parts(pl, prec, serve), pl->L * pitch, w.part,
                           mixed ? w.rowscale : nullptr, mixed ? pl->col_scale : nullptr, pl->op_scale, b_sub, out,
                           norm_parts, nnorm, st, row_passes(pl, true, prec), fac ? pl->fac.bcol : nullptr));
@@ -973,6 +1023,9 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
     // (of the first line group)
     const FacArgs fwd_fac = fac_on(pl, precision) ? fac_args(LineJob{pl, w.rt, pl->nup, &w}, 0, true) : FacArgs{};
     const FacArgs adj_fac = fac_on(pl, precision) ? fac_args(LineJob{pl, b, pl->nb2, &w}, 0, false) : FacArgs{};
+    const bool split = split_on(pl, precision);
+    const SplitArgs fwd_split = split ? split_args(LineJob{pl, w.rt, pl->nup, &w}, true) : SplitArgs{};
+    const SplitArgs adj_split = split ? split_args(LineJob{pl, b, pl->nb2, &w}, false) : SplitArgs{};
     const bool mixed = precision == MPI3D_MIXED;
     hipError_t err = mixed && kernel == 0 ? launch_to_bf16(pl->nvox, x, w.xb, st) : hipSuccess;
     // the mixed signal kernels read fp16 operand lines: prepared once, untimed
@@ -992,6 +1045,8 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
                 err = gemm_signal_fwd(pl, w.rt, pl->nup, w.part, st) == MPI3D_OK ? hipSuccess : hipErrorUnknown;
             else if (fac_on(pl, precision))
                 err = launch_fac_fwd(fwd_fac, st);
+            else if (split)
+                err = launch_split(fwd_split, true, st);
             else
                 err = launch_sig_fwd(pl, precision, a, st);
             break;
@@ -1000,6 +1055,8 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
                 err = gemm_signal_adj(pl, b, w.rt, pl->nup, st) == MPI3D_OK ? hipSuccess : hipErrorUnknown;
             else if (fac_on(pl, precision))
                 err = launch_fac_adj(adj_fac, st);
+            else if (split)
+                err = launch_split(adj_split, false, st);
             else
                 err = launch_sig_adj(pl, precision, a, st);
             break;

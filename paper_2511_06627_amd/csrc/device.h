@@ -148,6 +148,25 @@ __device__ __forceinline__ void lds_pipelined(Frag frag, Prod prod)
     }
 }
 
+// A float as the sum of two fp16 values: hi = rn16(v), lo = rn16(v - hi).
+// With |v| <= 2^15 the pair holds v to 2^-23 relative down to |v| = 2^-3 and
+// to an absolute 2^-25 below (2^-40 of the largest value), so a product taken
+// as hi hi + hi lo + lo hi drops only lo lo, 2^-22 of it at most.
+__device__ __forceinline__ void split8(const float (&v)[8], f16x8 &hi, f16x8 &lo)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) hi[e] = (_Float16)v[e];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) lo[e] = (_Float16)(v[e] - (float)hi[e]);
+}
+
+// The exponent e that brings a line of largest magnitude m into [2^14, 2^15)
+// (0 for a line of zeros or with a non-finite entry).
+__device__ __forceinline__ int line_exponent(float m)
+{
+    return m > 0.f && m < __builtin_inff() ? 15 - __builtin_amdgcn_frexp_expf(m) : 0;
+}
+
 // s_waitcnt vmcnt(n) lgkmcnt(0) (expcnt not waited for), n < 64
 template <int N>
 __device__ __forceinline__ void wait_vm_lgkm()

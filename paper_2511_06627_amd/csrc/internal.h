@@ -69,6 +69,22 @@ __host__ __device__ inline long job_line(const SigJob &j, int r)
     return (long)g * j.map_nz + j.map_off + (long)j.map_step * (r - g * j.map_per);
 }
 
+// The dense FP32 signal stage on fp16 pairs (FP32 plans without the mixed
+// operator, no tensor PSF, T no multiple of 32 or otherwise not factored):
+// both contractions as three fp16 products each, lines scaled by a power of
+// two each, tables by one for all.
+struct SplitArgs {
+    SigJob jobs[2];          // line groups: kf16 / ka16 are their split PSF tables, tile0 their first block tile
+    int njobs, config;       // config: see split_config
+    const __half *ff, *fa;   // split band tables
+    float *part;             // fwd: [nsplit][line][pitch]; adj: [nsplit][ngroups][line][pitch]
+    long part_stride;
+    int pitch;
+    int nu, nup, nb2, nct, nchunks, nsplit, ngroups, tgroups;
+    float s_scale;           // the time tile's scale before it is split again
+    int out_exp;             // power of two of the results above a line's own
+};
+
 // The band DFT factored over drive cycles (FP32), one launch per line group
 // (each with its own PSF tables; under the tensor PSF np = R + 1 of them, the
 // forward's lines being np symmetric line sums laid end to end): time
@@ -223,6 +239,18 @@ struct mpi3d_plan {
         int *unit0, *qbin;
         int *bcol;                // [nb] column of bin j's real part in the forward's partial sums
     } fac;
+    // dense FP32 signal stage on fp16 pairs (see SplitArgs): chosen at plan time
+    // where the band DFT does not factor
+    struct Split {
+        bool on = false;
+        struct Dir {
+            int config, ngroups, nsplit;
+        } fwd, adj;
+        int nct;                  // column tiles (32 columns) of the kept bins
+        float s_scale, g_scale;
+        int fwd_exp, adj_exp;
+        __half *kf, *ka, *ff, *fa;
+    } split;
     uint64_t line_key;             // equal keys <=> identical line tables
     // projection configuration
     mpi3d::FwdConfig fwd32, fwd16;  // forward projection, fp32 and bf16 gathers
@@ -311,6 +339,10 @@ int sig_fused_supported(int nupf, int gct);
 // sums (psplit blocks of 32 U columns); adjoint writes Z then nsplit_adj
 // splits of nup-column partial sums.
 int fac_supported(int nup, int zst, int cj, int np);
+// Kernel configuration i of the dense split stage: 1 and its column tiles a
+// group and waves a block if it is for nup samples, 0 if not, -1 past the last.
+int split_config(int i, int nup, int *gt, int *waves);
+hipError_t launch_split(const SplitArgs &a, bool fwd, hipStream_t st);
 hipError_t launch_fac_fwd(const FacArgs &a, hipStream_t st);
 hipError_t launch_fac_adj(const FacArgs &a, hipStream_t st);
 // one kernel of those stages: forward PSF contraction + residue DFT, forward

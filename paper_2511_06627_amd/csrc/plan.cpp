@@ -212,9 +212,42 @@ void choose_split(const mpi3d_plan *pl, bool fp32, mpi3d_plan::SigCfg &c, int nu
     c.serve_nsplit = (pl->nchunks + c.serve_cps - 1) / c.serve_cps;
 }
 
+// Kernel configuration and time splits of the dense stage on fp16 pairs: the
+// least estimated time.  Measured over all configurations and 2 to 32 splits at
+// six scans: a block (one a CU) takes about 12 us besides its chunks; a chunk
+// its products at 32 cycles each, 2.2 GHz, 80% busy with two waves a SIMD and
+// 62% with one; each split costs the reduction
+// one more partial sum (its chain of loads, about 0.1 us, and its bytes written
+// and read at 4 TB/s).
+void choose_dense_split(const mpi3d_plan *pl, bool fwd, mpi3d_plan::Split::Dir &d)
+{
+    const int nct = pl->split.nct;
+    double best = 1e30;
+    for (int i = 0;; ++i) {
+        int gt, waves;
+        const int fits = split_config(i, pl->nup, &gt, &waves);
+        if (fits < 0) break;
+        if (!fits) continue;
+        const int ng = (nct + gt - 1) / gt;
+        long tg = 0;
+        for (int gi = 0; gi < pl->n_line_groups; ++gi) tg += (pl->groups[gi].rows + 32 * waves - 1) / (32 * waves);
+        const double chunk = (3.0 * pl->nup / 16 + 6.0 * gt) * 32 / 2.2e9 * (waves == 8 ? 2 / 0.80 : 1 / 0.62);
+        const double per_split =
+            fwd ? 1e-7 + 8.0 * pl->L * 32 * nct / 4e12 : ng * (1e-7 + 8.0 * pl->L * pl->nup / 4e12);
+        for (int ns = 1; ns <= std::min(pl->nchunks, 128); ++ns) {
+            const double t = (double)((tg * ng * ns + 255) / 256) * (12e-6 + (pl->nchunks + ns - 1) / ns * chunk) +
+                             ns * per_split;
+            if (t < best * (1.0 - 1e-9)) {
+                best = t;
+                d = {i, ng, ns};
+            }
+        }
+    }
+}
+
 // The operator workspace's layout (bytes from its base), with or without the
-// factored FP32 stage.
-void op_layout(mpi3d_plan *pl, bool fac)
+// factored FP32 stage or the dense one on fp16 pairs.
+void op_layout(mpi3d_plan *pl, bool fac, bool split = false)
 {
     const mpi3d_plan::Fac &f = pl->fac;
     const bool mixed = pl->precisions & (1 << MPI3D_MIXED);
@@ -222,8 +255,8 @@ void op_layout(mpi3d_plan *pl, bool fac)
     auto put = [&](size_t bytes) { o = align256(o); size_t r = o; o += bytes; return r; };
     pl->ws_rt = put(sizeof(float) * pl->L * pl->nup);
     size_t parts = 0;   // split partial sums: forward [splits][L][nbp2], adjoint [splits][groups][L][nup]
-    for (int i = fac ? 1 : 0; i < 2; ++i) {
-        if (fac && !mixed) break;
+    for (int i = fac || split ? 1 : 0; i < 2; ++i) {
+        if ((fac || split) && !mixed) break;
         const mpi3d_plan::SigCfg &c = pl->sc[i];
         parts = std::max(parts, (size_t)std::max(c.nsplit, c.serve_nsplit) *
                                     std::max<size_t>(pl->nbp2, (size_t)c.ngroups * pl->nup));
@@ -235,6 +268,9 @@ void op_layout(mpi3d_plan *pl, bool fac)
     if (fac)   // adjoint: nsplit blocks of nup-column lines; forward: psplit of 32 U columns
         part_floats =
             std::max(part_floats, (size_t)pl->L * std::max(f.nsplit_adj * pl->n_passes * pl->nup, f.psplit * 32 * f.U));
+    if (split)
+        part_floats = std::max({part_floats, (size_t)pl->L * pl->split.fwd.nsplit * 32 * pl->split.nct,
+                                (size_t)pl->L * pl->split.adj.nsplit * pl->split.adj.ngroups * pl->nup});
     pl->ws_part = put(sizeof(float) * part_floats);
     pl->ws_norm = put(sizeof(double) * pl->max_parts);
     // per tensor-PSF pass: the forward's symmetric line sums, their
@@ -589,6 +625,13 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         for (int j = 0; j < 2 * NB; ++j)
             if (!std::isfinite(g->rx_filter[j])) { delete pl; return MPI3D_EINVAL; }
 
+    std::vector<double> phase((size_t)2 * T);     // cos, sin of 2 pi n / T
+    for (int n = 0; n < T; ++n) {
+        const double a = 2.0 * kPi * (double)n / T;
+        phase[2 * n] = std::cos(a);
+        phase[2 * n + 1] = std::sin(a);
+    }
+
     // ---- band DFT factored over drive cycles (FP32) --------------------------
     // t = n1 + P n2 (T = C P, C = 32 or 64): the kept bin omega_j
     // contributes e^{2 pi i omega_j n1 / T} e^{2 pi i (omega_j mod C) n2 / C},
@@ -868,11 +911,9 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             for (int j = 0; j < NB; ++j) {
                 double dre = 1.0, dim = 0.0;
                 if (g->rx_filter) { dre = g->rx_filter[2 * j]; dim = g->rx_filter[2 * j + 1]; }
-                for (int n1 = 0; n1 < P; ++n1) {
-                    const long ph = (long)(((unsigned long long)bins[j] * (unsigned long long)n1) %
-                                           (unsigned long long)T);
-                    const double a = 2.0 * kPi * (double)ph / T;
-                    const double co = std::cos(a), si = std::sin(a);
+                long ph = 0;                      // bins[j] n1 mod T
+                for (int n1 = 0; n1 < P; ++n1, ph += bins[j], ph -= ph >= T ? T : 0) {
+                    const double co = phase[2 * ph], si = phase[2 * ph + 1];
                     Gt[2 * ((size_t)j * P + n1)] = (dre * co - dim * si) * inv;
                     Gt[2 * ((size_t)j * P + n1) + 1] = (dre * si + dim * co) * inv;
                 }
@@ -940,24 +981,135 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         }
     }
 
+    // ---- dense FP32 stage on fp16 pairs: what does not factor, except for
+    // plans with the mixed operator (for the reason above) and tensor PSFs ----
+    if ((precisions & (1 << MPI3D_FP32)) && !(precisions & (1 << MPI3D_MIXED)) && !pl->fac.on && !pl->fused &&
+        NPASS == 1 && (double)pl->nchunks * ((pl->nb2 + 31) / 32) * 4096 < 2147483647.0 &&
+        (double)pl->nchunks * NUP * 128 < 2147483647.0) {
+        mpi3d_plan::Split &sp = pl->split;
+        sp.nct = (pl->nb2 + 31) / 32;
+        choose_dense_split(pl, true, sp.fwd);
+        choose_dense_split(pl, false, sp.adj);
+        // a scan that fits the no-allocation entry point's scratch still does
+        op_layout(pl, false);
+        const size_t dense_ws = pl->op_ws_bytes;
+        op_layout(pl, false, true);
+        sp.on = !(dense_ws <= MPI3D_NOALLOC_SCRATCH_BYTES && pl->op_ws_bytes > MPI3D_NOALLOC_SCRATCH_BYTES);
+    }
+
     // band DFT F[n][c] (real columns: 2j = Re, 2j+1 = Im)
     // -- not for a plan whose only signal stage is the factored one
     const bool precomp = precisions & (1 << MPI3D_PRECOMPOSED), mixed = precisions & (1 << MPI3D_MIXED);
-    const bool dense = !pl->fac.on;      // the dense FP32 kernels' tables
+    const bool split = pl->split.on;
+    const bool dense = !pl->fac.on && !split;      // the fp32 MFMA kernels' tables
     std::vector<double> F;
-    if (dense || mixed || precomp) {
+    if (dense || split || mixed || precomp) {
         F.assign((size_t)TP * NBP2, 0.0);
         const double inv = 1.0 / std::sqrt((double)T);
         for (int j = 0; j < NB; ++j) {
             double dre = 1.0, dim = 0.0;
             if (g->rx_filter) { dre = g->rx_filter[2 * j]; dim = g->rx_filter[2 * j + 1]; }
-            for (int n = 0; n < T; ++n) {
-                long ph = (long)(((unsigned long long)bins[j] * (unsigned long long)n) % (unsigned long long)T);
-                double a = 2.0 * kPi * (double)ph / T;
-                double c = std::cos(a), s = std::sin(a);
+            long ph = 0;                          // bins[j] n mod T
+            for (int n = 0; n < T; ++n, ph += bins[j], ph -= ph >= T ? T : 0) {
+                const double c = phase[2 * ph], s = phase[2 * ph + 1];
                 F[(size_t)n * NBP2 + 2 * j] = (dre * c - dim * s) * inv;
                 F[(size_t)n * NBP2 + 2 * j + 1] = (dre * s + dim * c) * inv;
             }
+        }
+    }
+
+    // split tables: fragments of 64 lanes x 8 halves, hi then lo, chunk after
+    // chunk of 32 times
+    //  kf [p / 16]: K[time l % 32][p = 16 ks + 8 (l / 32) + e]
+    //  ff [32 columns][time step]: F[time 16 q + tp16(e, l / 32)][column 32 g + l % 32]
+    //  fa [column / 16]: F[time l % 32][column 16 ks + 8 (l / 32) + e]
+    //  ka [time step][p / 32]: K[time 16 q + tp16(e, l / 32)][p = 32 pt + l % 32]
+    std::vector<uint16_t> skf, ska, sff, sfa;
+    if (split) {
+        mpi3d_plan::Split &sp = pl->split;
+        auto tp16 = [](int e2, int h) { return 8 * (e2 / 4) + 4 * h + (e2 % 4); };
+        // tables scaled so their largest entries are in [2^14, 2^15); the time
+        // tiles of lines below 2^15 kept below 2^15 by the largest row sums
+        double kmax = 0, ksum = 0, fmax = 0, fsum = 0;
+        for (size_t n = 0; n < (size_t)n_ktab * T; ++n) {
+            const double *row = &K[KE * (n / T) + n % T * NUP];
+            double sum = 0;
+            for (int p = 0; p < NUP; ++p) {
+                kmax = std::max(kmax, std::fabs(row[p]));
+                sum += std::fabs(row[p]);
+            }
+            ksum = std::max(ksum, sum);
+        }
+        for (int n = 0; n < T; ++n) {
+            double sum = 0;
+            for (int c = 0; c < 2 * NB; ++c) {
+                const double v = std::fabs(F[(size_t)n * NBP2 + c]);
+                fmax = std::max(fmax, v);
+                sum += v;
+            }
+            fsum = std::max(fsum, sum);
+        }
+        int kexp = 0, fexp = 0, s1 = 0, s2 = 0;
+        if (kmax > 0) {
+            std::frexp(kmax, &kexp);
+            kexp = 15 - kexp;
+            std::frexp(std::ldexp(ksum, kexp), &s1);
+        }
+        if (fmax > 0) {
+            std::frexp(fmax, &fexp);
+            fexp = 15 - fexp;
+            std::frexp(std::ldexp(fsum, fexp), &s2);
+        }
+        sp.s_scale = (float)std::ldexp(1.0, -s1);
+        sp.g_scale = (float)std::ldexp(1.0, -s2);
+        sp.fwd_exp = kexp - s1 + fexp;
+        sp.adj_exp = fexp - s2 + kexp;
+        // one chunk's 32 x n table as A fragments by row (time, 16 columns a
+        // step) and by column (32 columns a tile, 16 times a step)
+        std::vector<uint16_t> ph, plo;
+        auto pairs = [&](const double *src, size_t pitch, int n, int pad, double sc) {
+            ph.assign((size_t)32 * pad, 0);
+            plo.assign((size_t)32 * pad, 0);
+            for (int i = 0; i < 32; ++i)
+                for (int p = 0; p < n; ++p)
+                    half_pair(src[(size_t)i * pitch + p] * sc, ph[(size_t)i * pad + p], plo[(size_t)i * pad + p]);
+        };
+        auto by_time = [&](uint16_t *dst, int pad) {
+            for (int ks = 0; ks < pad / 16; ++ks)
+                for (int l = 0; l < 64; ++l)
+                    for (int e2 = 0; e2 < 8; ++e2) {
+                        const size_t o = ((size_t)ks * 2 * 64 + l) * 8 + e2;
+                        const size_t i = (size_t)(l % 32) * pad + 16 * ks + 8 * (l / 32) + e2;
+                        dst[o] = ph[i];
+                        dst[o + 512] = plo[i];
+                    }
+        };
+        auto by_column = [&](uint16_t *dst, int pad, int tile_stride, int step_stride) {
+            for (int g2 = 0; g2 < pad / 32; ++g2)
+                for (int q = 0; q < 2; ++q)
+                    for (int l = 0; l < 64; ++l)
+                        for (int e2 = 0; e2 < 8; ++e2) {
+                            const size_t o = ((size_t)(g2 * tile_stride + q * step_stride) * 2 * 64 + l) * 8 + e2;
+                            const size_t i = (size_t)(16 * q + tp16(e2, l / 32)) * pad + 32 * g2 + l % 32;
+                            dst[o] = ph[i];
+                            dst[o + 512] = plo[i];
+                        }
+        };
+        const int CP = 32 * sp.nct;
+        skf.assign(2 * KE * n_ktab, 0);
+        ska.assign(2 * KE * n_ktab, 0);
+        sff.assign((size_t)2 * TP * CP, 0);
+        sfa.assign((size_t)2 * TP * CP, 0);
+        for (int c = 0; c < NC; ++c) {
+            for (int tb = 0; tb < n_ktab; ++tb) {
+                const size_t o = 2 * KE * tb + (size_t)c * 64 * NUP;
+                pairs(&K[KE * tb + (size_t)32 * c * NUP], NUP, NUP, NUP, std::ldexp(1.0, kexp));
+                by_time(&skf[o], NUP);
+                by_column(&ska[o], NUP, 1, NUP / 32);
+            }
+            pairs(&F[(size_t)32 * c * NBP2], NBP2, 2 * NB, CP, std::ldexp(1.0, fexp));
+            by_column(&sff[(size_t)c * 64 * CP], CP, 2, 1);
+            by_time(&sfa[(size_t)c * 64 * CP], CP);
         }
     }
 
@@ -1013,6 +1165,10 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     const size_t o_funit0 = fac ? place(sizeof(int) * funit0.size()) : 0;
     const size_t o_fqbin = fac ? place(sizeof(int) * fqbin.size()) : 0;
     const size_t o_fbcol = fac ? place(sizeof(int) * fbcol.size()) : 0;
+    const size_t o_skf = split ? place(sizeof(_Float16) * skf.size()) : 0;
+    const size_t o_ska = split ? place(sizeof(_Float16) * ska.size()) : 0;
+    const size_t o_sff = split ? place(sizeof(_Float16) * sff.size()) : 0;
+    const size_t o_sfa = split ? place(sizeof(_Float16) * sfa.size()) : 0;
     if (mixed) {
         o_kf16 = place(sizeof(__half) * KE * n_ktab);
         o_ff16 = place(sizeof(__half) * (size_t)TP * NBP2);
@@ -1197,12 +1353,18 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         ok = ok && hipMemcpy(pl->kff, kff.data(), sizeof(float) * KEF, hipMemcpyHostToDevice) == hipSuccess;
         ok = ok && hipMemcpy(pl->kaf, kaf.data(), sizeof(float) * KEF, hipMemcpyHostToDevice) == hipSuccess;
     }
+    auto up = [&](auto *&dst, size_t o, const auto &v) {
+        dst = reinterpret_cast<std::remove_reference_t<decltype(dst)>>(tb + o);
+        ok = ok && hipMemcpy(dst, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice) == hipSuccess;
+    };
+    if (split) {
+        up(pl->split.kf, o_skf, skf);
+        up(pl->split.ka, o_ska, ska);
+        up(pl->split.ff, o_sff, sff);
+        up(pl->split.fa, o_sfa, sfa);
+    }
     if (fac) {
         mpi3d_plan::Fac &f = pl->fac;
-        auto up = [&](auto *&dst, size_t o, const auto &v) {
-            dst = reinterpret_cast<std::remove_reference_t<decltype(dst)>>(tb + o);
-            ok = ok && hipMemcpy(dst, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice) == hipSuccess;
-        };
         up(f.kf, o_fkf, fkf);
         up(f.ka, o_fka, fka);
         up(f.ef, o_fef, fef);
@@ -1247,7 +1409,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     }
 
     // ---- workspace layouts -------------------------------------------------
-    op_layout(pl, pl->fac.on);
+    op_layout(pl, pl->fac.on, pl->split.on);
     {
         size_t o = 0;
         auto put = [&](size_t bytes) { o = align256(o); size_t r = o; o += bytes; return r; };
@@ -1274,7 +1436,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         int ints[] = {pl->nu, pl->nup, pl->nt, pl->harm_lo, pl->harm_hi, pl->half_band, pl->nbp2,
                       pl->sc[0].pairs, pl->sc[0].ngroups, pl->sc[0].gct, pl->sc[1].pairs, pl->sc[1].ngroups,
                       pl->sc[1].gct, precisions, n_classes, psf_rows, drive_axes, drive_axes == 2 ? pl->nz : 0,
-                      pl->fused ? pl->nupf : 0, pl->fused ? pl->scf.gct : 0, pl->fac.on ? pl->fac.C : 0};
+                      pl->fused ? pl->nupf : 0, pl->fused ? pl->scf.gct : 0, pl->fac.on ? pl->fac.C : 0, pl->split.on};
         double dbl[] = {pl->P, pl->a, pl->w, pl->raster_sweep, drive_axes == 2 ? pl->a_z : 0.0};
         mix(ints, sizeof(ints));
         mix(dbl, sizeof(dbl));

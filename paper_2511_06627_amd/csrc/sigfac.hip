@@ -73,18 +73,6 @@ __device__ __forceinline__ FacPos fac_pos(const FacArgs &a, int nsplit)
     return p;
 }
 
-// A float as the sum of two fp16 values: hi = rn16(v), lo = rn16(v - hi).
-// With |v| <= 2^15 the pair holds v to 2^-23 relative down to |v| = 2^-3 and
-// to an absolute 2^-25 below (2^-40 of the largest value), so a product taken
-// as hi hi + hi lo + lo hi drops only lo lo, 2^-22 of it at most.
-__device__ __forceinline__ void split8(const float (&v)[8], f16x8 &hi, f16x8 &lo)
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e) hi[e] = (_Float16)v[e];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) lo[e] = (_Float16)(v[e] - (float)hi[e]);
-}
-
 // The same pair in one 32-bit word (hi in the low half), and eight of them as
 // MFMA operands.
 __device__ __forceinline__ uint32_t pack_split(float v)
@@ -103,13 +91,6 @@ __device__ __forceinline__ void unpack8(const uint32_t (&w)[8], f16x8 &hi, f16x8
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     hi = __builtin_bit_cast(f16x8, u32x4{a[0], a[1], a[2], a[3]});
     lo = __builtin_bit_cast(f16x8, u32x4{b[0], b[1], b[2], b[3]});
-}
-
-// The exponent e that brings a line of largest magnitude m into [2^14, 2^15)
-// (0 for a line of zeros or with a non-finite entry).
-__device__ __forceinline__ int line_exponent(float m)
-{
-    return m > 0.f && m < __builtin_inff() ? 15 - __builtin_amdgcn_frexp_expf(m) : 0;
 }
 
 // The PSF table of the line-tile kernels in LDS.  A chunk (32 times x NUP
@@ -174,7 +155,7 @@ constexpr int fwd_waves(int nup, int np) { return np * nup <= 256 ? kFacWaves : 
 // registers (2 NP NUP / 64 words a lane, hi and lo), so above 256 samples a
 // block is 4 waves of up to 512 registers.  At 192 x 192 x 96, 36 angles,
 // T = 8192, four tables: 169 us against 628 for the dense pass on fp32 MFMA
-// (0.76 PFLOP/s of fp16 products; with one wave a SIMD the splits of a time
+// (0.8 PFLOP/s of fp16 products; with one wave a SIMD the splits of a time
 // tile are not hidden), the adjoint 167 against 598.
 template <int NUP, int ZST, int CJ, int NP>
 __global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) void fac_fwd_kernel(FacArgs a)

@@ -1,0 +1,343 @@
+// The dense FP32 signal stage on fp16 pairs (gfx950 v_mfma_f32_32x32x16_f16):
+// for scans whose T is no multiple of 32, so that the band DFT does not factor
+// over drive cycles.
+//
+// Per 32-time chunk c and line tile, forward: the PSF contraction
+// S[time][line] = sum_p K[time][p] rho[p][line], then the band DFT
+// b[column][line] += sum_time F[column][time] S[time][line]; adjoint the
+// transpose of both.  Every operand is held as two fp16 values (split8: three
+// products in place of one fp32 product at 1/16 of the rate); lines are scaled
+// by a power of two each, tables by one for all.  The time tile's result
+// registers are the second contraction's operand as they stand, so nothing
+// crosses lanes.  A wave holds 32 lines and GT column tiles (accumulators
+// forward, data operands adjoint: GT 16 registers, the samples taking
+// NUP / 2); column groups of their own blocks repeat the PSF contraction,
+// (NUP / 16) 3 products of a chunk against the group's 6 GT.  Splits over T
+// fill the chip; their partial sums are added in a fixed order afterwards.
+//
+// Against the same stages on fp32 MFMA (forward, adjoint, with reductions): a
+// raster of 131 x 117 x 37, 23 angles, T = 6001, 434 columns: 96 -> 51 us,
+// 93 -> 46; 192 x 192 x 96, 36 angles, T = 8101: 365 -> 165, 326 -> 149;
+// 256 x 256 x 128, 60 angles, T = 10001, 658 columns: 1149 -> 850, 1135 -> 896
+// (a chunk's products 60 to 80% of the matrix rate; what keeps small scans off
+// it is some 12 us a block for its lines, first chunks and results).  Error
+// against float64: that of the fp32 form or less.
+
+#include "device.h"
+
+namespace mpi3d {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+namespace {
+
+// A chunk's tables in LDS, 1 KB fragments: the PSF table's NUP / 8 (hi, lo),
+// then the column group's 4 GT.  Three buffers, moved by buffer loads (the
+// chunk after next while one is used), one barrier a chunk without a fence:
+// each wave waits for its own part of the next chunk first.  Where the waves
+// do not divide the fragments the last ones are moved twice (the same bytes).
+template <int NUP, int GT, int WAVES>
+struct ChunkStage {
+    static constexpr int kPsf = NUP / 8;
+    static constexpr int kFrags = kPsf + 4 * GT;
+    static constexpr int kOps = (kFrags + WAVES - 1) / WAVES;   // fragments a wave moves per chunk
+    static constexpr int kBytes = 3 * kFrags * 1024;
+    __amdgpu_buffer_rsrc_t psf, band;
+    int nct, tile0, last;
+
+    // chunks [c0, c0 + n) of the tables; column tiles from ct on (past the
+    // group's last tile: the next chunk's, or zeros past the table, unused)
+    __device__ __forceinline__ ChunkStage(const __half *k, const __half *f, int c0, int n, int nct_, int ct)
+        : psf(buffer_table((const char *)k + (size_t)c0 * kPsf * 1024, n * (kPsf * 1024))),
+          band(buffer_table((const char *)f + (size_t)c0 * nct_ * 4096, n * nct_ * 4096)), nct(nct_), tile0(ct),
+          last(n - 1)
+    {
+    }
+    // chunk c (counted from c0; the last one again past it, unused)
+    __device__ __forceinline__ void load(int c, f16x8 *lds, int buf, int wave, int lane) const
+    {
+        const int cc = min(c, last);
+#pragma unroll
+        for (int k = 0; k < kOps; ++k) {
+            const int f = min(k * WAVES + wave, kFrags - 1);
+            f16x8 *dst = lds + (buf * kFrags + f) * 64;
+            if (f < kPsf)
+                buffer_dma16(psf, dst, lane * 16, (cc * kPsf + f) * 1024);
+            else
+                buffer_dma16(band, dst, lane * 16, ((cc * nct + tile0) * 4 + f - kPsf) * 1024);
+        }
+    }
+};
+
+// Position of a wave: blocks are ordered split, column group, line tiles, so
+// that neighbours (one XCD's) share a chunk range and with it the tables in L2.
+struct SplitPos {
+    int job, tile, group, split, c0, c1;
+};
+
+template <int WAVES>
+__device__ __forceinline__ SplitPos split_pos(const SplitArgs &a)
+{
+    const int lb = xcd_logical(blockIdx.x, gridDim.x);
+    SplitPos p;
+    const int sg = lb / a.tgroups, tg = lb - sg * a.tgroups;
+    p.split = sg / a.ngroups;
+    p.group = sg - p.split * a.ngroups;
+    p.job = a.njobs > 1 && tg >= a.jobs[1].tile0 ? 1 : 0;
+    p.tile = (tg - a.jobs[p.job].tile0) * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    p.c0 = (int)((unsigned)(p.split * a.nchunks) / (unsigned)a.nsplit);   // (at most 2^17 chunks, 128 splits)
+    p.c1 = (int)((unsigned)((p.split + 1) * a.nchunks) / (unsigned)a.nsplit);
+    return p;
+}
+
+// A line's scaled pairs in the 16-value steps of the MFMA operands (value
+// 16 ks + 8 h + e in element e): the n values from column col0 of line il of
+// `base` (il < 0: zeros), lines `stride` floats apart, by VEC-float loads where
+// they are aligned.  Past the values the last word of the line is read and
+// masked off: every load is unconditional, so all are in flight at once.
+// Returns the line's exponent.
+template <int NKS, int VEC>
+__device__ __forceinline__ int split_line(const float *base, long il, int stride, int col0, int n, int h,
+                                          f16x8 (&hi)[NKS], f16x8 (&lo)[NKS])
+{
+    typedef float vec __attribute__((ext_vector_type(VEC)));
+    const float *src = base + (size_t)(il >= 0 ? il : 0) * stride;
+    float v[NKS][8];
+    if (stride % VEC == 0 && col0 % VEC == 0 && (uintptr_t)base % (4 * VEC) == 0) {
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; e += VEC) {
+                const int p = 16 * ks + 8 * h + e;
+                const vec w = *reinterpret_cast<const vec *>(src + min(col0 + p, stride - VEC));
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) v[ks][e + i] = (il >= 0) & (p + i < n) ? w[i] : 0.f;
+            }
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int p = 16 * ks + 8 * h + e;
+                const float w = src[col0 + min(p, n - 1)];
+                v[ks][e] = (il >= 0) & (p < n) ? w : 0.f;
+            }
+    }
+    float m = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[ks][e]));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    const int le = line_exponent(m);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+        float w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = __builtin_ldexpf(v[ks][e], le);
+        split8(w, hi[ks], lo[ks]);
+    }
+    return le;
+}
+
+// Result rows of a 32 x 32 tile (8 (s / 4) + 4 h + s % 4) of this lane's line,
+// scaled back, as 16-byte words.
+__device__ __forceinline__ void store_tile(float *dst, const f32x16 &v, int exp)
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f32x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = __builtin_ldexpf(v[4 * q + e], exp);
+        *reinterpret_cast<f32x4 *>(dst + 8 * q) = w;
+    }
+}
+
+template <int NUP, int GT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitArgs a)
+{
+    using Stage = ChunkStage<NUP, GT, WAVES>;
+    constexpr int NKS = NUP / 16;
+    extern __shared__ __align__(16) f16x8 lk[];
+    const SplitPos sp = split_pos<WAVES>(a);
+    const SigJob &job = a.jobs[sp.job];
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = sp.tile * 32 + (lane & 31);
+    // a wave past the last tile still stages (and with one wave a SIMD computes,
+    // too: a branch around the products costs copies of their accumulators)
+    const bool active = WAVES == 4 || sp.tile * 32 < job.rows;
+    const long il = r < job.rows ? job_line(job, r) : -1;
+    const Stage stage(job.kf16, a.ff, sp.c0, sp.c1 - sp.c0, a.nct, sp.group * GT);
+    stage.load(0, lk, 0, wave, lane);
+    stage.load(1, lk, 1, wave, lane);
+
+    f16x8 rh[NKS], rl[NKS];
+    const int le = split_line<NKS, 4>((const float *)job.in, il, job.in_stride, 0, a.nu, h, rh, rl);
+    f32x16 acc[GT];
+#pragma unroll
+    for (int g = 0; g < GT; ++g) acc[g] = 0.f;
+    const float sscale = a.s_scale;
+    wait_vm_lgkm<Stage::kOps>();
+    block_barrier_nofence();
+
+    int buf = 0, nbuf = 2;
+    for (int c = sp.c0; c < sp.c1; ++c) {
+        stage.load(c - sp.c0 + 2, lk, nbuf, wave, lane);
+        if (active) {
+            const f16x8 *kb = lk + buf * Stage::kFrags * 64 + lane;
+            f32x16 S = 0.f;
+            lds_pipelined<2 * NKS, 6>([&](int i) { return kb[i * 64]; },
+                                      [&](int i, const f16x8 &f) {
+                                          S = MFMA16(f, rh[i / 2], S);
+                                          if (i % 2 == 0) S = MFMA16(f, rl[i / 2], S);
+                                      });
+            f16x8 sh[2], sl[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                float w[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = S[8 * q + e] * sscale;
+                split8(w, sh[q], sl[q]);
+            }
+            // fragments [tile][time step][hi, lo], taken time step by time step
+            // so that consecutive products go to different accumulators
+            const f16x8 *fb = kb + Stage::kPsf * 64;
+            lds_pipelined<4 * GT, 6>([&](int i) { return fb[((i / 2 % GT) * 4 + i / (2 * GT) * 2 + i % 2) * 64]; },
+                                     [&](int i, const f16x8 &f) {
+                                         const int q = i / (2 * GT), g = i / 2 % GT;
+                                         acc[g] = MFMA16(f, sh[q], acc[g]);
+                                         if (i % 2 == 0) acc[g] = MFMA16(f, sl[q], acc[g]);
+                                     });
+        }
+        wait_vm_lgkm<Stage::kOps>();      // the next chunk is in, this wave's reads are done
+        block_barrier_nofence();
+        buf = buf == 2 ? 0 : buf + 1;
+        nbuf = nbuf == 2 ? 0 : nbuf + 1;
+    }
+    wait_vm_lgkm<0>();   // the repeated loads still in flight land before the LDS is handed on
+    if (il < 0) return;
+    float *out = a.part + (size_t)sp.split * a.part_stride + (size_t)il * a.pitch + 4 * h;
+#pragma unroll
+    for (int g = 0; g < GT; ++g) {
+        const int ct = sp.group * GT + g;
+        if (ct < a.nct) store_tile(out + 32 * ct, acc[g], -(le + a.out_exp));
+    }
+}
+
+template <int NUP, int GT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitArgs a)
+{
+    using Stage = ChunkStage<NUP, GT, WAVES>;
+    constexpr int PT = NUP / 32, NZS = 2 * GT;
+    extern __shared__ __align__(16) f16x8 lk[];
+    const SplitPos sp = split_pos<WAVES>(a);
+    const SigJob &job = a.jobs[sp.job];
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = sp.tile * 32 + (lane & 31);
+    const bool active = WAVES == 4 || sp.tile * 32 < job.rows;
+    const long il = r < job.rows ? job_line(job, r) : -1;
+    const Stage stage(job.ka16, a.fa, sp.c0, sp.c1 - sp.c0, a.nct, sp.group * GT);
+    stage.load(0, lk, 0, wave, lane);
+    stage.load(1, lk, 1, wave, lane);
+
+    f16x8 zh[NZS], zl[NZS];
+    const int col0 = sp.group * GT * 32;
+    const int le = split_line<NZS, 2>((const float *)job.in, il, job.in_stride, col0, a.nb2 - col0, h, zh, zl);
+    f32x16 acc[PT];
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) acc[pt] = 0.f;
+    const float gscale = a.s_scale;
+    wait_vm_lgkm<Stage::kOps>();
+    block_barrier_nofence();
+
+    int buf = 0, nbuf = 2;
+    for (int c = sp.c0; c < sp.c1; ++c) {
+        stage.load(c - sp.c0 + 2, lk, nbuf, wave, lane);
+        if (active) {
+            const f16x8 *kb = lk + buf * Stage::kFrags * 64 + lane;
+            f32x16 G = 0.f;
+            // fragments [16-column step][hi, lo]
+            lds_pipelined<2 * NZS, 6>([&](int i) { return kb[(Stage::kPsf + i) * 64]; },
+                                      [&](int i, const f16x8 &f) {
+                                          G = MFMA16(f, zh[i / 2], G);
+                                          if (i % 2 == 0) G = MFMA16(f, zl[i / 2], G);
+                                      });
+            f16x8 gh[2], gl[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                float w[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = G[8 * q + e] * gscale;
+                split8(w, gh[q], gl[q]);
+            }
+            // fragments [time step][detector tile][hi, lo]
+            lds_pipelined<4 * PT, 6>([&](int i) { return kb[i * 64]; },
+                                     [&](int i, const f16x8 &f) {
+                                         const int q = i / (2 * PT), pt = i / 2 % PT;
+                                         acc[pt] = MFMA16(f, gh[q], acc[pt]);
+                                         if (i % 2 == 0) acc[pt] = MFMA16(f, gl[q], acc[pt]);
+                                     });
+        }
+        wait_vm_lgkm<Stage::kOps>();
+        block_barrier_nofence();
+        buf = buf == 2 ? 0 : buf + 1;
+        nbuf = nbuf == 2 ? 0 : nbuf + 1;
+    }
+    wait_vm_lgkm<0>();
+    if (il < 0) return;
+    float *out = a.part + (size_t)(sp.split * a.ngroups + sp.group) * a.part_stride + (size_t)il * a.pitch + 4 * h;
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) store_tile(out + 32 * pt, acc[pt], -(le + a.out_exp));
+}
+
+typedef void (*SplitKernel)(SplitArgs);
+struct SplitEntry {
+    int nup, gt, waves;
+    SplitKernel fwd, adj;
+    int lds;
+};
+#define ENTRY(N, G, W) {N, G, W, split_fwd_kernel<N, G, W>, split_adj_kernel<N, G, W>, ChunkStage<N, G, W>::kBytes}
+// (two waves a SIMD, or one with as many columns as three chunks in LDS hold)
+const SplitEntry kSplit[] = {
+    ENTRY(64, 4, 8), ENTRY(64, 6, 8), ENTRY(64, 8, 8), ENTRY(64, 4, 4), ENTRY(64, 6, 4), ENTRY(64, 8, 4),
+    ENTRY(128, 4, 8), ENTRY(128, 6, 8), ENTRY(128, 7, 8), ENTRY(128, 8, 8), ENTRY(128, 4, 4), ENTRY(128, 6, 4), ENTRY(128, 7, 4), ENTRY(128, 8, 4),
+    ENTRY(192, 4, 8), ENTRY(192, 5, 8), ENTRY(192, 6, 8), ENTRY(192, 4, 4), ENTRY(192, 5, 4), ENTRY(192, 7, 4),
+    ENTRY(256, 3, 8), ENTRY(256, 4, 8), ENTRY(256, 3, 4), ENTRY(256, 5, 4)};
+#undef ENTRY
+constexpr int kEntries = sizeof(kSplit) / sizeof(kSplit[0]);
+
+}  // namespace
+
+int split_config(int i, int nup, int *gt, int *waves)
+{
+    if (i < 0 || i >= kEntries) return -1;
+    *gt = kSplit[i].gt;
+    *waves = kSplit[i].waves;
+    return kSplit[i].nup == nup ? 1 : 0;
+}
+
+hipError_t launch_split(const SplitArgs &a, bool fwd, hipStream_t st)
+{
+    if (a.config < 0 || a.config >= kEntries) return hipErrorInvalidValue;
+    const SplitEntry &e = kSplit[a.config];
+    int tg = 0;
+    for (int j = 0; j < a.njobs; ++j) {
+        if (a.jobs[j].tile0 != tg || a.jobs[j].rows < 1) return hipErrorInvalidValue;
+        tg += (a.jobs[j].rows + 32 * e.waves - 1) / (32 * e.waves);
+    }
+    if (e.nup != a.nup || a.njobs < 1 || a.njobs > 2 || tg != a.tgroups || a.nsplit < 1 || a.nsplit > a.nchunks || a.nsplit > 128 ||
+        a.nchunks > (1 << 17) ||
+        a.ngroups != (a.nct + e.gt - 1) / e.gt || a.nct != (a.nb2 + 31) / 32 || a.pitch % 4 ||
+        a.pitch < (fwd ? 32 * a.nct : a.nup) || (double)a.nchunks * a.nct * 4096 >= 2147483647.0 ||
+        (double)a.nchunks * a.nup * 128 >= 2147483647.0)
+        return hipErrorInvalidValue;
+    const SplitKernel k = fwd ? e.fwd : e.adj;
+    const hipError_t err = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, e.lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(k, dim3(a.tgroups * a.ngroups * a.nsplit), dim3(64 * e.waves), e.lds, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace mpi3d

@@ -120,3 +120,37 @@ def test_two_line_groups():
     y = np.asarray(random_data(g, 12)).reshape(g.n_lines, -1).astype(np.complex64)
     got = plan.signal_adj(torch.from_numpy(y.reshape(plan.data_shape)).cuda()).cpu().numpy()
     assert _line_errors(got, signal.adjoint(g, y).reshape(plan.lines_shape)).max() <= TOL
+
+
+@pytest.mark.parametrize("nx,nz,M,T,hi,hb", [(32, 3, 2, 1999, 15, 2), (64, 16, 9, 2050, 11, 3), (70, 37, 11, 3001, 31, 3),
+                                             (128, 33, 24, 2500, 9, 2), (131, 12, 7, 6001, 31, 3),
+                                             (192, 50, 30, 4999, 31, 3), (200, 5, 3, 2047, 7, 2), (256, 64, 40, 2999, 40, 3)])
+@pytest.mark.parametrize("raster", [False, True])
+def test_dense_split_stages(nx, nz, M, T, hi, hb, raster):
+    """T no multiple of 32: the dense stage, at one and several column groups, few and many lines."""
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    args = (nx, 12, nz, M, T, T / 128 + 1 / 3, 2.0, 1, hi, hb)
+    sweep = nx / 2.0 if raster else 0.0
+    g = oracle_geometry(*args)
+    g.raster_sweep = sweep
+    plan = Plan(*args, 1.0, raster_sweep=sweep)
+    assert plan.dft_cycles == 0
+    rng = np.random.default_rng(13)
+    rho = rng.uniform(0, 1, (g.n_lines, g.n_u)).astype(np.float32)
+    rho[1] *= 1e-20
+    rho[2] = 0.0
+    got = plan.signal_fwd(torch.from_numpy(rho.reshape(plan.lines_shape)).cuda()).cpu().numpy()
+    want = signal.forward(g, rho)
+    zero = np.arange(g.n_lines) == 2
+    assert not got.reshape(g.n_lines, -1)[zero].any()
+    ef = _line_errors(got.reshape(g.n_lines, -1)[~zero], want.reshape(g.n_lines, -1)[~zero]).max()
+    y = np.asarray(random_data(g, 14)).reshape(g.n_lines, -1).astype(np.complex64)
+    y[1] *= 1e20
+    y[2] = 0.0
+    got = plan.signal_adj(torch.from_numpy(y.reshape(plan.data_shape)).cuda()).cpu().numpy()
+    want = signal.adjoint(g, y)
+    assert not got.reshape(g.n_lines, -1)[zero].any()
+    ea = _line_errors(got.reshape(g.n_lines, -1)[~zero], want.reshape(g.n_lines, -1)[~zero]).max()
+    print("dense split %dx%d M %d T %d raster %d: forward %.2e adjoint %.2e" % (nx, nz, M, T, raster, ef, ea), flush=True)
+    assert ef <= TOL and ea <= TOL
