@@ -441,18 +441,18 @@ static int lines_to_volume(const mpi3d_plan *pl, int prec, const OpWs &w, bool s
 }
 
 // P x into the workspace lines; the mixed path gathers from a bf16 copy
-// (xb, or x converted into the workspace when xb is null).
+// (xb, or with xb null x: converted into the workspace, or by the kernel).
 static int project_into(const mpi3d_plan *pl, int prec, const float *x, const uint16_t *xb, const OpWs &w,
                         hipStream_t st)
 {
     if (prec == MPI3D_MIXED) {
-        if (!xb) {
+        if (!xb && !pl->band.bf16) {
             TRY(launch_to_bf16(pl->nvox, x, w.xb, st));
             xb = w.xb;
         }
-        TRY(launch_project(pl, nullptr, xb, w.rt, st));
+        TRY(launch_project16(pl, x, xb, w.rt, st));
     } else {
-        TRY(launch_project(pl, x, nullptr, w.rt, st));
+        TRY(launch_project(pl, x, w.rt, st));
     }
     return MPI3D_OK;
 }
@@ -559,7 +559,7 @@ static int gemm_signal_adj(const mpi3d_plan *pl, const float *data, float *lines
 static int apply_forward(const mpi3d_plan *pl, int prec, const float *x, float *out, const OpWs &w, hipStream_t st)
 {
     if (prec == MPI3D_PRECOMPOSED) {
-        TRY(launch_project(pl, x, nullptr, w.rt, st));
+        TRY(launch_project(pl, x, w.rt, st));
         return gemm_signal_fwd(pl, w.rt, pl->nup, out, st);
     }
     TRYRC(project_into(pl, prec, x, nullptr, w, st));
@@ -1034,7 +1034,7 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
     if (err == hipSuccess) err = hipEventRecord(e0, st);
     for (int i = 0; err == hipSuccess && i < repeats; ++i) {
         switch (kernel) {
-        case 0: err = mixed ? launch_project(pl, nullptr, w.xb, w.rt, st) : launch_project(pl, x, nullptr, w.rt, st);
+        case 0: err = mixed ? launch_project16(pl, nullptr, w.xb, w.rt, st) : launch_project(pl, x, w.rt, st);
             break;
         case 1:
             err = mixed ? launch_backproject16(pl, w.rtb, w.rtsc, x, nullptr, 0.0, nullptr, nullptr, st)

@@ -129,6 +129,14 @@ __device__ __forceinline__ f32x16 pair_sum(float *xs, int parity, int pair, int 
     return r;
 }
 
+// bf16 bits of v, rounded to nearest even
+__device__ __forceinline__ uint16_t bf16_bits(float v)
+{
+    uint32_t u = __float_as_uint(v);
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return (uint16_t)(u >> 16);
+}
+
 // N products whose table operands come from LDS: fragment j is read WIN
 // products ahead of its use, and a scheduling barrier after every product
 // keeps that distance.

@@ -254,10 +254,10 @@ struct mpi3d_plan {
     uint64_t line_key;             // equal keys <=> identical line tables
     // projection configuration
     mpi3d::FwdConfig fwd32, fwd16;  // forward projection, fp32 and bf16 gathers
-    // fp32 forward projection in four-slice texels: base rows (steep angles) and
-    // columns (the others) of a band, blocks (0: not taken) and blocks a slice
-    // group and angle class
-    struct { int rows, cols, blocks, parts[2]; } band;
+    // forward projection in four-slice texels: base rows (steep angles) and
+    // columns (the others) of a band, blocks, blocks a slice group and angle
+    // class; taken for fp32 gathers, for bf16 ones
+    struct { int rows, cols, blocks, parts[2]; bool fp32, bf16; } band;
     int n_steep;
     int *order;
     float *ay1;
@@ -314,8 +314,10 @@ namespace mpi3d {
 // Launchers (return hipError_t of the launch).
 // The operator's projection into the workspace lines rt [L][nup]: the x-drive
 // lines, then (dual drive) the z-drive lines transposed from them.
-hipError_t launch_project(const mpi3d_plan *pl, const float *x, const uint16_t *xb, float *rt,
-                          hipStream_t st);
+hipError_t launch_project(const mpi3d_plan *pl, const float *x, float *rt, hipStream_t st);
+// The mixed operator's: gathers of the volume's bf16 copy xb, or (null; only
+// where the plan has band.bf16) of x rounded to bf16 on the way.
+hipError_t launch_project16(const mpi3d_plan *pl, const float *x, const uint16_t *xb, float *rt, hipStream_t st);
 // The operator's backprojection of the workspace lines rt: with the dual drive
 // the z-drive lines are first added, transposed, into the x-drive lines (rt
 // is modified).

@@ -585,7 +585,15 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         const double x = (double)((fc.blocks + 255) / 256) * ((units + fc.blocks - 1) / fc.blocks) * NU * len;
         const double other = fc.slices == 2 ? 9e-6 + (pl->nx % 4 ? 0.35e-9 : 0.26e-9) * x
                                             : 3e-6 + (fc.n_bands > 1 ? 0.23e-9 : 0.155e-9) * x;
-        if (best > 0.92 * other) pl->band.blocks = 0;
+        pl->band.fp32 = best <= 0.92 * other;
+        // bf16 gathers: in one band their slice pairs cost 0.2 to 0.24 ns a ray
+        // sample, within a tenth of the four-slice kernel's time from 128^2 x 128
+        // x 36 to 160^2 x 128 x 60, and stay; in row bands 15 us and 0.36 ns
+        // (measured 0.36 to 0.45).
+        const mpi3d::FwdConfig &hc = pl->fwd16;
+        const long hunits = (long)((pl->nz + 1) / 2) * M;
+        const double hx = (double)((hc.blocks + 255) / 256) * ((hunits + hc.blocks - 1) / hc.blocks) * NU * len;
+        pl->band.bf16 = (precisions & (1 << MPI3D_MIXED)) && hc.n_bands > 1 && best <= 0.92 * (15e-6 + 0.36e-9 * hx);
     }
 
     // PSF kernel K[n][p] of every table (n < T, p < NU; zero padding

@@ -439,6 +439,9 @@ __global__ __launch_bounds__(kFwdThreads) void proj_fwd_kernel(ProjArgs a, const
 // bank conflicts (16 lanes read over up to 23 texels, so two share a bank
 // whatever the pitch).  Measured 432 -> 240 us at 256 x 256 x 128, 60 angles;
 // 285 -> 127 us at 224 x 224 x 112, 48; 82 -> 71 us at 192 x 192 x 96, 36.
+// The mixed operator's gathers (bf16 values, widened as they are staged; no
+// bf16 copy where the caller has none) against row bands of its slice pairs:
+// 385 -> 209 us, 242 -> 130, 97 -> 78 at 256 x 256 x 64, 24.
 // ---------------------------------------------------------------------------
 constexpr int kBandRays = 2;                     // rays a thread owns
 constexpr int kBandSlices = 4;
@@ -542,20 +545,30 @@ __device__ __forceinline__ void pair_sum(const SamplePair &g, float (&acc)[kBand
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// A staged value: the volume's, its bf16 copy's, or (Round16) the volume's
+// rounded to bf16 as that copy would be.
+struct Round16 {
+    float v;
+};
+__device__ __forceinline__ float staged(float v) { return v; }
+__device__ __forceinline__ float staged(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
+__device__ __forceinline__ float staged(Round16 v) { return staged(bf16_bits(v.v)); }
+
 // Stages LDS rows 0 .. rows - 1 of cols texels (grid rows j0 + r - 1, grid
 // columns i0 + c - 1; zeros outside the grid and past the last slice).
-__device__ __forceinline__ void stage_band4(float4 *lds, const float *vol, int k0, const ProjArgs &a, int j0, int i0,
+template <class V>
+__device__ __forceinline__ void stage_band4(float4 *lds, const V *vol, int k0, const ProjArgs &a, int j0, int i0,
                                             int rows, int cols, int W, int tid)
 {
     constexpr int U = 10;      // a full band (10240 texels) in one round of loads
     const int total = rows * cols;
     const size_t slice = (size_t)a.nx * a.ny;
     const int ns = min(kBandSlices, a.nz - k0);
-    const float *v0 = vol + (size_t)k0 * slice;
+    const V *v0 = vol + (size_t)k0 * slice;
     const int dr = kFwdThreads / cols, dc = kFwdThreads - dr * cols;
     int r = tid / cols, c = tid - r * cols;
     for (int e0 = tid; e0 < total; e0 += U * kFwdThreads) {
-        float v[U][kBandSlices];
+        V v[U][kBandSlices];
         int dst[U];
         unsigned inside = 0;
 #pragma unroll
@@ -579,13 +592,14 @@ __device__ __forceinline__ void stage_band4(float4 *lds, const float *vol, int k
         for (int u = 0; u < U; ++u)
             if (dst[u] >= 0) {
                 const bool in = inside & (1u << u);
-                lds[dst[u]] = make_float4(in ? v[u][0] : 0.f, in && ns > 1 ? v[u][1] : 0.f,
-                                          in && ns > 2 ? v[u][2] : 0.f, in && ns > 3 ? v[u][3] : 0.f);
+                lds[dst[u]] = make_float4(in ? staged(v[u][0]) : 0.f, in && ns > 1 ? staged(v[u][1]) : 0.f,
+                                          in && ns > 2 ? staged(v[u][2]) : 0.f, in && ns > 3 ? staged(v[u][3]) : 0.f);
             }
     }
 }
 
-__global__ __launch_bounds__(kFwdThreads) void proj_fwd_band_kernel(ProjArgs a, const float *vol, int out_stride)
+template <class V>
+__global__ __launch_bounds__(kFwdThreads) void proj_fwd_band_kernel(ProjArgs a, const V *vol, int out_stride)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int nb = gridDim.x;
@@ -1035,28 +1049,32 @@ static hipError_t launch_fwd(const mpi3d_plan *pl, const typename Texel<T>::V *v
     return hipGetLastError();
 }
 
+template <class V>
+static hipError_t launch_band(const mpi3d_plan *pl, const V *x, float *rt, int out_stride, hipStream_t st)
+{
+    ProjArgs a = base_args(pl);
+    a.rt = rt;
+    a.band_rows = pl->band.rows;
+    a.band_cols = pl->band.cols;
+    const int texels = std::max((a.band_rows + 1) * proj_pitch(a.nx), (a.ny + 2) * ((a.band_cols + 1) | 1));
+    const int nm[2] = {a.n_steep, a.M - a.n_steep};
+    for (int k = 0; k < 2; ++k) {
+        a.parts[k] = pl->band.parts[k];
+        if (nm[k] > 0 && (a.parts[k] < 1 || (long)((nm[k] + a.parts[k] - 1) / a.parts[k]) * a.nu > kFwdThreads * kBandRays))
+            return hipErrorInvalidValue;
+    }
+    if (texels > kBandTexels) return hipErrorInvalidValue;
+    const int lds = 16 * texels;
+    hipError_t e = hipFuncSetAttribute((const void *)proj_fwd_band_kernel<V>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(proj_fwd_band_kernel<V>, dim3(pl->band.blocks), dim3(kFwdThreads), lds, st, a, x, out_stride);
+    return hipGetLastError();
+}
+
 static hipError_t launch_fwd32(const mpi3d_plan *pl, const float *x, float *rt, int out_stride, hipStream_t st)
 {
-    if (pl->band.blocks > 0) {
-        ProjArgs a = base_args(pl);
-        a.rt = rt;
-        a.band_rows = pl->band.rows;
-        a.band_cols = pl->band.cols;
-        const int texels = std::max((a.band_rows + 1) * proj_pitch(a.nx), (a.ny + 2) * ((a.band_cols + 1) | 1));
-        const int nm[2] = {a.n_steep, a.M - a.n_steep};
-        for (int k = 0; k < 2; ++k) {
-            a.parts[k] = pl->band.parts[k];
-            if (nm[k] > 0 && (a.parts[k] < 1 || (long)((nm[k] + a.parts[k] - 1) / a.parts[k]) * a.nu > kFwdThreads * kBandRays))
-                return hipErrorInvalidValue;
-        }
-        if (texels > kBandTexels) return hipErrorInvalidValue;
-        const int lds = 16 * texels;
-        hipError_t e = hipFuncSetAttribute((const void *)proj_fwd_band_kernel,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(proj_fwd_band_kernel, dim3(pl->band.blocks), dim3(kFwdThreads), lds, st, a, x, out_stride);
-        return hipGetLastError();
-    }
+    if (pl->band.fp32) return launch_band(pl, x, rt, out_stride, st);
     if (pl->fwd32.slices == 2) return launch_fwd<float2>(pl, x, pl->fwd32, rt, out_stride, st);
     return launch_fwd<float>(pl, x, pl->fwd32, rt, out_stride, st);
 }
@@ -1066,10 +1084,21 @@ hipError_t launch_project_strided(const mpi3d_plan *pl, const float *x, float *r
     return launch_fwd32(pl, x, rt, out_stride, st);
 }
 
-// xb non-null: gather from the bf16 copy (mixed path)
-hipError_t launch_project(const mpi3d_plan *pl, const float *x, const uint16_t *xb, float *rt, hipStream_t st)
+hipError_t launch_project(const mpi3d_plan *pl, const float *x, float *rt, hipStream_t st)
 {
-    hipError_t e = xb ? launch_fwd<uint32_t>(pl, xb, pl->fwd16, rt, pl->nup, st) : launch_fwd32(pl, x, rt, pl->nup, st);
+    hipError_t e = launch_fwd32(pl, x, rt, pl->nup, st);
+    if (e == hipSuccess && pl->drive_axes == 2) e = launch_zlines(pl, rt, false, st);
+    return e;
+}
+
+hipError_t launch_project16(const mpi3d_plan *pl, const float *x, const uint16_t *xb, float *rt, hipStream_t st)
+{
+    hipError_t e;
+    if (pl->band.bf16)
+        e = xb ? launch_band(pl, xb, rt, pl->nup, st)
+               : launch_band(pl, reinterpret_cast<const Round16 *>(x), rt, pl->nup, st);
+    else
+        e = xb ? launch_fwd<uint32_t>(pl, xb, pl->fwd16, rt, pl->nup, st) : hipErrorInvalidValue;
     if (e == hipSuccess && pl->drive_axes == 2) e = launch_zlines(pl, rt, false, st);
     return e;
 }

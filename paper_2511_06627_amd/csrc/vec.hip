@@ -9,7 +9,7 @@
 
 #include <cmath>
 
-#include "internal.h"
+#include "device.h"
 
 namespace mpi3d {
 
@@ -347,12 +347,7 @@ __global__ __launch_bounds__(kThreads) void update_p_kernel(float *__restrict__ 
         const float v = init ? s[idx] : fmaf(bf, p[idx], s[idx]);
         p[idx] = v;
         sq += (double)v * (double)v;
-        if (pb) {
-            // round to nearest even bf16
-            uint32_t u = __float_as_uint(v);
-            u += 0x7fffu + ((u >> 16) & 1u);
-            pb[idx] = (uint16_t)(u >> 16);
-        }
+        if (pb) pb[idx] = bf16_bits(v);
     }
     const double t = block_sum(sq, red);
     if (threadIdx.x == 0) parts_p[blockIdx.x] = t;
@@ -360,11 +355,8 @@ __global__ __launch_bounds__(kThreads) void update_p_kernel(float *__restrict__ 
 
 __global__ __launch_bounds__(kThreads) void to_bf16_kernel(long n, const float *x, uint16_t *xb)
 {
-    for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads) {
-        uint32_t u = __float_as_uint(x[idx]);
-        u += 0x7fffu + ((u >> 16) & 1u);
-        xb[idx] = (uint16_t)(u >> 16);
-    }
+    for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads)
+        xb[idx] = bf16_bits(x[idx]);
 }
 
 __global__ __launch_bounds__(kThreads) void clamp_kernel(float *x, long n)

@@ -58,3 +58,35 @@ def test_angles_beyond_half_turn():
     want = projector.project(g, np.asarray(x, dtype=np.float64))
     got = plan.project(torch.from_numpy(np.ascontiguousarray(x)).float().cuda()).cpu().numpy()
     assert rel_l2(got, want) <= TOL32
+
+
+@pytest.mark.parametrize("shape", [(211, 230, 13, 60), (256, 209, 34, 33)])
+def test_band_projection_bf16(shape):
+    """The mixed operator's gathers in large volumes: the volume rounded to bf16 on the way, the fp32 kernel's sums."""
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    nx, ny, nz, M = shape
+    plan = Plan(nx, ny, nz, M, 2048, 2048 / 256 + 1 / 3, 2.0, 1, 4, 1, 1.0, precisions=("fp32", "mixed"))
+    x = torch.rand(plan.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(6))
+    x16 = x.to(torch.bfloat16).float()
+    got = plan.forward(x, precision="mixed")
+    assert torch.equal(got, plan.forward(x16, precision="mixed"))
+    # the fp32 projections of the same values (their sums perhaps in another
+    # order, 1e-6 apart): of the signal stage's fp16 operands (a unit is 2^-11
+    # to 2^-10 of a value) some 0.4% round the other way, 2^-10 sqrt(0.004) = 6e-5
+    want = plan.signal_fwd(plan.project(x16), precision="mixed")
+    assert float((got - want).norm() / want.norm()) <= 1e-4
+    # a solver's iterations gather from a bf16 copy of their own: one CGLS step
+    # along p = A^H b is alpha p, alpha = |p|^2 / (|A p|^2 + lam |p|^2)
+    b = plan.forward(x)
+    got, _ = plan.solve(b, 1e-3, precision="mixed", refine_sweeps=1, inner_iters=1)
+    p = plan.adjoint(b, precision="mixed")
+    if not torch.isfinite(p).all() or float((got.double() * p.double()).sum()) == 0.0:
+        raise AssertionError("empty step")
+    q = plan.forward(p, precision="mixed")
+    pp = float((p.double() ** 2).sum())
+    alpha = pp / (float((q.to(torch.complex128).abs() ** 2).sum()) + 1e-3 * pp)
+    # fp32 against mixed first residuals and directions: the mixed operator's own error
+    rel = float((got.double() - alpha * p.double()).norm() / (alpha * p.double()).norm())
+    print("one mixed step: %.2e" % rel, flush=True)
+    assert rel <= 5e-3
