@@ -608,11 +608,11 @@ void Cgls::init(const mpi3d_plan *plan, const float *b_, float *x_, void *ws, do
 
 int Cgls::restart_a(bool x_zero, hipStream_t st)
 {
-    if (!started) TRY(launch_scal_init(scal, st));
     if (x_zero) {
-        TRY(launch_copy(r, b, 2 * pl->L * pl->nb, st));
+        TRY(launch_start(x, pl->nvox, r, b, 2 * pl->L * pl->nb, started ? nullptr : scal, st));
         return MPI3D_OK;
     }
+    if (!started) TRY(launch_scal_init(scal, st));
     return project_into(pl, MPI3D_FP32, x, nullptr, w, st);
 }
 
@@ -626,12 +626,8 @@ int Cgls::restart_c(hipStream_t st)
 {
     float *grad = corr ? g0 : s;
     TRYRC(lines_to_volume(pl, MPI3D_FP32, w, serve, grad, x, lambda, parts_s, &ns, st));
-    TRY(launch_beta(scal, parts_s, ns, 1, started ? 0 : 1, hist, step, st));
-    TRY(launch_update_p2(p, grad, pb, pl->nvox, scal, parts_p, &np, 1, st));
-    if (corr) {
-        TRY(launch_fill(d, pl->nvox, 0.f, st));
-        TRY(launch_fill(r, 2 * pl->L * pl->nb, 0.f, st));
-    }
+    TRY(launch_update_p(p, grad, pb, pl->nvox, scal, parts_s, ns, parts_p, &np, 1, started ? 0 : 1, hist, step,
+                        corr ? d : nullptr, corr ? r : nullptr, 2 * pl->L * pl->nb, st));
     started = true;
     return MPI3D_OK;
 }
@@ -651,16 +647,15 @@ int Cgls::iter_a(int prec, hipStream_t st)
 int Cgls::iter_b(int prec, hipStream_t st)
 {
     TRYRC(reduce_forward(pl, prec, w, serve, q, nullptr, parts_q, &nq, st));
-    TRY(launch_alpha(scal, parts_q, nq, parts_p, np, lambda, hist, step, st));
-    TRY(launch_update_xr2(corr ? d : x, p, r, q, pl->nvox, 2 * pl->L * pl->nb, scal, st));
+    TRY(launch_update_xr(corr ? d : x, p, r, q, pl->nvox, 2 * pl->L * pl->nb, scal, parts_q, nq, parts_p, np, lambda,
+                         hist, step, st));
     return MPI3D_OK;
 }
 
 int Cgls::iter_c(int prec, hipStream_t st)
 {
     TRYRC(lines_to_volume(pl, prec, w, serve, s, corr ? d : x, lambda, parts_s, &ns, st, corr ? g0 : nullptr));
-    TRY(launch_beta(scal, parts_s, ns, 0, 0, hist, step, st));
-    TRY(launch_update_p2(p, s, pb, pl->nvox, scal, parts_p, &np, 0, st));
+    TRY(launch_update_p(p, s, pb, pl->nvox, scal, parts_s, ns, parts_p, &np, 0, 0, hist, step, nullptr, nullptr, 0, st));
     ++step;
     return MPI3D_OK;
 }
@@ -954,7 +949,6 @@ extern "C" int mpi3d_solve(const mpi3d_plan *pl, const float *b, float *x, const
         cg.corr = true;
     }
     bool xz = o->x0_is_zero != 0;
-    if (xz) TRY(launch_fill(x, pl->nvox, 0.f, st));
     if (o->precision == MPI3D_FP32) {
         TRYRC(cg.restart(xz, st));
         for (int it = 0; it < o->iters; ++it) {

@@ -423,14 +423,13 @@ int scal_slot_bad();
 int scal_slot_gamma();
 int scal_slot_gamma0();
 hipError_t launch_scal_init(double *scal, hipStream_t st);
-hipError_t launch_alpha(double *scal, const double *parts_q, int nq, const double *parts_p, int np, double lambda,
-                        double *hist, int step, hipStream_t st);
-hipError_t launch_beta(double *scal, const double *parts_s, int ns, int restart, int first, double *hist, int step,
-                       hipStream_t st);
-hipError_t launch_update_xr2(float *x, const float *p, float *r, const float *q, long nvox, long ndata,
-                             const double *scal, hipStream_t st);
-hipError_t launch_update_p2(float *p, const float *s, uint16_t *pb, long n, const double *scal, double *parts_p,
-                            int *np_out, int init, hipStream_t st);
+hipError_t launch_update_xr(float *x, const float *p, float *r, const float *q, long nvox, long ndata, double *scal,
+                            const double *parts_q, int nq, const double *parts_p, int np, double lambda, double *hist,
+                            int step, hipStream_t st);
+hipError_t launch_update_p(float *p, const float *s, uint16_t *pb, long n, double *scal, const double *parts_s, int ns,
+                           double *parts_p, int *np_out, int init, int first, double *hist, int step, float *d,
+                           float *r, long ndata, hipStream_t st);
+hipError_t launch_start(float *x, long nvox, float *r, const float *b, long ndata, double *scal, hipStream_t st);
 hipError_t launch_clamp(float *x, long n, hipStream_t st);
 hipError_t launch_fill(float *x, long n, float v, hipStream_t st);
 hipError_t launch_copy(float *dst, const float *src, long n, hipStream_t st);
@@ -519,7 +518,7 @@ struct Cgls {
     void init(const mpi3d_plan *plan, const float *b_, float *x_, void *ws, double lam, double *h);
     // restart: r = b - A32 x (or b when x is zero), s = A32^T r - lambda x,
     // gamma = |s|^2, p = s.  Phases around the two signal launches:
-    int restart_a(bool x_zero, hipStream_t st);       // projection of x (or r = b)
+    int restart_a(bool x_zero, hipStream_t st);       // projection of x (or x = 0, r = b)
     int restart_b(bool x_zero, hipStream_t st);       // r = b - (A x)
     int restart_c(hipStream_t st);                    // s (or g0), gamma, p; corr: d = 0, r = 0
     int finish_sweep(bool clamp, hipStream_t st);     // corr: x += d (then clamp); else clamp

@@ -137,7 +137,6 @@ int run_group(mpi3d_state *const *g, int n, StepKind kind, int prec, hipStream_t
         for (int i = 0; i < n; ++i) {
             mpi3d_state *s = g[i];
             const bool xz = s->first && s->o.x0_is_zero;
-            if (xz) TRY(launch_fill(s->cg.x, s->pl->nvox, 0.f, st));
             TRYRC(s->cg.restart_a(xz, st));
             if (!xz) jobs[nf++] = LineJob{s->pl, s->cg.w.rt, s->pl->nup, &s->cg.w};
         }

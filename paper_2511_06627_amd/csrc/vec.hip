@@ -269,62 +269,54 @@ __global__ __launch_bounds__(kThreads) void row_scale_kernel(long rows, int ncol
 }
 
 // Scalar slots (doubles) of one solve.
-enum { S_GAMMA = 0, S_DELTA, S_ALPHA, S_BETA, S_BAD, S_GAMMA0, S_STEP, S_NSLOTS };
+enum { S_GAMMA = 0, S_DELTA, S_ALPHA, S_BETA, S_BAD, S_GAMMA0, S_STEP, S_PREV, S_NSLOTS };
 
 __device__ double sum_parts(const double *parts, int n, double *red)
 {
     double v = 0.0;
+#pragma unroll 8
     for (int i = threadIdx.x; i < n; i += kThreads) v += parts[i];
     return block_sum(v, red);
 }
 
-// delta = |q|^2 + lambda |p|^2, alpha = gamma / delta
-__global__ __launch_bounds__(kThreads) void alpha_kernel(double *scal, const double *parts_q, int nq,
-                                                          const double *parts_p, int np, double lambda,
-                                                          double *hist, int step)
+// The CGLS updates with their scalars.  Every block adds the norm partials
+// itself, in the order one block would (some 2 us, in place of a launch of
+// about 5 us in the iteration's serial chain; a 64^3 x 24-angle iteration:
+// alpha 5.8 + update 4.5 -> 6.4 us, beta 3.0 + update 3.6 -> 4.9); block 0 writes
+// the scalars, into slots that no block of the same launch reads: the update of
+// x and r reads GAMMA and copies it to PREV, that of p reads PREV and writes
+// GAMMA.
+
+// delta = |q|^2 + lambda |p|^2, alpha = gamma / delta;
+// x = x + alpha p, r = r - alpha q
+__global__ __launch_bounds__(kThreads) void update_xr_kernel(float *__restrict__ x, const float *__restrict__ p,
+                                                              float *__restrict__ r, const float *__restrict__ q,
+                                                              long nvox, long ndata, double *scal,
+                                                              const double *parts_q, int nq, const double *parts_p,
+                                                              int np, double lambda, double *hist, int step)
 {
     __shared__ double red[kThreads / 64];
+    __shared__ double sh;
     const double qq = sum_parts(parts_q, nq, red);
     __syncthreads();
     const double pp = sum_parts(parts_p, np, red);
     if (threadIdx.x == 0) {
-        const double delta = qq + lambda * pp;
-        const double alpha = scal[S_GAMMA] / delta;
-        scal[S_DELTA] = delta;
-        scal[S_ALPHA] = alpha;
-        if (!isfinite(alpha)) scal[S_BAD] = 1.0;
-        if (hist) {
-            hist[4 * step + 0] = scal[S_GAMMA];
-            hist[4 * step + 1] = delta;
-            hist[4 * step + 2] = alpha;
+        const double gamma = scal[S_GAMMA], delta = qq + lambda * pp, alpha = gamma / delta;
+        sh = alpha;
+        if (blockIdx.x == 0) {
+            scal[S_DELTA] = delta;
+            scal[S_ALPHA] = alpha;
+            scal[S_PREV] = gamma;
+            if (!isfinite(alpha)) scal[S_BAD] = 1.0;
+            if (hist) {
+                hist[4 * step + 0] = gamma;
+                hist[4 * step + 1] = delta;
+                hist[4 * step + 2] = alpha;
+            }
         }
     }
-}
-
-// gamma' = |s|^2; beta = gamma'/gamma (restart: beta = 0, and on the first
-// start gamma0 = gamma')
-__global__ __launch_bounds__(kThreads) void beta_kernel(double *scal, const double *parts_s, int ns, int restart,
-                                                         int first, double *hist, int step)
-{
-    __shared__ double red[kThreads / 64];
-    const double g = sum_parts(parts_s, ns, red);
-    if (threadIdx.x == 0) {
-        double beta = 0.0;
-        if (!restart) beta = g / scal[S_GAMMA];
-        if (first) scal[S_GAMMA0] = g;
-        scal[S_GAMMA] = g;
-        scal[S_BETA] = beta;
-        if (!isfinite(g) || !isfinite(beta)) scal[S_BAD] = 1.0;
-        if (hist && !restart) hist[4 * step + 3] = beta;
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void update_xr_kernel(float *__restrict__ x, const float *__restrict__ p,
-                                                              float *__restrict__ r, const float *__restrict__ q,
-                                                              long nvox, long ndata, const double *scal)
-{
-    const double alpha = scal[S_ALPHA];
-    const float af = (float)alpha;
+    __syncthreads();
+    const float af = (float)sh;
     const long n = nvox + ndata;
     for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads) {
         if (idx < nvox) x[idx] = fmaf(af, p[idx], x[idx]);
@@ -335,22 +327,59 @@ __global__ __launch_bounds__(kThreads) void update_xr_kernel(float *__restrict__
     }
 }
 
-// p = s + beta p (beta from scal), optional bf16 shadow, partial |p|^2
+// gamma' = |s|^2, beta = gamma' / gamma; p = s + beta p, optional bf16 shadow,
+// partial |p|^2.  init (a restart; on the first, `first`, gamma0 = gamma'):
+// beta = 0, p = s, and d and r (where given) are cleared.
 __global__ __launch_bounds__(kThreads) void update_p_kernel(float *__restrict__ p, const float *__restrict__ s,
-                                                             uint16_t *pb, long n, const double *scal,
-                                                             double *parts_p, int init)
+                                                             uint16_t *pb, long n, double *scal,
+                                                             const double *parts_s, int ns, double *parts_p, int init,
+                                                             int first, double *hist, int step, float *d, float *r,
+                                                             long ndata)
 {
     __shared__ double red[kThreads / 64];
-    const float bf = (float)scal[S_BETA];
+    __shared__ double sh;
+    if (!init || blockIdx.x == 0) {
+        const double g = sum_parts(parts_s, ns, red);
+        if (threadIdx.x == 0) {
+            double beta = 0.0;
+            if (!init) beta = g / scal[S_PREV];
+            sh = beta;
+            if (blockIdx.x == 0) {
+                if (first) scal[S_GAMMA0] = g;
+                scal[S_GAMMA] = g;
+                scal[S_BETA] = beta;
+                if (!isfinite(g) || !isfinite(beta)) scal[S_BAD] = 1.0;
+                if (hist && !init) hist[4 * step + 3] = beta;
+            }
+        }
+        __syncthreads();
+    }
+    const float bf = init ? 0.f : (float)sh;
     double sq = 0.0;
     for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads) {
         const float v = init ? s[idx] : fmaf(bf, p[idx], s[idx]);
         p[idx] = v;
         sq += (double)v * (double)v;
         if (pb) pb[idx] = bf16_bits(v);
+        if (d) d[idx] = 0.f;
     }
+    if (r)
+        for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < ndata; idx += (long)gridDim.x * kThreads)
+            r[idx] = 0.f;
     const double t = block_sum(sq, red);
     if (threadIdx.x == 0) parts_p[blockIdx.x] = t;
+}
+
+// A solve's start from x = 0: x cleared, r = b, the scalars cleared (scal may be null).
+__global__ __launch_bounds__(kThreads) void start_kernel(float *x, long nvox, float *r, const float *b, long ndata,
+                                                          double *scal)
+{
+    if (scal && blockIdx.x == 0 && threadIdx.x < S_NSLOTS) scal[threadIdx.x] = 0.0;
+    const long n = nvox + ndata;
+    for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads) {
+        if (idx < nvox) x[idx] = 0.f;
+        else r[idx - nvox] = b[idx - nvox];
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void to_bf16_kernel(long n, const float *x, uint16_t *xb)
@@ -542,35 +571,29 @@ hipError_t launch_to_bf16(long n, const float *x, uint16_t *xb, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_alpha(double *scal, const double *parts_q, int nq, const double *parts_p, int np, double lambda,
-                        double *hist, int step, hipStream_t st)
-{
-    hipLaunchKernelGGL(alpha_kernel, dim3(1), dim3(kThreads), 0, st, scal, parts_q, nq, parts_p, np, lambda, hist,
-                       step);
-    return hipGetLastError();
-}
-
-hipError_t launch_beta(double *scal, const double *parts_s, int ns, int restart, int first, double *hist, int step,
-                       hipStream_t st)
-{
-    hipLaunchKernelGGL(beta_kernel, dim3(1), dim3(kThreads), 0, st, scal, parts_s, ns, restart, first, hist, step);
-    return hipGetLastError();
-}
-
-hipError_t launch_update_xr2(float *x, const float *p, float *r, const float *q, long nvox, long ndata,
-                             const double *scal, hipStream_t st)
+hipError_t launch_update_xr(float *x, const float *p, float *r, const float *q, long nvox, long ndata, double *scal,
+                            const double *parts_q, int nq, const double *parts_p, int np, double lambda, double *hist,
+                            int step, hipStream_t st)
 {
     hipLaunchKernelGGL(update_xr_kernel, dim3(grid_for(nvox + ndata)), dim3(kThreads), 0, st, x, p, r, q, nvox,
-                       ndata, scal);
+                       ndata, scal, parts_q, nq, parts_p, np, lambda, hist, step);
     return hipGetLastError();
 }
 
-hipError_t launch_update_p2(float *p, const float *s, uint16_t *pb, long n, const double *scal, double *parts_p,
-                            int *np_out, int init, hipStream_t st)
+hipError_t launch_update_p(float *p, const float *s, uint16_t *pb, long n, double *scal, const double *parts_s, int ns,
+                           double *parts_p, int *np_out, int init, int first, double *hist, int step, float *d,
+                           float *r, long ndata, hipStream_t st)
 {
     const int g = grid_for(n);
     if (np_out) *np_out = g;
-    hipLaunchKernelGGL(update_p_kernel, dim3(g), dim3(kThreads), 0, st, p, s, pb, n, scal, parts_p, init);
+    hipLaunchKernelGGL(update_p_kernel, dim3(g), dim3(kThreads), 0, st, p, s, pb, n, scal, parts_s, ns, parts_p, init,
+                       first, hist, step, d, r, ndata);
+    return hipGetLastError();
+}
+
+hipError_t launch_start(float *x, long nvox, float *r, const float *b, long ndata, double *scal, hipStream_t st)
+{
+    hipLaunchKernelGGL(start_kernel, dim3(grid_for(nvox + ndata)), dim3(kThreads), 0, st, x, nvox, r, b, ndata, scal);
     return hipGetLastError();
 }
 

@@ -1,0 +1,54 @@
+"""The solvers' fused scalar and vector updates: nothing is read before it is written.
+
+A solve in a workspace and a result of NaN bytes gives the bits of one in
+zeroed memory, with many more voxels than data and the reverse, from x = 0 and
+from a given x, alone and as served steps; and the float64 scalars it records
+are those of the update formulas.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {"voxels": (96, 90, 40, 2, 7), "data": (33, 20, 9, 40, 31)}   # nx, ny, nz, M, harm_hi
+
+
+@pytest.mark.parametrize("prec", ["fp32", "mixed"])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_solve_in_unwritten_memory(name, prec):
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    nx, ny, nz, M, hi = SHAPES[name]
+    plan = Plan(nx, ny, nz, M, 2048, 2048 / 64 + 1 / 3, 2.0, 1, hi, 2, 1.0 / 64, precisions=("fp32", "mixed"))
+    gen = torch.Generator("cuda").manual_seed(3)
+    b = torch.view_as_complex(torch.randn(*plan.data_shape, 2, device="cuda", generator=gen))
+    kw = dict(iters=3) if prec == "fp32" else dict(precision="mixed", refine_sweeps=2, inner_iters=2)
+    out = []
+    for fill in (0, 255):
+        ws = plan.workspace("solve")
+        ws.view(torch.uint8).fill_(fill)
+        x0, _ = plan.solve(b, 1e-2, ws=ws, report=False, **kw)
+        ws.view(torch.uint8).fill_(fill)
+        x1, _ = plan.solve(b, 1e-2, x=0.5 * x0, ws=ws, report=False, **kw)
+        assert torch.isfinite(x0).all() and torch.isfinite(x1).all()
+        out.append((x0, x1))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_recorded_scalars(name):
+    """alpha = gamma / delta and beta = gamma' / gamma from the recorded norms, step after step."""
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    nx, ny, nz, M, hi = SHAPES[name]
+    plan = Plan(nx, ny, nz, M, 2048, 2048 / 64 + 1 / 3, 2.0, 1, hi, 2, 1.0 / 64)
+    b = torch.view_as_complex(torch.randn(*plan.data_shape, 2, device="cuda",
+                                          generator=torch.Generator("cuda").manual_seed(4)))
+    h = torch.zeros(4 * 4, dtype=torch.float64, device="cuda")
+    _, rep = plan.solve(b, 1e-2, iters=4, history=h)
+    h = h.cpu().numpy().reshape(4, 4)                       # gamma, delta, alpha, beta
+    s0 = plan.adjoint(b)
+    assert h[0, 0] == pytest.approx(float((s0.double() ** 2).sum()), rel=1e-12)
+    assert np.array_equal(h[:, 2], h[:, 0] / h[:, 1])
+    np.testing.assert_allclose(h[:-1, 3] * h[:-1, 0], h[1:, 0], rtol=1e-14)
+    assert rep.gamma == pytest.approx(h[3, 3] * h[3, 0], rel=1e-14) and rep.gamma0 == h[0, 0]
