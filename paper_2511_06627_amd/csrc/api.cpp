@@ -784,7 +784,8 @@ static int momentum_solve(const mpi3d_plan *pl, const float *b, float *x, const 
     OpWs w = carve_op(pl, ws + pl->sw_op);
     float *r = (float *)(ws + pl->sw_r);
     double *scal = (double *)(ws + pl->sw_scal);
-    double *parts = (double *)(ws + pl->sw_parts);
+    double *parts2 = (double *)(ws + pl->sw_parts);   // two steps' partials
+    int np = 0;
     float *bufs[3] = {(float *)(ws + pl->sw_s), (float *)(ws + pl->sw_p), (float *)(ws + pl->sw_v)};
     const double tt = o->reg == MPI3D_REG_FD ? fd_normal_norm(pl) : 1.0;
     double tau = o->tau;
@@ -792,7 +793,7 @@ static int momentum_solve(const mpi3d_plan *pl, const float *b, float *x, const 
         // ||A^T A||_2 by power iteration in the workspace (q holds A v)
         double nrm = 0.0;
         int its = 0;
-        TRYRC(power_norm(pl, w, bufs[0], bufs[1], (float *)(ws + pl->sw_q), parts + pl->max_parts, parts, 1e-7,
+        TRYRC(power_norm(pl, w, bufs[0], bufs[1], (float *)(ws + pl->sw_q), parts2 + pl->max_parts, parts2, 1e-7,
                          std::min(1000, pl->max_parts), st, &nrm, &its));
         tau = 1.0 / (nrm * nrm + o->lambda * tt);
     }
@@ -812,10 +813,13 @@ static int momentum_solve(const mpi3d_plan *pl, const float *b, float *x, const 
         TRYRC(lines_to_volume(pl, MPI3D_FP32, w, false, g, nullptr, 0.0, nullptr, nullptr, st));
         // x_{k+1} into x_{k-1}'s buffer, y_{k+1} over g; beta of step k+1
         const float beta = (float)((double)k / (double)(k + 3));
-        int np = 0;
+        double *parts = parts2 + (k & 1) * pl->max_parts;
+        const double *prev = parts2 + (1 - (k & 1)) * pl->max_parts;
+        const int nprev = np;
         TRY(launch_momentum(y, g, xk, xprev, g, pl->nx, pl->ny, pl->nz, (float)tau, (float)(tau * o->lambda), beta,
-                            o->reg == MPI3D_REG_FD ? 1 : 0, o->clamp_every > 0 ? 1 : 0, parts, &np, st));
-        TRY(launch_step_norm(scal, parts, np, k == 1 ? 1 : 0, st));
+                            o->reg == MPI3D_REG_FD ? 1 : 0, o->clamp_every > 0 ? 1 : 0, parts, &np, scal, prev, nprev,
+                            k == 2 ? 1 : 0, st));
+        if (k == o->iters) TRY(launch_step_norm(scal, parts, np, k == 1 ? 1 : 0, st));
         float *xn = xprev;
         xprev = xk;
         xk = xn;

@@ -438,7 +438,7 @@ hipError_t launch_scale_by(float *v, const float *z, long n, const double *norms
 hipError_t launch_add_to(float *x, const float *d, long n, int clamp, hipStream_t st);
 hipError_t launch_momentum(const float *y, const float *g, const float *x, float *x_new, float *y_new, int nx,
                            int ny, int nz, float tau, float taulam, float beta, int fd, int nonneg, double *parts,
-                           int *nparts, hipStream_t st);
+                           int *nparts, double *scal, const double *prev, int nprev, int first, hipStream_t st);
 hipError_t launch_step_norm(double *scal, const double *parts, int n, int first, hipStream_t st);
 
 // Strided projection launchers (public stage entry points use stride n_u).

@@ -8,6 +8,7 @@
 // on the device: no host round trip per iteration.
 
 #include <cmath>
+#include <type_traits>
 
 #include "device.h"
 
@@ -30,28 +31,49 @@ __device__ __forceinline__ double block_sum(double v, double *red)
     return t;  // valid in thread 0
 }
 
-// sum_s pp[s * stride] in float64, in split order; eight loads in flight
-// (a chain of rounds of loads, not bandwidth, is what many splits cost)
-__device__ __forceinline__ double sum_splits(const float *__restrict__ pp, int n, long stride)
+// N consecutive floats as one word (4 N bytes aligned), N sums
+template <int N>
+struct Words {
+    typedef float type __attribute__((ext_vector_type(N)));
+};
+template <>
+struct Words<1> {
+    typedef float type;
+};
+template <int N>
+struct Sums {
+    double v[N];
+};
+template <int N>
+__device__ __forceinline__ float word(const typename Words<N>::type &w, int i)
 {
-    double v = 0.0;
+    if constexpr (N == 1) return w;
+    else return w[i];
+}
+
+// sum_s pp[s * stride] in float64, in split order, of N neighbours; eight
+// loads in flight (a chain of rounds of loads, not bandwidth, is what many
+// splits cost)
+template <int N>
+__device__ __forceinline__ Sums<N> sum_splits(const float *__restrict__ pp, int n, long stride)
+{
+    typedef typename Words<N>::type W;
+    Sums<N> v{};
     int s = 0;
-    for (; s + 8 <= n; s += 8) {
-        float a[8];
+    auto block = [&](auto count) {
+        constexpr int C = decltype(count)::value;
+        W a[C];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] = pp[(long)(s + j) * stride];
+        for (int j = 0; j < C; ++j) a[j] = *reinterpret_cast<const W *>(pp + (long)(s + j) * stride);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v += (double)a[j];
-    }
-    for (; s + 4 <= n; s += 4) {
-        const float a0 = pp[(long)s * stride], a1 = pp[(long)(s + 1) * stride];
-        const float a2 = pp[(long)(s + 2) * stride], a3 = pp[(long)(s + 3) * stride];
-        v += (double)a0;
-        v += (double)a1;
-        v += (double)a2;
-        v += (double)a3;
-    }
-    for (; s < n; ++s) v += (double)pp[(long)s * stride];
+        for (int j = 0; j < C; ++j)
+#pragma unroll
+            for (int i = 0; i < N; ++i) v.v[i] += (double)word<N>(a[j], i);
+        s += C;
+    };
+    while (s + 8 <= n) block(std::integral_constant<int, 8>{});
+    while (s + 4 <= n) block(std::integral_constant<int, 4>{});
+    while (s < n) block(std::integral_constant<int, 1>{});
     return v;
 }
 
@@ -63,12 +85,16 @@ __device__ __forceinline__ double sum_splits(const float *__restrict__ pp, int n
 // read (row_scale[e * lines + row]); adjoint, pass 0 of the line itself and
 // pass e of the lines e before and after it within its angle, each divided
 // by the scale of that line's data (row_scale[line]).  In pass order.
-__device__ __forceinline__ double sum_unscaled(const float *__restrict__ pp, int nparts, long stride, long row,
-                                               const float *__restrict__ row_scale, RowPasses rp)
+template <int N>
+__device__ __forceinline__ Sums<N> sum_unscaled(const float *__restrict__ pp, int nparts, long stride, long row,
+                                                const float *__restrict__ row_scale, RowPasses rp)
 {
     if (rp.npass <= 1) {
-        const double v = sum_splits(pp, nparts, stride);
-        return row_scale ? v / (double)row_scale[row] : v;
+        Sums<N> v = sum_splits<N>(pp, nparts, stride);
+        if (row_scale)
+#pragma unroll
+            for (int i = 0; i < N; ++i) v.v[i] /= (double)row_scale[row];
+        return v;
     }
     // passes: blocks of nparts / npass splits; the fused adjoint: every split
     // holds all passes, pass e at column offset e pass_cols of each line
@@ -78,26 +104,28 @@ __device__ __forceinline__ double sum_unscaled(const float *__restrict__ pp, int
     const int nline = zl ? rp.nzc : rp.nz;
     const int R = min(zl ? rp.rz : rp.rx, rp.npass - 1);
     const int k = (int)(zl ? (row - rp.zbase) % rp.nzc : row % rp.nz);
-    double v = 0.0;
+    Sums<N> v{};
     for (int e = 0; e <= R; ++e) {
         const float *pe = pp + (long)e * pass_off;
-        if (rp.fwd) {
-            const double t = sum_splits(pe, per, stride);
-            v += row_scale ? t / (double)row_scale[(long)e * rp.lines + row] : t;
-            continue;
-        }
-        for (int sg = e == 0 ? 1 : -1; sg <= 1; sg += 2) {
-            const int d = sg * e;
+        for (int sg = e == 0 || rp.fwd ? 1 : -1; sg <= 1; sg += 2) {
+            const int d = rp.fwd ? 0 : sg * e;
             if (k + d < 0 || k + d >= nline) continue;
-            const double t = sum_splits(pe + (long)d * rp.pitch, per, stride);
-            v += row_scale ? t / (double)row_scale[row + d] : t;
+            const Sums<N> t = sum_splits<N>(pe + (long)d * rp.pitch, per, stride);
+            const float *sc = row_scale ? row_scale + (rp.fwd ? (long)e * rp.lines + row : row + d) : nullptr;
+#pragma unroll
+            for (int i = 0; i < N; ++i) v.v[i] += sc ? t.v[i] / (double)*sc : t.v[i];
         }
     }
     return v;
 }
 
 // out[row][c] = sign * sum_s part[s][row][c] * col_scale[c] / row_scale[row] (+ b_sub);
-// bcol (factored stage): column c = 2 j + part of bin j is column bcol[j] + part of part
+// bcol (factored stage): column c = 2 j + part of bin j is column bcol[j] + part of part.
+// N = 2: a bin's both parts a thread (out and b_sub 8-byte aligned), else one
+// value.  I: the element index's type, 32 bits where it fits -- with 64-bit
+// divisions and single values a 256 x 256 x 128 scan's 5 million values took
+// 21 us, the bytes 10.
+template <int N, class I>
 __global__ __launch_bounds__(kThreads) void reduce_fwd_kernel(long rows, int nb2, int nbp2, int nparts,
                                                                long part_stride, const float *__restrict__ part,
                                                                const float *__restrict__ row_scale,
@@ -106,20 +134,28 @@ __global__ __launch_bounds__(kThreads) void reduce_fwd_kernel(long rows, int nb2
                                                                double *norm_parts, RowPasses rp,
                                                                const int *__restrict__ bcol)
 {
+    typedef typename Words<N>::type W;
     __shared__ double red[kThreads / 64];
-    const long n = rows * nb2;
+    const I n = (I)(rows * nb2 / N), per = (I)(nb2 / N);
     double sq = 0.0;
-    for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads) {
-        const long row = idx / nb2;
-        const int c = (int)(idx - row * nb2);
+    for (I idx = (I)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (I)gridDim.x * kThreads) {
+        const I row = idx / per;
+        const int c = N * (int)(idx - row * per);
         const int pc = bcol ? bcol[c >> 1] + (c & 1) : c;
-        const double v0 = sum_unscaled(part + row * nbp2 + pc, nparts, part_stride, row, row_scale, rp);
-        double v = v0 * scale;
-        if (col_scale) v *= (double)col_scale[c];
-        if (b_sub) v = (double)b_sub[idx] - v;
-        const float o = (float)v;
-        out[idx] = o;
-        sq += (double)o * (double)o;
+        const Sums<N> v0 = sum_unscaled<N>(part + (long)row * nbp2 + pc, nparts, part_stride, row, row_scale, rp);
+        W bs = {}, o;
+        if (b_sub) bs = reinterpret_cast<const W *>(b_sub)[idx];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            double v = v0.v[i] * scale;
+            if (col_scale) v *= (double)col_scale[c + i];
+            if (b_sub) v = (double)word<N>(bs, i) - v;
+            const float f = (float)v;
+            if constexpr (N == 1) o = f;
+            else o[i] = f;
+            sq += (double)f * (double)f;
+        }
+        reinterpret_cast<W *>(out)[idx] = o;
     }
     if (norm_parts) {
         const double t = block_sum(sq, red);
@@ -127,24 +163,31 @@ __global__ __launch_bounds__(kThreads) void reduce_fwd_kernel(long rows, int nb2
     }
 }
 
-// out[row][p] = scale * sum_s part[s][row][p] / row_scale[row]   (p < nu)
+// out[row][p] = scale * sum_s part[s][row][p] / row_scale[row]   (p < nu),
+// N values a thread (out and its rows 4 N bytes aligned)
+template <int N, class I>
 __global__ __launch_bounds__(kThreads) void reduce_lines_kernel(long rows, int nu, int nup, int out_stride,
                                                                  int nparts, long part_stride,
                                                                  const float *__restrict__ part,
                                                                  const float *__restrict__ row_scale, double scale,
                                                                  float *out, RowPasses rp)
 {
-    const long n = rows * out_stride;
-    for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads) {
-        const long row = idx / out_stride;
-        const int p = (int)(idx - row * out_stride);
-        float o = 0.f;
+    typedef typename Words<N>::type W;
+    const I n = (I)(rows * out_stride / N), per = (I)(out_stride / N);
+    for (I idx = (I)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (I)gridDim.x * kThreads) {
+        const I row = idx / per;
+        const int p = N * (int)(idx - row * per);
+        W o = {};
         if (p < nu) {
-            double v = sum_unscaled(part + row * nup + p, nparts, part_stride, row, row_scale, rp);
-            v *= scale;
-            o = (float)v;
+            const Sums<N> v = sum_unscaled<N>(part + (long)row * nup + p, nparts, part_stride, row, row_scale, rp);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const float f = p + i < nu ? (float)(v.v[i] * scale) : 0.f;
+                if constexpr (N == 1) o = f;
+                else o[i] = f;
+            }
         }
-        out[idx] = o;
+        reinterpret_cast<W *>(out)[idx] = o;
     }
 }
 
@@ -209,8 +252,8 @@ __global__ __launch_bounds__(kThreads) void lines16_kernel(long rows, int nu, in
             if (lines_in) {
                 o = lines_in[row * nup + p];
             } else {
-                const double t = sum_unscaled(part + row * nup + p, nparts, part_stride, row, row_scale, rp);
-                o = (float)(t * scale);
+                const Sums<1> t = sum_unscaled<1>(part + row * nup + p, nparts, part_stride, row, row_scale, rp);
+                o = (float)(t.v[0] * scale);
             }
         }
         v[j] = o;
@@ -416,30 +459,47 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(float *dst, const float 
         dst[idx] = src[idx];
 }
 
+// scal[S_GAMMA] = sum of the step partials (and S_GAMMA0 on the first step)
+__device__ __forceinline__ void step_norm(double *scal, const double *parts, int n, int first, double *red)
+{
+    const double t = sum_parts(parts, n, red);
+    if (threadIdx.x == 0) {
+        scal[S_GAMMA] = t;
+        if (first) scal[S_GAMMA0] = t;
+        if (!isfinite(t)) scal[S_BAD] = 1.0;
+    }
+    __syncthreads();
+}
+
 // One step of the paper's iteration (eq. iters) after g = A^T (b - A y):
 //   x_new = P(y + tau g - tau lambda T^T T y),  P = clamp at 0 when nonneg
 //   y_new = x_new + beta (x_new - x)            (the next momentum point)
 // T^T T y is the 7-point finite-difference Laplacian with no term across the
 // volume boundary (fd = 1) or y itself (fd = 0).  y_new may alias g: every
 // thread reads g only at its own voxel before writing y_new there.  A block
-// partial of |x_new - y|^2 (the step) goes to parts.
+// partial of |x_new - y|^2 (the step) goes to parts; block 0 also adds the
+// previous step's (prev, nprev of them; first: that was the first step), in
+// place of a launch of its own.
+template <class I>      // the voxel index's type: 32 bits where it fits (its divisions: 13.5 us of 128 x 128 x 64 in 64)
 __global__ __launch_bounds__(kThreads) void momentum_kernel(const float *__restrict__ y, const float *g,
                                                              const float *__restrict__ x, float *__restrict__ x_new,
                                                              float *y_new, int nx, int ny, int nz, float tau,
                                                              float taulam, float beta, int fd, int nonneg,
-                                                             double *parts)
+                                                             double *parts, double *scal, const double *prev,
+                                                             int nprev, int first)
 {
     __shared__ double red[kThreads / 64];
-    const long n = (long)nx * ny * nz;
-    const long sxy = (long)nx * ny;
+    if (nprev > 0 && blockIdx.x == 0) step_norm(scal, prev, nprev, first, red);
+    const I n = (I)nx * ny * nz;
+    const I sxy = (I)nx * ny;
     double sq = 0.0;
-    for (long idx = (long)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (long)gridDim.x * kThreads) {
+    for (I idx = (I)blockIdx.x * kThreads + threadIdx.x; idx < n; idx += (I)gridDim.x * kThreads) {
         const float yc = y[idx];
         float ty = yc;
         if (fd) {
-            const int i = (int)(idx % nx);
-            const int j = (int)((idx / nx) % ny);
-            const int k = (int)(idx / sxy);
+            const I line = idx / (I)nx;
+            const int i = (int)(idx - line * (I)nx);
+            const int k = (int)(line / (I)ny), j = (int)(line - (I)k * (I)ny);
             float acc = 0.f;
             if (i > 0) acc += yc - y[idx - 1];
             if (i + 1 < nx) acc += yc - y[idx + 1];
@@ -461,16 +521,10 @@ __global__ __launch_bounds__(kThreads) void momentum_kernel(const float *__restr
     if (threadIdx.x == 0) parts[blockIdx.x] = t;
 }
 
-// scal[S_GAMMA] = sum of the step partials (and S_GAMMA0 on the first step)
 __global__ __launch_bounds__(kThreads) void step_norm_kernel(double *scal, const double *parts, int n, int first)
 {
     __shared__ double red[kThreads / 64];
-    const double t = sum_parts(parts, n, red);
-    if (threadIdx.x == 0) {
-        scal[S_GAMMA] = t;
-        if (first) scal[S_GAMMA0] = t;
-        if (!isfinite(t)) scal[S_BAD] = 1.0;
-    }
+    step_norm(scal, parts, n, first, red);
 }
 
 // Power iteration on A^T A: norms[k] = |z| from the partials of |z|^2.
@@ -517,10 +571,16 @@ hipError_t launch_reduce_fwd(long rows, int nb2, int nbp2, int nparts, long part
                              float *out, double *norm_parts, int *nnorm, hipStream_t st, RowPasses rp,
                              const int *bcol)
 {
-    const int g = grid_for(rows * nb2, kReduceBlocks);
+    // (wide words where they leave a block a CU: A^T A of a 32^3 scan with 8
+    // angles 58.0 us with them, 57.3 without)
+    const bool two = rows * nb2 >= 2 * 256 * kThreads && (uintptr_t)out % 8 == 0 && (uintptr_t)b_sub % 8 == 0 && nb2 % 2 == 0 && nbp2 % 2 == 0;
+    const bool i32 = rows * nb2 < 0x70000000l;      // (and a grid's stride past it)
+    const int g = grid_for(two ? rows * nb2 / 2 : rows * nb2, kReduceBlocks);
     if (nnorm) *nnorm = g;
-    hipLaunchKernelGGL(reduce_fwd_kernel, dim3(g), dim3(kThreads), 0, st, rows, nb2, nbp2, nparts, part_stride,
-                       part, row_scale, col_scale, scale, b_sub, out, norm_parts, rp, bcol);
+    const auto k = two ? i32 ? reduce_fwd_kernel<2, unsigned> : reduce_fwd_kernel<2, long>
+                       : i32 ? reduce_fwd_kernel<1, unsigned> : reduce_fwd_kernel<1, long>;
+    hipLaunchKernelGGL(k, dim3(g), dim3(kThreads), 0, st, rows, nb2, nbp2, nparts, part_stride, part, row_scale,
+                       col_scale, scale, b_sub, out, norm_parts, rp, bcol);
     return hipGetLastError();
 }
 
@@ -528,9 +588,13 @@ hipError_t launch_reduce_lines_strided(long rows, int nu, int nup, int out_strid
                                        const float *part, const float *row_scale, double scale, float *out,
                                        hipStream_t st, RowPasses rp)
 {
-    const int g = grid_for(rows * out_stride, kReduceBlocks);
-    hipLaunchKernelGGL(reduce_lines_kernel, dim3(g), dim3(kThreads), 0, st, rows, nu, nup, out_stride, nparts,
-                       part_stride, part, row_scale, scale, out, rp);
+    const bool four = rows * out_stride >= 4 * 256 * kThreads && (uintptr_t)out % 16 == 0 && out_stride % 4 == 0;
+    const bool i32 = rows * out_stride < 0x70000000l;
+    const int g = grid_for(four ? rows * out_stride / 4 : rows * out_stride, kReduceBlocks);
+    const auto k = four ? i32 ? reduce_lines_kernel<4, unsigned> : reduce_lines_kernel<4, long>
+                        : i32 ? reduce_lines_kernel<1, unsigned> : reduce_lines_kernel<1, long>;
+    hipLaunchKernelGGL(k, dim3(g), dim3(kThreads), 0, st, rows, nu, nup, out_stride, nparts, part_stride, part,
+                       row_scale, scale, out, rp);
     return hipGetLastError();
 }
 
@@ -629,13 +693,13 @@ hipError_t launch_add_to(float *x, const float *d, long n, int clamp, hipStream_
 
 hipError_t launch_momentum(const float *y, const float *g, const float *x, float *x_new, float *y_new, int nx,
                            int ny, int nz, float tau, float taulam, float beta, int fd, int nonneg, double *parts,
-                           int *nparts, hipStream_t st)
+                           int *nparts, double *scal, const double *prev, int nprev, int first, hipStream_t st)
 {
     const long n = (long)nx * ny * nz;
-    const int b = grid_for(n);
+    const int b = grid_for(n, kReduceBlocks);
     if (nparts) *nparts = b;
-    hipLaunchKernelGGL(momentum_kernel, dim3(b), dim3(kThreads), 0, st, y, g, x, x_new, y_new, nx, ny, nz, tau,
-                       taulam, beta, fd, nonneg, parts);
+    hipLaunchKernelGGL(n < 0x70000000l ? momentum_kernel<unsigned> : momentum_kernel<long>, dim3(b), dim3(kThreads), 0, st, y, g, x, x_new, y_new, nx, ny, nz, tau,
+                       taulam, beta, fd, nonneg, parts, scal, prev, nprev, first);
     return hipGetLastError();
 }
 

@@ -52,3 +52,26 @@ def test_recorded_scalars(name):
     assert np.array_equal(h[:, 2], h[:, 0] / h[:, 1])
     np.testing.assert_allclose(h[:-1, 3] * h[:-1, 0], h[1:, 0], rtol=1e-14)
     assert rep.gamma == pytest.approx(h[3, 3] * h[3, 0], rel=1e-14) and rep.gamma0 == h[0, 0]
+
+
+@pytest.mark.parametrize("nu,nz,M,rows", [(64, 5, 7, 0), (33, 3, 7, 0), (130, 4, 7, 0), (64, 6, 7, 2), (128, 90, 24, 0),
+                                          (126, 92, 24, 0), (64, 120, 36, 2)])
+def test_reductions_at_any_alignment(nu, nz, M, rows):
+    """Results at 4-, 8- and 16-byte aligned addresses, rows of whole and of broken vectors: the same bits."""
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    plan = Plan(nu, 20, nz, M, 2048, 2048 / 64 + 1 / 3, 2.0, 1, 15, 2, 1.0, psf_rows=rows)
+    gen = torch.Generator("cuda").manual_seed(5)
+    rho = torch.rand(plan.lines_shape, device="cuda", generator=gen)
+    y = plan.signal_fwd(rho)
+    ref = plan.signal_adj(y)
+    nl, nd = rho.numel(), 2 * y.numel()
+    for off in (1, 2, 3):
+        out = torch.full((nl + 8,), float("nan"), device="cuda")
+        assert torch.equal(plan.signal_adj(y, out=out[off:off + nl].view(plan.lines_shape)), ref)
+        assert torch.isnan(out[:off]).all() and torch.isnan(out[off + nl:]).all()
+        inp = torch.empty(nl + 8, device="cuda")[off:off + nl].view(plan.lines_shape).copy_(rho)
+        assert torch.equal(plan.signal_fwd(inp), y)
+    buf = torch.full((nd + 8,), float("nan"), device="cuda")
+    out = torch.view_as_complex(buf[2:2 + nd].view(*plan.data_shape, 2))
+    assert torch.equal(plan.signal_fwd(rho, out=out), y) and torch.isnan(buf[2 + nd:]).all()
