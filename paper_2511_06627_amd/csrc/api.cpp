@@ -533,6 +533,7 @@ static int gemm_signal(const mpi3d_plan *pl, bool fwd, const float *in, int ld_i
         g.n = r.n;
         g.m = fwd ? pl->nb2 : pl->nu;
         g.k = fwd ? pl->nu : pl->nb2;
+        g.mw = !fwd && r.beta == 0.f && ld_out == pl->nup ? pl->nup : g.m;
         g.batch = r.batch;
         g.in0 = r.in0;
         g.out0 = r.out0;
@@ -571,8 +572,6 @@ static int apply_forward(const mpi3d_plan *pl, int prec, const float *x, float *
 static int apply_adjoint(const mpi3d_plan *pl, int prec, const float *y, float *xo, const OpWs &w, hipStream_t st)
 {
     if (prec == MPI3D_PRECOMPOSED) {
-        // the pad columns n_u..n_up of the lines stay as the projection left them (zero)
-        TRY(launch_fill(w.rt, pl->L * pl->nup, 0.f, st));
         TRYRC(gemm_signal_adj(pl, y, w.rt, pl->nup, st));
         TRY(launch_backproject(pl, w.rt, xo, nullptr, 0.0, nullptr, nullptr, st));
         return MPI3D_OK;

@@ -75,3 +75,22 @@ def test_reductions_at_any_alignment(nu, nz, M, rows):
     buf = torch.full((nd + 8,), float("nan"), device="cuda")
     out = torch.view_as_complex(buf[2:2 + nd].view(*plan.data_shape, 2))
     assert torch.equal(plan.signal_fwd(rho, out=out), y) and torch.isnan(buf[2 + nd:]).all()
+
+
+@pytest.mark.parametrize("nu,kw", [(33, {}), (100, dict(raster_sweep=20.0)), (129, dict(psf_rows=2)), (64, {}),
+                                   (70, dict(drive_axes=2))])
+def test_precomposed_adjoint_pads(nu, kw):
+    """The precomposed adjoint's line padding is written, whatever the workspace held."""
+    import torch
+    from paper_2511_06627_amd.plan import Plan
+    plan = Plan(nu, 40, 9, 6, 2048, 2048 / 64 + 1 / 3, 2.0, 1, 15, 2, 1.0, precisions=("fp32", "precomposed"), **kw)
+    y = torch.view_as_complex(torch.randn(*plan.data_shape, 2, device="cuda",
+                                          generator=torch.Generator("cuda").manual_seed(6)))
+    out = []
+    for fill in (0, 255):
+        ws = plan.workspace()
+        ws.view(torch.uint8).fill_(fill)
+        out.append(plan.adjoint(y, precision="precomposed", ws=ws))
+    assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1])
+    want = plan.adjoint(y)
+    assert float((out[0] - want).norm() / want.norm()) <= 1e-5
