@@ -40,6 +40,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 FP32_PEAK_TFLOPS = 157.3
 FP16_PEAK_TFLOPS = 2500.0
+# FP32 products taken as three fp16 products each (hi + lo operands)
+SPLIT_PEAK_TFLOPS = FP16_PEAK_TFLOPS / 3
 
 
 def log(msg):
@@ -178,30 +180,43 @@ def signal_flops(cfg):
     return 2.0 * L * (cfg.n_u * cfg.n_t + 2 * cfg.n_bins * cfg.n_t)
 
 
+def fac_columns(cfg, plan):
+    """Real columns of the factored band DFT's phase sums: cos and sin of each
+    residue pair {r, C - r} of the kept bins mod C (the signal is real), of 0
+    and C / 2 the cosine alone."""
+    C = plan.dft_cycles
+    res = set()
+    for k in range(cfg.harm_lo, cfg.harm_hi + 1):
+        c = int(k * cfg.drive_cycles + 0.5)
+        res.update(min((c + d) % C, -(c + d) % C) for d in range(-cfg.half_band, cfg.half_band + 1))
+    return sum(1 if 2 * r % C == 0 else 2 for r in res)
+
+
 def fac_flops(cfg, plan, kernel):
     """Algorithmic flops of one launch of a kernel of the band DFT factored over
-    drive cycles (t = n1 + P n2, T = C P, R residues of the kept bins mod C),
-    real arithmetic over all L lines:
-      fac_fwd / fac_adj       2 L T (Nu + 2R): the PSF contraction and the
-                              C-point residue DFT (real signal, complex twiddles);
+    drive cycles (t = n1 + P n2, T = C P, S real columns of phase sums), real
+    arithmetic over all L lines, an fp32 product counted once (the kernels take
+    it as three fp16 products):
+      fac_fwd / fac_adj       2 L T (Nu + S): the PSF contraction and the
+                              C-point residue DFT;
       fac_fwd_out / fac_adj_in 8 L P nb: each bin's P-point complex sum."""
     L, T = cfg.n_lines, cfg.n_t
     P = T // plan.dft_cycles
     if kernel in ("fac_fwd", "fac_adj"):
-        return 2.0 * L * T * (cfg.n_u + 2 * plan.dft_residues)
+        return 2.0 * L * T * (cfg.n_u + fac_columns(cfg, plan))
     return 8.0 * L * P * cfg.n_bins
 
 
 def fac_bytes(cfg, plan, kernel):
     """Algorithmic HBM bytes of one launch of a factored band-DFT kernel: its
-    inputs and outputs once (lines 4 L Nu, phase sums 4 L P 2R, data 8 L nb)
-    and its tables once (PSF table 4 T Nu and residue twiddles 8 C R for the
+    inputs and outputs once (lines 4 L Nu, phase sums 4 L P S, data 8 L nb)
+    and its tables once (PSF table 4 T Nu and residue twiddles 4 C S for the
     contraction kernels; per-bin phase twiddles 8 P nb for the outer sums)."""
-    L, T, C, R = cfg.n_lines, cfg.n_t, plan.dft_cycles, plan.dft_residues
+    L, T, C, S = cfg.n_lines, cfg.n_t, plan.dft_cycles, fac_columns(cfg, plan)
     P = T // C
-    phase = 4.0 * L * P * 2 * R
+    phase = 4.0 * L * P * S
     if kernel in ("fac_fwd", "fac_adj"):
-        return 4.0 * L * cfg.n_u + phase + 4.0 * T * cfg.n_u + 8.0 * C * R
+        return 4.0 * L * cfg.n_u + phase + 4.0 * T * cfg.n_u + 4.0 * C * S
     return phase + 8.0 * L * cfg.n_bins + 8.0 * P * cfg.n_bins
 
 
@@ -753,14 +768,16 @@ def operator_leg(torch, plan, cfg, x, b, warmup, steps, with_mixed=True):
         fd = fac_flops(cfg, plan, dom)
         achieved = fd / (kf[dom] * 1e-3) / 1e12
         out["roofline"] = {"bound": "mfma", "kernel": dom, "achieved": round(achieved, 2),
-                           "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / FP32_PEAK_TFLOPS, 4),
+                           "peak": round(SPLIT_PEAK_TFLOPS, 1), "unit": "TFLOP/s",
+                           "frac": round(achieved / SPLIT_PEAK_TFLOPS, 4),
+                           "products": "3 fp16 per fp32 product: peak = fp16 dense / 3",
                            "traffic": measured_traffic(cfg.name, dom), "flops_per_launch": fd,
                            "algorithmic_bytes_per_launch": fac_bytes(cfg, plan, dom)}
         for k in facs:
             fk = fac_flops(cfg, plan, k)
             a = fk / (kf[k] * 1e-3) / 1e12
             kernels[k] = {"ms": round(kf[k], 4), "flops": fk, "tflops": round(a, 2),
-                          "mfma_frac": round(a / FP32_PEAK_TFLOPS, 4),
+                          "mfma_frac": round(a / SPLIT_PEAK_TFLOPS, 4),
                           "hbm_bytes_measured": measured_traffic(cfg.name, k),
                           "hbm_bytes_algorithmic": fac_bytes(cfg, plan, k)}
         stage = {"signal_fwd": ("fac_fwd", "fac_fwd_out"), "signal_adj": ("fac_adj_in", "fac_adj")}
@@ -817,8 +834,10 @@ def operator_leg(torch, plan, cfg, x, b, warmup, steps, with_mixed=True):
 # ---------------------------------------------------------------------------
 KERNEL_KEYS = (("fac_fwd_kernel", "fac_fwd"), ("fac_fwd_out_kernel", "fac_fwd_out"), ("fac_adj_in_kernel", "fac_adj_in"),
                ("fac_adj_kernel", "fac_adj"),
-               ("sig_fwd_f32", "signal_fwd"), ("sig_adj_f32", "signal_adj"), ("sig_fwd_f16", "signal_fwd_mixed"),
+               ("sig_fwd_f32", "signal_fwd"), ("sig_adj_f32", "signal_adj"), ("split_fwd_kernel", "signal_fwd"),
+               ("split_adj_kernel", "signal_adj"), ("sig_fwd_f16", "signal_fwd_mixed"),
                ("sig_adj_f16", "signal_adj_mixed"), ("proj_fwd_kernel<unsigned int>", "project_mixed"),
+               ("proj_fwd_band_kernel<float>", "project"), ("proj_fwd_band_kernel", "project_mixed"),
                ("proj_fwd_kernel", "project"), ("proj_adj_f16", "backproject_mixed"),
                ("proj_adj_kernel", "backproject"))
 

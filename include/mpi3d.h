@@ -68,13 +68,14 @@ enum {
     MPI3D_ENONFINITE = -5  /* a solver norm became NaN or infinite */
 };
 
-/* Operator precision.  FP32: projection in fp32, signal contractions on fp32
- * MFMA; with one PSF table and one line group the plan may factor the band
- * DFT over drive cycles (Appendix A's sum regrouped exactly over t = n1 + P n2,
- * T = C P: a C-point DFT at the residues of the kept bins mod C, then a P-point
- * sum per bin; mpi3d_plan_info.dft_cycles), when that needs less MFMA work --
- * the same operator with the sums in another order.  MIXED: the projection gathers a bf16 copy of the volume, the
- * backprojection fp16 lines with a power-of-two scale per line, and the
+/* Operator precision.  FP32: projection in fp32, signal contractions with fp32
+ * sums of fp32 products -- taken on the fp32 matrix unit, or as three products
+ * of fp16 pairs (hi + lo, errors against FP64 as small).  The plan may factor
+ * the band DFT over drive cycles (Appendix A's sum regrouped exactly over
+ * t = n1 + P n2, T = C P: a C-point DFT at the residues of the kept bins mod C,
+ * then a P-point sum per bin; mpi3d_plan_info.dft_cycles), when that needs less
+ * time -- the same operator with the sums in another order.  MIXED: the
+ * projection gathers the volume's values rounded to bf16, the backprojection fp16 lines with a power-of-two scale per line, and the
  * signal contractions run on fp16 MFMA with fp32 accumulation, per-line
  * power-of-two scaling and per-harmonic-band scaling.  PRECOMPOSED:
  * the lines of one PSF table share one trajectory, so A_DC = S D_Gamma F V E H B
@@ -346,6 +347,7 @@ void mpi3d_state_destroy(mpi3d_state *state);
  *             (MIXED, kernels 2 and 3: the per-line scales and fp16 operand
  *             lines are prepared once, outside the timed launches)
  *   kernels 4-7, FP32 plans with dft_cycles > 0 only (else MPI3D_EINVAL):
+ *             (a raster or two drive axes: those of the first line group)
  *   kernel 4  forward PSF contraction + C-point residue DFT (writes the
  *             workspace's phase sums)
  *   kernel 5  forward P-point outer sum per bin (reads the phase sums)
