@@ -129,6 +129,24 @@ __device__ __forceinline__ f32x16 pair_sum(float *xs, int parity, int pair, int 
     return r;
 }
 
+// N result tiles' rows row0 + 8 (j / 4) + j % 4 to lines of `pitch` floats, a row
+// at a time: one branch a row, not one a value (with the line loads left
+// unguarded and the first tile waiting for its own slice alone: fp16 forward at
+// 128 x 128 x 64, 24 angles 23.9 -> 21.7 us, at 192 x 192 x 96, 36 62 -> 60).
+template <int N>
+__device__ __forceinline__ void store_rows(const SigJob &job, int row0, int pitch, float *out, const f32x16 (&v)[N])
+{
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int row = row0 + 8 * (j / 4) + j % 4;
+        if (row < job.rows) {
+            float *o = out + (size_t)job_line(job, row) * pitch;
+#pragma unroll
+            for (int g = 0; g < N; ++g) o[g * 32] = v[g][j];
+        }
+    }
+}
+
 // bf16 bits of v, rounded to nearest even
 __device__ __forceinline__ uint16_t bf16_bits(float v)
 {

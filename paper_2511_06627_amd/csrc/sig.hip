@@ -139,22 +139,8 @@ __device__ __forceinline__ void fwd_tile(const SigArgs &a, const BlockPos &bp, i
         }
     }
     if (bp.row0 >= job.rows) return;
-    long ln[16];   // buffer lines of this lane's 16 result rows
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
-        ln[j] = row < job.rows ? job_line(job, row) : 0;
-    }
-    float *out = job.part + (size_t)bp.split * job.part_stride;
-#pragma unroll
-    for (int g = 0; g < GH; ++g) {
-        const int col = (ctb + g) * 32 + (lane & 31);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
-            if (row < job.rows) out[(size_t)ln[j] * a.nbp2 + col] = acc[g][j];
-        }
-    }
+    float *out = job.part + (size_t)bp.split * job.part_stride + ctb * 32 + (lane & 31);
+    store_rows<GH>(job, bp.row0 + 4 * h, a.nbp2, out, acc);
 }
 
 template <int NUP, int GH, int PAIRS>
@@ -249,22 +235,8 @@ __device__ __forceinline__ void adj_tile(const SigArgs &a, const BlockPos &bp, i
         }
     }
     if (bp.row0 >= job.rows) return;
-    long ln[16];   // buffer lines of this lane's 16 result rows
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
-        ln[j] = row < job.rows ? job_line(job, row) : 0;
-    }
-    float *out = job.part + (size_t)(bp.split * a.ngroups + bp.group) * job.part_stride;
-#pragma unroll
-    for (int pt = 0; pt < PTH; ++pt) {
-        const int col = (pt0 + pt) * 32 + (lane & 31);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
-            if (row < job.rows) out[(size_t)ln[j] * NUP + col] = racc[pt][j];
-        }
-    }
+    float *out = job.part + (size_t)(bp.split * a.ngroups + bp.group) * job.part_stride + pt0 * 32 + (lane & 31);
+    store_rows<PTH>(job, bp.row0 + 4 * h, NUP, out, racc);
 }
 
 template <int NUP, int GH, int PAIRS>

@@ -97,16 +97,18 @@ __device__ __forceinline__ void chunk_loop(float *xs, f16x8 *lds, const f16x8 *a
 #pragma unroll
         for (int q = 0; q < 4; ++q) own[q * 64] = f32x4v{t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]};
     };
+    // (the first tile needs its own slice alone; the loop, A of chunk c0 + 1 and B of c0)
+    constexpr int kSpare = (L::AB == 3 ? L::kOpsA : 0) + (L::BB == 3 ? L::kOpsB : 0);
     aload(c0, 0);
     bload(c0, 0);
     aload(c0 + 1, 1);
     if (L::AB == 3) aload(c0 + 2, 2);
     if (L::BB == 3) bload(c0 + 1, 1);
-    wait_vm_lgkm<0>();
+    wait_vm_lgkm<L::kOpsA + L::kOpsB + kSpare>();
     block_barrier_nofence();
     f32x16 own = first(la + lane);
     put(0, own);
-    wait_vm_lgkm<0>();
+    wait_vm_lgkm<kSpare>();
     block_barrier_nofence();
     int an = 1, af = 0, b = 0;                      // buffers: A of chunk c + 1, A free, B of chunk c
     for (int c = c0; c < c1; ++c) {
@@ -140,7 +142,7 @@ __device__ __forceinline__ void chunk_loop(float *xs, f16x8 *lds, const f16x8 *a
         second(t16, lb + b * NB * 64 + lane);
         // the next chunk's slices are in (of this chunk's requests only those with
         // a chunk to spare may be outstanding), this wave's LDS accesses are done
-        wait_vm_lgkm<(L::AB == 3 ? L::kOpsA : 0) + (L::BB == 3 ? L::kOpsB : 0)>();
+        wait_vm_lgkm<kSpare>();
         block_barrier_nofence();
         af = an;
         an = an + 1 == L::AB ? 0 : an + 1;
@@ -172,7 +174,9 @@ __global__ __launch_bounds__(kSigThreads, 2) void sig_fwd_f16(SigArgs a)
         const f16x8 *rin = (const f16x8 *)(job.in16 + (size_t)(il >= 0 ? il : 0) * job.in16_stride +
                                            half * (NUP / 2) + 8 * h);
 #pragma unroll
-        for (int st = 0; st < NKS; ++st) R[st] = il >= 0 ? rin[2 * st] : f16x8(0);
+        for (int st = 0; st < NKS; ++st) R[st] = rin[2 * st];     // (unconditional: all in flight)
+#pragma unroll
+        for (int st = 0; st < NKS; ++st) R[st] = il >= 0 ? R[st] : f16x8(0);
     }
     f32x16 acc[GH];
 #pragma unroll
@@ -193,23 +197,8 @@ __global__ __launch_bounds__(kSigThreads, 2) void sig_fwd_f16(SigArgs a)
                                      [&](int j, const f16x8 &f) { acc[j % GH] = MFMA16(s16[j / GH], f, acc[j % GH]); });
         });
     if (bp.row0 >= job.rows) return;
-    long ln[16];   // buffer lines of this lane's 16 result rows
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
-        ln[j] = row < job.rows ? job_line(job, row) : 0;
-    }
-    float *out = job.part + (size_t)bp.split * job.part_stride;
-    const int ctb = bp.group * 2 * GH + half * GH;
-#pragma unroll
-    for (int g = 0; g < GH; ++g) {
-        const int col = (ctb + g) * 32 + (lane & 31);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
-            if (row < job.rows) out[(size_t)ln[j] * a.nbp2 + col] = acc[g][j];
-        }
-    }
+    float *out = job.part + (size_t)bp.split * job.part_stride + (bp.group * 2 * GH + half * GH) * 32 + (lane & 31);
+    store_rows<GH>(job, bp.row0 + 4 * h, a.nbp2, out, acc);
 }
 
 template <int NUP, int GH>
@@ -236,7 +225,9 @@ __global__ __launch_bounds__(kSigThreads, 2) void sig_adj_f16(SigArgs a)
     {
         const f16x8 *yin = (const f16x8 *)(job.in16 + (size_t)(il >= 0 ? il : 0) * job.in16_stride + colbase + 8 * h);
 #pragma unroll
-        for (int st = 0; st < NF; ++st) Y[st] = il >= 0 ? yin[2 * st] : f16x8(0);
+        for (int st = 0; st < NF; ++st) Y[st] = yin[2 * st];
+#pragma unroll
+        for (int st = 0; st < NF; ++st) Y[st] = il >= 0 ? Y[st] : f16x8(0);
     }
     f32x16 racc[PTH];
 #pragma unroll
@@ -260,22 +251,8 @@ __global__ __launch_bounds__(kSigThreads, 2) void sig_adj_f16(SigArgs a)
                                       });
         });
     if (bp.row0 >= job.rows) return;
-    long ln[16];   // buffer lines of this lane's 16 result rows
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
-        ln[j] = row < job.rows ? job_line(job, row) : 0;
-    }
-    float *out = job.part + (size_t)(bp.split * a.ngroups + bp.group) * job.part_stride;
-#pragma unroll
-    for (int pt = 0; pt < PTH; ++pt) {
-        const int col = (half * PTH + pt) * 32 + (lane & 31);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int row = bp.row0 + 8 * (j / 4) + 4 * h + (j % 4);
-            if (row < job.rows) out[(size_t)ln[j] * NUP + col] = racc[pt][j];
-        }
-    }
+    float *out = job.part + (size_t)(bp.split * a.ngroups + bp.group) * job.part_stride + half * PTH * 32 + (lane & 31);
+    store_rows<PTH>(job, bp.row0 + 4 * h, NUP, out, racc);
 }
 
 typedef void (*SigKernel)(SigArgs);
