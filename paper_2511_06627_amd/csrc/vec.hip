@@ -2,7 +2,7 @@
 //
 // Every float64 norm is formed the same way: each block sums its elements'
 // squares in float64 (fixed per-thread order, then a fixed tree), writes one
-// partial, and a single-block scalar kernel adds the partials in index
+// partial, and whichever kernel needs the norm adds the partials in one fixed
 // order.  Results therefore do not depend on timing, and the CGLS scalars
 // (Sec. 3.3 solve of eq. nummodel; see the header for the recurrences) stay
 // on the device: no host round trip per iteration.
