@@ -154,7 +154,7 @@ static FacArgs fac_args(const LineJob &lj, int gi, bool fwd)
     a.job.map_off = lg.off;
     a.job.map_step = lg.step;
     a.ef = f.ef; a.ea = f.ea; a.wf = f.wf; a.wa = f.wa;
-    a.unit0 = f.unit0; a.qbin = f.qbin;
+    a.unit0 = f.unit0; a.qbin = f.qbin; a.wexp = f.wexp;
     a.y = lj.w->fac;
     a.lexp = lj.w->lexp;
     a.ylines = (lg.rows + 31) / 32 * 32;
@@ -166,7 +166,7 @@ static FacArgs fac_args(const LineJob &lj, int gi, bool fwd)
     a.fwd_part_stride = pj->L * 32 * f.U;
     a.tiles = (lg.rows + 31) / 32;
     a.s_scale = f.s_scale; a.g_scale = f.g_scale; a.y_scale = f.y_scale; a.z_scale = f.z_scale;
-    a.y_exp = f.y_exp; a.z_exp = f.z_exp; a.w_exp = f.w_exp; a.r_exp = f.r_exp;
+    a.y_exp = f.y_exp; a.z_exp = f.z_exp; a.r_exp = f.r_exp;
     return a;
 }
 
@@ -205,6 +205,7 @@ static SplitArgs split_args(const LineJob &lj, bool fwd)
     a.nsplit = d.nsplit; a.ngroups = d.ngroups;
     a.s_scale = fwd ? s.s_scale : s.g_scale;
     a.out_exp = fwd ? s.fwd_exp : s.adj_exp;
+    a.cexp = fwd ? s.fexp : s.aexp;
     return a;
 }
 

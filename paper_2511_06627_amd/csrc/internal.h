@@ -72,7 +72,8 @@ __host__ __device__ inline long job_line(const SigJob &j, int r)
 // The dense FP32 signal stage on fp16 pairs (FP32 plans without the mixed
 // operator, no tensor PSF, T no multiple of 32 or otherwise not factored):
 // both contractions as three fp16 products each, lines scaled by a power of
-// two each, tables by one for all.
+// two each, the PSF tables by one for all, the band tables by one a column (a
+// bin behind a weak receive filter keeps its bits).
 struct SplitArgs {
     SigJob jobs[2];          // line groups: kf16 / ka16 are their split PSF tables, tile0 their first block tile
     int njobs, config;       // config: see split_config
@@ -82,7 +83,10 @@ struct SplitArgs {
     int pitch;
     int nu, nup, nb2, nct, nchunks, nsplit, ngroups, tgroups;
     float s_scale;           // the time tile's scale before it is split again
-    int out_exp;             // power of two of the results above a line's own
+    int out_exp;             // power of two of the results above a line's own (forward: and above
+                             // their column's)
+    const int *cexp;         // [32 nct] forward: exponents of the band table's columns; adjoint: of the
+                             // power of two a column's data is taken by (null: all 0)
 };
 
 // The band DFT factored over drive cycles (FP32), one launch per line group
@@ -110,7 +114,9 @@ struct FacArgs {
     const __half *wf, *wa;   // outer sums, fragment pairs: forward per unit and 8-phase stage (B
                              // operand), adjoint per slot and 16-phase stage (A operand)
     const int *unit0;        // [R + 1] first unit of slot q
-    const int *qbin;         // [R][qmax] bins of slot q (-1: none)
+    const int *qbin;         // [R][qmax] bins of slot q: the bin in the low half (0xffff: none), in the
+                             // high half the exponent of the power of two its data is taken by
+    const int *wexp;         // [32 U] exponents of the forward table's columns
     uint32_t *y;             // phase sums Y or Z per 32-line tile, [P][yc][32 lines] (column 2 slot +
                              // cos/sin), words of split pairs; ylines = 32 tiles; then a spare row of
                              // P yc words taking the stores that carry nothing
@@ -133,9 +139,11 @@ struct FacArgs {
     // Power-of-two scales: of the time signal before its split (forward,
     // adjoint), of Y and Z before theirs.  A line of Y holds Y 2^lexp (lexp: the
     // line's exponent + y_exp), of Z likewise (+ z_exp); the forward's partial
-    // sums are results 2^-(lexp + w_exp), the adjoint's 2^-(lexp + r_exp).
+    // sums are results 2^-(lexp + wexp of the column), the adjoint's 2^-(lexp +
+    // r_exp).  The outer tables hold each bin's weights by a power of two of its
+    // own, so a bin behind a weak receive filter keeps its bits.
     float s_scale, g_scale, y_scale, z_scale;
-    int y_exp, z_exp, w_exp, r_exp;
+    int y_exp, z_exp, r_exp;
 };
 
 struct SigArgs {
@@ -232,11 +240,11 @@ struct mpi3d_plan {
         int C, P, cj, R, zst, U, qmax, nsplit, nsplit_adj, psplit, zsplit, nzstage;
         int res;                  // distinct residues of the kept bins mod C
         float s_scale, g_scale, y_scale, z_scale;
-        int y_exp, z_exp, w_exp, r_exp;
+        int y_exp, z_exp, r_exp;
         long max_rows;            // lines of the largest line group
         long k_stride;            // halves between the line groups' tables in kf and in ka
         __half *kf, *ka, *ef, *ea, *wf, *wa;
-        int *unit0, *qbin;
+        int *unit0, *qbin, *wexp;
         int *bcol;                // [nb] column of bin j's real part in the forward's partial sums
     } fac;
     // dense FP32 signal stage on fp16 pairs (see SplitArgs): chosen at plan time
@@ -250,6 +258,7 @@ struct mpi3d_plan {
         float s_scale, g_scale;
         int fwd_exp, adj_exp;
         __half *kf, *ka, *ff, *fa;
+        int *fexp, *aexp;         // [32 nct]; aexp null where all bins share one exponent
     } split;
     uint64_t line_key;             // equal keys <=> identical line tables
     // projection configuration

@@ -114,6 +114,28 @@ inline void half_pair(double v, uint16_t &hi, uint16_t &lo)
     lo = half_bits(v - h, &l);
 }
 
+// |D_j| of the receive filter (null: 1).
+double bin_gain(const float *rx, int j) { return rx ? std::hypot((double)rx[2 * j], (double)rx[2 * j + 1]) : 1.0; }
+
+// Exponents e_j with |D_j| scale 2^e_j in [2^14, 2^15) for bins j < nb, and the
+// smallest of them (the strongest bin's).  A bin with D_j = 0 gets a large one:
+// its data then drops out of an adjoint's lines.
+std::vector<int> bin_exponents(const float *rx, int nb, double scale, int *least)
+{
+    constexpr int kNone = 5000;
+    std::vector<int> ex(nb, kNone);
+    *least = kNone;
+    for (int j = 0; j < nb; ++j) {
+        const double d = bin_gain(rx, j) * scale;
+        if (!(d > 0)) continue;
+        int e = 0;
+        std::frexp(d * 1.0000001, &e);
+        ex[j] = 15 - e;
+        *least = std::min(*least, ex[j]);
+    }
+    return ex;
+}
+
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
@@ -649,7 +671,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     // sine) share another.  Taken when its time per line, by the rates below,
     // is under the dense form's; C minimises it.
     std::vector<uint16_t> fkf, fka, fef, fea, fwf, fwa;   // fp16 bits
-    std::vector<int> funit0, fubin, fqbin, fbcol;
+    std::vector<int> funit0, fubin, fqbin, fbcol, fwexp;
     // A plan that also holds the mixed operator takes it only where the bins'
     // residues bunch (at most 24 distinct): its refinement sweeps start from
     // the FP32 operator, and their inner iterations blow a difference in its
@@ -747,10 +769,9 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             const int QM = f.qmax;
             qb.resize(f.R);
             for (int j = 0; j < NB; ++j) qb[slot[slot_of(bins[j] % bestC, bestC)]].push_back(j);
-            fqbin.assign((size_t)f.R * QM, -1);
+            fqbin.assign((size_t)f.R * QM, 0xffff);   // (bins: below, with their exponents)
             fbcol.assign(NB, 0);
             for (int q = 0; q < f.R; ++q) {
-                for (size_t i = 0; i < qb[q].size(); ++i) fqbin[(size_t)q * QM + i] = qb[q][i];
                 funit0.push_back((int)fubin.size() / 16);
                 for (size_t i = 0; i < qb[q].size(); ++i) fbcol[qb[q][i]] = 2 * ((int)fubin.size() + (int)i);
                 for (size_t i0 = 0; i0 < qb[q].size(); i0 += 16)
@@ -936,28 +957,28 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                 const double sg = 2 * r < C ? 1.0 : -1.0;
                 return cb == 0 ? -sg * gi : sg * gr;
             };
-            // outer tables scaled by 2^wexp so that no weight exceeds 2^15; the
-            // adjoint's sums over a slot's bins are below 2^zsum of that
-            double wmax = 0, gsum = 0;
+            // outer tables: bin j's weights by 2^wex[j], which brings the largest
+            // possible one (|D_j| / sqrt(T)) into [2^14, 2^15).  The forward undoes
+            // it per column; the adjoint takes bin j's data by 2^(wref - wex[j])
+            // (qbin), and its sums over a slot's bins are below 2^zsum
+            int wref = 0, zsum = 0;
+            const std::vector<int> wex = bin_exponents(g->rx_filter, NB, inv, &wref);
+            double gsum = 0;
             for (int q = 0; q < f.R; ++q) {
                 double sum = 0;
-                for (int j : qb[q]) {
-                    double d = 1.0;
-                    if (g->rx_filter) d = std::hypot((double)g->rx_filter[2 * j], (double)g->rx_filter[2 * j + 1]);
-                    wmax = std::max(wmax, d * inv);
-                    sum += 1.4142136 * d * inv;      // |re| + |im| of a weight
+                for (size_t i = 0; i < qb[q].size(); ++i) {
+                    const int j = qb[q][i];
+                    sum += 1.4142136 * std::ldexp(bin_gain(g->rx_filter, j) * inv, wex[j]);   // |re| + |im| of a weight
+                    fqbin[(size_t)q * QM + i] = (int)((unsigned)(wref - wex[j]) << 16 | (unsigned)j);
                 }
                 gsum = std::max(gsum, sum);
             }
-            int wexp = 0, zsum = 0;
-            if (wmax > 0) {
-                std::frexp(wmax * 1.0000001, &wexp);
-                wexp = 15 - wexp;
-                std::frexp(std::ldexp(gsum, wexp), &zsum);
-            }
-            f.w_exp = wexp;
+            if (gsum > 0) std::frexp(gsum, &zsum);
             f.z_scale = (float)std::ldexp(1.0, -zsum);
-            f.z_exp = wexp - zsum;
+            f.z_exp = wref - zsum;
+            fwexp.assign((size_t)32 * f.U, 0);
+            for (int c = 0; c < 32 * f.U; ++c)
+                if (fubin[c / 2] >= 0) fwexp[c] = wex[fubin[c / 2]];
             // forward outer B operand [unit][8-phase stage][hi, lo]: k = (column of
             // Y = l / 32, phase 8 stg + e), column l % 32 = (bin of the unit, re/im)
             const int nst8 = (P + 7) / 8;
@@ -968,7 +989,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                         const int col = l % 32, jb = fubin[(size_t)u * 16 + col / 2];
                         if (jb < 0) continue;
                         const size_t o = (((size_t)u * nst8 + n1 / 8) * 2 * 64 + l) * 8 + n1 % 8;
-                        half_pair(std::ldexp(weight(jb, n1, l / 32, col % 2), wexp), fwf[o], fwf[o + 512]);
+                        half_pair(std::ldexp(weight(jb, n1, l / 32, col % 2), wex[jb]), fwf[o], fwf[o + 512]);
                     }
             // adjoint outer A operand [slot][16-phase stage][bin step][hi, lo]: row
             // l % 32 = (phase 16 stg + row / 2, column of Z = row % 2), k = (bin
@@ -979,12 +1000,12 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                     for (int ks = 0; ks < QM / 8; ++ks)
                         for (int l = 0; l < 64; ++l)
                             for (int e2 = 0; e2 < 8; ++e2) {
-                                const int jb = fqbin[(size_t)q * QM + 8 * ks + 4 * (l / 32) + e2 / 2];
+                                const int jb = (int16_t)fqbin[(size_t)q * QM + 8 * ks + 4 * (l / 32) + e2 / 2];
                                 const int n1 = 16 * stg + (l % 32) / 2;
                                 if (jb < 0 || n1 >= P) continue;
                                 const size_t o =
                                     ((((size_t)q * f.nzstage + stg) * (QM / 8) + ks) * 2 * 64 + l) * 8 + e2;
-                                half_pair(std::ldexp(weight(jb, n1, l % 2, e2 % 2), wexp), fwa[o], fwa[o + 512]);
+                                half_pair(std::ldexp(weight(jb, n1, l % 2, e2 % 2), wex[jb]), fwa[o], fwa[o + 512]);
                             }
         }
     }
@@ -1033,12 +1054,18 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     //  fa [column / 16]: F[time l % 32][column 16 ks + 8 (l / 32) + e]
     //  ka [time step][p / 32]: K[time 16 q + tp16(e, l / 32)][p = 32 pt + l % 32]
     std::vector<uint16_t> skf, ska, sff, sfa;
+    std::vector<int> sfexp, saexp;
     if (split) {
         mpi3d_plan::Split &sp = pl->split;
         auto tp16 = [](int e2, int h) { return 8 * (e2 / 4) + 4 * h + (e2 % 4); };
-        // tables scaled so their largest entries are in [2^14, 2^15); the time
-        // tiles of lines below 2^15 kept below 2^15 by the largest row sums
-        double kmax = 0, ksum = 0, fmax = 0, fsum = 0;
+        // tables scaled so their largest entries (the band table's: a bin's) are in
+        // [2^14, 2^15); the time tiles of lines below 2^15 kept below 2^15 by the
+        // largest row sums
+        int fref = 0;
+        const std::vector<int> fex = bin_exponents(g->rx_filter, NB, 1.0 / std::sqrt((double)T), &fref);
+        std::vector<double> fsc(NB);
+        for (int j = 0; j < NB; ++j) fsc[j] = bin_gain(g->rx_filter, j) > 0 ? std::ldexp(1.0, fex[j]) : 0.0;
+        double kmax = 0, ksum = 0, fsum = 0;
         for (size_t n = 0; n < (size_t)n_ktab * T; ++n) {
             const double *row = &K[KE * (n / T) + n % T * NUP];
             double sum = 0;
@@ -1051,36 +1078,37 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         for (int n = 0; n < T; ++n) {
             double sum = 0;
             for (int c = 0; c < 2 * NB; ++c) {
-                const double v = std::fabs(F[(size_t)n * NBP2 + c]);
-                fmax = std::max(fmax, v);
-                sum += v;
+                sum += std::fabs(F[(size_t)n * NBP2 + c]) * fsc[c / 2];
             }
             fsum = std::max(fsum, sum);
         }
-        int kexp = 0, fexp = 0, s1 = 0, s2 = 0;
+        int kexp = 0, s1 = 0, s2 = 0;
         if (kmax > 0) {
             std::frexp(kmax, &kexp);
             kexp = 15 - kexp;
             std::frexp(std::ldexp(ksum, kexp), &s1);
         }
-        if (fmax > 0) {
-            std::frexp(fmax, &fexp);
-            fexp = 15 - fexp;
-            std::frexp(std::ldexp(fsum, fexp), &s2);
-        }
+        if (fsum > 0) std::frexp(fsum, &s2);
         sp.s_scale = (float)std::ldexp(1.0, -s1);
         sp.g_scale = (float)std::ldexp(1.0, -s2);
-        sp.fwd_exp = kexp - s1 + fexp;
-        sp.adj_exp = fexp - s2 + kexp;
+        sp.fwd_exp = kexp - s1;
+        sp.adj_exp = fref - s2 + kexp;
+        sfexp.assign((size_t)32 * sp.nct, 0);
+        saexp.assign((size_t)32 * sp.nct, 0);
+        for (int c = 0; c < 2 * NB; ++c) {
+            sfexp[c] = fex[c / 2];
+            saexp[c] = fref - fex[c / 2];
+        }
+        const double ksc = std::ldexp(1.0, kexp);
         // one chunk's 32 x n table as A fragments by row (time, 16 columns a
         // step) and by column (32 columns a tile, 16 times a step)
         std::vector<uint16_t> ph, plo;
-        auto pairs = [&](const double *src, size_t pitch, int n, int pad, double sc) {
+        auto pairs = [&](const double *src, size_t pitch, int n, int pad, auto scale) {
             ph.assign((size_t)32 * pad, 0);
             plo.assign((size_t)32 * pad, 0);
             for (int i = 0; i < 32; ++i)
                 for (int p = 0; p < n; ++p)
-                    half_pair(src[(size_t)i * pitch + p] * sc, ph[(size_t)i * pad + p], plo[(size_t)i * pad + p]);
+                    half_pair(src[(size_t)i * pitch + p] * scale(p), ph[(size_t)i * pad + p], plo[(size_t)i * pad + p]);
         };
         auto by_time = [&](uint16_t *dst, int pad) {
             for (int ks = 0; ks < pad / 16; ++ks)
@@ -1111,11 +1139,11 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         for (int c = 0; c < NC; ++c) {
             for (int tb = 0; tb < n_ktab; ++tb) {
                 const size_t o = 2 * KE * tb + (size_t)c * 64 * NUP;
-                pairs(&K[KE * tb + (size_t)32 * c * NUP], NUP, NUP, NUP, std::ldexp(1.0, kexp));
+                pairs(&K[KE * tb + (size_t)32 * c * NUP], NUP, NUP, NUP, [&](int) { return ksc; });
                 by_time(&skf[o], NUP);
                 by_column(&ska[o], NUP, 1, NUP / 32);
             }
-            pairs(&F[(size_t)32 * c * NBP2], NBP2, 2 * NB, CP, std::ldexp(1.0, fexp));
+            pairs(&F[(size_t)32 * c * NBP2], NBP2, 2 * NB, CP, [&](int p) { return fsc[p / 2]; });
             by_column(&sff[(size_t)c * 64 * CP], CP, 2, 1);
             by_time(&sfa[(size_t)c * 64 * CP], CP);
         }
@@ -1173,10 +1201,13 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
     const size_t o_funit0 = fac ? place(sizeof(int) * funit0.size()) : 0;
     const size_t o_fqbin = fac ? place(sizeof(int) * fqbin.size()) : 0;
     const size_t o_fbcol = fac ? place(sizeof(int) * fbcol.size()) : 0;
+    const size_t o_fwexp = fac ? place(sizeof(int) * fwexp.size()) : 0;
     const size_t o_skf = split ? place(sizeof(_Float16) * skf.size()) : 0;
     const size_t o_ska = split ? place(sizeof(_Float16) * ska.size()) : 0;
     const size_t o_sff = split ? place(sizeof(_Float16) * sff.size()) : 0;
     const size_t o_sfa = split ? place(sizeof(_Float16) * sfa.size()) : 0;
+    const size_t o_sfexp = split ? place(sizeof(int) * sfexp.size()) : 0;
+    const size_t o_saexp = split ? place(sizeof(int) * saexp.size()) : 0;
     if (mixed) {
         o_kf16 = place(sizeof(__half) * KE * n_ktab);
         o_ff16 = place(sizeof(__half) * (size_t)TP * NBP2);
@@ -1370,6 +1401,9 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         up(pl->split.ka, o_ska, ska);
         up(pl->split.ff, o_sff, sff);
         up(pl->split.fa, o_sfa, sfa);
+        up(pl->split.fexp, o_sfexp, sfexp);
+        up(pl->split.aexp, o_saexp, saexp);
+        if (std::all_of(saexp.begin(), saexp.end(), [](int e) { return e == 0; })) pl->split.aexp = nullptr;
     }
     if (fac) {
         mpi3d_plan::Fac &f = pl->fac;
@@ -1382,6 +1416,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         up(f.unit0, o_funit0, funit0);
         up(f.qbin, o_fqbin, fqbin);
         up(f.bcol, o_fbcol, fbcol);
+        up(f.wexp, o_fwexp, fwexp);
     }
     if (precomp) {
         pl->gt = (float *)(tb + o_gt);

@@ -394,7 +394,10 @@ __device__ __forceinline__ void fwd_out(const FacArgs &a, int q, int t0, int ps)
     for (int t = 0; t < kOutTiles; ++t)
 #pragma unroll
         for (int j = 0; j < 16; ++j)
-            e[t][j] = a.lexp[min(t0 + t, a.tiles - 1) * 32 + 4 * h + 8 * (j / 4) + j % 4] + a.w_exp;
+            e[t][j] = a.lexp[min(t0 + t, a.tiles - 1) * 32 + 4 * h + 8 * (j / 4) + j % 4];
+    int we[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) we[u] = a.wexp[(u0 + u) * 32 + (lane & 31)];
     OutStage<NU> g0, g1;
     load(s0, g0);
     int stg = s0;
@@ -418,7 +421,7 @@ __device__ __forceinline__ void fwd_out(const FacArgs &a, int q, int t0, int ps)
             if (row >= job.rows) continue;
             float *o = job.part + ps * a.fwd_part_stride + (size_t)job_line(job, row) * a.ucols + u0 * 32 + (lane & 31);
 #pragma unroll
-            for (int u = 0; u < NU; ++u) o[32 * u] = __builtin_ldexpf(acc[t][u][j], -e[t][j]);
+            for (int u = 0; u < NU; ++u) o[32 * u] = __builtin_ldexpf(acc[t][u][j], -(e[t][j] + we[u]));
         }
     }
 }
@@ -451,7 +454,7 @@ constexpr int kInWaves = kFacInWaves;
 template <int RPW, int KST>
 __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
 {
-    __shared__ float lmax[kInWaves][32];
+    __shared__ int lmax[kInWaves][32];
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = blockIdx.x, zsp = blockIdx.y;
@@ -480,10 +483,13 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
     table_load(s0, ta);
     // B operands: bins 8 ks + 4 h + 0..3 of the wave's slots, re/im.  The bin
     // numbers are requested together, then the data (clamped addresses,
-    // masked values), so the loads overlap.
+    // masked values), so the loads overlap.  A bin's data takes the power of two
+    // that its weights were raised by; the line's largest exponent counts it, so
+    // nothing underflows on the way.
     f16x8 bh[RPW][KST], bl[RPW][KST];
     {
         float v[RPW][KST][8];
+        int ex[RPW][KST][4];
         const float *yin = (const float *)job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride;
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
@@ -493,7 +499,11 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
 #pragma unroll
             for (int ks = 0; ks < KST; ++ks)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) jb[ks][e] = qb[8 * ks + e];
+                for (int e = 0; e < 4; ++e) {
+                    const int w = qb[8 * ks + e];
+                    jb[ks][e] = (int16_t)w;
+                    ex[i][ks][e] = w >> 16;
+                }
 #pragma unroll
             for (int ks = 0; ks < KST; ++ks)
 #pragma unroll
@@ -504,20 +514,24 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
                     v[i][ks][e] = ok ? w : 0.f;
                 }
         }
-        float m = 0.f;
+        constexpr int kZero = -10000;         // below every exponent
+        int m = kZero;
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
 #pragma unroll
             for (int ks = 0; ks < KST; ++ks)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[i][ks][e]));
-        m = fmaxf(m, __shfl_xor(m, 32));
+                for (int e = 0; e < 8; ++e) {
+                    const float w = v[i][ks][e];
+                    m = max(m, w != 0.f ? __builtin_amdgcn_frexp_expf(w) + ex[i][ks][e / 2] : kZero);
+                }
+        m = max(m, __shfl_xor(m, 32));
         if (lane < 32) lmax[wave][lane] = m;
         __syncthreads();
-        m = 0.f;
+        m = kZero;
 #pragma unroll
-        for (int w = 0; w < kInWaves; ++w) m = fmaxf(m, lmax[w][lane & 31]);
-        const int le = line_exponent(m);
+        for (int w = 0; w < kInWaves; ++w) m = max(m, lmax[w][lane & 31]);
+        const int le = m > kZero ? 15 - m : 0;
         if (wave == 0 && lane < 32) a.lexp[r] = le + a.z_exp;   // (every stage range writes the same)
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
@@ -525,7 +539,7 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
             for (int ks = 0; ks < KST; ++ks) {
                 float w[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) w[e] = __builtin_ldexpf(v[i][ks][e], le);
+                for (int e = 0; e < 8; ++e) w[e] = __builtin_ldexpf(v[i][ks][e], le + ex[i][ks][e / 2]);
                 split8(w, bh[i][ks], bl[i][ks]);
             }
     }

@@ -7,7 +7,8 @@
 // b[column][line] += sum_time F[column][time] S[time][line]; adjoint the
 // transpose of both.  Every operand is held as two fp16 values (split8: three
 // products in place of one fp32 product at 1/16 of the rate); lines are scaled
-// by a power of two each, tables by one for all.  The time tile's result
+// by a power of two each, the PSF tables by one for all, the band tables by one
+// a column.  The time tile's result
 // registers are the second contraction's operand as they stand, so nothing
 // crosses lanes.  A wave holds 32 lines and GT column tiles (accumulators
 // forward, data operands adjoint: GT 16 registers, the samples taking
@@ -95,10 +96,12 @@ __device__ __forceinline__ SplitPos split_pos(const SplitArgs &a)
 // `base` (il < 0: zeros), lines `stride` floats apart, by VEC-float loads where
 // they are aligned.  Past the values the last word of the line is read and
 // masked off: every load is unconditional, so all are in flight at once.
-// Returns the line's exponent.
+// cexp (null: 0): exponents of the powers of two the values are taken by, from
+// col0 on; the line's largest exponent counts them, so nothing underflows on
+// the way.  Returns the line's exponent.
 template <int NKS, int VEC>
 __device__ __forceinline__ int split_line(const float *base, long il, int stride, int col0, int n, int h,
-                                          f16x8 (&hi)[NKS], f16x8 (&lo)[NKS])
+                                          const int *cexp, f16x8 (&hi)[NKS], f16x8 (&lo)[NKS])
 {
     typedef float vec __attribute__((ext_vector_type(VEC)));
     const float *src = base + (size_t)(il >= 0 ? il : 0) * stride;
@@ -123,6 +126,28 @@ __device__ __forceinline__ int split_line(const float *base, long il, int stride
                 v[ks][e] = (il >= 0) & (p < n) ? w : 0.f;
             }
     }
+    if (cexp) {
+        constexpr int kZero = -10000;             // below every exponent
+        int m = kZero;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int x = cexp[min(16 * ks + 8 * h + e, n - 1)];
+                m = max(m, v[ks][e] != 0.f ? __builtin_amdgcn_frexp_expf(v[ks][e]) + x : kZero);
+            }
+        m = max(m, __shfl_xor(m, 32));
+        const int le = m > kZero ? 15 - m : 0;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            float w[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                w[e] = __builtin_ldexpf(v[ks][e], le + cexp[min(16 * ks + 8 * h + e, n - 1)]);
+            split8(w, hi[ks], lo[ks]);
+        }
+        return le;
+    }
     float m = 0.f;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks)
@@ -141,14 +166,15 @@ __device__ __forceinline__ int split_line(const float *base, long il, int stride
 }
 
 // Result rows of a 32 x 32 tile (8 (s / 4) + 4 h + s % 4) of this lane's line,
-// scaled back, as 16-byte words.
-__device__ __forceinline__ void store_tile(float *dst, const f32x16 &v, int exp)
+// scaled back (rexp: by an exponent a row as well, from row 4 h on; null: none),
+// as 16-byte words.
+__device__ __forceinline__ void store_tile(float *dst, const f32x16 &v, int exp, const int *rexp)
 {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         f32x4 w;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = __builtin_ldexpf(v[4 * q + e], exp);
+        for (int e = 0; e < 4; ++e) w[e] = __builtin_ldexpf(v[4 * q + e], exp - (rexp ? rexp[8 * q + e] : 0));
         *reinterpret_cast<f32x4 *>(dst + 8 * q) = w;
     }
 }
@@ -173,7 +199,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
     stage.load(1, lk, 1, wave, lane);
 
     f16x8 rh[NKS], rl[NKS];
-    const int le = split_line<NKS, 4>((const float *)job.in, il, job.in_stride, 0, a.nu, h, rh, rl);
+    const int le = split_line<NKS, 4>((const float *)job.in, il, job.in_stride, 0, a.nu, h, nullptr, rh, rl);
     f32x16 acc[GT];
 #pragma unroll
     for (int g = 0; g < GT; ++g) acc[g] = 0.f;
@@ -221,7 +247,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
         const int ct = sp.group * GT + g;
-        if (ct < a.nct) store_tile(out + 32 * ct, acc[g], -(le + a.out_exp));
+        if (ct < a.nct) store_tile(out + 32 * ct, acc[g], -(le + a.out_exp), a.cexp + 32 * ct + 4 * h);
     }
 }
 
@@ -244,7 +270,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
 
     f16x8 zh[NZS], zl[NZS];
     const int col0 = sp.group * GT * 32;
-    const int le = split_line<NZS, 2>((const float *)job.in, il, job.in_stride, col0, a.nb2 - col0, h, zh, zl);
+    const int le = split_line<NZS, 2>((const float *)job.in, il, job.in_stride, col0, a.nb2 - col0, h,
+                                         a.cexp ? a.cexp + col0 : nullptr, zh, zl);
     f32x16 acc[PT];
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) acc[pt] = 0.f;
@@ -289,7 +316,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
     if (il < 0) return;
     float *out = a.part + (size_t)(sp.split * a.ngroups + sp.group) * a.part_stride + (size_t)il * a.pitch + 4 * h;
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) store_tile(out + 32 * pt, acc[pt], -(le + a.out_exp));
+    for (int pt = 0; pt < PT; ++pt) store_tile(out + 32 * pt, acc[pt], -(le + a.out_exp), nullptr);
 }
 
 typedef void (*SplitKernel)(SplitArgs);
@@ -333,6 +360,7 @@ hipError_t launch_split(const SplitArgs &a, bool fwd, hipStream_t st)
         a.pitch < (fwd ? 32 * a.nct : a.nup) || (double)a.nchunks * a.nct * 4096 >= 2147483647.0 ||
         (double)a.nchunks * a.nup * 128 >= 2147483647.0)
         return hipErrorInvalidValue;
+    if (fwd && !a.cexp) return hipErrorInvalidValue;
     const SplitKernel k = fwd ? e.fwd : e.adj;
     const hipError_t err = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, e.lds);
     if (err != hipSuccess) return err;
