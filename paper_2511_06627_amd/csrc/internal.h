@@ -85,8 +85,8 @@ struct SplitArgs {
     float s_scale;           // the time tile's scale before it is split again
     int out_exp;             // power of two of the results above a line's own (forward: and above
                              // their column's)
-    const int *cexp;         // [32 nct] forward: exponents of the band table's columns; adjoint: of the
-                             // power of two a column's data is taken by (null: all 0)
+    const int *cexp;         // forward: exponents of the band table's columns; adjoint: of the power of
+                             // two a column's data is taken by (null: all 0)
 };
 
 // The band DFT factored over drive cycles (FP32), one launch per line group
@@ -258,7 +258,7 @@ struct mpi3d_plan {
         float s_scale, g_scale;
         int fwd_exp, adj_exp;
         __half *kf, *ka, *ff, *fa;
-        int *fexp, *aexp;         // [32 nct]; aexp null where all bins share one exponent
+        int *fexp, *aexp;         // [32 (nct + 8)]; aexp null where all bins share one exponent
     } split;
     uint64_t line_key;             // equal keys <=> identical line tables
     // projection configuration

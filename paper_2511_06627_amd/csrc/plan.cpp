@@ -1093,8 +1093,8 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         sp.g_scale = (float)std::ldexp(1.0, -s2);
         sp.fwd_exp = kexp - s1;
         sp.adj_exp = fref - s2 + kexp;
-        sfexp.assign((size_t)32 * sp.nct, 0);
-        saexp.assign((size_t)32 * sp.nct, 0);
+        sfexp.assign((size_t)32 * (sp.nct + 8), 0);      // (a last column group reads past nct)
+        saexp.assign((size_t)32 * (sp.nct + 8), 0);
         for (int c = 0; c < 2 * NB; ++c) {
             sfexp[c] = fex[c / 2];
             saexp[c] = fref - fex[c / 2];

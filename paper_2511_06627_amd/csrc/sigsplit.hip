@@ -96,10 +96,10 @@ __device__ __forceinline__ SplitPos split_pos(const SplitArgs &a)
 // `base` (il < 0: zeros), lines `stride` floats apart, by VEC-float loads where
 // they are aligned.  Past the values the last word of the line is read and
 // masked off: every load is unconditional, so all are in flight at once.
-// cexp (null: 0): exponents of the powers of two the values are taken by, from
-// col0 on; the line's largest exponent counts them, so nothing underflows on
-// the way.  Returns the line's exponent.
-template <int NKS, int VEC>
+// EXP: cexp holds the exponents of the powers of two the values are taken by,
+// from col0 on (16-byte aligned, padded); the line's largest exponent counts
+// them, so nothing underflows on the way.  Returns the line's exponent.
+template <int NKS, int VEC, bool EXP>
 __device__ __forceinline__ int split_line(const float *base, long il, int stride, int col0, int n, int h,
                                           const int *cexp, f16x8 (&hi)[NKS], f16x8 (&lo)[NKS])
 {
@@ -126,25 +126,39 @@ __device__ __forceinline__ int split_line(const float *base, long il, int stride
                 v[ks][e] = (il >= 0) & (p < n) ? w : 0.f;
             }
     }
-    if (cexp) {
+    if constexpr (EXP) {
+        // (a step's exponents at a time, read twice: the registers hold no more)
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        auto exps = [&](int ks, int (&x)[8]) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const i32x4 w = *reinterpret_cast<const i32x4 *>(cexp + 16 * ks + 8 * h + 4 * q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[4 * q + e] = w[e];
+            }
+        };
         constexpr int kZero = -10000;             // below every exponent
         int m = kZero;
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
+        for (int ks = 0; ks < NKS; ++ks) {
+            int x[8];
+            exps(ks, x);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int x = cexp[min(16 * ks + 8 * h + e, n - 1)];
-                m = max(m, v[ks][e] != 0.f ? __builtin_amdgcn_frexp_expf(v[ks][e]) + x : kZero);
-            }
+            for (int e = 0; e < 8; ++e)
+                m = max(m, v[ks][e] != 0.f ? __builtin_amdgcn_frexp_expf(v[ks][e]) + x[e] : kZero);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         m = max(m, __shfl_xor(m, 32));
         const int le = m > kZero ? 15 - m : 0;
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
+            int x[8];
+            exps(ks, x);
             float w[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                w[e] = __builtin_ldexpf(v[ks][e], le + cexp[min(16 * ks + 8 * h + e, n - 1)]);
+            for (int e = 0; e < 8; ++e) w[e] = __builtin_ldexpf(v[ks][e], le + x[e]);
             split8(w, hi[ks], lo[ks]);
+            __builtin_amdgcn_sched_barrier(0);
         }
         return le;
     }
@@ -199,7 +213,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
     stage.load(1, lk, 1, wave, lane);
 
     f16x8 rh[NKS], rl[NKS];
-    const int le = split_line<NKS, 4>((const float *)job.in, il, job.in_stride, 0, a.nu, h, nullptr, rh, rl);
+    const int le = split_line<NKS, 4, false>((const float *)job.in, il, job.in_stride, 0, a.nu, h, nullptr, rh, rl);
     f32x16 acc[GT];
 #pragma unroll
     for (int g = 0; g < GT; ++g) acc[g] = 0.f;
@@ -251,7 +265,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
     }
 }
 
-template <int NUP, int GT, int WAVES>
+// EXP: bins of unequal gain (a.cexp)
+template <int NUP, int GT, int WAVES, bool EXP>
 __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitArgs a)
 {
     using Stage = ChunkStage<NUP, GT, WAVES>;
@@ -270,8 +285,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
 
     f16x8 zh[NZS], zl[NZS];
     const int col0 = sp.group * GT * 32;
-    const int le = split_line<NZS, 2>((const float *)job.in, il, job.in_stride, col0, a.nb2 - col0, h,
-                                         a.cexp ? a.cexp + col0 : nullptr, zh, zl);
+    const int le = split_line<NZS, 2, EXP>((const float *)job.in, il, job.in_stride, col0, a.nb2 - col0, h,
+                                              a.cexp + col0, zh, zl);
     f32x16 acc[PT];
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) acc[pt] = 0.f;
@@ -322,10 +337,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
 typedef void (*SplitKernel)(SplitArgs);
 struct SplitEntry {
     int nup, gt, waves;
-    SplitKernel fwd, adj;
+    SplitKernel fwd, adj, adj_exp;
     int lds;
 };
-#define ENTRY(N, G, W) {N, G, W, split_fwd_kernel<N, G, W>, split_adj_kernel<N, G, W>, ChunkStage<N, G, W>::kBytes}
+#define ENTRY(N, G, W) {N, G, W, split_fwd_kernel<N, G, W>, split_adj_kernel<N, G, W, false>, split_adj_kernel<N, G, W, true>, ChunkStage<N, G, W>::kBytes}
 // (two waves a SIMD, or one with as many columns as three chunks in LDS hold)
 const SplitEntry kSplit[] = {
     ENTRY(64, 4, 8), ENTRY(64, 6, 8), ENTRY(64, 8, 8), ENTRY(64, 4, 4), ENTRY(64, 6, 4), ENTRY(64, 8, 4),
@@ -361,7 +376,7 @@ hipError_t launch_split(const SplitArgs &a, bool fwd, hipStream_t st)
         (double)a.nchunks * a.nup * 128 >= 2147483647.0)
         return hipErrorInvalidValue;
     if (fwd && !a.cexp) return hipErrorInvalidValue;
-    const SplitKernel k = fwd ? e.fwd : e.adj;
+    const SplitKernel k = fwd ? e.fwd : a.cexp ? e.adj_exp : e.adj;
     const hipError_t err = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, e.lds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(k, dim3(a.tgroups * a.ngroups * a.nsplit), dim3(64 * e.waves), e.lds, st, a);
