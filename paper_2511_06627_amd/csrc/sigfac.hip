@@ -646,7 +646,7 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
     __builtin_amdgcn_sched_barrier(0);
     Stage::load(ka, 0, c1 - c0, lk, 0, wave, lane);
     Stage::load(ka, NS, c1 - c0, lk, 1, wave, lane);
-    const float gscale = a.g_scale;
+    const float sign = chain_sign(fp.split, fp.tile), gscale = a.g_scale * sign;
     wait_vm_lgkm<Stage::kOps>();
     block_barrier_nofence();
 
@@ -712,7 +712,7 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
         if (row >= job.rows) continue;
         float *o = out + (size_t)job_line(job, row) * a.adj_pitch + pass * NUP + (lane & 31);
 #pragma unroll
-        for (int pt = 0; pt < PT; ++pt) o[pt * 32] = __builtin_ldexpf(racc[pt][j], -(e[j] + a.r_exp));
+        for (int pt = 0; pt < PT; ++pt) o[pt * 32] = __builtin_ldexpf(racc[pt][j] * sign, -(e[j] + a.r_exp));
     }
 }
 

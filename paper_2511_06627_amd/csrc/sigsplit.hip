@@ -179,16 +179,16 @@ __device__ __forceinline__ int split_line(const float *base, long il, int stride
     return le;
 }
 
-// Result rows of a 32 x 32 tile (8 (s / 4) + 4 h + s % 4) of this lane's line,
-// scaled back (rexp: by an exponent a row as well, from row 4 h on; null: none),
+// Result rows of a 32 x 32 tile (8 (s / 4) + 4 h + s % 4) of this lane's line, by
+// the chain's sign and scaled back (rexp: by an exponent a row as well, from row 4 h on; null: none),
 // as 16-byte words.
-__device__ __forceinline__ void store_tile(float *dst, const f32x16 &v, int exp, const int *rexp)
+__device__ __forceinline__ void store_tile(float *dst, const f32x16 &v, float sign, int exp, const int *rexp)
 {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         f32x4 w;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = __builtin_ldexpf(v[4 * q + e], exp - (rexp ? rexp[8 * q + e] : 0));
+        for (int e = 0; e < 4; ++e) w[e] = __builtin_ldexpf(v[4 * q + e] * sign, exp - (rexp ? rexp[8 * q + e] : 0));
         *reinterpret_cast<f32x4 *>(dst + 8 * q) = w;
     }
 }
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
     f32x16 acc[GT];
 #pragma unroll
     for (int g = 0; g < GT; ++g) acc[g] = 0.f;
-    const float sscale = a.s_scale;
+    const float sign = chain_sign(sp.split, sp.tile), sscale = a.s_scale * sign;
     wait_vm_lgkm<Stage::kOps>();
     block_barrier_nofence();
 
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
         const int ct = sp.group * GT + g;
-        if (ct < a.nct) store_tile(out + 32 * ct, acc[g], -(le + a.out_exp), a.cexp + 32 * ct + 4 * h);
+        if (ct < a.nct) store_tile(out + 32 * ct, acc[g], sign, -(le + a.out_exp), a.cexp + 32 * ct + 4 * h);
     }
 }
 
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
     f32x16 acc[PT];
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) acc[pt] = 0.f;
-    const float gscale = a.s_scale;
+    const float sign = chain_sign(sp.split, sp.tile), gscale = a.s_scale * sign;
     wait_vm_lgkm<Stage::kOps>();
     block_barrier_nofence();
 
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
     if (il < 0) return;
     float *out = a.part + (size_t)(sp.split * a.ngroups + sp.group) * a.part_stride + (size_t)il * a.pitch + 4 * h;
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) store_tile(out + 32 * pt, acc[pt], -(le + a.out_exp), nullptr);
+    for (int pt = 0; pt < PT; ++pt) store_tile(out + 32 * pt, acc[pt], sign, -(le + a.out_exp), nullptr);
 }
 
 typedef void (*SplitKernel)(SplitArgs);
