@@ -240,7 +240,9 @@ void choose_split(const mpi3d_plan *pl, bool fp32, mpi3d_plan::SigCfg &c, int nu
 // its products at 32 cycles each, 2.2 GHz, 80% busy with two waves a SIMD and
 // 62% with one; each split costs the reduction
 // one more partial sum (its chain of loads, about 0.1 us, and its bytes written
-// and read at 4 TB/s).
+// and read at 4 TB/s).  Within 5% of each other, the forward takes ranges of at
+// most 24 chunks (64^3, 24 angles, T = 4001: 18 chunks in place of 26, whose
+// longer sums cost 4% more error than fp32 MFMA has).
 void choose_dense_split(const mpi3d_plan *pl, bool fwd, mpi3d_plan::Split::Dir &d)
 {
     const int nct = pl->split.nct;
@@ -257,8 +259,9 @@ void choose_dense_split(const mpi3d_plan *pl, bool fwd, mpi3d_plan::Split::Dir &
         const double per_split =
             fwd ? 1e-7 + 8.0 * pl->L * 32 * nct / 4e12 : ng * (1e-7 + 8.0 * pl->L * pl->nup / 4e12);
         for (int ns = 1; ns <= std::min(pl->nchunks, 128); ++ns) {
-            const double t = (double)((tg * ng * ns + 255) / 256) * (12e-6 + (pl->nchunks + ns - 1) / ns * chunk) +
-                             ns * per_split;
+            const int len = (pl->nchunks + ns - 1) / ns;
+            double t = (double)((tg * ng * ns + 255) / 256) * (12e-6 + len * chunk) + ns * per_split;
+            if (fwd && waves == 4 && len > 24) t *= 1.05;
             if (t < best * (1.0 - 1e-9)) {
                 best = t;
                 d = {i, ng, ns};

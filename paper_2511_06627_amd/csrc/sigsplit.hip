@@ -193,6 +193,31 @@ __device__ __forceinline__ void store_tile(float *dst, const f32x16 &v, float si
     }
 }
 
+// A chunk's time tile from NS fragment pairs (hi, lo) at kb and the operand's
+// pairs.  LOW: the small products (hi lo, lo hi) first, so that only the large ones
+// round a full sum (the hi fragments are read twice).
+template <int NS, bool LOW>
+__device__ __forceinline__ f32x16 chunk_tile(const f16x8 *kb, const f16x8 (&hi)[NS], const f16x8 (&lo)[NS])
+{
+    f32x16 t = 0.f;
+    if constexpr (LOW) {
+        lds_pipelined<3 * NS, 6>([&](int i) { return kb[(i < 2 * NS ? i : 2 * (i - 2 * NS)) * 64]; },
+                                 [&](int i, const f16x8 &f) {
+                                     t = MFMA16(f, i < 2 * NS && i % 2 == 0 ? lo[i / 2] : hi[i < 2 * NS ? i / 2 : i - 2 * NS], t);
+                                 });
+    } else {
+        lds_pipelined<2 * NS, 6>([&](int i) { return kb[i * 64]; },
+                                 [&](int i, const f16x8 &f) {
+                                     t = MFMA16(f, hi[i / 2], t);
+                                     if (i % 2 == 0) t = MFMA16(f, lo[i / 2], t);
+                                 });
+    }
+    return t;
+}
+// One wave a SIMD: that order, and accumulators of their own for the small
+// products of the second contraction, for which it has the registers.
+constexpr bool own_low(int waves) { return waves == 4; }
+
 template <int NUP, int GT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitArgs a)
 {
@@ -214,9 +239,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
 
     f16x8 rh[NKS], rl[NKS];
     const int le = split_line<NKS, 4, false>((const float *)job.in, il, job.in_stride, 0, a.nu, h, nullptr, rh, rl);
-    f32x16 acc[GT];
+    constexpr bool LOW = own_low(WAVES);
+    f32x16 acc[GT], low[LOW ? GT : 1];
 #pragma unroll
-    for (int g = 0; g < GT; ++g) acc[g] = 0.f;
+    for (int g = 0; g < GT; ++g) acc[g] = low[LOW ? g : 0] = 0.f;
     const float sign = chain_sign(sp.split, sp.tile), sscale = a.s_scale * sign;
     wait_vm_lgkm<Stage::kOps>();
     block_barrier_nofence();
@@ -226,12 +252,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
         stage.load(c - sp.c0 + 2, lk, nbuf, wave, lane);
         if (active) {
             const f16x8 *kb = lk + buf * Stage::kFrags * 64 + lane;
-            f32x16 S = 0.f;
-            lds_pipelined<2 * NKS, 6>([&](int i) { return kb[i * 64]; },
-                                      [&](int i, const f16x8 &f) {
-                                          S = MFMA16(f, rh[i / 2], S);
-                                          if (i % 2 == 0) S = MFMA16(f, rl[i / 2], S);
-                                      });
+            const f32x16 S = chunk_tile<NKS, LOW>(kb, rh, rl);
             f16x8 sh[2], sl[2];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
@@ -246,8 +267,13 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
             lds_pipelined<4 * GT, 6>([&](int i) { return fb[((i / 2 % GT) * 4 + i / (2 * GT) * 2 + i % 2) * 64]; },
                                      [&](int i, const f16x8 &f) {
                                          const int q = i / (2 * GT), g = i / 2 % GT;
-                                         acc[g] = MFMA16(f, sh[q], acc[g]);
-                                         if (i % 2 == 0) acc[g] = MFMA16(f, sl[q], acc[g]);
+                                         f32x16 &l = LOW ? low[LOW ? g : 0] : acc[g];
+                                         if (i % 2 == 0) {
+                                             acc[g] = MFMA16(f, sh[q], acc[g]);
+                                             l = MFMA16(f, sl[q], l);
+                                         } else {
+                                             l = MFMA16(f, sh[q], l);
+                                         }
                                      });
         }
         wait_vm_lgkm<Stage::kOps>();      // the next chunk is in, this wave's reads are done
@@ -261,6 +287,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
         const int ct = sp.group * GT + g;
+        if constexpr (LOW) acc[g] += low[g];
         if (ct < a.nct) store_tile(out + 32 * ct, acc[g], sign, -(le + a.out_exp), a.cexp + 32 * ct + 4 * h);
     }
 }
@@ -287,9 +314,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
     const int col0 = sp.group * GT * 32;
     const int le = split_line<NZS, 2, EXP>((const float *)job.in, il, job.in_stride, col0, a.nb2 - col0, h,
                                               a.cexp + col0, zh, zl);
-    f32x16 acc[PT];
+    constexpr bool LOW = own_low(WAVES);
+    f32x16 acc[PT], low[LOW ? PT : 1];
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) acc[pt] = 0.f;
+    for (int pt = 0; pt < PT; ++pt) acc[pt] = low[LOW ? pt : 0] = 0.f;
     const float sign = chain_sign(sp.split, sp.tile), gscale = a.s_scale * sign;
     wait_vm_lgkm<Stage::kOps>();
     block_barrier_nofence();
@@ -299,13 +327,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
         stage.load(c - sp.c0 + 2, lk, nbuf, wave, lane);
         if (active) {
             const f16x8 *kb = lk + buf * Stage::kFrags * 64 + lane;
-            f32x16 G = 0.f;
-            // fragments [16-column step][hi, lo]
-            lds_pipelined<2 * NZS, 6>([&](int i) { return kb[(Stage::kPsf + i) * 64]; },
-                                      [&](int i, const f16x8 &f) {
-                                          G = MFMA16(f, zh[i / 2], G);
-                                          if (i % 2 == 0) G = MFMA16(f, zl[i / 2], G);
-                                      });
+            const f32x16 G = chunk_tile<NZS, LOW>(kb + Stage::kPsf * 64, zh, zl);   // fragments [16-column step][hi, lo]
             f16x8 gh[2], gl[2];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
@@ -318,8 +340,13 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
             lds_pipelined<4 * PT, 6>([&](int i) { return kb[i * 64]; },
                                      [&](int i, const f16x8 &f) {
                                          const int q = i / (2 * PT), pt = i / 2 % PT;
-                                         acc[pt] = MFMA16(f, gh[q], acc[pt]);
-                                         if (i % 2 == 0) acc[pt] = MFMA16(f, gl[q], acc[pt]);
+                                         f32x16 &l = LOW ? low[LOW ? pt : 0] : acc[pt];
+                                         if (i % 2 == 0) {
+                                             acc[pt] = MFMA16(f, gh[q], acc[pt]);
+                                             l = MFMA16(f, gl[q], l);
+                                         } else {
+                                             l = MFMA16(f, gh[q], l);
+                                         }
                                      });
         }
         wait_vm_lgkm<Stage::kOps>();
@@ -331,7 +358,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
     if (il < 0) return;
     float *out = a.part + (size_t)(sp.split * a.ngroups + sp.group) * a.part_stride + (size_t)il * a.pitch + 4 * h;
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) store_tile(out + 32 * pt, acc[pt], sign, -(le + a.out_exp), nullptr);
+    for (int pt = 0; pt < PT; ++pt) {
+        if constexpr (LOW) acc[pt] += low[pt];
+        store_tile(out + 32 * pt, acc[pt], sign, -(le + a.out_exp), nullptr);
+    }
 }
 
 typedef void (*SplitKernel)(SplitArgs);
