@@ -130,83 +130,103 @@ static int adj_parts(const mpi3d_plan *pl, int prec, bool serve)
     return (fused_pass(pl, prec) ? 1 : pl->n_passes) * nsplit_of(pl, prec, serve) * sig_cfg(pl, prec).ngroups;
 }
 
-// Line group gi of a line job; fwd under the tensor PSF: the lines are the
-// virtual lines of symmetric sums in the workspace.
-static FacArgs fac_args(const LineJob &lj, int gi, bool fwd)
+// Line group gi of plan pj: tables and sizes, no jobs yet.
+static FacArgs fac_args(const mpi3d_plan *pj, int gi)
 {
-    const mpi3d_plan *pj = lj.pl;
     const mpi3d_plan::Fac &f = pj->fac;
-    const mpi3d_plan::LineGroup &lg = pj->groups[gi];
-    const int np = pj->n_passes;
     FacArgs a{};
-    a.job.in = fwd && np > 1 ? lj.w->sig : lj.in;
-    a.job.in_stride = fwd && np > 1 ? np * pj->nup : lj.in_stride;
-    a.job.part = lj.w->part;
-    a.np = np;
-    a.adj_pitch = np * pj->nup;
-    a.job.part_stride = pj->L * a.adj_pitch;
+    a.np = pj->n_passes;
+    a.adj_pitch = a.np * pj->nup;
     a.kf = f.kf + gi * f.k_stride;
     a.ka = f.ka + gi * f.k_stride;
     a.ka_stride = 2 * (long)pj->k_elems;
-    a.job.rows = lg.rows;
-    a.job.map_per = lg.per;
-    a.job.map_nz = lg.gnz;
-    a.job.map_off = lg.off;
-    a.job.map_step = lg.step;
     a.ef = f.ef; a.ea = f.ea; a.wf = f.wf; a.wa = f.wa;
     a.unit0 = f.unit0; a.qbin = f.qbin; a.wexp = f.wexp;
-    a.y = lj.w->fac;
-    a.lexp = lj.w->lexp;
-    a.ylines = (lg.rows + 31) / 32 * 32;
     a.nu = pj->nu; a.nup = pj->nup;
     a.P = f.P; a.cj = f.cj; a.ucols = 32 * f.U;
     a.yc = 2 * f.zst; a.zst = f.zst; a.R = f.R; a.U = f.U; a.qmax = f.qmax;
-    a.nsplit = f.nsplit; a.nsplit_adj = f.nsplit_adj; a.nzstage = f.nzstage;
-    a.psplit = f.psplit; a.zsplit = f.zsplit;
-    a.fwd_part_stride = pj->L * 32 * f.U;
-    a.tiles = (lg.rows + 31) / 32;
+    a.nzstage = f.nzstage;
     a.s_scale = f.s_scale; a.g_scale = f.g_scale; a.y_scale = f.y_scale; a.z_scale = f.z_scale;
     a.y_exp = f.y_exp; a.z_exp = f.z_exp; a.r_exp = f.r_exp;
     return a;
 }
 
-// Every line group of a line job, one launch.
-static SplitArgs split_args(const LineJob &lj, bool fwd)
+// Line group gi of a line job; fwd under the tensor PSF: the lines are the
+// virtual lines of symmetric sums in the workspace.
+static FacJob fac_job(const LineJob &lj, int gi, bool fwd)
 {
     const mpi3d_plan *pj = lj.pl;
+    const mpi3d_plan::Fac &f = pj->fac;
+    const mpi3d_plan::LineGroup &lg = pj->groups[gi];
+    const int np = pj->n_passes;
+    FacJob j{};
+    j.in = fwd && np > 1 ? lj.w->sig : lj.in;
+    j.in_stride = fwd && np > 1 ? np * pj->nup : lj.in_stride;
+    j.part = lj.w->part;
+    j.part_stride = pj->L * np * pj->nup;
+    j.fwd_part_stride = pj->L * 32 * f.U;
+    j.y = lj.w->fac;
+    j.lexp = lj.w->lexp;
+    j.rows = lg.rows;
+    j.tiles = (lg.rows + 31) / 32;
+    j.ylines = j.tiles * 32;
+    j.map_per = lg.per;
+    j.map_nz = lg.gnz;
+    j.map_off = lg.off;
+    j.map_step = lg.step;
+    j.nsplit = f.nsplit; j.nsplit_adj = f.nsplit_adj;
+    j.psplit = f.psplit; j.zsplit = f.zsplit;
+    return j;
+}
+
+// One job's arguments.
+static FacBatch fac_single(const LineJob &lj, int gi, bool fwd)
+{
+    FacBatch b{};
+    b.a = fac_args(lj.pl, gi);
+    b.jobs[b.njobs++] = fac_job(lj, gi, fwd);
+    return b;
+}
+
+// The dense stage on fp16 pairs of plan pj: tables and sizes, no jobs yet.
+static SplitArgs split_args(const mpi3d_plan *pj, bool fwd)
+{
     const mpi3d_plan::Split &s = pj->split;
     const mpi3d_plan::Split::Dir &d = fwd ? s.fwd : s.adj;
     SplitArgs a{};
-    int gt = 0, waves = 8;
-    (void)split_config(d.config, pj->nup, &gt, &waves);
     a.config = d.config;
-    a.njobs = pj->n_line_groups;
-    for (int gi = 0; gi < a.njobs; ++gi) {
-        const mpi3d_plan::LineGroup &lg = pj->groups[gi];
-        SigJob &sj = a.jobs[gi];
-        sj.in = lj.in;
-        sj.in_stride = lj.in_stride;
-        sj.kf16 = s.kf + 2 * (size_t)lg.table * pj->k_elems;
-        sj.ka16 = s.ka + 2 * (size_t)lg.table * pj->k_elems;
-        sj.rows = lg.rows;
-        sj.tile0 = a.tgroups;
-        a.tgroups += (lg.rows + 32 * waves - 1) / (32 * waves);
-        sj.map_per = lg.per;
-        sj.map_nz = lg.gnz;
-        sj.map_off = lg.off;
-        sj.map_step = lg.step;
-    }
-    a.ff = s.ff; a.fa = s.fa;
-    a.part = lj.w->part;
+    a.nlines = pj->n_line_groups;
+    for (int gi = 0; gi < a.nlines; ++gi) a.k[gi] = (fwd ? s.kf : s.ka) + 2 * (size_t)pj->groups[gi].table * pj->k_elems;
+    a.f = fwd ? s.ff : s.fa;
     a.pitch = fwd ? 32 * s.nct : pj->nup;
-    a.part_stride = pj->L * a.pitch;
     a.nu = pj->nu; a.nup = pj->nup; a.nb2 = pj->nb2; a.nct = s.nct;
     a.nchunks = pj->nchunks;
-    a.nsplit = d.nsplit; a.ngroups = d.ngroups;
+    a.ngroups = d.ngroups;
     a.s_scale = fwd ? s.s_scale : s.g_scale;
     a.out_exp = fwd ? s.fwd_exp : s.adj_exp;
     a.cexp = fwd ? s.fexp : s.aexp;
     return a;
+}
+
+// Every line group of a line job.
+static SplitJob split_job(const LineJob &lj, bool fwd)
+{
+    const mpi3d_plan *pj = lj.pl;
+    const mpi3d_plan::Split::Dir &d = fwd ? pj->split.fwd : pj->split.adj;
+    int gt = 0, waves = 8;
+    (void)split_config(d.config, pj->nup, &gt, &waves);
+    SplitJob j{};
+    j.in = lj.in;
+    j.in_stride = lj.in_stride;
+    j.part = lj.w->part;
+    j.part_stride = pj->L * (fwd ? 32 * pj->split.nct : pj->nup);
+    j.nsplit = d.nsplit;
+    for (int gi = 0; gi < pj->n_line_groups; ++gi) {
+        const mpi3d_plan::LineGroup &lg = pj->groups[gi];
+        j.lines[gi] = {lg.rows, j.tgroups, lg.per, lg.gnz, lg.off, lg.step};
+        j.tgroups += (lg.rows + 32 * waves - 1) / (32 * waves);
+    }
+    return j;
 }
 
 // The kernel jobs of one line job: one per line group (trajectory class of a
@@ -317,24 +337,44 @@ static int sig_jobs(bool fwd, int prec, const LineJob *jobs, int n, bool serve, 
     if (n < 1) return MPI3D_EINVAL;
     const mpi3d_plan *pl = jobs[0].pl;
     if (fac_on(pl, prec)) {
-        // one factored stage per line job (its own phase sums in its workspace)
-        // and line group after line group
+        // line group after line group (a workspace holds one's phase sums), the
+        // line jobs of each sharing launches and the first one's tables.  (A step of
+        // 16 served 32^3 scans, 8 angles, FP32: with launches of their own 1034 us,
+        // shared 604; on fp32 MFMA, shared, 686.)
         for (int j = 0; j < n; ++j) {
             const mpi3d_plan *pj = jobs[j].pl;
             if (pj->line_key != pl->line_key || !pj->fac.on) return MPI3D_EINVAL;
             if (fwd && pj->n_passes > 1)
                 TRY(launch_sym_lines(jobs[j].in, jobs[j].in_stride, pj->nu, pj->nup, row_passes(pj, true, MPI3D_MIXED),
                                      jobs[j].w->sig, pj->nup, pj->nupf, st));
-            for (int gi = 0; gi < pj->n_line_groups; ++gi)
-                TRY(fwd ? launch_fac_fwd(fac_args(jobs[j], gi, true), st)
-                        : launch_fac_adj(fac_args(jobs[j], gi, false), st));
+        }
+        for (int gi = 0; gi < pl->n_line_groups; ++gi) {
+            FacBatch b{};
+            b.a = fac_args(pl, gi);
+            for (int j = 0; j < n; ++j) {
+                b.jobs[b.njobs++] = fac_job(jobs[j], gi, fwd);
+                if (b.njobs < kMaxFacJobs && j + 1 < n) continue;
+                TRY(fwd ? launch_fac_fwd(b, st) : launch_fac_adj(b, st));
+                b.njobs = 0;
+            }
         }
         return MPI3D_OK;
     }
     if (split_on(pl, prec)) {
-        for (int j = 0; j < n; ++j) {
+        // line jobs of one kernel configuration share launches
+        for (int j = 0; j < n; ++j)
             if (jobs[j].pl->line_key != pl->line_key || !jobs[j].pl->split.on) return MPI3D_EINVAL;
-            TRY(launch_split(split_args(jobs[j], fwd), fwd, st));
+        std::vector<char> done(n, 0);
+        for (int i = 0; i < n; ++i) {
+            if (done[i]) continue;
+            SplitArgs a = split_args(jobs[i].pl, fwd);
+            for (int j = i; j < n && a.njobs < kMaxSplitJobs; ++j) {
+                const mpi3d_plan::Split &s = jobs[j].pl->split;
+                if (done[j] || (fwd ? s.fwd : s.adj).config != a.config) continue;
+                a.jobs[a.njobs++] = split_job(jobs[j], fwd);
+                done[j] = 1;
+            }
+            TRY(launch_split(a, fwd, st));
         }
         return MPI3D_OK;
     }
@@ -1019,11 +1059,19 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
     }
     // the factored band DFT's stages and kernels (FP32 plans that take it)
     // (of the first line group)
-    const FacArgs fwd_fac = fac_on(pl, precision) ? fac_args(LineJob{pl, w.rt, pl->nup, &w}, 0, true) : FacArgs{};
-    const FacArgs adj_fac = fac_on(pl, precision) ? fac_args(LineJob{pl, b, pl->nb2, &w}, 0, false) : FacArgs{};
+    FacBatch fwd_fac{}, adj_fac{};
+    if (fac_on(pl, precision)) {
+        fwd_fac = fac_single(LineJob{pl, w.rt, pl->nup, &w}, 0, true);
+        adj_fac = fac_single(LineJob{pl, b, pl->nb2, &w}, 0, false);
+    }
     const bool split = split_on(pl, precision);
-    const SplitArgs fwd_split = split ? split_args(LineJob{pl, w.rt, pl->nup, &w}, true) : SplitArgs{};
-    const SplitArgs adj_split = split ? split_args(LineJob{pl, b, pl->nb2, &w}, false) : SplitArgs{};
+    SplitArgs fwd_split{}, adj_split{};
+    if (split) {
+        fwd_split = split_args(pl, true);
+        adj_split = split_args(pl, false);
+        fwd_split.jobs[fwd_split.njobs++] = split_job(LineJob{pl, w.rt, pl->nup, &w}, true);
+        adj_split.jobs[adj_split.njobs++] = split_job(LineJob{pl, b, pl->nb2, &w}, false);
+    }
     const bool mixed = precision == MPI3D_MIXED;
     hipError_t err = mixed && kernel == 0 ? launch_to_bf16(pl->nvox, x, w.xb, st) : hipSuccess;
     // the mixed signal kernels read fp16 operand lines: prepared once, untimed

@@ -63,7 +63,8 @@ struct SigJob {
     int map_per, map_nz, map_off, map_step;
 };
 
-__host__ __device__ inline long job_line(const SigJob &j, int r)
+template <class Job>
+__host__ __device__ inline long job_line(const Job &j, int r)
 {
     const int g = r / j.map_per;
     return (long)g * j.map_nz + j.map_off + (long)j.map_step * (r - g * j.map_per);
@@ -74,14 +75,28 @@ __host__ __device__ inline long job_line(const SigJob &j, int r)
 // both contractions as three fp16 products each, lines scaled by a power of
 // two each, the PSF tables by one for all, the band tables by one a column (a
 // bin behind a weak receive filter keeps its bits).
-struct SplitArgs {
-    SigJob jobs[2];          // line groups: kf16 / ka16 are their split PSF tables, tile0 their first block tile
-    int njobs, config;       // config: see split_config
-    const __half *ff, *fa;   // split band tables
+// One launch covers one scan, or several served together (jobs).
+struct SplitLines {          // a line group of a job
+    int rows, tile0;         // lines; first block tile in the job
+    int map_per, map_nz, map_off, map_step;   // row map (see SigJob)
+};
+struct SplitJob {
+    const float *in;         // input lines, in_stride floats apart
     float *part;             // fwd: [nsplit][line][pitch]; adj: [nsplit][ngroups][line][pitch]
     long part_stride;
+    int in_stride, nsplit, tgroups;
+    int blk0;                // first block of this job in the launch
+    SplitLines lines[2];
+};
+constexpr int kMaxSplitJobs = 16;
+
+struct SplitArgs {
+    SplitJob jobs[kMaxSplitJobs];
+    int njobs, nlines, config;      // nlines: line groups; config: see split_config
+    const __half *k[2];      // the line groups' split PSF tables, as the direction takes them
+    const __half *f;         // split band table
     int pitch;
-    int nu, nup, nb2, nct, nchunks, nsplit, ngroups, tgroups;
+    int nu, nup, nb2, nct, nchunks, ngroups;
     float s_scale;           // the time tile's scale before it is split again
     int out_exp;             // power of two of the results above a line's own (forward: and above
                              // their column's)
@@ -89,8 +104,10 @@ struct SplitArgs {
                              // two a column's data is taken by (null: all 0)
 };
 
-// The band DFT factored over drive cycles (FP32), one launch per line group
-// (each with its own PSF tables; under the tensor PSF np = R + 1 of them, the
+// The band DFT factored over drive cycles (FP32): launches of one line group
+// (each has its own PSF tables) of one scan, or of several served together (jobs,
+// each with the split of its own scan, so a line's sums do not depend on which
+// others share the launch; under the tensor PSF np = R + 1 of them, the
 // forward's lines being np symmetric line sums laid end to end): time
 // t = n1 + P n2 with n1 < P, n2 < C, T = C P, C = 32 or 64.  The time signal is real, so its C-point DFT over n2 needs one slot of
 // two columns (cos, sin) per residue pair {r, C - r} of the kept bins mod C;
@@ -106,8 +123,25 @@ constexpr int kFacWaves = 8;        // waves (32-line tiles) per block of the li
                                     // (two per SIMD: one hides the other's wait at the stage barrier)
 constexpr int kFacInWaves = 8;      // waves of the adjoint outer sum; wave w takes slots w + 8 i
 
+struct FacJob {
+    const float *in;         // input lines, in_stride floats apart
+    float *part;             // partial sums
+    long part_stride;        // floats between the adjoint's blocks of them
+    long fwd_part_stride;    // floats between the forward outer sum's
+    uint32_t *y;             // phase sums Y or Z per 32-line tile, [P][yc][32 lines] (column 2 slot +
+                             // cos/sin), words of split pairs; ylines = 32 tiles; then a spare row of
+                             // P yc words taking the stores that carry nothing
+    int *lexp;               // [ylines] power-of-two exponent of each line's Y or Z
+    int in_stride, ylines;
+    int rows, tiles;         // lines, 32-line tiles
+    int map_per, map_nz, map_off, map_step;   // row map (see SigJob)
+    int nsplit, nsplit_adj;  // phase ranges of the forward and adjoint line-tile kernels
+    int psplit, zsplit;      // stage ranges of the forward outer sum (partial sums each) and of the
+                             // adjoint outer sum (disjoint phases of Z)
+    int blk0;                // first block of this job in a launch of several
+};
+
 struct FacArgs {
-    SigJob job;              // input lines, partial sums (part, part_stride), row map
     const __half *kf, *ka;   // PSF tables, time rows in chunk order (n1, 32-cycle block), as fp16
                              // fragment pairs hi, lo scaled by a power of two
     const __half *ef, *ea;   // residue DFT (both as A operands), pairs hi, lo of 2^14 E
@@ -117,11 +151,6 @@ struct FacArgs {
     const int *qbin;         // [R][qmax] bins of slot q: the bin in the low half (0xffff: none), in the
                              // high half the exponent of the power of two its data is taken by
     const int *wexp;         // [32 U] exponents of the forward table's columns
-    uint32_t *y;             // phase sums Y or Z per 32-line tile, [P][yc][32 lines] (column 2 slot +
-                             // cos/sin), words of split pairs; ylines = 32 tiles; then a spare row of
-                             // P yc words taking the stores that carry nothing
-    int *lexp;               // [ylines] power-of-two exponent of each line's Y or Z
-    int ylines;
     int nu, nup;
     int np;                  // tables a line (1: no tensor PSF)
     long ka_stride;          // halves between the tables of ka
@@ -130,12 +159,7 @@ struct FacArgs {
     int yc, zst, R, U;       // yc = 2 zst
     int ucols;               // 32 U: columns of the forward's partial sums (unit, bin, re/im)
     int qmax;
-    int nsplit, nsplit_adj;  // phase ranges of the forward and adjoint line-tile kernels
-    int psplit, zsplit;      // stage ranges of the forward outer sum (partial sums each) and of the
-                             // adjoint outer sum (disjoint phases of Z)
-    long fwd_part_stride;    // floats between the forward outer sum's partial-sum blocks
     int nzstage;             // 16-phase stages of the adjoint outer sum
-    int tiles;               // 32-line tiles of the job
     // Power-of-two scales: of the time signal before its split (forward,
     // adjoint), of Y and Z before theirs.  A line of Y holds Y 2^lexp (lexp: the
     // line's exponent + y_exp), of Z likewise (+ z_exp); the forward's partial
@@ -144,6 +168,16 @@ struct FacArgs {
     // own, so a bin behind a weak receive filter keeps its bits.
     float s_scale, g_scale, y_scale, z_scale;
     int y_exp, z_exp, r_exp;
+    FacJob job;              // a launch of one scan
+};
+
+// Several scans' jobs.  A kernel variant of its own: looking the job up costs a
+// launch 0.6 us (32^3, 8 angles, A then A^T 57.3 -> 59.1 us).
+constexpr int kMaxFacJobs = 16;
+struct FacBatch {
+    FacArgs a;               // (without a.job)
+    int njobs;
+    FacJob jobs[kMaxFacJobs];
 };
 
 struct SigArgs {
@@ -353,13 +387,14 @@ int fac_supported(int nup, int zst, int cj, int np);
 // Kernel configuration i of the dense split stage: 1 and its column tiles a
 // group and waves a block if it is for nup samples, 0 if not, -1 past the last.
 int split_config(int i, int nup, int *gt, int *waves);
-hipError_t launch_split(const SplitArgs &a, bool fwd, hipStream_t st);
-hipError_t launch_fac_fwd(const FacArgs &a, hipStream_t st);
-hipError_t launch_fac_adj(const FacArgs &a, hipStream_t st);
+hipError_t launch_split(SplitArgs &a, bool fwd, hipStream_t st);   // (sets the jobs' blk0)
+// (b.njobs scans' jobs, b.a their common tables and sizes; the launches set blk0)
+hipError_t launch_fac_fwd(FacBatch &b, hipStream_t st);
+hipError_t launch_fac_adj(FacBatch &b, hipStream_t st);
 // one kernel of those stages: forward PSF contraction + residue DFT, forward
 // outer sum, adjoint outer sum, adjoint residue DFT + PSF contraction
 enum { kFacFwdInner = 0, kFacFwdOuter = 1, kFacAdjOuter = 2, kFacAdjInner = 3 };
-hipError_t launch_fac_part(const FacArgs &a, int part, hipStream_t st);
+hipError_t launch_fac_part(FacBatch &b, int part, hipStream_t st);
 
 // Precomposed signal stage (gemm.hip): C[i][j] = alpha sum_q A_i[q] W[q][j]
 // (+ beta C[i][j] when beta != 0) for i < n, j < m, q < k, over `batch`

@@ -42,6 +42,8 @@
 // 8(s/4) + 4(l/32) + s%4, column l%32.  Every table is pre-swizzled so a
 // lane's operand is one 16-byte word and a wave's 1 KB fragment is contiguous.
 
+#include <type_traits>
+
 #include "device.h"
 
 namespace mpi3d {
@@ -59,12 +61,33 @@ struct FacPos {
     int tile, n1a, n1b, split;
 };
 
-template <int WAVES>
-__device__ __forceinline__ FacPos fac_pos(const FacArgs &a, int nsplit)
+// Kernel arguments of a launch of one job or of several.
+template <bool BATCH>
+using Args = std::conditional_t<BATCH, FacBatch, FacArgs>;
+__device__ __forceinline__ const FacArgs &common(const FacArgs &a) { return a; }
+__device__ __forceinline__ const FacArgs &common(const FacBatch &b) { return b.a; }
+
+// The job of this block; block: its number in it (several jobs: blocks are laid
+// one job after the other, else `one`).
+__device__ __forceinline__ const FacJob &fac_job(const FacArgs &a, int &block, int one)
 {
-    const int nb = gridDim.x;
-    const int lb = xcd_logical(blockIdx.x, nb);
-    const int tgroups = (a.tiles + WAVES - 1) / WAVES;
+    block = one;
+    return a.job;
+}
+__device__ __forceinline__ const FacJob &fac_job(const FacBatch &b, int &block, int)
+{
+    int jb = 0;
+    for (int j = 1; j < b.njobs; ++j)
+        if ((int)blockIdx.x >= b.jobs[j].blk0) jb = j;
+    block = (int)blockIdx.x - b.jobs[jb].blk0;
+    return b.jobs[jb];
+}
+
+template <int WAVES>
+__device__ __forceinline__ FacPos fac_pos(const FacArgs &a, const FacJob &job, int block, int nsplit)
+{
+    const int tgroups = (job.tiles + WAVES - 1) / WAVES;
+    const int lb = xcd_logical(block, tgroups * nsplit);
     FacPos p;
     p.split = lb / tgroups;
     p.tile = (lb - p.split * tgroups) * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -157,9 +180,10 @@ constexpr int fwd_waves(int nup, int np) { return np * nup <= 256 ? kFacWaves : 
 // T = 8192, four tables: 169 us against 628 for the dense pass on fp32 MFMA
 // (0.8 PFLOP/s of fp16 products; with one wave a SIMD the splits of a time
 // tile are not hidden), the adjoint 167 against 598.
-template <int NUP, int ZST, int CJ, int NP>
-__global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) void fac_fwd_kernel(FacArgs a)
+template <int NUP, int ZST, int CJ, int NP, bool BATCH>
+__global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) void fac_fwd_kernel(Args<BATCH> args)
 {
+    const FacArgs &a = common(args);
     constexpr int WAVES = fwd_waves(NUP, NP), NS = stage_chunks(NUP, NP);
     using Stage = PsfStage<NUP, NS, WAVES>;
     constexpr int NKS = NUP / 16;                     // PSF contraction steps a table
@@ -168,10 +192,11 @@ __global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) vo
     constexpr int GRP = NP == 1 && NS > CJ ? NS : CJ;            // chunks of one loop body
     extern __shared__ __align__(16) f16x8 lk[];
     f16x8 *ebuf = lk + 3 * Stage::kFrags * 64;
-    const FacPos fp = fac_pos<WAVES>(a, a.nsplit);
+    int block;
+    const FacJob &job = fac_job(args, block, blockIdx.x);
+    const FacPos fp = fac_pos<WAVES>(a, job, block, job.nsplit);
     if (fp.n1a >= fp.n1b) return;                 // the whole block
-    const bool active = fp.tile < a.tiles;        // a wave past the last tile still stages
-    const SigJob &job = a.job;
+    const bool active = fp.tile < job.tiles;      // a wave past the last tile still stages
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = fp.tile * 32 + (lane & 31);
@@ -187,7 +212,7 @@ __global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) vo
     // the line: samples 16 ks + 8 h + 0..7, scaled and split
     f16x8 rh[NP * NKS], rl[NP * NKS];
     {
-        const float *rin = (const float *)job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride;
+        const float *rin = job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride;
         const bool vec = job.in_stride % 4 == 0 && (uintptr_t)job.in % 16 == 0 && job.in_stride >= NP * NUP;
         auto get4 = [&](int ks, float (&v)[8]) {     // 16-byte loads
 #pragma unroll
@@ -249,11 +274,11 @@ __global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) vo
             }
         }
         // (every phase range writes the same exponent)
-        if (active && h == 0) a.lexp[r] = le + a.y_exp;
+        if (active && h == 0) job.lexp[r] = le + a.y_exp;
     }
     const float sscale = a.s_scale, yscale = a.y_scale;
     // this lane's line in the wave's Y tile (column 4 h of each group of 8)
-    uint32_t *yrow = a.y + ((size_t)(active ? fp.tile : 0) * a.P * YC + 4 * h) * 32 + (lane & 31);
+    uint32_t *yrow = job.y + ((size_t)(active ? fp.tile : 0) * a.P * YC + 4 * h) * 32 + (lane & 31);
 
     f32x16 acc[RCT];
 #pragma unroll
@@ -340,6 +365,7 @@ __global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) vo
 // lines in L1).
 constexpr int kOutTiles = 2;
 constexpr int kOutWaves = 4;
+__host__ __device__ constexpr int out_groups(int tiles) { return (tiles + kOutTiles * kOutWaves - 1) / (kOutTiles * kOutWaves); }
 
 template <int NU>
 struct OutStage {
@@ -348,15 +374,14 @@ struct OutStage {
 };
 
 template <int NU>
-__device__ __forceinline__ void fwd_out(const FacArgs &a, int q, int t0, int ps)
+__device__ __forceinline__ void fwd_out(const FacArgs &a, const FacJob &job, int q, int t0, int ps)
 {
     const int lane = threadIdx.x & 63, h = lane >> 5;
-    const SigJob &job = a.job;
     const int u0 = a.unit0[q];
     const int nst = (a.P + 7) / 8;
-    const int s0 = (int)((long)ps * nst / a.psplit), s1 = (int)((long)(ps + 1) * nst / a.psplit);
-    const uint32_t *y0 = a.y + ((size_t)t0 * a.P * a.yc + 2 * q) * 32 + lane;   // column 2 q + h, line l % 32
-    const size_t tstep = t0 + 1 < a.tiles ? (size_t)a.P * a.yc * 32 : 0;        // (a missing second tile: the first)
+    const int s0 = (int)((long)ps * nst / job.psplit), s1 = (int)((long)(ps + 1) * nst / job.psplit);
+    const uint32_t *y0 = job.y + ((size_t)t0 * a.P * a.yc + 2 * q) * 32 + lane;   // column 2 q + h, line l % 32
+    const size_t tstep = t0 + 1 < job.tiles ? (size_t)a.P * a.yc * 32 : 0;        // (a missing second tile: the first)
     const f16x8 *w0 = (const f16x8 *)a.wf + (size_t)u0 * nst * 128 + lane;
     f32x16 acc[kOutTiles][NU];
 #pragma unroll
@@ -394,7 +419,7 @@ __device__ __forceinline__ void fwd_out(const FacArgs &a, int q, int t0, int ps)
     for (int t = 0; t < kOutTiles; ++t)
 #pragma unroll
         for (int j = 0; j < 16; ++j)
-            e[t][j] = a.lexp[min(t0 + t, a.tiles - 1) * 32 + 4 * h + 8 * (j / 4) + j % 4];
+            e[t][j] = job.lexp[min(t0 + t, job.tiles - 1) * 32 + 4 * h + 8 * (j / 4) + j % 4];
     int we[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) we[u] = a.wexp[(u0 + u) * 32 + (lane & 31)];
@@ -414,27 +439,37 @@ __device__ __forceinline__ void fwd_out(const FacArgs &a, int q, int t0, int ps)
 #pragma unroll
     for (int t = 0; t < kOutTiles; ++t) {
         const int row0 = (t0 + t) * 32 + 4 * h;
-        if (t0 + t >= a.tiles) break;
+        if (t0 + t >= job.tiles) break;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int row = row0 + 8 * (j / 4) + j % 4;
             if (row >= job.rows) continue;
-            float *o = job.part + ps * a.fwd_part_stride + (size_t)job_line(job, row) * a.ucols + u0 * 32 + (lane & 31);
+            float *o = job.part + ps * job.fwd_part_stride + (size_t)job_line(job, row) * a.ucols + u0 * 32 + (lane & 31);
 #pragma unroll
             for (int u = 0; u < NU; ++u) o[32 * u] = __builtin_ldexpf(acc[t][u][j], -(e[t][j] + we[u]));
         }
     }
 }
 
-__global__ __launch_bounds__(64 * kOutWaves) void fac_fwd_out_kernel(FacArgs a)
+// (blocks of a job: tile groups, slots, stage ranges)
+template <bool BATCH>
+__global__ __launch_bounds__(64 * kOutWaves) void fac_fwd_out_kernel(Args<BATCH> args)
 {
-    const int t0 = kOutTiles * (blockIdx.x * kOutWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
-    const int q = blockIdx.y;
-    if (t0 >= a.tiles) return;
+    const FacArgs &a = common(args);
+    int group, q = blockIdx.y, ps = blockIdx.z;
+    const FacJob &job = fac_job(args, group, blockIdx.x);
+    if constexpr (BATCH) {
+        const int tg = out_groups(job.tiles), sq = group / tg;
+        group -= sq * tg;
+        ps = sq / a.R;
+        q = sq - ps * a.R;
+    }
+    const int t0 = kOutTiles * (group * kOutWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    if (t0 >= job.tiles) return;
     if (a.unit0[q + 1] - a.unit0[q] == 1)
-        fwd_out<1>(a, q, t0, blockIdx.z);
+        fwd_out<1>(a, job, q, t0, ps);
     else
-        fwd_out<2>(a, q, t0, blockIdx.z);
+        fwd_out<2>(a, job, q, t0, ps);
 }
 
 // Adjoint outer sum: Z from the data, one block of kInWaves waves per 32-line
@@ -451,21 +486,26 @@ __global__ __launch_bounds__(64 * kOutWaves) void fac_fwd_out_kernel(FacArgs a)
 // or 24 of up to 24 -- what the registers of two waves a SIMD hold.
 constexpr int kInWaves = kFacInWaves;
 
-template <int RPW, int KST>
-__global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
+template <int RPW, int KST, bool BATCH>
+__global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(Args<BATCH> args)
 {
+    const FacArgs &a = common(args);
     __shared__ int lmax[kInWaves][32];
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = blockIdx.x, zsp = blockIdx.y;
-    const SigJob &job = a.job;
+    int tile, zsp = blockIdx.y;
+    const FacJob &job = fac_job(args, tile, blockIdx.x);
+    if constexpr (BATCH) {
+        zsp = tile / job.tiles;
+        tile -= zsp * job.tiles;
+    }
     const int row0 = tile * 32;
     const int r = row0 + (lane & 31);
     const long il = r < job.rows ? job_line(job, r) : -1;
     constexpr int QM = 8 * KST;
     // this block's stages [s0, s1): range zsp of zsplit
     const int nst = a.nzstage;
-    const int s0 = (int)((long)zsp * nst / a.zsplit), s1 = (int)((long)(zsp + 1) * nst / a.zsplit);
+    const int s0 = (int)((long)zsp * nst / job.zsplit), s1 = (int)((long)(zsp + 1) * nst / job.zsplit);
     const int sfull = min(s1, a.P / 16);          // stages of 16 phases
     const float zscale = a.z_scale;
     auto table_load = [&](int stg, f16x8 (&t)[RPW][KST][2]) {
@@ -490,7 +530,7 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
     {
         float v[RPW][KST][8];
         int ex[RPW][KST][4];
-        const float *yin = (const float *)job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride;
+        const float *yin = job.in + (size_t)(il >= 0 ? il : 0) * job.in_stride;
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const int q = wave + kInWaves * i;
@@ -532,7 +572,7 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
 #pragma unroll
         for (int w = 0; w < kInWaves; ++w) m = max(m, lmax[w][lane & 31]);
         const int le = m > kZero ? 15 - m : 0;
-        if (wave == 0 && lane < 32) a.lexp[r] = le + a.z_exp;   // (every stage range writes the same)
+        if (wave == 0 && lane < 32) job.lexp[r] = le + a.z_exp;   // (every stage range writes the same)
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
 #pragma unroll
@@ -543,8 +583,8 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
                 split8(w, bh[i][ks], bl[i][ks]);
             }
     }
-    uint32_t *const zt = a.y + (size_t)tile * 32 * a.P * a.yc;
-    uint32_t *const spare = a.y + (size_t)a.ylines * a.P * a.yc;
+    uint32_t *const zt = job.y + (size_t)tile * 32 * a.P * a.yc;
+    uint32_t *const spare = job.y + (size_t)job.ylines * a.P * a.yc;
     // result row 8 (s / 4) + 4 h + s % 4: phase row / 2, column row % 2
     auto stage = [&](int stg, const f16x8 (&t)[RPW][KST][2], bool full) {
 #pragma unroll
@@ -599,11 +639,12 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(FacArgs a)
 // Split fp16 products and PSF-table stages as in the forward; Z comes in split
 // pairs scaled by a power of two per line (lexp, undone in the partial sums),
 // the next phase's words being requested before a phase's chunks.  The tensor
-// PSF's tables are taken by blocks of their own (blockIdx.y = offset e, whose
-// lines are columns e NUP .. of the partial sums).
-template <int NUP, int ZST, int CJ>
-__global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
+// PSF's tables are taken by blocks of their own (offset e's, whose lines are
+// columns e NUP .. of the partial sums).
+template <int NUP, int ZST, int CJ, bool BATCH>
+__global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(Args<BATCH> args)
 {
+    const FacArgs &a = common(args);
     constexpr int NS = stage_chunks(NUP, 1);
     using Stage = PsfStage<NUP, NS, kFacWaves>;
     constexpr int PT = NUP / 32;          // detector tiles
@@ -612,10 +653,16 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
     constexpr int GRP = NS > CJ ? NS : CJ;
     extern __shared__ __align__(16) f16x8 lk[];
     f16x8 *ebuf = lk + 3 * Stage::kFrags * 64;
-    const FacPos fp = fac_pos<kFacWaves>(a, a.nsplit_adj);
+    int block, pass = blockIdx.y;
+    const FacJob &job = fac_job(args, block, blockIdx.x);
+    if constexpr (BATCH) {
+        const int per_pass = (job.tiles + kFacWaves - 1) / kFacWaves * job.nsplit_adj;
+        pass = block / per_pass;
+        block -= pass * per_pass;
+    }
+    const FacPos fp = fac_pos<kFacWaves>(a, job, block, job.nsplit_adj);
     if (fp.n1a >= fp.n1b) return;                 // the whole block
-    const bool active = fp.tile < a.tiles;        // a wave past the last tile still stages
-    const SigJob &job = a.job;
+    const bool active = fp.tile < job.tiles;      // a wave past the last tile still stages
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c0 = fp.n1a * CJ, c1 = fp.n1b * CJ;
@@ -623,14 +670,13 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
     f32x16 racc[PT];
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) racc[pt] = 0.f;
-    const int pass = blockIdx.y;
     const __amdgpu_buffer_rsrc_t ka = Stage::table(a.ka + pass * a.ka_stride, c0, c1 - c0);
     const f16x8 *ea = (const f16x8 *)a.ea;
     for (int idx = tid; idx < CJ * NE * 64; idx += 64 * kFacWaves) ebuf[idx] = ea[idx];
     // Z of this line tile, [phase][2 slot + part][32 lines]: this lane's line,
     // columns 16 ks + 8 h + 0..7 (past the last: a repeated column times zero
     // table entries)
-    const uint32_t *zrow = a.y + (size_t)(active ? fp.tile : 0) * 32 * a.P * ZC + (lane & 31);
+    const uint32_t *zrow = job.y + (size_t)(active ? fp.tile : 0) * 32 * a.P * ZC + (lane & 31);
     auto zload = [&](int n1, uint32_t (&z)[NZS][8]) {
         const uint32_t *zp = zrow + (size_t)n1 * ZC * 32;
 #pragma unroll
@@ -705,7 +751,7 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
     const int row0 = fp.tile * 32 + 4 * h;
     int e[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) e[j] = a.lexp[row0 + 8 * (j / 4) + j % 4];
+    for (int j = 0; j < 16; ++j) e[j] = job.lexp[row0 + 8 * (j / 4) + j % 4];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         const int row = row0 + 8 * (j / 4) + j % 4;
@@ -716,22 +762,27 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(FacArgs a)
     }
 }
 
-typedef void (*FacKernel)(FacArgs);
 constexpr int kFacNups[] = {64, 128, 192, 256};
-// C = 32 (CJ = 1): 16 slots hold every residue; C = 64 (CJ = 2): 16 to 24
+template <bool BATCH>
+struct Kernels {
+    typedef void (*Kernel)(Args<BATCH>);
+    // C = 32 (CJ = 1): 16 slots hold every residue; C = 64 (CJ = 2): 16 to 24
 #define FWD_ROW(NUP) \
-    {fac_fwd_kernel<NUP, 16, 1, 1>, fac_fwd_kernel<NUP, 16, 2, 1>, fac_fwd_kernel<NUP, 20, 2, 1>, fac_fwd_kernel<NUP, 24, 2, 1>}
+    {fac_fwd_kernel<NUP, 16, 1, 1, BATCH>, fac_fwd_kernel<NUP, 16, 2, 1, BATCH>, fac_fwd_kernel<NUP, 20, 2, 1, BATCH>, fac_fwd_kernel<NUP, 24, 2, 1, BATCH>}
 #define ADJ_ROW(NUP) \
-    {fac_adj_kernel<NUP, 16, 1>, fac_adj_kernel<NUP, 16, 2>, fac_adj_kernel<NUP, 20, 2>, fac_adj_kernel<NUP, 24, 2>}
-const FacKernel kFacFwd[4][4] = {FWD_ROW(64), FWD_ROW(128), FWD_ROW(192), FWD_ROW(256)};
-const FacKernel kFacAdj[4][4] = {ADJ_ROW(64), ADJ_ROW(128), ADJ_ROW(192), ADJ_ROW(256)};
+    {fac_adj_kernel<NUP, 16, 1, BATCH>, fac_adj_kernel<NUP, 16, 2, BATCH>, fac_adj_kernel<NUP, 20, 2, BATCH>, fac_adj_kernel<NUP, 24, 2, BATCH>}
+    static constexpr Kernel fwd[4][4] = {FWD_ROW(64), FWD_ROW(128), FWD_ROW(192), FWD_ROW(256)};
+    static constexpr Kernel adj[4][4] = {ADJ_ROW(64), ADJ_ROW(128), ADJ_ROW(192), ADJ_ROW(256)};
 #undef FWD_ROW
 #undef ADJ_ROW
-// tensor lines of 2 to 4 sums, at most 768 samples (what the registers hold), C = 32
-#define NP_ROW(NUP) {fac_fwd_kernel<NUP, 16, 1, 2>, fac_fwd_kernel<NUP, 16, 1, 3>, fac_fwd_kernel<NUP, 16, 1, 4>}
-const FacKernel kFacFwdNp[4][3] = {NP_ROW(64), NP_ROW(128), NP_ROW(192),
-                                   {fac_fwd_kernel<256, 16, 1, 2>, fac_fwd_kernel<256, 16, 1, 3>, nullptr}};
+    // tensor lines of 2 to 4 sums, at most 768 samples (what the registers hold), C = 32
+#define NP_ROW(NUP) {fac_fwd_kernel<NUP, 16, 1, 2, BATCH>, fac_fwd_kernel<NUP, 16, 1, 3, BATCH>, fac_fwd_kernel<NUP, 16, 1, 4, BATCH>}
+    static constexpr Kernel fwd_np[4][3] = {
+        NP_ROW(64), NP_ROW(128), NP_ROW(192), {fac_fwd_kernel<256, 16, 1, 2, BATCH>, fac_fwd_kernel<256, 16, 1, 3, BATCH>, nullptr}};
 #undef NP_ROW
+    static constexpr Kernel adj_in[2] = {fac_adj_in_kernel<2, 4, BATCH>, fac_adj_in_kernel<3, 3, BATCH>};
+    static constexpr Kernel fwd_out = fac_fwd_out_kernel<BATCH>;
+};
 
 int fac_zst_slot(int zst, int cj)
 {
@@ -754,14 +805,35 @@ int fac_supported(int nup, int zst, int cj, int np)
     return fac_nup_slot(nup) >= 0 && cj >= 1 && cj <= 2 && fac_zst_slot(zst, cj) >= 0;
 }
 
-static bool fac_args_ok(const FacArgs &a)
+static bool fac_args_ok(const FacBatch &b, int part)
 {
-    return a.tiles > 0 && a.P > 0 && a.cj > 0 && a.nsplit >= 1 && a.nsplit <= a.P && a.nsplit_adj >= 1 &&
-           a.nsplit_adj <= a.P && a.yc == 2 * a.zst && (a.qmax == 32 ? a.R <= 2 * kInWaves : a.qmax == 24 && a.R <= 3 * kInWaves) && a.R <= a.zst &&
-           a.U >= a.R && a.U <= 2 * a.R && a.ucols == 32 * a.U && a.nzstage == (a.P + 15) / 16 &&
-           fac_supported(a.nup, a.zst, a.cj, a.np) && a.np >= 1 && a.adj_pitch == a.np * a.nup && a.job.rows <= a.tiles * 32 &&
-           a.ylines >= a.tiles * 32 && (long)(a.ylines + 1) * a.P * a.yc < 0x7fffffffL && a.psplit >= 1 &&
-           a.psplit <= (a.P + 7) / 8 && a.zsplit >= 1 && a.zsplit <= a.nzstage;
+    const FacArgs &a = b.a;
+    if (b.njobs < 1 || b.njobs > kMaxFacJobs || a.P < 1 || a.cj < 1 || a.np < 1 || a.yc != 2 * a.zst || a.R > a.zst ||
+        !(a.qmax == 32 ? a.R <= 2 * kInWaves : a.qmax == 24 && a.R <= 3 * kInWaves) || a.U < a.R || a.U > 2 * a.R ||
+        a.ucols != 32 * a.U || a.nzstage != (a.P + 15) / 16 || !fac_supported(a.nup, a.zst, a.cj, a.np) ||
+        a.adj_pitch != a.np * a.nup)
+        return false;
+    for (int i = 0; i < b.njobs; ++i) {
+        const FacJob &j = b.jobs[i];
+        if (j.rows < 1 || j.rows > j.tiles * 32 || j.ylines < j.tiles * 32 || (long)(j.ylines + 1) * a.P * a.yc >= 0x7fffffffL ||
+            j.nsplit < 1 || j.nsplit > a.P || j.nsplit_adj < 1 || j.nsplit_adj > a.P || j.psplit < 1 ||
+            j.psplit > (a.P + 7) / 8 || j.zsplit < 1 || j.zsplit > a.nzstage)
+            return false;
+        if (a.np > 1 && part == kFacFwdInner && (j.in_stride != a.np * a.nup || (uintptr_t)j.in % 16)) return false;
+    }
+    return true;
+}
+
+// Grid of kernel `part` of one job.
+static dim3 fac_grid(const FacArgs &a, const FacJob &j, int part)
+{
+    const int waves = fwd_waves(a.nup, a.np);
+    switch (part) {
+    case kFacFwdInner: return dim3((j.tiles + waves - 1) / waves * j.nsplit);
+    case kFacFwdOuter: return dim3(out_groups(j.tiles), a.R, j.psplit);
+    case kFacAdjOuter: return dim3(j.tiles, j.zsplit);
+    default: return dim3((j.tiles + kFacWaves - 1) / kFacWaves * j.nsplit_adj, a.np);
+    }
 }
 
 // LDS bytes of a line-tile kernel: three PSF-table stages and its residue
@@ -771,62 +843,66 @@ static size_t fac_lds(int nup, int np, int nfrag)
     return 1024 * (size_t)(3 * stage_chunks(nup, np) * (nup / 8) + nfrag);
 }
 
-hipError_t launch_fac_part(const FacArgs &a, int part, hipStream_t st)
+template <bool BATCH>
+static hipError_t launch_part(const Args<BATCH> &args, const FacArgs &a, int part, dim3 grid, hipStream_t st)
 {
-    if (a.job.rows <= 0) return hipSuccess;
-    if (a.np > 1 && part == kFacFwdInner && (a.job.in_stride != a.np * a.nup || (uintptr_t)a.job.in % 16)) return hipErrorInvalidValue;
-    if (!fac_args_ok(a) || part < 0 || part > 3) return hipErrorInvalidValue;
-    hipError_t e = hipSuccess;
+    using K = Kernels<BATCH>;
+    typename K::Kernel k;
+    int threads = 64 * kFacWaves;
+    size_t lds = 0;
     switch (part) {
-    case kFacFwdInner: {
-        const size_t lds = fac_lds(a.nup, a.np, a.cj * 4 * ((a.yc + 31) / 32));
-        const FacKernel k = a.np > 1 ? kFacFwdNp[fac_nup_slot(a.nup)][a.np - 2]
-                                     : kFacFwd[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
-        const int waves = fwd_waves(a.nup, a.np);
-        if (lds > 64 * 1024) {
-            e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(k, dim3((a.tiles + waves - 1) / waves * a.nsplit), dim3(64 * waves), lds, st, a);
+    case kFacFwdInner:
+        k = a.np > 1 ? K::fwd_np[fac_nup_slot(a.nup)][a.np - 2] : K::fwd[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
+        threads = 64 * fwd_waves(a.nup, a.np);
+        lds = fac_lds(a.nup, a.np, a.cj * 4 * ((a.yc + 31) / 32));
         break;
-    }
-    case kFacFwdOuter: {
-        const int per = kOutTiles * kOutWaves;
-        hipLaunchKernelGGL(fac_fwd_out_kernel, dim3((a.tiles + per - 1) / per, a.R, a.psplit), dim3(64 * kOutWaves), 0,
-                           st, a);
+    case kFacFwdOuter:
+        k = K::fwd_out;
+        threads = 64 * kOutWaves;
         break;
-    }
     case kFacAdjOuter:
-        if (a.qmax == 32)
-            hipLaunchKernelGGL((fac_adj_in_kernel<2, 4>), dim3(a.tiles, a.zsplit), dim3(64 * kInWaves), 0, st, a);
-        else
-            hipLaunchKernelGGL((fac_adj_in_kernel<3, 3>), dim3(a.tiles, a.zsplit), dim3(64 * kInWaves), 0, st, a);
+        k = K::adj_in[a.qmax == 32 ? 0 : 1];
+        threads = 64 * kInWaves;
         break;
-    default: {
-        const size_t lds = fac_lds(a.nup, 1, a.cj * 2 * ((a.yc + 15) / 16));
-        const FacKernel k = kFacAdj[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
-        if (lds > 64 * 1024) {
-            e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(k, dim3((a.tiles + kFacWaves - 1) / kFacWaves * a.nsplit_adj, a.np), dim3(64 * kFacWaves),
-                           lds, st, a);
+    default:
+        k = K::adj[fac_nup_slot(a.nup)][fac_zst_slot(a.zst, a.cj)];
+        lds = fac_lds(a.nup, 1, a.cj * 2 * ((a.yc + 15) / 16));
         break;
     }
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
     }
+    hipLaunchKernelGGL(k, grid, dim3(threads), lds, st, args);
     return hipGetLastError();
 }
 
-hipError_t launch_fac_fwd(const FacArgs &a, hipStream_t st)
+hipError_t launch_fac_part(FacBatch &b, int part, hipStream_t st)
 {
-    hipError_t e = launch_fac_part(a, kFacFwdInner, st);
-    return e == hipSuccess ? launch_fac_part(a, kFacFwdOuter, st) : e;
+    if (part < 0 || part > 3 || !fac_args_ok(b, part)) return hipErrorInvalidValue;
+    if (b.njobs == 1) {
+        b.a.job = b.jobs[0];
+        return launch_part<false>(b.a, b.a, part, fac_grid(b.a, b.a.job, part), st);
+    }
+    int blocks = 0;
+    for (int i = 0; i < b.njobs; ++i) {
+        const dim3 g = fac_grid(b.a, b.jobs[i], part);
+        b.jobs[i].blk0 = blocks;
+        blocks += (int)(g.x * g.y * g.z);
+    }
+    return launch_part<true>(b, b.a, part, dim3(blocks), st);
 }
 
-hipError_t launch_fac_adj(const FacArgs &a, hipStream_t st)
+hipError_t launch_fac_fwd(FacBatch &b, hipStream_t st)
 {
-    hipError_t e = launch_fac_part(a, kFacAdjOuter, st);
-    return e == hipSuccess ? launch_fac_part(a, kFacAdjInner, st) : e;
+    const hipError_t e = launch_fac_part(b, kFacFwdInner, st);
+    return e == hipSuccess ? launch_fac_part(b, kFacFwdOuter, st) : e;
+}
+
+hipError_t launch_fac_adj(FacBatch &b, hipStream_t st)
+{
+    const hipError_t e = launch_fac_part(b, kFacAdjOuter, st);
+    return e == hipSuccess ? launch_fac_part(b, kFacAdjInner, st) : e;
 }
 
 }  // namespace mpi3d

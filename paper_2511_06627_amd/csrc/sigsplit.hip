@@ -73,21 +73,25 @@ struct ChunkStage {
 // Position of a wave: blocks are ordered split, column group, line tiles, so
 // that neighbours (one XCD's) share a chunk range and with it the tables in L2.
 struct SplitPos {
-    int job, tile, group, split, c0, c1;
+    int job, lines, tile, group, split, c0, c1;
 };
 
 template <int WAVES>
 __device__ __forceinline__ SplitPos split_pos(const SplitArgs &a)
 {
-    const int lb = xcd_logical(blockIdx.x, gridDim.x);
     SplitPos p;
-    const int sg = lb / a.tgroups, tg = lb - sg * a.tgroups;
+    p.job = 0;
+    for (int j = 1; j < a.njobs; ++j)
+        if ((int)blockIdx.x >= a.jobs[j].blk0) p.job = j;
+    const SplitJob &job = a.jobs[p.job];
+    const int lb = xcd_logical((int)blockIdx.x - job.blk0, job.tgroups * a.ngroups * job.nsplit);
+    const int sg = lb / job.tgroups, tg = lb - sg * job.tgroups;
     p.split = sg / a.ngroups;
     p.group = sg - p.split * a.ngroups;
-    p.job = a.njobs > 1 && tg >= a.jobs[1].tile0 ? 1 : 0;
-    p.tile = (tg - a.jobs[p.job].tile0) * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    p.c0 = (int)((unsigned)(p.split * a.nchunks) / (unsigned)a.nsplit);   // (at most 2^17 chunks, 128 splits)
-    p.c1 = (int)((unsigned)((p.split + 1) * a.nchunks) / (unsigned)a.nsplit);
+    p.lines = a.nlines > 1 && tg >= job.lines[1].tile0 ? 1 : 0;
+    p.tile = (tg - job.lines[p.lines].tile0) * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    p.c0 = (int)((unsigned)(p.split * a.nchunks) / (unsigned)job.nsplit);   // (at most 2^17 chunks, 128 splits)
+    p.c1 = (int)((unsigned)((p.split + 1) * a.nchunks) / (unsigned)job.nsplit);
     return p;
 }
 
@@ -225,20 +229,21 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
     constexpr int NKS = NUP / 16;
     extern __shared__ __align__(16) f16x8 lk[];
     const SplitPos sp = split_pos<WAVES>(a);
-    const SigJob &job = a.jobs[sp.job];
+    const SplitJob &job = a.jobs[sp.job];
+    const SplitLines &lines = job.lines[sp.lines];
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = sp.tile * 32 + (lane & 31);
     // a wave past the last tile still stages (and with one wave a SIMD computes,
     // too: a branch around the products costs copies of their accumulators)
-    const bool active = WAVES == 4 || sp.tile * 32 < job.rows;
-    const long il = r < job.rows ? job_line(job, r) : -1;
-    const Stage stage(job.kf16, a.ff, sp.c0, sp.c1 - sp.c0, a.nct, sp.group * GT);
+    const bool active = WAVES == 4 || sp.tile * 32 < lines.rows;
+    const long il = r < lines.rows ? job_line(lines, r) : -1;
+    const Stage stage(a.k[sp.lines], a.f, sp.c0, sp.c1 - sp.c0, a.nct, sp.group * GT);
     stage.load(0, lk, 0, wave, lane);
     stage.load(1, lk, 1, wave, lane);
 
     f16x8 rh[NKS], rl[NKS];
-    const int le = split_line<NKS, 4, false>((const float *)job.in, il, job.in_stride, 0, a.nu, h, nullptr, rh, rl);
+    const int le = split_line<NKS, 4, false>(job.in, il, job.in_stride, 0, a.nu, h, nullptr, rh, rl);
     constexpr bool LOW = own_low(WAVES);
     f32x16 acc[GT], low[LOW ? GT : 1];
 #pragma unroll
@@ -283,7 +288,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_fwd_kernel(SplitA
     }
     wait_vm_lgkm<0>();   // the repeated loads still in flight land before the LDS is handed on
     if (il < 0) return;
-    float *out = a.part + (size_t)sp.split * a.part_stride + (size_t)il * a.pitch + 4 * h;
+    float *out = job.part + (size_t)sp.split * job.part_stride + (size_t)il * a.pitch + 4 * h;
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
         const int ct = sp.group * GT + g;
@@ -300,19 +305,20 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
     constexpr int PT = NUP / 32, NZS = 2 * GT;
     extern __shared__ __align__(16) f16x8 lk[];
     const SplitPos sp = split_pos<WAVES>(a);
-    const SigJob &job = a.jobs[sp.job];
+    const SplitJob &job = a.jobs[sp.job];
+    const SplitLines &lines = job.lines[sp.lines];
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = sp.tile * 32 + (lane & 31);
-    const bool active = WAVES == 4 || sp.tile * 32 < job.rows;
-    const long il = r < job.rows ? job_line(job, r) : -1;
-    const Stage stage(job.ka16, a.fa, sp.c0, sp.c1 - sp.c0, a.nct, sp.group * GT);
+    const bool active = WAVES == 4 || sp.tile * 32 < lines.rows;
+    const long il = r < lines.rows ? job_line(lines, r) : -1;
+    const Stage stage(a.k[sp.lines], a.f, sp.c0, sp.c1 - sp.c0, a.nct, sp.group * GT);
     stage.load(0, lk, 0, wave, lane);
     stage.load(1, lk, 1, wave, lane);
 
     f16x8 zh[NZS], zl[NZS];
     const int col0 = sp.group * GT * 32;
-    const int le = split_line<NZS, 2, EXP>((const float *)job.in, il, job.in_stride, col0, a.nb2 - col0, h,
+    const int le = split_line<NZS, 2, EXP>(job.in, il, job.in_stride, col0, a.nb2 - col0, h,
                                               a.cexp + col0, zh, zl);
     constexpr bool LOW = own_low(WAVES);
     f32x16 acc[PT], low[LOW ? PT : 1];
@@ -356,7 +362,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void split_adj_kernel(SplitA
     }
     wait_vm_lgkm<0>();
     if (il < 0) return;
-    float *out = a.part + (size_t)(sp.split * a.ngroups + sp.group) * a.part_stride + (size_t)il * a.pitch + 4 * h;
+    float *out = job.part + (size_t)(sp.split * a.ngroups + sp.group) * job.part_stride + (size_t)il * a.pitch + 4 * h;
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) {
         if constexpr (LOW) acc[pt] += low[pt];
@@ -390,26 +396,31 @@ int split_config(int i, int nup, int *gt, int *waves)
     return kSplit[i].nup == nup ? 1 : 0;
 }
 
-hipError_t launch_split(const SplitArgs &a, bool fwd, hipStream_t st)
+hipError_t launch_split(SplitArgs &a, bool fwd, hipStream_t st)
 {
-    if (a.config < 0 || a.config >= kEntries) return hipErrorInvalidValue;
-    const SplitEntry &e = kSplit[a.config];
-    int tg = 0;
-    for (int j = 0; j < a.njobs; ++j) {
-        if (a.jobs[j].tile0 != tg || a.jobs[j].rows < 1) return hipErrorInvalidValue;
-        tg += (a.jobs[j].rows + 32 * e.waves - 1) / (32 * e.waves);
-    }
-    if (e.nup != a.nup || a.njobs < 1 || a.njobs > 2 || tg != a.tgroups || a.nsplit < 1 || a.nsplit > a.nchunks || a.nsplit > 128 ||
-        a.nchunks > (1 << 17) ||
-        a.ngroups != (a.nct + e.gt - 1) / e.gt || a.nct != (a.nb2 + 31) / 32 || a.pitch % 4 ||
-        a.pitch < (fwd ? 32 * a.nct : a.nup) || (double)a.nchunks * a.nct * 4096 >= 2147483647.0 ||
-        (double)a.nchunks * a.nup * 128 >= 2147483647.0)
+    if (a.config < 0 || a.config >= kEntries || a.njobs < 1 || a.njobs > kMaxSplitJobs || a.nlines < 1 || a.nlines > 2)
         return hipErrorInvalidValue;
-    if (fwd && !a.cexp) return hipErrorInvalidValue;
+    const SplitEntry &e = kSplit[a.config];
+    if (e.nup != a.nup || a.nchunks > (1 << 17) || a.ngroups != (a.nct + e.gt - 1) / e.gt || a.nct != (a.nb2 + 31) / 32 ||
+        a.pitch % 4 || a.pitch < (fwd ? 32 * a.nct : a.nup) || (double)a.nchunks * a.nct * 4096 >= 2147483647.0 ||
+        (double)a.nchunks * a.nup * 128 >= 2147483647.0 || (fwd && !a.cexp))
+        return hipErrorInvalidValue;
+    int blocks = 0;
+    for (int i = 0; i < a.njobs; ++i) {
+        SplitJob &j = a.jobs[i];
+        int tg = 0;
+        for (int l = 0; l < a.nlines; ++l) {
+            if (j.lines[l].tile0 != tg || j.lines[l].rows < 1) return hipErrorInvalidValue;
+            tg += (j.lines[l].rows + 32 * e.waves - 1) / (32 * e.waves);
+        }
+        if (tg != j.tgroups || j.nsplit < 1 || j.nsplit > a.nchunks || j.nsplit > 128) return hipErrorInvalidValue;
+        j.blk0 = blocks;
+        blocks += j.tgroups * a.ngroups * j.nsplit;
+    }
     const SplitKernel k = fwd ? e.fwd : a.cexp ? e.adj_exp : e.adj;
     const hipError_t err = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, e.lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k, dim3(a.tgroups * a.ngroups * a.nsplit), dim3(64 * e.waves), e.lds, st, a);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(64 * e.waves), e.lds, st, a);
     return hipGetLastError();
 }
 
