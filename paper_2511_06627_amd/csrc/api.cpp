@@ -151,9 +151,9 @@ static FacArgs fac_args(const mpi3d_plan *pj, int gi)
     return a;
 }
 
-// Line group gi of a line job; fwd under the tensor PSF: the lines are the
-// virtual lines of symmetric sums in the workspace.
-static FacJob fac_job(const LineJob &lj, int gi, bool fwd)
+// Tiles t0 .. t0 + range - 1 of line group gi of a line job; fwd under the tensor
+// PSF: the lines are the virtual lines of symmetric sums in the workspace.
+static FacJob fac_job(const LineJob &lj, int gi, int t0, bool fwd)
 {
     const mpi3d_plan *pj = lj.pl;
     const mpi3d_plan::Fac &f = pj->fac;
@@ -167,8 +167,9 @@ static FacJob fac_job(const LineJob &lj, int gi, bool fwd)
     j.fwd_part_stride = pj->L * 32 * f.U;
     j.y = lj.w->fac;
     j.lexp = lj.w->lexp;
-    j.rows = lg.rows;
-    j.tiles = (lg.rows + 31) / 32;
+    j.row0 = 32 * t0;
+    j.rows = std::min(lg.rows, 32 * (t0 + f.range));
+    j.tiles = (j.rows - j.row0 + 31) / 32;
     j.ylines = j.tiles * 32;
     j.map_per = lg.per;
     j.map_nz = lg.gnz;
@@ -179,13 +180,35 @@ static FacJob fac_job(const LineJob &lj, int gi, bool fwd)
     return j;
 }
 
-// One job's arguments.
-static FacBatch fac_single(const LineJob &lj, int gi, bool fwd)
+// The launches of a factored stage, in order: line group after line group and
+// range after range of a group's tiles (a workspace holds one range's phase sums),
+// the line jobs of each sharing launches and the first one's tables.  (A step of
+// 16 served 32^3 scans, 8 angles, FP32: with launches of their own 1034 us, shared
+// 604; on fp32 MFMA, shared, 686.)
+template <class Launch>
+static int fac_launches(const LineJob *jobs, int n, bool fwd, Launch launch)
 {
-    FacBatch b{};
-    b.a = fac_args(lj.pl, gi);
-    b.jobs[b.njobs++] = fac_job(lj, gi, fwd);
-    return b;
+    const mpi3d_plan *pl = jobs[0].pl;
+    for (int gi = 0; gi < pl->n_line_groups; ++gi) {
+        FacBatch b{};
+        b.a = fac_args(pl, gi);
+        for (int r = 0, left = 1; left; ++r) {
+            left = 0;
+            for (int j = 0; j <= n; ++j) {
+                if (b.njobs == kMaxFacJobs || (j == n && b.njobs > 0)) {
+                    TRY(launch(b, gi));
+                    b.njobs = 0;
+                }
+                if (j == n) break;
+                const mpi3d_plan *pj = jobs[j].pl;
+                const int t0 = r * pj->fac.range;
+                if (32 * t0 >= pj->groups[gi].rows) continue;
+                b.jobs[b.njobs++] = fac_job(jobs[j], gi, t0, fwd);
+                left = 1;
+            }
+        }
+    }
+    return MPI3D_OK;
 }
 
 // The dense stage on fp16 pairs of plan pj: tables and sizes, no jobs yet.
@@ -337,10 +360,6 @@ static int sig_jobs(bool fwd, int prec, const LineJob *jobs, int n, bool serve, 
     if (n < 1) return MPI3D_EINVAL;
     const mpi3d_plan *pl = jobs[0].pl;
     if (fac_on(pl, prec)) {
-        // line group after line group (a workspace holds one's phase sums), the
-        // line jobs of each sharing launches and the first one's tables.  (A step of
-        // 16 served 32^3 scans, 8 angles, FP32: with launches of their own 1034 us,
-        // shared 604; on fp32 MFMA, shared, 686.)
         for (int j = 0; j < n; ++j) {
             const mpi3d_plan *pj = jobs[j].pl;
             if (pj->line_key != pl->line_key || !pj->fac.on) return MPI3D_EINVAL;
@@ -348,17 +367,8 @@ static int sig_jobs(bool fwd, int prec, const LineJob *jobs, int n, bool serve, 
                 TRY(launch_sym_lines(jobs[j].in, jobs[j].in_stride, pj->nu, pj->nup, row_passes(pj, true, MPI3D_MIXED),
                                      jobs[j].w->sig, pj->nup, pj->nupf, st));
         }
-        for (int gi = 0; gi < pl->n_line_groups; ++gi) {
-            FacBatch b{};
-            b.a = fac_args(pl, gi);
-            for (int j = 0; j < n; ++j) {
-                b.jobs[b.njobs++] = fac_job(jobs[j], gi, fwd);
-                if (b.njobs < kMaxFacJobs && j + 1 < n) continue;
-                TRY(fwd ? launch_fac_fwd(b, st) : launch_fac_adj(b, st));
-                b.njobs = 0;
-            }
-        }
-        return MPI3D_OK;
+        return fac_launches(jobs, n, fwd,
+                            [&](FacBatch &b, int) { return fwd ? launch_fac_fwd(b, st) : launch_fac_adj(b, st); });
     }
     if (split_on(pl, prec)) {
         // line jobs of one kernel configuration share launches
@@ -1057,13 +1067,16 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
             a.jobs[c] = kj[c];
         }
     }
-    // the factored band DFT's stages and kernels (FP32 plans that take it)
-    // (of the first line group)
-    FacBatch fwd_fac{}, adj_fac{};
-    if (fac_on(pl, precision)) {
-        fwd_fac = fac_single(LineJob{pl, w.rt, pl->nup, &w}, 0, true);
-        adj_fac = fac_single(LineJob{pl, b, pl->nb2, &w}, 0, false);
-    }
+    // the factored band DFT's stages and kernels (of the first line group)
+    auto fac = [&](bool fwd, int part) {
+        const LineJob lj{pl, fwd ? w.rt : b, fwd ? pl->nup : pl->nb2, &w};
+        const int rc = fac_launches(&lj, 1, fwd, [&](FacBatch &fb, int gi) {
+            if (gi > 0) return hipSuccess;
+            if (part >= 0) return launch_fac_part(fb, part, st);
+            return fwd ? launch_fac_fwd(fb, st) : launch_fac_adj(fb, st);
+        });
+        return rc == MPI3D_OK ? hipSuccess : hipErrorUnknown;
+    };
     const bool split = split_on(pl, precision);
     SplitArgs fwd_split{}, adj_split{};
     if (split) {
@@ -1090,7 +1103,7 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
             if (precision == MPI3D_PRECOMPOSED)
                 err = gemm_signal_fwd(pl, w.rt, pl->nup, w.part, st) == MPI3D_OK ? hipSuccess : hipErrorUnknown;
             else if (fac_on(pl, precision))
-                err = launch_fac_fwd(fwd_fac, st);
+                err = fac(true, -1);
             else if (split)
                 err = launch_split(fwd_split, true, st);
             else
@@ -1100,16 +1113,16 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
             if (precision == MPI3D_PRECOMPOSED)
                 err = gemm_signal_adj(pl, b, w.rt, pl->nup, st) == MPI3D_OK ? hipSuccess : hipErrorUnknown;
             else if (fac_on(pl, precision))
-                err = launch_fac_adj(adj_fac, st);
+                err = fac(false, -1);
             else if (split)
                 err = launch_split(adj_split, false, st);
             else
                 err = launch_sig_adj(pl, precision, a, st);
             break;
-        case 4: err = launch_fac_part(fwd_fac, kFacFwdInner, st); break;
-        case 5: err = launch_fac_part(fwd_fac, kFacFwdOuter, st); break;
-        case 6: err = launch_fac_part(adj_fac, kFacAdjOuter, st); break;
-        default: err = launch_fac_part(adj_fac, kFacAdjInner, st); break;
+        case 4: err = fac(true, kFacFwdInner); break;
+        case 5: err = fac(true, kFacFwdOuter); break;
+        case 6: err = fac(false, kFacAdjOuter); break;
+        default: err = fac(false, kFacAdjInner); break;
         }
     }
     if (err == hipSuccess) err = hipEventRecord(e1, st);

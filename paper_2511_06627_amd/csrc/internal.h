@@ -105,7 +105,8 @@ struct SplitArgs {
 };
 
 // The band DFT factored over drive cycles (FP32): launches of one line group
-// (each has its own PSF tables) of one scan, or of several served together (jobs,
+// (each has its own PSF tables; a range of its tiles at a time where the phase
+// sums of all would not fit the workspace) of one scan, or of several served together (jobs,
 // each with the split of its own scan, so a line's sums do not depend on which
 // others share the launch; under the tensor PSF np = R + 1 of them, the
 // forward's lines being np symmetric line sums laid end to end): time
@@ -133,7 +134,7 @@ struct FacJob {
                              // P yc words taking the stores that carry nothing
     int *lexp;               // [ylines] power-of-two exponent of each line's Y or Z
     int in_stride, ylines;
-    int rows, tiles;         // lines, 32-line tiles
+    int row0, rows, tiles;   // rows row0 .. rows - 1 of the line group, as 32-line tiles
     int map_per, map_nz, map_off, map_step;   // row map (see SigJob)
     int nsplit, nsplit_adj;  // phase ranges of the forward and adjoint line-tile kernels
     int psplit, zsplit;      // stage ranges of the forward outer sum (partial sums each) and of the
@@ -271,7 +272,9 @@ struct mpi3d_plan {
     // time when it pays; tables in the plan's allocation
     struct Fac {
         bool on = false;
-        int C, P, cj, R, zst, U, qmax, nsplit, nsplit_adj, psplit, zsplit, nzstage;
+        int C, P, cj, R, zst, U, qmax, nzstage;
+        int range;                // 32-line tiles a launch takes (the workspace holds their phase sums)
+        int nsplit, nsplit_adj, psplit, zsplit;
         int res;                  // distinct residues of the kept bins mod C
         float s_scale, g_scale, y_scale, z_scale;
         int y_exp, z_exp, r_exp;

@@ -243,7 +243,8 @@ void choose_split(const mpi3d_plan *pl, bool fp32, mpi3d_plan::SigCfg &c, int nu
 // and read at 4 TB/s).  Within 5% of each other, the forward takes ranges of at
 // most 24 chunks (64^3, 24 angles, T = 4001: 18 chunks in place of 26, whose
 // longer sums cost 4% more error than fp32 MFMA has).
-void choose_dense_split(const mpi3d_plan *pl, bool fwd, mpi3d_plan::Split::Dir &d)
+// room: bytes for the partial sums.  Returns the time (1e30 where nothing fits).
+double choose_dense_split(const mpi3d_plan *pl, bool fwd, double room, mpi3d_plan::Split::Dir &d)
 {
     const int nct = pl->split.nct;
     double best = 1e30;
@@ -260,6 +261,7 @@ void choose_dense_split(const mpi3d_plan *pl, bool fwd, mpi3d_plan::Split::Dir &
             fwd ? 1e-7 + 8.0 * pl->L * 32 * nct / 4e12 : ng * (1e-7 + 8.0 * pl->L * pl->nup / 4e12);
         for (int ns = 1; ns <= std::min(pl->nchunks, 128); ++ns) {
             const int len = (pl->nchunks + ns - 1) / ns;
+            if (4.0 * pl->L * ns * (fwd ? 32 * nct : ng * pl->nup) > room) break;
             double t = (double)((tg * ng * ns + 255) / 256) * (12e-6 + len * chunk) + ns * per_split;
             if (fwd && waves == 4 && len > 24) t *= 1.05;
             if (t < best * (1.0 - 1e-9)) {
@@ -268,6 +270,7 @@ void choose_dense_split(const mpi3d_plan *pl, bool fwd, mpi3d_plan::Split::Dir &
             }
         }
     }
+    return best;
 }
 
 // The operator workspace's layout (bytes from its base), with or without the
@@ -308,10 +311,135 @@ void op_layout(mpi3d_plan *pl, bool fac, bool split = false)
     pl->ws_rtb = put(mixed ? sizeof(uint16_t) * pl->L * pl->nup : 0);
     pl->ws_rtsc = put(mixed ? sizeof(float) * pl->L : 0);
     pl->ws_sig = put(np > 1 ? sizeof(float) * np * pl->L * pl->nup : 0);
-    const long tile_lines = (f.max_rows + 31) / 32 * 32;   // one line group at a time
+    const long tile_lines = 32l * f.range;   // a range of one line group at a time
     pl->ws_fac = put(fac ? sizeof(uint32_t) * (tile_lines + 1) * f.P * 2 * f.zst : 0);
     pl->ws_lexp = put(fac ? sizeof(int) * tile_lines : 0);
     pl->op_ws_bytes = align256(o);
+}
+
+// The dense stage on fp16 pairs: its splits within the workspace that the fp32 MFMA
+// form takes, or the no-allocation entry point's scratch if that is more.  Returns
+// the time of a forward and an adjoint, 1e30 for plans without such a stage: those
+// with the mixed operator (for the reason given at the factored stage's choice),
+// tensor PSFs, and where nothing fits.
+double choose_pairs(mpi3d_plan *pl)
+{
+    const int precisions = pl->precisions;
+    if (!(precisions & (1 << MPI3D_FP32)) || (precisions & (1 << MPI3D_MIXED)) || pl->n_passes > 1 ||
+        (double)pl->nchunks * ((pl->nb2 + 31) / 32) * 4096 >= 2147483647.0 ||
+        (double)pl->nchunks * pl->nup * 128 >= 2147483647.0)
+        return 1e30;
+    mpi3d_plan::Split &sp = pl->split;
+    sp.nct = (pl->nb2 + 31) / 32;
+    op_layout(pl, false);
+    const double bound = std::max<double>(pl->op_ws_bytes, MPI3D_NOALLOC_SCRATCH_BYTES);
+    const double room = bound - 512.0 - (double)(pl->op_ws_bytes - (pl->ws_norm - pl->ws_part));
+    return choose_dense_split(pl, true, room, sp.fwd) + choose_dense_split(pl, false, room, sp.adj);
+}
+
+// Bytes of phase sums of a scan whose bins bunch, else 0: at most 24 residues mod C
+// (32 or 64), and under 3/4 of the dense form's products in the factored form even
+// with a pair of columns for every residue and fp32 products alone.
+double bunched_phase_bytes(const mpi3d_plan *pl, const std::vector<long> &bins)
+{
+    if (pl->n_ktab > 1 || pl->n_line_groups > 1 || pl->n_passes > 1) return 0;
+    const int T = pl->nt;
+    double best = 0.75 * T * (pl->nup + pl->nbp2), bytes = 0;
+    for (int C = 32; C <= T && C <= 64; C += 32) {
+        if (T % C) continue;
+        std::vector<int> cnt(C, 0);
+        for (long b : bins) ++cnt[b % C];
+        int R = 0, U = 0;
+        for (int c : cnt) {
+            R += c > 0;
+            U += (c + 15) / 16;
+        }
+        if (R > 24 || *std::max_element(cnt.begin(), cnt.end()) > 24) continue;
+        const int zst = (R + 3) / 4 * 4, P = T / C;
+        const double cost = (double)T * (pl->nup + 32 * ((2 * zst + 31) / 32)) + 64.0 * ((P + 7) / 8 * 8) * U;
+        if (cost < best) {
+            best = cost;
+            bytes = 8.0 * P * zst * ((pl->L + 31) / 32 * 32 + 1);
+        }
+    }
+    return bytes;
+}
+
+// Tiles a launch of the factored stage takes and the splits of its kernels: the
+// least estimated time of a forward and an adjoint among those whose workspace
+// stays within the bound.  The bound is the no-allocation entry point's scratch, or
+// what the scan's dense form takes if that is more, so that a scan whose dense form
+// fits the scratch does.  Scans whose bins bunch may take their phase sums
+// (bunched) on top: those past the scratch never fitted it, and ranges would cost
+// them 3 to 9% (256 x 256 x 128 in two ranges, forward 489 -> 503 us, adjoint 416 ->
+// 454; 192 x 192 x 96, A then A^T, 303 -> 329).  dense: the dense form's seconds a line
+// and direction.  False where nothing fits, or where what was held back is estimated
+// slower than a dense form (a 64 x 64 x 300 raster, 24 angles, T = 12288: in ranges of
+// tiles 482 us for A and A^T, dense on fp16 pairs 300; 192 x 192 x 303, 12 angles, 491
+// and 346, unbounded 384).
+//
+// The outer sums' forward waves are of two tiles and a slot, the adjoint's blocks of a
+// tile; small launches also split the phase stages (8 and 16 phases) until about
+// 2048 waves (256 blocks) run.  The line-tile kernels take 8 tiles a block, one block
+// a CU: a block takes about 4 us to load its lines and first stages, then its phases
+// at two waves a SIMD (MFMAs of 32 cycles at about 60% busy, 2.4 GHz); each phase
+// range of the adjoint costs the reduction one more partial sum (its chain of loads,
+// about 0.1 us, and the bytes at 4 TB/s).
+bool choose_fac_ranges(mpi3d_plan *pl, double bunched, double dense)
+{
+    mpi3d_plan::Fac &f = pl->fac;
+    const int np = pl->n_passes, nup = pl->nup;
+    const double t_phase = f.cj * (3.0 * nup / 16 + 6.0 * ((2 * f.zst + 31) / 32)) * 64 / 0.6 / 2.4e9;
+    auto splits = [&](long groups, int most, double per_range, double &t) {
+        int nbest = 1;
+        t = 1e30;
+        for (int ns = 1; ns <= std::min({f.P, 256, most}); ++ns) {
+            const double tn = (double)((groups * ns + 255) / 256) * (4e-6 + (f.P + ns - 1) / ns * t_phase) + ns * per_range;
+            if (tn < t * (1.0 - 1e-9)) {
+                t = tn;
+                nbest = ns;
+            }
+        }
+        return nbest;
+    };
+    op_layout(pl, false);
+    const double bound = std::max<double>(pl->op_ws_bytes + bunched, MPI3D_NOALLOC_SCRATCH_BYTES);
+    const long tiles = (f.max_rows + 31) / 32;
+    mpi3d_plan::Fac best = f;
+    double tbest = 1e30;
+    bool found = false, free = false;       // free: nothing was held back
+    for (long n = 1; n <= tiles; ++n) {
+        f.range = (int)((tiles + n - 1) / n);
+        if (n > 1) f.range = (f.range + kFacWaves - 1) / kFacWaves * kFacWaves;
+        if (n > 1 && (tiles + f.range - 1) / f.range < n) continue;      // as few ranges have this length
+        // what is left of the bound for the partial sums
+        f.psplit = f.nsplit_adj = 0;
+        op_layout(pl, true);
+        const size_t kept = pl->ws_norm - pl->ws_part, rest = pl->op_ws_bytes - kept;
+        const double room = bound - 512.0 - (double)rest;
+        const long most_out = (long)(room / (4.0 * pl->L * 32 * f.U)), most_adj = (long)(room / (4.0 * pl->L * nup * np));
+        if (most_out < 1 || most_adj < 1 || (double)kept > room) continue;   // (kept: the mixed operator's)
+        const long psplit = std::max<long>(1, std::min<long>({8, 2048 / ((f.range + 1) / 2 * f.R), (f.P + 7) / 8}));
+        f.psplit = (int)std::min(psplit, most_out);
+        f.zsplit = (int)std::max<long>(1, std::min<long>({8, 256 / f.range, (f.P + 15) / 16}));
+        // (tensor lines: the forward's blocks are of 4 tiles, the adjoint's are np times as many)
+        const long tgroups = (f.range + kFacWaves - 1) / kFacWaves;
+        double tf, ta;
+        f.nsplit = splits(np * nup <= 256 ? tgroups : (f.range + 3) / 4, 256, 0.0, tf);
+        f.nsplit_adj = splits(tgroups * np, (int)std::min<long>(most_adj, 256), 1e-7 + 8.0 * pl->L * nup * np / 4e12, ta);
+        // the outer sums: their launches, the phase sums' bytes at 4 TB/s
+        const double t = pl->n_line_groups * n * (tf + ta + 10e-6) + 32.0 * f.P * f.zst * pl->L / 4e12;
+        if (t < tbest) {
+            tbest = t;
+            best = f;
+            found = true;
+            free = n == 1 && f.psplit == psplit && f.nsplit_adj < most_adj;
+        }
+        if (f.psplit == psplit && f.nsplit_adj < most_adj) break;
+    }
+    f = best;
+    const double other = 2 * dense * pl->L + 30e-6;
+    return found && (free || tbest < (bunched > 0 ? other : std::min(other, choose_pairs(pl))));
 }
 
 template <class T>
@@ -782,43 +910,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             }
             f.U = (int)fubin.size() / 16;
             funit0.push_back(f.U);
-            // The outer sums: forward waves of two tiles and a slot, adjoint
-            // blocks of a tile; small scans also split the phase stages (8 and
-            // 16 phases) until about 2048 waves (256 blocks) run.
-            const long tiles = (f.max_rows + 31) / 32;
-            f.psplit = (int)std::max<long>(1, std::min<long>({8, 2048 / ((tiles + 1) / 2 * f.R), (f.P + 7) / 8}));
-            f.zsplit = (int)std::max<long>(1, std::min<long>({8, 256 / tiles, (f.P + 15) / 16}));
-            // Phase ranges of the line-tile kernels (8 tiles a block, one block a
-            // CU): the least estimated time.  A block takes about 4 us to load
-            // its lines and first stages, then its phases at two waves a SIMD
-            // (MFMAs of 32 cycles at about 60% busy, 2.4 GHz); each range of
-            // the adjoint costs the reduction one more partial sum (its chain
-            // of loads, about 0.1 us, and the bytes at 4 TB/s).
-            const long tgroups = (tiles + kFacWaves - 1) / kFacWaves;
-            const double t_phase = f.cj * (3.0 * NUP / 16 + 6.0 * ((2 * f.zst + 31) / 32)) * 64 / 0.6 / 2.4e9;
-            auto splits = [&](long groups, double per_range) {
-                double tbest = 1e30;
-                int nbest = 1;
-                for (int ns = 1; ns <= std::min(f.P, 256); ++ns) {
-                    const double t = (double)((groups * ns + 255) / 256) * (4e-6 + (f.P + ns - 1) / ns * t_phase) +
-                                     ns * per_range;
-                    if (t < tbest * (1.0 - 1e-9)) {
-                        tbest = t;
-                        nbest = ns;
-                    }
-                }
-                return nbest;
-            };
-            // (tensor lines: the forward's blocks are of 4 tiles, the adjoint's are np times as many)
-            f.nsplit = splits(NPASS * NUP <= 256 ? tgroups : (tiles + 3) / 4, 0.0);
-            f.nsplit_adj = splits(tgroups * NPASS, 1e-7 + 8.0 * pl->L * NUP * NPASS / 4e12);
-            // a scan whose bins bunch little and that fits the no-allocation
-            // entry point's scratch in the dense form stays dense where the
-            // phase sums would not fit it
-            op_layout(pl, false);
-            const size_t dense_ws = pl->op_ws_bytes;
-            op_layout(pl, true);
-            f.on = (f.res <= 24 && n_ktab == 1) || !(dense_ws <= MPI3D_NOALLOC_SCRATCH_BYTES && pl->op_ws_bytes > MPI3D_NOALLOC_SCRATCH_BYTES);
+            f.on = choose_fac_ranges(pl, bunched_phase_bytes(pl, bins), 2.0 * T * (NPASS * NUP + NBP2) / 1.1e14);
         }
         if (pl->fac.on) {
             mpi3d_plan::Fac &f = pl->fac;
@@ -1013,21 +1105,8 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         }
     }
 
-    // ---- dense FP32 stage on fp16 pairs: what does not factor, except for
-    // plans with the mixed operator (for the reason above) and tensor PSFs ----
-    if ((precisions & (1 << MPI3D_FP32)) && !(precisions & (1 << MPI3D_MIXED)) && !pl->fac.on && !pl->fused &&
-        NPASS == 1 && (double)pl->nchunks * ((pl->nb2 + 31) / 32) * 4096 < 2147483647.0 &&
-        (double)pl->nchunks * NUP * 128 < 2147483647.0) {
-        mpi3d_plan::Split &sp = pl->split;
-        sp.nct = (pl->nb2 + 31) / 32;
-        choose_dense_split(pl, true, sp.fwd);
-        choose_dense_split(pl, false, sp.adj);
-        // a scan that fits the no-allocation entry point's scratch still does
-        op_layout(pl, false);
-        const size_t dense_ws = pl->op_ws_bytes;
-        op_layout(pl, false, true);
-        sp.on = !(dense_ws <= MPI3D_NOALLOC_SCRATCH_BYTES && pl->op_ws_bytes > MPI3D_NOALLOC_SCRATCH_BYTES);
-    }
+    // ---- dense FP32 stage on fp16 pairs: what does not factor ----------------
+    if (!pl->fac.on) pl->split.on = choose_pairs(pl) < 1e30;
 
     // band DFT F[n][c] (real columns: 2j = Re, 2j+1 = Im)
     // -- not for a plan whose only signal stage is the factored one

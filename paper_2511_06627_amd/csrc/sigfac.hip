@@ -200,7 +200,7 @@ __global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) vo
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = fp.tile * 32 + (lane & 31);
-    const long il = active && r < job.rows ? job_line(job, r) : -1;
+    const long il = active && job.row0 + r < job.rows ? job_line(job, job.row0 + r) : -1;
     const int c0 = fp.n1a * CJ, c1 = fp.n1b * CJ;
 
     const __amdgpu_buffer_rsrc_t kf = Stage::table(a.kf, c0 * NP, (c1 - c0) * NP);
@@ -442,7 +442,7 @@ __device__ __forceinline__ void fwd_out(const FacArgs &a, const FacJob &job, int
         if (t0 + t >= job.tiles) break;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int row = row0 + 8 * (j / 4) + j % 4;
+            const int row = job.row0 + row0 + 8 * (j / 4) + j % 4;
             if (row >= job.rows) continue;
             float *o = job.part + ps * job.fwd_part_stride + (size_t)job_line(job, row) * a.ucols + u0 * 32 + (lane & 31);
 #pragma unroll
@@ -501,7 +501,7 @@ __global__ __launch_bounds__(64 * kInWaves, 2) void fac_adj_in_kernel(Args<BATCH
     }
     const int row0 = tile * 32;
     const int r = row0 + (lane & 31);
-    const long il = r < job.rows ? job_line(job, r) : -1;
+    const long il = job.row0 + r < job.rows ? job_line(job, job.row0 + r) : -1;
     constexpr int QM = 8 * KST;
     // this block's stages [s0, s1): range zsp of zsplit
     const int nst = a.nzstage;
@@ -754,7 +754,7 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(Args<BATCH> 
     for (int j = 0; j < 16; ++j) e[j] = job.lexp[row0 + 8 * (j / 4) + j % 4];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-        const int row = row0 + 8 * (j / 4) + j % 4;
+        const int row = job.row0 + row0 + 8 * (j / 4) + j % 4;
         if (row >= job.rows) continue;
         float *o = out + (size_t)job_line(job, row) * a.adj_pitch + pass * NUP + (lane & 31);
 #pragma unroll
@@ -815,7 +815,7 @@ static bool fac_args_ok(const FacBatch &b, int part)
         return false;
     for (int i = 0; i < b.njobs; ++i) {
         const FacJob &j = b.jobs[i];
-        if (j.rows < 1 || j.rows > j.tiles * 32 || j.ylines < j.tiles * 32 || (long)(j.ylines + 1) * a.P * a.yc >= 0x7fffffffL ||
+        if (j.row0 < 0 || j.row0 % 32 || j.row0 >= j.rows || j.rows - j.row0 > j.tiles * 32 || j.ylines < j.tiles * 32 || (long)(j.ylines + 1) * a.P * a.yc >= 0x7fffffffL ||
             j.nsplit < 1 || j.nsplit > a.P || j.nsplit_adj < 1 || j.nsplit_adj > a.P || j.psplit < 1 ||
             j.psplit > (a.P + 7) / 8 || j.zsplit < 1 || j.zsplit > a.nzstage)
             return false;
