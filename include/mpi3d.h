@@ -340,8 +340,8 @@ void mpi3d_state_destroy(mpi3d_state *state);
  *   kernel 1  backprojection        reads the workspace, writes x_dev
  *   kernel 2  signal forward contraction (time signal + band DFT), reads
  *             the workspace's projections (an FP32 plan that factors the band
- *             DFT over drive cycles, dft_cycles > 0: its two launches,
- *             kernels 4 and 5)
+ *             DFT over drive cycles, dft_cycles > 0: its launches, kernels 4
+ *             and 5, for every line group)
  *   kernel 3  signal adjoint contraction, reads b_dev (factored: kernels 6
  *             and 7)
  *             (MIXED, kernels 2 and 3: the per-line scales and fp16 operand

@@ -1067,12 +1067,11 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
             a.jobs[c] = kj[c];
         }
     }
-    // the factored band DFT's stages and kernels (of the first line group)
+    // the factored band DFT's stages (every line group) and kernels (the first's)
     auto fac = [&](bool fwd, int part) {
         const LineJob lj{pl, fwd ? w.rt : b, fwd ? pl->nup : pl->nb2, &w};
         const int rc = fac_launches(&lj, 1, fwd, [&](FacBatch &fb, int gi) {
-            if (gi > 0) return hipSuccess;
-            if (part >= 0) return launch_fac_part(fb, part, st);
+            if (part >= 0) return gi == 0 ? launch_fac_part(fb, part, st) : hipSuccess;
             return fwd ? launch_fac_fwd(fb, st) : launch_fac_adj(fb, st);
         });
         return rc == MPI3D_OK ? hipSuccess : hipErrorUnknown;
