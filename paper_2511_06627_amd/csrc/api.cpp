@@ -584,7 +584,6 @@ static int gemm_signal(const mpi3d_plan *pl, bool fwd, const float *in, int ld_i
         g.n = r.n;
         g.m = fwd ? pl->nb2 : pl->nu;
         g.k = fwd ? pl->nu : pl->nb2;
-        g.mw = !fwd && r.beta == 0.f && ld_out == pl->nup ? pl->nup : g.m;
         g.batch = r.batch;
         g.in0 = r.in0;
         g.out0 = r.out0;

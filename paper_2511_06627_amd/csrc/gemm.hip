@@ -19,9 +19,9 @@
 // and four rows of W at its column (coalesced across the wave), the next
 // block's values loaded before this block's products (several blocks ahead
 // leave fewer waves a SIMD and were slower, 17 -> 20 us at 192 x 192 x 96, 36
-// angles).  Columns m .. mw - 1 of C are written as zeros: the pad of the lines
-// that a backprojection reads, formerly cleared by a launch of 5 us.  A 32x32 MFMA result
-// register s of lane l holds row 8(s/4) + 4(l/32) + s%4, column l%32.
+// angles).  Columns of C past m, a line's padding, are not written: nothing reads
+// them.  A 32x32 MFMA result register s of lane l holds row
+// 8(s/4) + 4(l/32) + s%4, column l%32.
 
 #include "device.h"
 
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(64 * kGemmWaves) void line_gemm_kernel(LineGemm g)
     __shared__ float part[kGemmWaves - 1][16][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int h = lane >> 5, r = lane & 31;
-    const int tiles_j = (g.mw + 31) / 32;
+    const int tiles_j = (g.m + 31) / 32;
     const int ti = (int)(blockIdx.x / tiles_j), tj = (int)(blockIdx.x % tiles_j);
     const long b = blockIdx.y;
     const long in_base = g.in0 + b * g.batch_lines, out_base = g.out0 + b * g.batch_lines;
@@ -83,9 +83,8 @@ __global__ __launch_bounds__(64 * kGemmWaves) void line_gemm_kernel(LineGemm g)
 
     f32x16 acc = 0.f;
     int k0 = 8 * wave;
-    const int kend = tj * 32 < g.m ? g.k : 0;         // a tile of pad columns: zeros
     Operands cur = gemm_load<VA>(g, arow, wcol, iok, jok, k0 + 4 * h);
-    for (; k0 < kend; k0 += 8 * kGemmWaves) {
+    for (; k0 < g.k; k0 += 8 * kGemmWaves) {
         const Operands nxt = gemm_load<VA>(g, arow, wcol, iok, jok, k0 + 8 * kGemmWaves + 4 * h);
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc = MFMA32(cur.a[t], cur.w[t], acc);
@@ -96,7 +95,7 @@ __global__ __launch_bounds__(64 * kGemmWaves) void line_gemm_kernel(LineGemm g)
         for (int s = 0; s < 16; ++s) part[wave - 1][s][lane] = acc[s];
     }
     __syncthreads();
-    if (wave > 0 || j >= g.mw) return;
+    if (wave > 0 || !jok) return;
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
         const int row = ti * 32 + 8 * (s / 4) + 4 * h + (s % 4);
@@ -115,8 +114,8 @@ __global__ __launch_bounds__(64 * kGemmWaves) void line_gemm_kernel(LineGemm g)
 hipError_t launch_line_gemm(const LineGemm &g, hipStream_t st)
 {
     if (g.n <= 0 || g.batch <= 0) return hipSuccess;
-    if (g.m <= 0 || g.k <= 0 || g.mw < g.m || g.batch > 65535) return hipErrorInvalidValue;
-    const long blocks = (long)((g.n + 31) / 32) * ((g.mw + 31) / 32);   // one 32 x 32 tile each
+    if (g.m <= 0 || g.k <= 0 || g.batch > 65535) return hipErrorInvalidValue;
+    const long blocks = (long)((g.n + 31) / 32) * ((g.m + 31) / 32);   // one 32 x 32 tile each
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
     // A's rows are 16- (8-) byte aligned when its base and row stride are
     const uintptr_t base = (uintptr_t)g.a;

@@ -412,7 +412,6 @@ struct LineGemm {
     float *c;
     long ldc;
     int n, m, k;
-    int mw;           // columns of C written: zeros from m on
     int batch;
     long in0, out0, batch_lines;
     int in_step, out_step;
