@@ -130,15 +130,13 @@ static int adj_parts(const mpi3d_plan *pl, int prec, bool serve)
     return (fused_pass(pl, prec) ? 1 : pl->n_passes) * nsplit_of(pl, prec, serve) * sig_cfg(pl, prec).ngroups;
 }
 
-// Line group gi of plan pj: tables and sizes, no jobs yet.
-static FacArgs fac_args(const mpi3d_plan *pj, int gi)
+// The factored stage of plan pj: tables and sizes, no jobs yet.
+static FacArgs fac_args(const mpi3d_plan *pj)
 {
     const mpi3d_plan::Fac &f = pj->fac;
     FacArgs a{};
     a.np = pj->n_passes;
     a.adj_pitch = a.np * pj->nup;
-    a.kf = f.kf + gi * f.k_stride;
-    a.ka = f.ka + gi * f.k_stride;
     a.ka_stride = 2 * (long)pj->k_elems;
     a.ef = f.ef; a.ea = f.ea; a.wf = f.wf; a.wa = f.wa;
     a.unit0 = f.unit0; a.qbin = f.qbin; a.wexp = f.wexp;
@@ -153,13 +151,16 @@ static FacArgs fac_args(const mpi3d_plan *pj, int gi)
 
 // Tiles t0 .. t0 + range - 1 of line group gi of a line job; fwd under the tensor
 // PSF: the lines are the virtual lines of symmetric sums in the workspace.
-static FacJob fac_job(const LineJob &lj, int gi, int t0, bool fwd)
+// The line group's tables are those of `tables`, a plan of equal tables.
+static FacJob fac_job(const mpi3d_plan *tables, const LineJob &lj, int gi, int t0, bool fwd)
 {
     const mpi3d_plan *pj = lj.pl;
     const mpi3d_plan::Fac &f = pj->fac;
     const mpi3d_plan::LineGroup &lg = pj->groups[gi];
     const int np = pj->n_passes;
     FacJob j{};
+    j.kf = tables->fac.kf + gi * f.k_stride;
+    j.ka = tables->fac.ka + gi * f.k_stride;
     j.in = fwd && np > 1 ? lj.w->sig : lj.in;
     j.in_stride = fwd && np > 1 ? np * pj->nup : lj.in_stride;
     j.part = lj.w->part;
@@ -180,34 +181,53 @@ static FacJob fac_job(const LineJob &lj, int gi, int t0, bool fwd)
     return j;
 }
 
-// The launches of a factored stage, in order: line group after line group and
-// range after range of a group's tiles (a workspace holds one range's phase sums),
-// the line jobs of each sharing launches and the first one's tables.  (A step of
-// 16 served 32^3 scans, 8 angles, FP32: with launches of their own 1034 us, shared
-// 604; on fp32 MFMA, shared, 686.)
+// The launches of a factored stage over line groups gi < groups, in order: line
+// group after line group and range after range of a group's tiles (a workspace
+// holds one range's phase sums), or all groups together; the line jobs of each
+// sharing launches and the first one's tables.  (A step of 16 served 32^3 scans, 8
+// angles, FP32: with launches of their own 1034 us, shared 604; on fp32 MFMA,
+// shared, 686.)
 template <class Launch>
-static int fac_launches(const LineJob *jobs, int n, bool fwd, Launch launch)
+static int fac_launches(const LineJob *jobs, int n, bool fwd, int groups, Launch launch)
 {
     const mpi3d_plan *pl = jobs[0].pl;
-    for (int gi = 0; gi < pl->n_line_groups; ++gi) {
-        FacBatch b{};
-        b.a = fac_args(pl, gi);
-        for (int r = 0, left = 1; left; ++r) {
-            left = 0;
-            for (int j = 0; j <= n; ++j) {
-                if (b.njobs == kMaxFacJobs || (j == n && b.njobs > 0)) {
-                    TRY(launch(b, gi));
-                    b.njobs = 0;
-                }
-                if (j == n) break;
-                const mpi3d_plan *pj = jobs[j].pl;
-                const int t0 = r * pj->fac.range;
-                if (32 * t0 >= pj->groups[gi].rows) continue;
-                b.jobs[b.njobs++] = fac_job(jobs[j], gi, t0, fwd);
-                left = 1;
-            }
+    FacBatch b{};
+    b.a = fac_args(pl);
+    auto flush = [&]() -> int {
+        if (b.njobs) TRY(launch(b));
+        b.njobs = 0;
+        return MPI3D_OK;
+    };
+    auto add = [&](const FacJob &j) -> int {
+        if (b.njobs == kMaxFacJobs) TRYRC(flush());
+        b.jobs[b.njobs++] = j;
+        return MPI3D_OK;
+    };
+    for (int j = 0; j < n; ++j) {
+        const mpi3d_plan::Fac &f = jobs[j].pl->fac;
+        if (!f.together) continue;
+        long held = 0;                       // lines of phase sums before this group's
+        for (int gi = 0; gi < groups; ++gi) {
+            FacJob fj = fac_job(pl, jobs[j], gi, 0, fwd);
+            fj.y += held * f.P * 2 * f.zst;
+            fj.lexp += held;
+            held += fj.ylines + 1;
+            TRYRC(add(fj));
         }
     }
+    TRYRC(flush());
+    for (int gi = 0; gi < groups; ++gi)
+        for (int r = 0, left = 1; left; ++r) {
+            left = 0;
+            for (int j = 0; j < n; ++j) {
+                const mpi3d_plan *pj = jobs[j].pl;
+                const int t0 = r * pj->fac.range;
+                if (pj->fac.together || 32 * t0 >= pj->groups[gi].rows) continue;
+                TRYRC(add(fac_job(pl, jobs[j], gi, t0, fwd)));
+                left = 1;
+            }
+            TRYRC(flush());
+        }
     return MPI3D_OK;
 }
 
@@ -367,8 +387,8 @@ static int sig_jobs(bool fwd, int prec, const LineJob *jobs, int n, bool serve, 
                 TRY(launch_sym_lines(jobs[j].in, jobs[j].in_stride, pj->nu, pj->nup, row_passes(pj, true, MPI3D_MIXED),
                                      jobs[j].w->sig, pj->nup, pj->nupf, st));
         }
-        return fac_launches(jobs, n, fwd,
-                            [&](FacBatch &b, int) { return fwd ? launch_fac_fwd(b, st) : launch_fac_adj(b, st); });
+        return fac_launches(jobs, n, fwd, pl->n_line_groups,
+                            [&](FacBatch &b) { return fwd ? launch_fac_fwd(b, st) : launch_fac_adj(b, st); });
     }
     if (split_on(pl, prec)) {
         // line jobs of one kernel configuration share launches
@@ -1069,8 +1089,8 @@ extern "C" int mpi3d_time_kernel(const mpi3d_plan *pl, int32_t kernel, int32_t p
     // the factored band DFT's stages (every line group) and kernels (the first's)
     auto fac = [&](bool fwd, int part) {
         const LineJob lj{pl, fwd ? w.rt : b, fwd ? pl->nup : pl->nb2, &w};
-        const int rc = fac_launches(&lj, 1, fwd, [&](FacBatch &fb, int gi) {
-            if (part >= 0) return gi == 0 ? launch_fac_part(fb, part, st) : hipSuccess;
+        const int rc = fac_launches(&lj, 1, fwd, part < 0 ? pl->n_line_groups : 1, [&](FacBatch &fb) {
+            if (part >= 0) return launch_fac_part(fb, part, st);
             return fwd ? launch_fac_fwd(fb, st) : launch_fac_adj(fb, st);
         });
         return rc == MPI3D_OK ? hipSuccess : hipErrorUnknown;

@@ -104,14 +104,15 @@ struct SplitArgs {
                              // two a column's data is taken by (null: all 0)
 };
 
-// The band DFT factored over drive cycles (FP32): launches of one line group
-// (each has its own PSF tables; a range of its tiles at a time where the phase
-// sums of all would not fit the workspace) of one scan, or of several served together (jobs,
-// each with the split of its own scan, so a line's sums do not depend on which
-// others share the launch; under the tensor PSF np = R + 1 of them, the
-// forward's lines being np symmetric line sums laid end to end): time
-// t = n1 + P n2 with n1 < P, n2 < C, T = C P, C = 32 or 64.  The time signal is real, so its C-point DFT over n2 needs one slot of
-// two columns (cos, sin) per residue pair {r, C - r} of the kept bins mod C;
+// The band DFT factored over drive cycles (FP32): time t = n1 + P n2 with
+// n1 < P, n2 < C, T = C P, C = 32 or 64.  A launch's jobs are line groups (each
+// has its own PSF table; np = R + 1 under the tensor PSF, the forward's lines
+// being np symmetric line sums laid end to end) of one scan or of several served
+// together, a range of a group's tiles at a time where the phase sums of all would
+// not fit the workspace.  Each job has the splits of its own scan, so a line's sums
+// do not depend on what shares the launch.  The time signal is real, so its
+// C-point DFT over n2 needs one slot of two columns (cos, sin) per residue pair
+// {r, C - r} of the kept bins mod C;
 // residues 0 and C / 2, whose sine columns vanish, share a slot (columns: the
 // plain and the alternating sum).  C = 32 always fits 16 slots; C = 64 is
 // taken where the harmonics bunch into at most 24.  The phase sums Y (forward)
@@ -125,6 +126,8 @@ constexpr int kFacWaves = 8;        // waves (32-line tiles) per block of the li
 constexpr int kFacInWaves = 8;      // waves of the adjoint outer sum; wave w takes slots w + 8 i
 
 struct FacJob {
+    const __half *kf, *ka;   // PSF tables, time rows in chunk order (n1, 32-cycle block), as fp16
+                             // fragment pairs hi, lo scaled by a power of two
     const float *in;         // input lines, in_stride floats apart
     float *part;             // partial sums
     long part_stride;        // floats between the adjoint's blocks of them
@@ -143,8 +146,6 @@ struct FacJob {
 };
 
 struct FacArgs {
-    const __half *kf, *ka;   // PSF tables, time rows in chunk order (n1, 32-cycle block), as fp16
-                             // fragment pairs hi, lo scaled by a power of two
     const __half *ef, *ea;   // residue DFT (both as A operands), pairs hi, lo of 2^14 E
     const __half *wf, *wa;   // outer sums, fragment pairs: forward per unit and 8-phase stage (B
                              // operand), adjoint per slot and 16-phase stage (A operand)
@@ -273,7 +274,9 @@ struct mpi3d_plan {
     struct Fac {
         bool on = false;
         int C, P, cj, R, zst, U, qmax, nzstage;
-        int range;                // 32-line tiles a launch takes (the workspace holds their phase sums)
+        int range;                // 32-line tiles of a group a launch takes (the workspace holds their phase sums)
+        bool together;            // every line group in one launch (range covers the largest)
+        long held_lines;          // lines whose phase sums the workspace holds, a spare one for each job among them
         int nsplit, nsplit_adj, psplit, zsplit;
         int res;                  // distinct residues of the kept bins mod C
         float s_scale, g_scale, y_scale, z_scale;

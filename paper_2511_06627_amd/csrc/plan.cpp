@@ -311,9 +311,8 @@ void op_layout(mpi3d_plan *pl, bool fac, bool split = false)
     pl->ws_rtb = put(mixed ? sizeof(uint16_t) * pl->L * pl->nup : 0);
     pl->ws_rtsc = put(mixed ? sizeof(float) * pl->L : 0);
     pl->ws_sig = put(np > 1 ? sizeof(float) * np * pl->L * pl->nup : 0);
-    const long tile_lines = 32l * f.range;   // a range of one line group at a time
-    pl->ws_fac = put(fac ? sizeof(uint32_t) * (tile_lines + 1) * f.P * 2 * f.zst : 0);
-    pl->ws_lexp = put(fac ? sizeof(int) * tile_lines : 0);
+    pl->ws_fac = put(fac ? sizeof(uint32_t) * f.held_lines * f.P * 2 * f.zst : 0);
+    pl->ws_lexp = put(fac ? sizeof(int) * f.held_lines : 0);
     pl->op_ws_bytes = align256(o);
 }
 
@@ -367,7 +366,8 @@ double bunched_phase_bytes(const mpi3d_plan *pl, const std::vector<long> &bins)
 
 // Tiles a launch of the factored stage takes and the splits of its kernels: the
 // least estimated time of a forward and an adjoint among those whose workspace
-// stays within the bound.  The bound is the no-allocation entry point's scratch, or
+// stays within the bound: every line group in one launch where that fits, else group
+// after group, in ranges of tiles.  The bound is the no-allocation entry point's scratch, or
 // what the scan's dense form takes if that is more, so that a scan whose dense form
 // fits the scratch does.  Scans whose bins bunch may take their phase sums
 // (bunched) on top: those past the scratch never fitted it, and ranges would cost
@@ -408,10 +408,22 @@ bool choose_fac_ranges(mpi3d_plan *pl, double bunched, double dense)
     mpi3d_plan::Fac best = f;
     double tbest = 1e30;
     bool found = false, free = false;       // free: nothing was held back
-    for (long n = 1; n <= tiles; ++n) {
-        f.range = (int)((tiles + n - 1) / n);
+    // n = 0: every line group in one launch; n > 0: group after group, in n ranges
+    for (long n = pl->n_line_groups > 1 ? 0 : 1; n <= tiles; ++n) {
+        f.together = n == 0;
+        f.range = (int)(n > 1 ? (tiles + n - 1) / n : tiles);
         if (n > 1) f.range = (f.range + kFacWaves - 1) / kFacWaves * kFacWaves;
         if (n > 1 && (tiles + f.range - 1) / f.range < n) continue;      // as few ranges have this length
+        long at_once = 0, tgroups = 0, fgroups = 0;     // tiles of a launch; blocks a phase range, adjoint and forward
+        f.held_lines = 0;
+        for (int gi = 0; gi < (f.together ? pl->n_line_groups : 1); ++gi) {
+            const long t = f.together ? (pl->groups[gi].rows + 31) / 32 : f.range;
+            at_once += t;
+            tgroups += (t + kFacWaves - 1) / kFacWaves;
+            fgroups += np * nup <= 256 ? (t + kFacWaves - 1) / kFacWaves : (t + 3) / 4;   // (tensor lines: blocks of 4 tiles)
+            f.held_lines += 32 * t + 1;
+        }
+        if ((double)f.held_lines * f.P * 2 * f.zst >= 2147483647.0) continue;
         // what is left of the bound for the partial sums
         f.psplit = f.nsplit_adj = 0;
         op_layout(pl, true);
@@ -419,21 +431,20 @@ bool choose_fac_ranges(mpi3d_plan *pl, double bunched, double dense)
         const double room = bound - 512.0 - (double)rest;
         const long most_out = (long)(room / (4.0 * pl->L * 32 * f.U)), most_adj = (long)(room / (4.0 * pl->L * nup * np));
         if (most_out < 1 || most_adj < 1 || (double)kept > room) continue;   // (kept: the mixed operator's)
-        const long psplit = std::max<long>(1, std::min<long>({8, 2048 / ((f.range + 1) / 2 * f.R), (f.P + 7) / 8}));
+        const long psplit = std::max<long>(1, std::min<long>({8, 2048 / ((at_once + 1) / 2 * f.R), (f.P + 7) / 8}));
         f.psplit = (int)std::min(psplit, most_out);
-        f.zsplit = (int)std::max<long>(1, std::min<long>({8, 256 / f.range, (f.P + 15) / 16}));
-        // (tensor lines: the forward's blocks are of 4 tiles, the adjoint's are np times as many)
-        const long tgroups = (f.range + kFacWaves - 1) / kFacWaves;
+        f.zsplit = (int)std::max<long>(1, std::min<long>({8, 256 / at_once, (f.P + 15) / 16}));
+        // (tensor lines: the adjoint's blocks are np times as many)
         double tf, ta;
-        f.nsplit = splits(np * nup <= 256 ? tgroups : (f.range + 3) / 4, 256, 0.0, tf);
+        f.nsplit = splits(fgroups, 256, 0.0, tf);
         f.nsplit_adj = splits(tgroups * np, (int)std::min<long>(most_adj, 256), 1e-7 + 8.0 * pl->L * nup * np / 4e12, ta);
         // the outer sums: their launches, the phase sums' bytes at 4 TB/s
-        const double t = pl->n_line_groups * n * (tf + ta + 10e-6) + 32.0 * f.P * f.zst * pl->L / 4e12;
+        const double t = (f.together ? 1 : pl->n_line_groups * n) * (tf + ta + 10e-6) + 32.0 * f.P * f.zst * pl->L / 4e12;
         if (t < tbest) {
             tbest = t;
             best = f;
             found = true;
-            free = n == 1 && f.psplit == psplit && f.nsplit_adj < most_adj;
+            free = n <= 1 && f.psplit == psplit && f.nsplit_adj < most_adj;
         }
         if (f.psplit == psplit && f.nsplit_adj < most_adj) break;
     }

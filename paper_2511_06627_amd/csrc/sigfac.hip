@@ -203,7 +203,7 @@ __global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) vo
     const long il = active && job.row0 + r < job.rows ? job_line(job, job.row0 + r) : -1;
     const int c0 = fp.n1a * CJ, c1 = fp.n1b * CJ;
 
-    const __amdgpu_buffer_rsrc_t kf = Stage::table(a.kf, c0 * NP, (c1 - c0) * NP);
+    const __amdgpu_buffer_rsrc_t kf = Stage::table(job.kf, c0 * NP, (c1 - c0) * NP);
     Stage::load(kf, 0, (c1 - c0) * NP, lk, 0, wave, lane);
     Stage::load(kf, NS, (c1 - c0) * NP, lk, 1, wave, lane);
     const f16x8 *ef = (const f16x8 *)a.ef;
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(64 * kFacWaves, 2) void fac_adj_kernel(Args<BATCH> 
     f32x16 racc[PT];
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) racc[pt] = 0.f;
-    const __amdgpu_buffer_rsrc_t ka = Stage::table(a.ka + pass * a.ka_stride, c0, c1 - c0);
+    const __amdgpu_buffer_rsrc_t ka = Stage::table(job.ka + pass * a.ka_stride, c0, c1 - c0);
     const f16x8 *ea = (const f16x8 *)a.ea;
     for (int idx = tid; idx < CJ * NE * 64; idx += 64 * kFacWaves) ebuf[idx] = ea[idx];
     // Z of this line tile, [phase][2 slot + part][32 lines]: this lane's line,

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 # name: (n_u, T, k_hi, half band), options, signal kernels' name, launches a step
 FORMS = {
     "factored": ((48, 2048, 15, 2), {}, "fac_", 4),
-    "factored_raster": ((48, 2048, 15, 2), {"raster_sweep": 24.0}, "fac_", 8),
+    "factored_raster": ((48, 2048, 15, 2), {"raster_sweep": 24.0}, "fac_", 4),
     "factored_tensor": ((48, 2048, 15, 2), {"psf_rows": 2}, "fac_", 4),
     "pairs": ((48, 3001, 15, 2), {}, "split_", 2),
     "pairs_raster": ((48, 3001, 15, 2), {"raster_sweep": 24.0}, "split_", 2),
