@@ -330,7 +330,9 @@ __global__ __launch_bounds__(kFwdThreads) void proj_fwd_kernel(ProjArgs a, const
                 if (ray >= nrays) continue;
                 const int m = m0 + ray / a.nu, p = ray % a.nu;
                 const float2 csv = a.cs[m];
-                const float c = csv.x, s = csv.y;
+                // samples lie symmetrically on a ray, so it is walked with sin >= 0
+                // (both signs in the bounds below cost 3% at 490 x 793 x 15, 6 angles)
+                const float c = csv.y < 0.f ? -csv.x : csv.x, s = fabsf(csv.y);
                 const float bx = a.ax[(size_t)m * a.nu + p];
                 const float by = a.ay[(size_t)m * a.nu + p];
                 // sample coordinates: fx = bx + y s in LDS columns (column 0 is grid
@@ -351,14 +353,12 @@ __global__ __launch_bounds__(kFwdThreads) void proj_fwd_kernel(ProjArgs a, const
                 const float byb = by - (float)jb0;
                 float ylo = -a.half_nr, yhi = a.half_nr;
                 float ilo = -a.half_nr, ihi = a.half_nr;
-                if (s != 0.f) {
+                if (s > 0.f) {
                     const float rs = 1.f / s;
-                    const float e0 = (-kRange - bx) * rs, e1 = ((float)(a.nx + 1) + kRange - bx) * rs;
-                    const float i0 = (kEdge - bx) * rs, i1 = ((float)(a.nx + 1) - kEdge - bx) * rs;
-                    ylo = fmaxf(ylo, fminf(e0, e1));
-                    yhi = fminf(yhi, fmaxf(e0, e1));
-                    ilo = fmaxf(ilo, fminf(i0, i1));
-                    ihi = fminf(ihi, fmaxf(i0, i1));
+                    ylo = fmaxf(ylo, (-kRange - bx) * rs);
+                    yhi = fminf(yhi, ((float)(a.nx + 1) + kRange - bx) * rs);
+                    ilo = fmaxf(ilo, (kEdge - bx) * rs);
+                    ihi = fminf(ihi, ((float)(a.nx + 1) - kEdge - bx) * rs);
                 } else if (bx < kEdge || bx > (float)(a.nx + 1) - kEdge) {
                     ihi = ilo - 2.f;
                 }
