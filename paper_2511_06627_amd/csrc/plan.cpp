@@ -827,9 +827,40 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         pl->fac.max_rows = std::max<long>(pl->fac.max_rows, pl->groups[gi].rows);
     }
     if ((precisions & (1 << MPI3D_FP32)) && same_coup && T % 32 == 0) {
-        // slot of residue r: 0 for r = 0 and C / 2, else min(r, C - r)
-        auto slot_of = [](long r, int C) { return (int)(2 * r == C ? 0 : std::min(r, C - r)); };
+        // least residue of r's pair: 0 for r = 0 and C / 2, else min(r, C - r)
+        auto least = [](long r, int C) { return (int)(2 * r == C ? 0 : std::min(r, C - r)); };
         auto slots_of = [](int R, int C) { return C == 32 ? 16 : std::max(16, (R + 3) / 4 * 4); };
+        // A slot: the bins (ascending) of a residue pair, or a part of them: the
+        // adjoint's outer sum takes 32 a slot with at most 16 slots, else 24 with at
+        // most 24, and a pair with more has several slots of equal columns (drive
+        // cycles in multiples of 64 with 17 harmonics and more put 34 in one).  Not
+        // in plans that may take the dense form on fp16 pairs, whose adjoint is
+        // faster than a few full slots (41 x 59 x 15, 28 angles, T = 8192, 64
+        // cycles, 59 harmonics: 20.5 and 31.5 us).  Empty where no such slots are
+        // enough.
+        const bool parts_of_pairs = (precisions & (1 << MPI3D_MIXED)) || NPASS > 1;
+        struct Slot {
+            int r;                    // least residue
+            std::vector<int> bins;
+        };
+        auto deal_slots = [&](int C) {
+            std::vector<std::vector<int>> pair(C / 2);
+            for (int j = 0; j < NB; ++j) pair[least(bins[j] % C, C)].push_back(j);
+            std::vector<Slot> out;
+            for (int cap : {32, 24}) {
+                bool fits = true;
+                out.clear();
+                for (int r = 0; r < C / 2; ++r) {
+                    const int n = (int)pair[r].size(), parts = (n + cap - 1) / cap;
+                    if (parts > 1 && !parts_of_pairs) fits = false;
+                    for (int i = 0; i < parts; ++i)
+                        out.push_back({r, {pair[r].begin() + (long)i * n / parts, pair[r].begin() + (long)(i + 1) * n / parts}});
+                }
+                if (fits && (int)out.size() <= (cap == 32 || C == 32 ? 16 : 24)) return out;
+            }
+            out.clear();
+            return out;
+        };
         // seconds per line: dense fp32 products at 1.1e14 flop/s; factored
         // split products (three each) at 8e14, the phase sums written and read
         // at 4 TB/s, the outer sum's fp32 products (32 columns a unit) at 1e14
@@ -837,22 +868,15 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         int bestC = 0;
         for (int C = 32; C <= T && C <= 64; C += 32) {
             if (T % C) continue;
-            std::vector<int> cnt(C / 2, 0);
             std::vector<char> seen(C, 0);
-            for (int j = 0; j < NB; ++j) {
-                ++cnt[slot_of(bins[j] % C, C)];
-                seen[bins[j] % C] = 1;
-            }
+            for (long b : bins) seen[b % C] = 1;
             if ((precisions & (1 << MPI3D_MIXED)) && std::count(seen.begin(), seen.end(), 1) > 24) continue;
-            int R = 0, U = 0, mx = 0;
-            for (int c : cnt)
-                if (c) {
-                    ++R;
-                    U += (c + 15) / 16;
-                    mx = std::max(mx, c);
-                }
+            const std::vector<Slot> slots = deal_slots(C);
+            const int R = (int)slots.size();
+            if (R == 0) continue;
+            int U = 0;
+            for (const Slot &q : slots) U += ((int)q.bins.size() + 15) / 16;
             const int zst = slots_of(R, C), rct = (2 * zst + 31) / 32, P = T / C;
-            if (!(R <= 16 && mx <= 32) && !(R <= 24 && mx <= 24)) continue;
             if (!fac_supported(NUP, zst, C / 32, NPASS) ||
                 (double)((pl->fac.max_rows + 31) / 32 * 32 + 1) * P * 2 * zst >= 2147483647.0 ||
                 4.0 * T * NUP * NPASS >= 2147483647.0)
@@ -876,41 +900,35 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             // not divide R) and spends a step per bin, so slots are dealt
             // largest first to the least loaded wave with room, and numbered
             // by (wave, turn).  Units: a slot's bins (ascending) 16 at a time.
-            std::vector<int> cnt(bestC / 2, 0), byc;
             std::vector<char> seen(bestC, 0);
-            for (int j = 0; j < NB; ++j) {
-                ++cnt[slot_of(bins[j] % bestC, bestC)];
-                seen[bins[j] % bestC] = 1;
-            }
+            for (long b : bins) seen[b % bestC] = 1;
             f.res = (int)std::count(seen.begin(), seen.end(), 1);
-            for (int r = 0; r < bestC / 2; ++r)
-                if (cnt[r]) byc.push_back(r);
-            std::stable_sort(byc.begin(), byc.end(), [&](int x, int y) { return cnt[x] > cnt[y]; });
-            const int nw = kFacInWaves, nr = (int)byc.size();
-            std::vector<std::vector<int>> wres(nw);
+            std::vector<Slot> slots = deal_slots(bestC);
+            std::stable_sort(slots.begin(), slots.end(),
+                             [](const Slot &x, const Slot &y) { return x.bins.size() > y.bins.size(); });
+            const int nw = kFacInWaves, nr = (int)slots.size();
+            std::vector<std::vector<int>> wslot(nw);
             std::vector<int> load(nw, 0), room(nw);
             for (int w = 0; w < nw; ++w) room[w] = nr / nw + (w < nr % nw ? 1 : 0);
-            for (int r : byc) {
+            for (int i = 0; i < nr; ++i) {
                 int bw2 = -1;
                 for (int w = 0; w < nw; ++w)
-                    if ((int)wres[w].size() < room[w] && (bw2 < 0 || load[w] < load[bw2])) bw2 = w;
-                wres[bw2].push_back(r);
-                load[bw2] += (cnt[r] + 3) / 4 * 4;
+                    if ((int)wslot[w].size() < room[w] && (bw2 < 0 || load[w] < load[bw2])) bw2 = w;
+                wslot[bw2].push_back(i);
+                load[bw2] += ((int)slots[i].bins.size() + 3) / 4 * 4;
             }
-            std::vector<int> slot(bestC / 2, -1);   // slot number of a least residue
-            res.assign(byc.size(), -1);
+            res.assign(nr, -1);
+            qb.resize(nr);
             for (int w = 0; w < nw; ++w)
-                for (size_t i = 0; i < wres[w].size(); ++i) {
+                for (size_t i = 0; i < wslot[w].size(); ++i) {
                     const int q = w + nw * (int)i;
-                    res[q] = wres[w][i];
-                    slot[wres[w][i]] = q;
+                    res[q] = slots[wslot[w][i]].r;
+                    qb[q] = slots[wslot[w][i]].bins;
                 }
             f.R = (int)res.size();
             f.zst = slots_of(f.R, bestC);
             f.qmax = f.R <= 16 ? 32 : 24;
             const int QM = f.qmax;
-            qb.resize(f.R);
-            for (int j = 0; j < NB; ++j) qb[slot[slot_of(bins[j] % bestC, bestC)]].push_back(j);
             fqbin.assign((size_t)f.R * QM, 0xffff);   // (bins: below, with their exponents)
             fbcol.assign(NB, 0);
             for (int q = 0; q < f.R; ++q) {
