@@ -338,8 +338,10 @@ double choose_pairs(mpi3d_plan *pl)
 
 // Bytes of phase sums of a scan whose bins bunch, else 0: at most 24 residues mod C
 // (32 or 64), and under 3/4 of the dense form's products in the factored form even
-// with a pair of columns for every residue and fp32 products alone.
-double bunched_phase_bytes(const mpi3d_plan *pl, const std::vector<long> &bins)
+// with a pair of columns for every residue and fp32 products alone.  least: with a
+// pair of columns for every residue, however few; else with the 16 pairs of columns
+// that the kernels are for at least.
+double bunched_phase_bytes(const mpi3d_plan *pl, const std::vector<long> &bins, bool least)
 {
     if (pl->n_ktab > 1 || pl->n_line_groups > 1 || pl->n_passes > 1) return 0;
     const int T = pl->nt;
@@ -358,7 +360,7 @@ double bunched_phase_bytes(const mpi3d_plan *pl, const std::vector<long> &bins)
         const double cost = (double)T * (pl->nup + 32 * ((2 * zst + 31) / 32)) + 64.0 * ((P + 7) / 8 * 8) * U;
         if (cost < best) {
             best = cost;
-            bytes = 8.0 * P * zst * ((pl->L + 31) / 32 * 32 + 1);
+            bytes = 8.0 * P * (least ? zst : std::max(16, zst)) * ((pl->L + 31) / 32 * 32 + 1);
         }
     }
     return bytes;
@@ -367,13 +369,15 @@ double bunched_phase_bytes(const mpi3d_plan *pl, const std::vector<long> &bins)
 // Tiles a launch of the factored stage takes and the splits of its kernels: the
 // least estimated time of a forward and an adjoint among those whose workspace
 // stays within the bound: every line group in one launch where that fits, else group
-// after group, in ranges of tiles.  The bound is the no-allocation entry point's scratch, or
-// what the scan's dense form takes if that is more, so that a scan whose dense form
-// fits the scratch does.  Scans whose bins bunch may take their phase sums
-// (bunched) on top: those past the scratch never fitted it, and ranges would cost
+// after group, in ranges of tiles.  The bound is the no-allocation entry point's
+// scratch, or what the scan's dense form takes if that is more, so that a scan whose
+// dense form fits the scratch does.  Scans whose bins bunch may take their phase sums
+// on top where even the least number of them is past the scratch: ranges would cost
 // them 3 to 9% (256 x 256 x 128 in two ranges, forward 489 -> 503 us, adjoint 416 ->
-// 454; 192 x 192 x 96, A then A^T, 303 -> 329).  dense: the dense form's seconds a line
-// and direction.  False where nothing fits, or where what was held back is estimated
+// 454; 192 x 192 x 96, A then A^T, 303 -> 329) and more where few angles leave CUs
+// idle (32 x 32 x 152, 54 angles, T = 6144, 32 cycles, 22 harmonics: contraction
+// 62 -> 108 us).  dense: the dense form's seconds a line and direction.  False where
+// nothing fits, or where what was held back is estimated
 // slower than a dense form (a 64 x 64 x 300 raster, 24 angles, T = 12288: in ranges of
 // tiles 482 us for A and A^T, dense on fp16 pairs 300; 192 x 192 x 303, 12 angles, 491
 // and 346, unbounded 384).
@@ -385,7 +389,7 @@ double bunched_phase_bytes(const mpi3d_plan *pl, const std::vector<long> &bins)
 // at two waves a SIMD (MFMAs of 32 cycles at about 60% busy, 2.4 GHz); each phase
 // range of the adjoint costs the reduction one more partial sum (its chain of loads,
 // about 0.1 us, and the bytes at 4 TB/s).
-bool choose_fac_ranges(mpi3d_plan *pl, double bunched, double dense)
+bool choose_fac_ranges(mpi3d_plan *pl, const std::vector<long> &bins, double dense)
 {
     mpi3d_plan::Fac &f = pl->fac;
     const int np = pl->n_passes, nup = pl->nup;
@@ -403,7 +407,9 @@ bool choose_fac_ranges(mpi3d_plan *pl, double bunched, double dense)
         return nbest;
     };
     op_layout(pl, false);
-    const double bound = std::max<double>(pl->op_ws_bytes + bunched, MPI3D_NOALLOC_SCRATCH_BYTES);
+    const double bunched = bunched_phase_bytes(pl, bins, false);
+    double bound = std::max<double>(pl->op_ws_bytes, MPI3D_NOALLOC_SCRATCH_BYTES);
+    if (pl->op_ws_bytes + bunched_phase_bytes(pl, bins, true) > bound) bound = pl->op_ws_bytes + bunched;
     const long tiles = (f.max_rows + 31) / 32;
     mpi3d_plan::Fac best = f;
     double tbest = 1e30;
@@ -939,7 +945,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             }
             f.U = (int)fubin.size() / 16;
             funit0.push_back(f.U);
-            f.on = choose_fac_ranges(pl, bunched_phase_bytes(pl, bins), 2.0 * T * (NPASS * NUP + NBP2) / 1.1e14);
+            f.on = choose_fac_ranges(pl, bins, 2.0 * T * (NPASS * NUP + NBP2) / 1.1e14);
         }
         if (pl->fac.on) {
             mpi3d_plan::Fac &f = pl->fac;

@@ -51,6 +51,18 @@ def _rel(a, b, dims):
     return float(((a - b).pow(2).sum(dims) / b.pow(2).sum(dims).clamp_min(1e-300)).sqrt().max())
 
 
+# bunched bins whose least phase sums are past the scratch: whole phase sums
+@pytest.mark.parametrize("scan", [((32, 33, 152, 54, 6144, 32.0, 22, 1), ("fp32", "mixed")),
+                                  ((25, 17, 92, 113, 8192, 128.0, 17, 0), ("fp32",))])
+def test_bunched_past_the_scratch_takes_no_ranges(scan):
+    from paper_2511_06627_amd import _lib
+    from paper_2511_06627_amd.plan import Plan
+    (nx, ny, nz, M, T, P, hi, hb), precisions = scan
+    plan = Plan(nx, ny, nz, M, T, P, 3.0, 1, hi, hb, 1e-3, precisions=precisions)
+    phases = (M * nz + 31) // 32 * 32 * (T // plan.dft_cycles) * 32 * 4
+    assert int(plan.info.op_ws_bytes) > max(phases, _lib.NOALLOC_SCRATCH_BYTES)
+
+
 @pytest.mark.parametrize("name", list(SCANS))
 def test_fits_and_agrees(name):
     import torch
