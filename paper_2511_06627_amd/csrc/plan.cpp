@@ -293,13 +293,24 @@ void op_layout(mpi3d_plan *pl, bool fac, bool split = false)
     if (pl->fused && !fac)   // one pass; adjoint lines of nupf
         part_floats = std::max(part_floats, (size_t)pl->L * std::max(pl->scf.nsplit, pl->scf.serve_nsplit) *
                                                 std::max<size_t>(pl->nbp2, (size_t)pl->nupf));
-    if (fac)   // adjoint: nsplit blocks of nup-column lines; forward: psplit of 32 U columns
-        part_floats =
-            std::max(part_floats, (size_t)pl->L * std::max(f.nsplit_adj * pl->n_passes * pl->nup, f.psplit * 32 * f.U));
     if (split)
         part_floats = std::max({part_floats, (size_t)pl->L * pl->split.fwd.nsplit * 32 * pl->split.nct,
                                 (size_t)pl->L * pl->split.adj.nsplit * pl->split.adj.ngroups * pl->nup});
-    pl->ws_part = put(sizeof(float) * part_floats);
+    size_t part_bytes = sizeof(float) * part_floats;
+    pl->ws_part = align256(o);
+    pl->ws_fac = pl->ws_lexp = pl->ws_part;
+    if (fac) {
+        // The factored stage's partial sums (adjoint: nsplit blocks of nup-column
+        // lines; forward: psplit of 32 U columns) and phase sums lie where the mixed
+        // operator has its partial sums: a request's calls follow one another, and
+        // none leaves any of them for the next.  End to end they took a 192 x 192 x
+        // 96 raster of 36 angles past the no-allocation scratch.
+        const size_t own = sizeof(float) * pl->L * std::max(f.nsplit_adj * pl->n_passes * pl->nup, f.psplit * 32 * f.U);
+        pl->ws_fac = align256(pl->ws_part + own);
+        pl->ws_lexp = align256(pl->ws_fac + sizeof(uint32_t) * f.held_lines * f.P * 2 * f.zst);
+        part_bytes = std::max(part_bytes, pl->ws_lexp + sizeof(int) * f.held_lines - pl->ws_part);
+    }
+    put(part_bytes);
     pl->ws_norm = put(sizeof(double) * pl->max_parts);
     // per tensor-PSF pass: the forward's symmetric line sums, their
     // scales and fp16 operands (one block each without coupling)
@@ -311,8 +322,6 @@ void op_layout(mpi3d_plan *pl, bool fac, bool split = false)
     pl->ws_rtb = put(mixed ? sizeof(uint16_t) * pl->L * pl->nup : 0);
     pl->ws_rtsc = put(mixed ? sizeof(float) * pl->L : 0);
     pl->ws_sig = put(np > 1 ? sizeof(float) * np * pl->L * pl->nup : 0);
-    pl->ws_fac = put(fac ? sizeof(uint32_t) * f.held_lines * f.P * 2 * f.zst : 0);
-    pl->ws_lexp = put(fac ? sizeof(int) * f.held_lines : 0);
     pl->op_ws_bytes = align256(o);
 }
 
@@ -433,10 +442,10 @@ bool choose_fac_ranges(mpi3d_plan *pl, const std::vector<long> &bins, double den
         // what is left of the bound for the partial sums
         f.psplit = f.nsplit_adj = 0;
         op_layout(pl, true);
-        const size_t kept = pl->ws_norm - pl->ws_part, rest = pl->op_ws_bytes - kept;
-        const double room = bound - 512.0 - (double)rest;
+        const size_t rest = pl->op_ws_bytes - (pl->ws_norm - pl->ws_part);
+        const double room = bound - 1024.0 - (double)rest - (double)(pl->ws_lexp + sizeof(int) * f.held_lines - pl->ws_part);
         const long most_out = (long)(room / (4.0 * pl->L * 32 * f.U)), most_adj = (long)(room / (4.0 * pl->L * nup * np));
-        if (most_out < 1 || most_adj < 1 || (double)kept > room) continue;   // (kept: the mixed operator's)
+        if (most_out < 1 || most_adj < 1) continue;
         const long psplit = std::max<long>(1, std::min<long>({8, 2048 / ((at_once + 1) / 2 * f.R), (f.P + 7) / 8}));
         f.psplit = (int)std::min(psplit, most_out);
         f.zsplit = (int)std::max<long>(1, std::min<long>({8, 256 / at_once, (f.P + 15) / 16}));

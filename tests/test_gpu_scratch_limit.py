@@ -28,7 +28,8 @@ SCANS = {
     "ranges_mixed_192": ((192, 16, 280, 12, 12288, 11, 3), {}, MIXED, True),
     "ranges_plain": ((64, 16, 70, 56, 16384, 11, 1), {}, MIXED, True),
     "ranges_raster": ((64, 16, 114, 52, 12288, 25, 1), {"raster_sweep": 32.0}, MIXED, True),
-    "ranges_dual": ((128, 16, 72, 18, 12288, 18, 2), {"drive_axes": 2}, MIXED, True),
+    "dual_128": ((128, 16, 72, 18, 12288, 18, 2), {"drive_axes": 2}, MIXED, False),
+    "ranges_dual": ((96, 16, 20, 47, 16384, 12, 3), {"drive_axes": 2}, MIXED, True),
     "ranges_tensor": ((64, 16, 37, 87, 16384, 24, 0), {"psf_rows": 1}, FP32, True),
 }
 
@@ -90,3 +91,33 @@ def test_fits_and_agrees(name):
     ea = _rel(at.reshape(-1, plan.n_u), aref.reshape(-1, plan.n_u), -1)
     print("  worst line: forward %.2e adjoint %.2e" % (ef, ea), flush=True)
     assert ef <= 1e-5 and ea <= 1e-5
+
+
+def test_operators_of_a_workspace_follow_one_another():
+    """Phase sums lie where the mixed operator has its partial sums; a 192 x 192 x 96
+    raster that holds both fits the scratch, and calls in one workspace, in any order,
+    give the bits of calls in workspaces of their own (filled with NaN before)."""
+    import torch
+    from paper_2511_06627_amd import _lib
+    from paper_2511_06627_amd.plan import Plan
+    plan = Plan(192, 192, 96, 36, 8192, 8192 / 256 + 1 / 3, 3.0, 1, 31, 3, 1e-3, raster_sweep=96.0,
+                precisions=("fp32", "mixed"))
+    assert plan.dft_cycles == 32 and int(plan.info.op_ws_bytes) <= _lib.NOALLOC_SCRATCH_BYTES
+    g = torch.Generator(device="cuda")
+    g.manual_seed(43)
+    x = torch.rand(plan.shape, generator=g, device="cuda")
+
+    def run(ws):
+        out = []
+        for prec in ("fp32", "mixed", "fp32"):
+            b = plan.forward(x, precision=prec, ws=fresh() if ws is None else ws)
+            out += [torch.view_as_real(b), plan.adjoint(b, precision=prec, ws=fresh() if ws is None else ws)]
+        return out
+
+    def fresh():
+        ws = plan.workspace("op")
+        ws.fill_(0xff)
+        return ws
+
+    for a, b in zip(run(None), run(plan.workspace("op"))):
+        assert torch.equal(a, b)
