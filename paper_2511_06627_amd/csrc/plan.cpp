@@ -739,9 +739,14 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         // and 0.155 ns (0.23 ns in row bands) slice by slice.  Measured at the
         // edges, old -> new: 64^3 x 24 11.9 -> 15.2 us, 192^2 x 64 x 36 54 -> 64
         // (not taken), 192^2 x 96 x 36 82 -> 71, 100^3 x 60 45 -> 37, 256^2 x 64 x 24
-        // 102 -> 77 (taken).  It has to win by a twelfth.
+        // 102 -> 77 (taken).  It has to win by a twelfth.  The longest block of the
+        // four-slice kernel has the longest rays; those of the others, of mixed
+        // angles, rays an eighth of the way to the shortest (216 x 327 x 82, 10
+        // angles: 69 us and 78 in four-slice texels, not taken).  Of 470 drawn
+        // volumes 64 are taken in FP32 and 23 in bf16, none over 3% slower.
         const int ng4 = (pl->nz + 3) / 4, nm[2] = {pl->n_steep, M - pl->n_steep};
         const int amax = 2 * kFwdThreads / NU, len = std::max(pl->nx, pl->ny);
+        const double len1 = 0.875 * len + 0.125 * std::min(pl->nx, pl->ny);
         const double stage = 16.0 * pl->nx * pl->ny * 25e-12;
         double best = 1e30;
         for (int amx = 1; amx <= amax; ++amx) {
@@ -761,7 +766,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         }
         const mpi3d::FwdConfig &fc = pl->fwd32;
         const long units = (long)((pl->nz + fc.slices - 1) / fc.slices) * M;
-        const double x = (double)((fc.blocks + 255) / 256) * ((units + fc.blocks - 1) / fc.blocks) * NU * len;
+        const double x = (double)((fc.blocks + 255) / 256) * ((units + fc.blocks - 1) / fc.blocks) * NU * len1;
         const double other = fc.slices == 2 ? 9e-6 + (pl->nx % 4 ? 0.35e-9 : 0.26e-9) * x
                                             : 3e-6 + (fc.n_bands > 1 ? 0.23e-9 : 0.155e-9) * x;
         pl->band.fp32 = best <= 0.92 * other;
@@ -771,7 +776,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         // (measured 0.36 to 0.45).
         const mpi3d::FwdConfig &hc = pl->fwd16;
         const long hunits = (long)((pl->nz + 1) / 2) * M;
-        const double hx = (double)((hc.blocks + 255) / 256) * ((hunits + hc.blocks - 1) / hc.blocks) * NU * len;
+        const double hx = (double)((hc.blocks + 255) / 256) * ((hunits + hc.blocks - 1) / hc.blocks) * NU * len1;
         pl->band.bf16 = (precisions & (1 << MPI3D_MIXED)) && hc.n_bands > 1 && best <= 0.92 * (15e-6 + 0.36e-9 * hx);
     }
 
