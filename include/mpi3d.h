@@ -70,14 +70,16 @@ enum {
 
 /* Operator precision.  FP32: projection in fp32, signal contractions with fp32
  * sums of fp32 products -- taken on the fp32 matrix unit, or as three products
- * of fp16 pairs (hi + lo, errors against FP64 as small).  The plan may factor
- * the band DFT over drive cycles (Appendix A's sum regrouped exactly over
- * t = n1 + P n2, T = C P: a C-point DFT at the residues of the kept bins mod C,
- * then a P-point sum per bin; mpi3d_plan_info.dft_cycles), when that needs less
- * time -- the same operator with the sums in another order.  MIXED: the
- * projection gathers the volume's values rounded to bf16, the backprojection fp16 lines with a power-of-two scale per line, and the
- * signal contractions run on fp16 MFMA with fp32 accumulation, per-line
- * power-of-two scaling and per-harmonic-band scaling.  PRECOMPOSED:
+ * of fp16 pairs (hi + lo; errors against FP64 no larger over the ranges
+ * measured).  The plan may factor the band DFT over drive cycles (Appendix A's
+ * sum regrouped exactly over t = n1 + P n2, T = C P: a C-point DFT at the
+ * residues of the kept bins mod C, then a P-point sum per bin;
+ * mpi3d_plan_info.dft_cycles), when that needs less time -- the same operator
+ * with the sums in another order.  MIXED: the projection gathers the volume's
+ * values rounded to bf16, the backprojection fp16 lines with a power-of-two
+ * scale per line, and the signal contractions run on fp16 MFMA with fp32
+ * accumulation, per-line power-of-two scaling and per-harmonic-band scaling.
+ * PRECOMPOSED:
  * the lines of one PSF table share one trajectory, so A_DC = S D_Gamma F V E H B
  * is one real 2n_bins x n_u matrix G per table (per raster sweep direction,
  * tensor-PSF row offset, or drive axis); the plan forms G = F^T K once in

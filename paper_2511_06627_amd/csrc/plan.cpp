@@ -11,7 +11,8 @@
 //   band DFT F[n][2j], F[n][2j+1]        Appendix A (+i, 1/sqrt(T)) on the kept
 //       = Re/Im(D_j e^{+2 pi i (omega_j n mod T)/T}) / sqrt(T)   bins (eq. bcompress,
 //                                        eq. DCmodel)
-// All table values are computed in float64 and rounded once.
+// All table values are computed in float64, then rounded once to fp32 or fp16, or
+// split into a pair of fp16 numbers (the high one rounded, the low one the rest).
 
 #include <algorithm>
 #include <cmath>

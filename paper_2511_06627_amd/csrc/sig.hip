@@ -1,6 +1,7 @@
 // Compressed signal model A_DC on fp32 MFMA (gfx950 v_mfma_f32_32x32x2_f32): the
-// FP32 stage of plans that also hold the mixed operator (unless their bins bunch)
-// and of tensor PSFs that do not factor; the others take fp16 pairs.
+// FP32 stage of plans that also hold the mixed operator (unless their bins bunch),
+// and of tensor PSFs that do not factor or whose phase sums do not fit; the others
+// take fp16 pairs.
 //
 // Forward, per FFL line (eq. stheta1 with eq. DCmodel):
 //   s[t]  = sum_p rho_theta[p] K[t][p]       K = c_A v_t L'((xi_t - u_p)/w)/w

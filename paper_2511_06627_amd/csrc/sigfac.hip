@@ -12,7 +12,8 @@
 // then, per bin, a P-point sum over the phase within a cycle,
 //   b[j] = sum_n1 G_j[n1] Y_r(j)[n1],   G_j[n1] = D_j e^{+2 pi i omega_j n1 / T} / sqrt(T).
 // s is real, so Y_{C-r} is the conjugate of Y_r: the two share one slot of two
-// columns (cos, sin), and C = 32 needs 16 slots whatever the bins are.  The
+// columns (cos, sin), and C = 32 needs 16 slots whatever the bins are (several
+// slots of equal columns where a pair has more bins than one takes).  The
 // adjoint is the exact transpose of both steps.
 //
 // Forward: fac_fwd_kernel runs the PSF contraction of a line tile chunk by
@@ -34,8 +35,9 @@
 // fp32 MFMA: fac_fwd 715 -> 202 us, fac_adj 654 -> 210, fac_fwd_out 131 -> 74,
 // fac_adj_in 142 -> 104 (1.1 PFLOP/s of fp16 products in the line-tile
 // kernels, as a large fp16 matrix product reaches on this card; the outer sums
-// write and read 315 MB of Y or Z at 3 to 4 TB/s); error of A against float64
-// 4.4e-7 -> 2.7e-7.
+// write and read 315 MB of Y or Z at 3 to 4 TB/s, as 113 MB that stay in the last
+// cache: what bounds them is the requests in flight, not the HBM); error of A
+// against float64 4.5e-7 -> 2.4e-7.
 //
 // MFMA operand conventions: lane l supplies A[l % 32][8 (l / 32) + e] and
 // B[8 (l / 32) + e][l % 32], e < 8; result register s of lane l holds row
@@ -359,7 +361,8 @@ __global__ __launch_bounds__(64 * fwd_waves(NUP, NP), fwd_waves(NUP, NP) / 4) vo
 // lane's operand is 8 packed words of its line, one per phase (two adjacent
 // 128-byte rows a load), and the slot's bins are one or two units of 16 (32
 // result columns, re/im).  The next stage's words and table fragments are
-// requested before a stage's products.  What bounds it: Y from HBM, and the
+// requested before a stage's products.  What bounds it: the loads in flight (one
+// stage ahead; Y at 4.0 TB/s, from HBM as from the last cache), and the
 // tables from L2 (about as many bytes again for one tile a wave, so a wave
 // takes two and the four waves of a block share the slot, hence its table
 // lines in L1).
@@ -481,8 +484,8 @@ __global__ __launch_bounds__(64 * kOutWaves) void fac_fwd_out_kernel(Args<BATCH>
 // 128-byte rows.  No LDS in the loop and no barriers; the next stage's table
 // fragments are requested before a stage's products, and slots in [R, zst)
 // are written as zeros (the spare row takes the stores of slots past zst, so
-// every stage issues the same stores).  What bounds it: Z to HBM, and the
-// tables from L2.  RPW slots a wave of KST steps: 16 slots of up to 32 bins
+// every stage issues the same stores).  What bounds it: the table loads from L2
+// in flight beside Z's stores (Z at 3.1 TB/s, to HBM as to the last cache).  RPW slots a wave of KST steps: 16 slots of up to 32 bins
 // or 24 of up to 24 -- what the registers of two waves a SIMD hold.
 constexpr int kInWaves = kFacInWaves;
 

@@ -1,6 +1,7 @@
 // The dense FP32 signal stage on fp16 pairs (gfx950 v_mfma_f32_32x32x16_f16):
-// for scans whose T is no multiple of 32, so that the band DFT does not factor
-// over drive cycles.
+// for scans whose band DFT does not factor over drive cycles (T no multiple of
+// 32, or more bins a residue than the factored stage takes), or whose phase sums
+// would have to be cut into ranges of line tiles that are slower.
 //
 // Per 32-time chunk c and line tile, forward: the PSF contraction
 // S[time][line] = sum_p K[time][p] rho[p][line], then the band DFT
@@ -16,13 +17,18 @@
 // (NUP / 16) 3 products of a chunk against the group's 6 GT.  Splits over T
 // fill the chip; their partial sums are added in a fixed order afterwards.
 //
+// The long sums keep the small products (hi lo, lo hi) in accumulators of their own
+// where the registers allow (blocks of 4 waves), and forward ranges of at most 24
+// chunks are preferred: against products of fp32 numbers on the fp32 matrix unit the
+// errors of 26 drawn scans are 0.4 to 1.0 times as large.
+//
 // Against the same stages on fp32 MFMA (forward, adjoint, with reductions): a
-// raster of 131 x 117 x 37, 23 angles, T = 6001, 434 columns: 96 -> 51 us,
-// 93 -> 46; 192 x 192 x 96, 36 angles, T = 8101: 365 -> 165, 326 -> 149;
-// 256 x 256 x 128, 60 angles, T = 10001, 658 columns: 1149 -> 850, 1135 -> 896
-// (a chunk's products 60 to 80% of the matrix rate; what keeps small scans off
-// it is some 12 us a block for its lines, first chunks and results).  Error
-// against float64: that of the fp32 form or less.
+// raster of 131 x 117 x 37, 23 angles, T = 6001, 434 columns: 96 -> 58 us,
+// 93 -> 49 (a normal product 246 -> 131); 192 x 192 x 96, 36 angles, T = 8101:
+// 365 -> 165, 326 -> 164; 256 x 256 x 128, 60 angles, T = 10001, 658 columns:
+// 1149 -> 826, 1135 -> 865 (a chunk's products 60 to 80% of the matrix rate; what
+// keeps small scans off
+// it is some 12 us a block for its lines, first chunks and results).
 
 #include "device.h"
 
