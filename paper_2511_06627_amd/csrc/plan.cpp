@@ -858,8 +858,10 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
         // in plans that may take the dense form on fp16 pairs, whose adjoint is
         // faster than a few full slots (41 x 59 x 15, 28 angles, T = 8192, 64
         // cycles, 59 harmonics: 20.5 and 31.5 us).  Empty where no such slots are
-        // enough.
-        const bool parts_of_pairs = (precisions & (1 << MPI3D_MIXED)) || NPASS > 1;
+        // enough, or a residue has more than 24 bins: so few residues leave the
+        // adjoint's time sums too few terms to average their roundings out (16
+        // samples, T = 6336, 64 cycles, 25 harmonics: error 1.0e-7 dense, 3.1e-7).
+        const bool parts_of_pairs = (precisions & (1 << MPI3D_MIXED)) && NPASS == 1 && pl->n_line_groups == 1;
         struct Slot {
             int r;                    // least residue
             std::vector<int> bins;
@@ -868,6 +870,9 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             std::vector<std::vector<int>> pair(C / 2);
             for (int j = 0; j < NB; ++j) pair[least(bins[j] % C, C)].push_back(j);
             std::vector<Slot> out;
+            std::vector<int> cnt(C, 0);
+            for (long b : bins) ++cnt[b % C];
+            if (*std::max_element(cnt.begin(), cnt.end()) > 24) return out;
             for (int cap : {32, 24}) {
                 bool fits = true;
                 out.clear();

@@ -22,8 +22,10 @@ CASES = {
     "residues_0_32": ((48, 20, 3, 11, 8192, 32.0, 2.0, 1, 34, 0), ("fp32", "mixed"), 64),
     "three_residues_38_bins": ((22, 23, 13, 5, 4096, 64.0, 2.0, 1, 19, 1), ("fp32", "mixed"), 64),
     "six_residues": ((80, 30, 1, 9, 4096, 32.0, 3.0, 1, 35, 1), ("fp32", "mixed"), 64),
-    "three_slots_a_pair": ((64, 20, 2, 17, 16384, 128.0, 2.0, 1, 50, 1), ("fp32", "mixed"), 64),
-    "c32": ((33, 20, 4, 9, 2016, 32.0, 2.0, 1, 25, 1), ("fp32", "mixed"), 32),
+    "full_residues": ((64, 20, 2, 17, 16384, 128.0, 2.0, 1, 24, 1), ("fp32", "mixed"), 64),
+    "c32": ((33, 20, 4, 9, 2016, 32.0, 2.0, 1, 24, 1), ("fp32", "mixed"), 32),
+    # a residue of 50 bins: not split (its rounding would not average out)
+    "full_pair_stays_dense": ((64, 20, 2, 17, 16384, 128.0, 2.0, 1, 50, 1), ("fp32", "mixed"), 0),
 }
 
 
