@@ -146,7 +146,7 @@ struct FacJob {
 };
 
 struct FacArgs {
-    const __half *ef, *ea;   // residue DFT (both as A operands), pairs hi, lo of 2^14 E
+    const __half *ef, *ea;   // residue DFT (both as A operands), pairs hi, lo of 2^14 E times a factor
     const __half *wf, *wa;   // outer sums, fragment pairs: forward per unit and 8-phase stage (B
                              // operand), adjoint per slot and 16-phase stage (A operand)
     const int *unit0;        // [R + 1] first unit of slot q

@@ -1059,6 +1059,31 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                 const double a = 2.0 * kPi * (double)ph / C;
                 return part ? std::sin(a) : std::cos(a);
             };
+            // E takes few distinct values (cosines of multiples of 2 pi / C), so the
+            // errors of its pairs are the same in every phase and add up: 2.1e-8 of its
+            // columns as they stand, 1.5e-9 (C = 32) and 5.9e-9 (C = 64) times a factor
+            // that was searched for among the multiples of 2^-20 in [1/2, 1].  What is
+            // left of a column's gain, <E', E> / <E, E> of the columns E' held, and the
+            // factor are divided out of the outer sums' weights.  (70 x 87 x 28, 10
+            // angles, T = 2816: A of positive lines 1.3e-8 low -> 3e-10, A^T A 9e-8 ->
+            // 6e-8, fp32 MFMA 4e-8; three CGLS iterations grow that to 1.5e-6 -> 1.0e-6.)
+            const double escale = C == 32 ? 0.8672637939453125 : 0.8797330856323242;
+            std::vector<double> gain(2 * f.R, 1.0);
+            std::vector<int> slot(NB);          // of a bin
+            for (int q = 0; q < f.R; ++q)
+                for (int j : qb[q]) slot[j] = q;
+            for (int col = 0; col < 2 * f.R; ++col) {
+                double num = 0, den = 0;
+                for (int n2 = 0; n2 < C; ++n2) {
+                    const double v = E(n2, col / 2, col % 2);
+                    double hi, lo;
+                    half_bits(std::ldexp(escale * v, 14), &hi);
+                    half_bits(std::ldexp(escale * v, 14) - hi, &lo);
+                    num += v * std::ldexp(hi + lo, -14);
+                    den += v * v;
+                }
+                if (den > 0) gain[col] = num / den;
+            }
             // ef [j][g][time step][hi, lo]: row = column 32 g + l % 32 (2 slot + part),
             // k = time 32 j + 16 q + tp16(e, l / 32)
             fef.assign((size_t)CJ * RCT * 4 * 512, 0);
@@ -1069,8 +1094,8 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                             for (int e2 = 0; e2 < 8; ++e2) {
                                 const int col = 32 * g2 + l % 32;
                                 const size_t o = ((((size_t)j * RCT + g2) * 2 + q) * 2 * 64 + l) * 8 + e2;
-                                half_pair(std::ldexp(E(32 * j + 16 * q + tp16(e2, l / 32), col / 2, col % 2), 14), fef[o],
-                                       fef[o + 512]);
+                                half_pair(std::ldexp(escale * E(32 * j + 16 * q + tp16(e2, l / 32), col / 2, col % 2), 14),
+                                          fef[o], fef[o + 512]);
                             }
             // ea [j][column step][hi, lo]: row = time 32 j + l % 32, k = column
             // 16 ks + 8 (l / 32) + e (2 slot + part)
@@ -1082,7 +1107,7 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
                             const int col = 16 * ks + 8 * (l / 32) + e2;
                             if (col >= YC) continue;
                             const size_t o = (((size_t)j * NZS + ks) * 2 * 64 + l) * 8 + e2;
-                            half_pair(std::ldexp(E(32 * j + l % 32, col / 2, col % 2), 14), fea[o], fea[o + 512]);
+                            half_pair(std::ldexp(escale * E(32 * j + l % 32, col / 2, col % 2), 14), fea[o], fea[o + 512]);
                         }
             // G_j[n1] = D_j e^{2 pi i (omega_j n1 mod T) / T} / sqrt(T)
             const double inv = 1.0 / std::sqrt((double)T);
@@ -1100,7 +1125,8 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             // weight of slot column cy (cos, sin) in part cb (re, im) of bin j:
             // residue r: b = G (c0 + i c1); C - r: G (c0 - i c1); 0: G c0; C / 2: G c1
             auto weight = [&](int j, int n1, int cy, int cb) -> double {
-                const double gr = Gt[2 * ((size_t)j * P + n1)], gi = Gt[2 * ((size_t)j * P + n1) + 1];
+                const double gn = gain[2 * slot[j] + cy];
+                const double gr = Gt[2 * ((size_t)j * P + n1)] / gn, gi = Gt[2 * ((size_t)j * P + n1) + 1] / gn;
                 const long r = bins[j] % C;
                 if (r == 0 || 2 * r == C) return (cy == 1) == (r != 0) ? (cb == 0 ? gr : gi) : 0.0;
                 if (cy == 0) return cb == 0 ? gr : gi;
@@ -1112,13 +1138,13 @@ extern "C" int mpi3d_plan_create(const mpi3d_geometry *g, int device, mpi3d_plan
             // it per column; the adjoint takes bin j's data by 2^(wref - wex[j])
             // (qbin), and its sums over a slot's bins are below 2^zsum
             int wref = 0, zsum = 0;
-            const std::vector<int> wex = bin_exponents(g->rx_filter, NB, inv, &wref);
+            const std::vector<int> wex = bin_exponents(g->rx_filter, NB, inv / escale, &wref);
             double gsum = 0;
             for (int q = 0; q < f.R; ++q) {
                 double sum = 0;
                 for (size_t i = 0; i < qb[q].size(); ++i) {
                     const int j = qb[q][i];
-                    sum += 1.4142136 * std::ldexp(bin_gain(g->rx_filter, j) * inv, wex[j]);   // |re| + |im| of a weight
+                    sum += 1.4142136 * std::ldexp(bin_gain(g->rx_filter, j) * inv / escale, wex[j]);   // |re| + |im| of a weight
                     fqbin[(size_t)q * QM + i] = (int)((unsigned)(wref - wex[j]) << 16 | (unsigned)j);
                 }
                 gsum = std::max(gsum, sum);
